@@ -97,10 +97,10 @@ void copris_set_launch_hook(copris_launch_hook_fn hook, void* user);
  *     lse[i][h]    = log sum_t exp(s_t)
  *
  * Work is split along the context, so a few very long resumed trajectories do not
- * serialise the step: for bf16 / D = 128 / page 16 the (kv head, page) slabs of the
- * whole pool form one stream that is cut into equal shares, one per wavefront, and
- * the pieces of a sequence are combined in share order; other shapes split every
- * context into 512-token chunks, combined in chunk order.  Either way the partition
+ * serialise the step: for pages of 8 tokens or of a multiple of 16 the 16-token pieces
+ * of the whole pool, per kv head, form one stream that is cut into equal shares, one per
+ * wavefront, and the parts of a sequence are combined in a fixed order; smaller pages split
+ * every context into 512-token chunks, combined in chunk order.  Either way the partition
  * depends on ctx_len only: results are bitwise reproducible and do not depend on the
  * physical page order.
  *

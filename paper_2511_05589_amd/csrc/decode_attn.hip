@@ -1,21 +1,21 @@
 // Paged-KV grouped-query decode attention for gfx950, split along the context.
 //
-// Tuned path (bf16, head_dim 128, page 16): the (kv head, page) slabs of the whole pool
-// are laid out as ONE flat sequence of "slots" (sequence-major, then kv head, then page)
-// and cut into equal contiguous shares, one per persistent wavefront ("stream-K"): the
-// split is balanced to one page whatever the length distribution, a 32k-token resumed
-// trajectory is simply spread over many wavefronts, and nothing is scheduled at run time.
+// Tuned path (pages of 8 tokens or of a multiple of 16): the contexts of the whole pool, in
+// pieces of 16 tokens per kv head, are laid out as ONE flat sequence of "slots" (sequence-major,
+// then kv head, then piece) and cut into equal contiguous shares, one per persistent wavefront
+// ("stream-K"): the split is balanced to one piece whatever the length distribution, a 32k-token
+// resumed trajectory is simply spread over many wavefronts, and nothing is scheduled at run time.
 //   split kernel   one wavefront per share.  It first derives its own start cursor
-//                  (sequence, kv head, page) from ctx_len with one wave-level prefix sum
+//                  (sequence, kv head, piece) from ctx_len with one wave-level prefix sum
 //                  (no separate pass over ctx_len, no extra launch), then walks its slots
 //                  with a wave-uniform cursor (physical pages from the block table, one
-//                  slot ahead) and a three-page-deep register prefetch.  Whenever the
+//                  slot ahead) and a register prefetch two to four slots deep.  Whenever the
 //                  (sequence, kv head) segment changes: a segment that lies wholly inside
 //                  the share is normalised and stored to `out` right there; one that a
 //                  share boundary cuts leaves its online-softmax partial (running max,
 //                  weight sum, weighted value sum of the g query heads of the kv head)
 //   merge kernel   per (sequence, kv head) that a boundary cuts: log-sum-exp combination
-//                  of the partials in share order, normalisation, store; it also writes
+//                  of the partials in a fixed order, normalisation, store; it also writes
 //                  the zeros of empty sequences
 // (For more than 4096 sequences a one-workgroup scan kernel computes the cursors first.)
 // The partition depends on ctx_len only, the merge order is fixed: results are bitwise
@@ -23,18 +23,23 @@
 //
 // The split kernel keeps the kernel HBM-bound by doing both contractions on the matrix
 // cores with the TOKENS (scores) or the head dimension (values) as the 16-row M side and
-// the 16-padded group of query heads as the N side:
-//     S^T[token][head] = K_page[token][:] . Q[head][:]          4 x mfma 16x16x32
-//     O^T[d][head]    += V_page^T[d][token] . P^T[token][head]  8 x mfma 16x16x16
+// the 16-padded group of query heads as the N side (bf16, head_dim 128):
+//     S^T[token][head] = K_slot[token][:] . Q[head][:]          4 x mfma 16x16x32
+//     O^T[d][head]    += V_slot^T[d][token] . P^T[token][head]  8 x mfma 16x16x16
 // With that orientation the score tile leaves the first product already in the register
 // layout the second one wants for P^T, and every per-head softmax quantity (max, sum,
-// rescale factor) lives in the lane that owns the head.  A (page, kv head) slab is one
-// contiguous 4 KB run: it is fetched with fully coalesced 16-byte loads, parked in LDS
-// with an XOR swizzle, and read back in MFMA operand layout (V through the transposing
-// LDS read).
+// rescale factor) lives in the lane that owns the head.  A slot's K (and V) is one
+// contiguous run (two when a page holds 8 tokens): it is fetched with fully coalesced 16-byte
+// loads, parked in LDS with an XOR swizzle, and read back in MFMA operand layout (V through the
+// transposing LDS read).  fp32 takes the same walk with mfma 16x16x4 in full fp32 (32 products
+// per 16 of head_dim and slot: the matrix pipes stay ahead of HBM).
+// Measured (whole call, 64 sequences, mean context 1949): bf16, head_dim 64, 16 / 4 heads,
+// 129 MB of K and V: 32 us, where the vector-ALU kernels took 370; fp32, head_dim 128, 12 / 2
+// heads, 256 MB: 64 us.
 //
-// Generic path (fp32, other head_dim / page sizes): a list of (sequence, 512-token chunk)
-// items, one workgroup per (item, kv head) on the vector ALU, same partial format.
+// Generic path (pages of 1, 2 or 4 tokens, more than 256 kv heads or 2^17 sequences): a list of
+// (sequence, 512-token chunk) items, one workgroup per (item, kv head) on the vector ALU, same
+// partial format.
 #include <type_traits>
 
 #include "copris_device.h"
@@ -263,20 +268,49 @@ __global__ __launch_bounds__(256) void attn_split_generic_kernel(
 }
 
 // --------------------------------------------------------------------------
-// a1/a2 (tuned): bf16, head_dim 128, page 16, g <= 16, flat slot stream.
+// a1/a2 (tuned): the flat slot stream.  bf16 or fp32, head_dim 64 or 128, pages of 8 tokens or
+// of a multiple of 16, g <= 16.
 // --------------------------------------------------------------------------
-constexpr int kD = 128;
-constexpr int kP = 16;
-constexpr int kPageGranules = kP * kD * 2 / 16;   // 256 16-byte granules per (page, kv head)
+constexpr int kP = 16;   // tokens per slot
 
-// The slot stream: for every sequence in batch order, for every kv head, the pages of the
-// context in order; one slot = one (page, kv head) = 16 tokens x 128 dims of K and of V.
+// A (token row) x (head_dim) slab of one slot in 16-byte granules.
+template <typename T, int D> struct Slab {
+  static constexpr int kRow = D * static_cast<int>(sizeof(T)) / 16;   // granules per token row: 8, 16 or 32
+  static constexpr int kAll = kP * kRow;                              // granules of K (and of V) per slot
+  static constexpr int kLoads = kAll / 64;                            // 16-byte loads per lane for K (and for V)
+  static constexpr int kDt = D / 16;                                  // 16-wide head_dim tiles of the value product
+  // LDS position (in granules) of granule c of token row `row`, chosen so that neither the
+  // row-wise fills nor the operand reads conflict: 16 granules are one sweep over the banks.
+  // K is read one granule column of sixteen rows at a time.
+  static __device__ __forceinline__ int k_at(int row, int c) {
+    return row * kRow + (c ^ (kRow == 8 ? (row >> 1) & 7 : row & 15));
+  }
+  // V is read in pairs of granules of eight rows (bf16, transposing read) or in fours of the
+  // rows r, r+4, r+8, r+12 (fp32, one element per lane).
+  static __device__ __forceinline__ int v_at(int row, int c) {
+    if (sizeof(T) == 4) return row * kRow + (c ^ (((row >> 2) & 3) << 2));
+    return row * kRow + (c ^ (kRow == 8 ? ((row >> 1) & 3) << 1 : (row & 7) << 1));
+  }
+};
+
+// The slot stream: for every sequence in batch order, for every kv head, the 16-token pieces of
+// the context in order; one slot = one (piece, kv head) = 16 tokens x head_dim of K and of V.
 // Wavefront w of the split kernel takes the slots [w*share, (w+1)*share).
 // This kernel (one workgroup) writes
-//   seq_pg[i] = pages of the sequences before i (seq_pg[C] = all pages),
+//   seq_pg[i] = pieces of the sequences before i (seq_pg[C] = all pieces),
 //   hdr[0] = slots in total, hdr[1] = share,
-//   start[w] = {sequence, kv head, page index, pages of that sequence} of slot w*share
+//   start[w] = {sequence, kv head, piece index, pieces of that sequence} of slot w*share
 //              (sequence = -1: no slots for this wavefront).
+
+// Slots per wavefront: an equal share, but no less than kMinShare: a shorter share makes more
+// partials to merge than its wavefront saves in time.  Whole call, one sequence of 8192 tokens,
+// 12 / 2 heads: 21.4 us with shares of 1, 16.1 of 2, 14.1 of 4, 16.0 of 8; pools of 16 and more
+// sequences have longer shares anyway.
+constexpr int kMinShare = 4;
+__device__ __forceinline__ int attn_share(int total) {
+  return max((total + kAttnWaves - 1) / kAttnWaves, kMinShare);
+}
+
 __global__ __launch_bounds__(kListThreads) void attn_scan_kernel(
     const int32_t* __restrict__ ctx_len, int C, int max_tokens, int Hkv, int32_t* __restrict__ hdr,
     int32_t* __restrict__ seq_pg, int4* __restrict__ start) {
@@ -307,7 +341,7 @@ __global__ __launch_bounds__(kListThreads) void attn_scan_kernel(
   }
   const int pages = s_carry;
   const int total = pages * Hkv;
-  const int share = total > 0 ? (total + kAttnWaves - 1) / kAttnWaves : 1;
+  const int share = attn_share(total);
   if (tid == 0) {
     seq_pg[C] = pages;
     hdr[0] = total;
@@ -340,40 +374,48 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return r;
 }
 
-struct PageRegs {
-  u32x4 k[4];
-  u32x4 v[4];
+__device__ __forceinline__ void store_out4(uint16_t* p, float a, float b, float c, float d) {
+  *reinterpret_cast<ushort4*>(p) = make_ushort4(f32_to_bf16(a), f32_to_bf16(b), f32_to_bf16(c), f32_to_bf16(d));
+}
+__device__ __forceinline__ void store_out4(float* p, float a, float b, float c, float d) {
+  *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
+}
+
+// One slot's K and V on their way through the registers.
+template <int N> struct SlotRegs {
+  u32x4 k[N];
+  u32x4 v[N];
 };
 
-__device__ __forceinline__ void load_page(PageRegs& r, const u32x4* __restrict__ kc,
-                                          const u32x4* __restrict__ vc, int page, int Hkv, int kvh,
+// base0 / base1: first granule of token rows 0..7 / 8..15 (wave-uniform; the two halves of a
+// slot lie in different pages when a page holds 8 tokens).
+template <typename S>
+__device__ __forceinline__ void load_slot(SlotRegs<S::kLoads>& r, const u32x4* __restrict__ kc,
+                                          const u32x4* __restrict__ vc, size_t base0, size_t base1,
                                           int lane) {
-  const size_t base = (static_cast<size_t>(page) * Hkv + kvh) * kPageGranules + lane;
   // non-temporal: every K / V byte is read once per call, and keeping the stream out of the
   // L2 leaves it to the block table, the queries and the partials (measured: the split kernel
   // 0.336 -> 0.305 ms at the 7B-shaped step)
 #pragma unroll
-  for (int i = 0; i < 4; ++i) r.k[i] = __builtin_nontemporal_load(kc + base + i * 64);
+  for (int i = 0; i < S::kLoads; ++i)
+    r.k[i] = __builtin_nontemporal_load(kc + (2 * i < S::kLoads ? base0 + i * 64 : base1 + (i - S::kLoads / 2) * 64) + lane);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) r.v[i] = __builtin_nontemporal_load(vc + base + i * 64);
+  for (int i = 0; i < S::kLoads; ++i)
+    r.v[i] = __builtin_nontemporal_load(vc + (2 * i < S::kLoads ? base0 + i * 64 : base1 + (i - S::kLoads / 2) * 64) + lane);
 }
-
-// LDS position (in 16-byte granules) of granule c of token row `row`.
-__device__ __forceinline__ int swz_k(int row, int c) { return row * 16 + (c ^ (row & 15)); }
-__device__ __forceinline__ int swz_v(int row, int c) { return row * 16 + (c ^ ((row & 7) << 1)); }
 
 // s_waitcnt vmcnt(0) with the other counters left alone (gfx9 encoding)
 #define COPRIS_WAIT_VM0() __builtin_amdgcn_s_waitcnt(0x0F70)
 
-// Pages of sequence i as the kernels count them.
-__device__ __forceinline__ int attn_pages_of(const int32_t* __restrict__ ctx_len, int i, int max_tokens) {
+// 16-token pieces of sequence i as the kernels count them.
+__device__ __forceinline__ int attn_pieces_of(const int32_t* __restrict__ ctx_len, int i, int max_tokens) {
   const int n = min(max(ctx_len[i], 0), max_tokens);
   return (n + kP - 1) / kP;
 }
 
-// One wavefront: total pages of the pool and the start cursor of slot `w * share` of the
+// One wavefront: total pieces of the pool and the start cursor of slot `w * share` of the
 // slot stream, from ctx_len alone.  Lane l owns the sequences [l*chunk, (l+1)*chunk); an
-// inclusive prefix sum over the lanes gives the pages before each lane's range; the one
+// inclusive prefix sum over the lanes gives the pieces before each lane's range; the one
 // lane whose range holds the slot walks its (at most `chunk`) sequences.  Returns the
 // cursor in every lane ({-1,..}: no slot for this wavefront) and total / share by reference.
 __device__ __forceinline__ int4 attn_derive_cursor(const int32_t* __restrict__ ctx_len, int C,
@@ -390,11 +432,11 @@ __device__ __forceinline__ int4 attn_derive_cursor(const int32_t* __restrict__ c
   if (chunk <= kReg) {
 #pragma unroll
     for (int j = 0; j < kReg; ++j) {
-      reg[j] = i0 + j < i1 ? attn_pages_of(ctx_len, i0 + j, max_tokens) : 0;
+      reg[j] = i0 + j < i1 ? attn_pieces_of(ctx_len, i0 + j, max_tokens) : 0;
       mine += reg[j];
     }
   } else {
-    for (int i = i0; i < i1; ++i) mine += attn_pages_of(ctx_len, i, max_tokens);
+    for (int i = i0; i < i1; ++i) mine += attn_pieces_of(ctx_len, i, max_tokens);
   }
   int incl = mine;
 #pragma unroll
@@ -404,7 +446,7 @@ __device__ __forceinline__ int4 attn_derive_cursor(const int32_t* __restrict__ c
   }
   const int pages = __shfl(incl, kWave - 1, kWave);
   total = pages * Hkv;
-  share = total > 0 ? (total + kAttnWaves - 1) / kAttnWaves : 1;
+  share = attn_share(total);
   const int64_t slot = static_cast<int64_t>(w) * share;
   int4 st = make_int4(-1, 0, 0, 0);
   if (slot >= total) return st;
@@ -428,7 +470,7 @@ __device__ __forceinline__ int4 attn_derive_cursor(const int32_t* __restrict__ c
       }
     } else {
       for (int i = i0; i < i1; ++i) {
-        const int npg = attn_pages_of(ctx_len, i, max_tokens);
+        const int npg = attn_pieces_of(ctx_len, i, max_tokens);
         if (slot < (pg0 + npg) * Hkv) {
           const int r = static_cast<int>(slot - pg0 * Hkv);
           st = make_int4(i, r / npg, r % npg, npg);
@@ -445,22 +487,33 @@ __device__ __forceinline__ int4 attn_derive_cursor(const int32_t* __restrict__ c
   return st;
 }
 
-// entry word of a slot: tokens of the page inside the context - 1 (4 bits), first / last
-// page of its (sequence, kv head) segment (1 + 1), kv head (8), sequence (17)
+// entry word of a slot: tokens of the piece inside the context - 1 (4 bits), first / last
+// piece of its (sequence, kv head) segment (1 + 1), kv head (8), sequence (17)
 constexpr int kCodeFirst = 1 << 4, kCodeLast = 1 << 5, kCodeKvhShift = 6, kCodeSeqShift = 14;
 constexpr int kAttnMaxSeqTuned = 1 << 17;
 constexpr int kAttnMaxSeqInKernelCursor = 4096;
 
-template <int NS, bool PRESCAN>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_split_flat_kernel(
-    const uint16_t* __restrict__ q, const u32x4* __restrict__ k_cache,
+// PG, tokens per page: 16 (a slot is a page's slab), 8 (a slot is two pages) or 0 (16 << lsp).
+// SPLIT_P (bf16): the weights enter the value product as two bf16 numbers, the rounded weight
+// and what the rounding left over, instead of as the rounded weight alone.  Without it their
+// rounding is as large as the result's own: error against 64 bits 2.1e-3 instead of 1.7e-3.
+// Two wavefronts per SIMD, except for slots of 16 KB (fp32, head_dim 128): their two stages
+// need more registers than half the file holds.
+template <typename T, int D> constexpr int kFlatWavesPerSimd = sizeof(T) * D > 256 ? 1 : 2;
+template <typename T, int D, bool PRESCAN, int PG, bool SPLIT_P, int NS>
+__global__ __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(kFlatWavesPerSimd<T, D>, kFlatWavesPerSimd<T, D>))) void attn_split_flat_kernel(
+    const T* __restrict__ q, const u32x4* __restrict__ k_cache,
     const u32x4* __restrict__ v_cache, const int32_t* __restrict__ block_table,
     const int32_t* __restrict__ ctx_len, const int32_t* __restrict__ hdr,
     const int4* __restrict__ start, float2* __restrict__ ws_ml, float* __restrict__ ws_acc,
-    uint16_t* __restrict__ out, float* __restrict__ lse, int C, int Hq, int Hkv, int g,
+    T* __restrict__ out, float* __restrict__ lse, int C, int Hq, int Hkv, int g, int lsp_,
     int max_pages, int max_tokens, float scale_log2e) {
-  __shared__ u32x4 lds_k[kPageGranules];
-  __shared__ u32x4 lds_v[kPageGranules];
+  using S = Slab<T, D>;
+  constexpr bool kBf16 = sizeof(T) == 2;
+  const int lsp = PG == 0 ? lsp_ : 0;
+  __shared__ u32x4 lds_k[S::kAll];
+  __shared__ u32x4 lds_v[S::kAll];
   const int lane = threadIdx.x;
   const int head = lane & 15;     // N index of both products: the query head of the group
   const int b = lane >> 4;        // k-group of the MFMA operand layouts
@@ -484,16 +537,35 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   const int64_t first = static_cast<int64_t>(wv) * share;
   const int n = static_cast<int>(min(static_cast<int64_t>(share), total - first));   // slots of this wavefront
 
-  // Fetch cursor over the slot stream (all wave-uniform): the next slot to request is page
-  // f_p of (sequence f_seq, kv head f_kvh); f_page is its physical page, read one slot ahead
-  // so that the table look-up is off the refill's path.
+  // Fetch cursor over the slot stream (all wave-uniform): the next slot to request is piece
+  // f_p of (sequence f_seq, kv head f_kvh); f_page (and f_page2, of its second half) is its
+  // physical page, read one slot ahead so that the table look-up is off the refill's path.
   int f_seq = st.x, f_kvh = st.y, f_p = st.z, f_npg = st.w;
   int f_ctx = min(max(ctx_len[f_seq], 0), max_tokens);
-  int f_page = block_table[static_cast<size_t>(f_seq) * max_pages + f_p];
-  auto next_entry = [&](int& page, int& code) __attribute__((always_inline)) {
-    page = f_page;
+  int f_page = 0, f_page2 = 0;
+  auto look_up = [&]() __attribute__((always_inline)) {
+    const int32_t* bt = block_table + static_cast<size_t>(f_seq) * max_pages;
+    if (PG == 8) {   // (the second page is not in use where the context ends in the first)
+      f_page = bt[2 * f_p];
+      f_page2 = bt[2 * f_p + (f_p * kP + 8 < f_ctx ? 1 : 0)];
+    } else {
+      f_page = bt[f_p >> lsp];
+    }
+  };
+  look_up();
+  // the cursor's slot -> registers, its entry word -> code; advances the cursor
+  auto fetch = [&](SlotRegs<S::kLoads>& r, int& code) __attribute__((always_inline)) {
     code = (min(kP, f_ctx - f_p * kP) - 1) | (f_p == 0 ? kCodeFirst : 0) |
            (f_p + 1 == f_npg ? kCodeLast : 0) | (f_kvh << kCodeKvhShift) | (f_seq << kCodeSeqShift);
+    const size_t slab = static_cast<size_t>(f_page) * Hkv + f_kvh;
+    size_t base0, base1;
+    if (PG == 8) {
+      base0 = slab * (8 * S::kRow);
+      base1 = (static_cast<size_t>(f_page2) * Hkv + f_kvh) * (8 * S::kRow);
+    } else {
+      base0 = ((slab << lsp) + (f_p & ((1 << lsp) - 1))) * S::kAll;
+      base1 = base0 + S::kAll / 2;
+    }
     if (++f_p == f_npg) {
       f_p = 0;
       if (++f_kvh == Hkv) {   // on to the next sequence that has a context
@@ -505,17 +577,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         }
       }
     }
-    f_page = f_seq < C ? block_table[static_cast<size_t>(f_seq) * max_pages + f_p] : 0;
+    if (f_seq < C) look_up();
+    load_slot<S>(r, k_cache, v_cache, base0, base1, lane);
   };
 
   // state of the segment (sequence, kv head) being accumulated
   int cur_seg = -1;
-  bf16x8 qf[4];
+  u32x4 qf[S::kLoads];
   float m_run = -INFINITY, l_run = 0.0f;
-  f32x4 o[8];
+  f32x4 o[S::kDt];
 
-  bool seg_whole = false;   // the segment began with its first page inside this share
-  bool seg_ends = false;    // the slot just processed was the segment's last page
+  bool seg_whole = false;   // the segment began with its first piece inside this share
+  bool seg_ends = false;    // the slot just processed was the segment's last piece
   auto flush = [&]() __attribute__((always_inline)) {   // result of (this wavefront, cur_seg)
     float l_all = l_run;
     l_all += __shfl_xor(l_all, 16, kWave);
@@ -526,39 +599,33 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       if (head < g) {
         const int seq = cur_seg / Hkv, kvh = cur_seg - seq * Hkv;
         const size_t oh = static_cast<size_t>(seq) * Hq + kvh * g + head;
-        uint16_t* dst = out + oh * kD + 4 * b;
+        T* dst = out + oh * D + 4 * b;
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) {
-          ushort4 r;
-          r.x = f32_to_bf16(o[dt][0] / l_all);
-          r.y = f32_to_bf16(o[dt][1] / l_all);
-          r.z = f32_to_bf16(o[dt][2] / l_all);
-          r.w = f32_to_bf16(o[dt][3] / l_all);
-          *reinterpret_cast<ushort4*>(dst + 16 * dt) = r;
-        }
+        for (int dt = 0; dt < S::kDt; ++dt)
+          store_out4(dst + 16 * dt, o[dt][0] / l_all, o[dt][1] / l_all, o[dt][2] / l_all, o[dt][3] / l_all);
         if (lse != nullptr && b == 0) lse[oh] = (m_run + __builtin_amdgcn_logf(l_all)) * kLn2;
       }
       return;
     }
     if (head < g) {
       const size_t slot = (static_cast<size_t>(wv) + cur_seg) * g + head;
-      float* dst = ws_acc + slot * kD + 4 * b;    // lane (head, b) owns d = 16dt + 4b + r
+      float* dst = ws_acc + slot * D + 4 * b;    // lane (head, b) owns d = 16dt + 4b + r
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt)
+      for (int dt = 0; dt < S::kDt; ++dt)
         *reinterpret_cast<float4*>(dst + 16 * dt) = make_float4(o[dt][0], o[dt][1], o[dt][2], o[dt][3]);
       if (b == 0) ws_ml[slot] = make_float2(m_run, l_all);
     }
   };
   auto begin_segment = [&](const int seq, const int kvh) __attribute__((always_inline)) {
     cur_seg = seq * Hkv + kvh;
-    // Q^T operand: lane (head, b) holds Q[head][32*kk + 8*b .. +8]; padded heads are zero
+    // Q^T operand: lane (head, b) holds granules 4*kk + b of Q[head]; padded heads are zero
     const u32x4* qrow =
-        reinterpret_cast<const u32x4*>(q + (static_cast<size_t>(seq) * Hq + kvh * g + head) * kD);
+        reinterpret_cast<const u32x4*>(q + (static_cast<size_t>(seq) * Hq + kvh * g + head) * D);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
+    for (int kk = 0; kk < S::kLoads; ++kk) {
       u32x4 x = {0u, 0u, 0u, 0u};
       if (head < g) x = qrow[kk * 4 + b];
-      qf[kk] = __builtin_bit_cast(bf16x8, x);
+      qf[kk] = x;
     }
     // complete these loads here (rare path) so that the common path never has to wait
     // for anything younger than its own page prefetches
@@ -566,16 +633,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     m_run = -INFINITY;
     l_run = 0.0f;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) o[dt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int dt = 0; dt < S::kDt; ++dt) o[dt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   };
 
-  // One slot: park its page in LDS, refill the registers with the page NS slots ahead,
-  // then both products.  `code` is the slot's entry word (wave-uniform).
+  // One slot: park it in LDS, refill the registers with the slot NS ahead, then both
+  // products.  `code` is the slot's entry word (wave-uniform).
   // steady: the slot NS ahead exists, so the refill is unconditional (which lets the
   // compiler count outstanding loads exactly and keep the younger stages in flight).
-  auto do_slot = [&](PageRegs& r, int& code, const int i, auto steady) __attribute__((always_inline)) {
+  auto do_slot = [&](SlotRegs<S::kLoads>& r, int& code, const int i, auto steady) __attribute__((always_inline)) {
     constexpr bool kSteady = decltype(steady)::value;
-    const int valid = (code & 15) + 1;           // tokens of this page inside the context
+    const int valid = (code & 15) + 1;           // tokens of this piece inside the context
     const int kvh = (code >> kCodeKvhShift) & 255, seq = code >> kCodeSeqShift;
     if (seq * Hkv + kvh != cur_seg) {
       if (cur_seg >= 0) flush();
@@ -583,20 +650,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
       seg_whole = (code & kCodeFirst) != 0;     // ... so far: it starts inside this share
     }
     seg_ends = (code & kCodeLast) != 0;
-    // granule (j*64+lane) = token row 4j+b, column granule `head`
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      lds_k[swz_k(4 * j + b, head)] = r.k[j];
-      lds_v[swz_v(4 * j + b, head)] = r.v[j];
+    for (int j = 0; j < S::kLoads; ++j) {
+      const int gi = j * 64 + lane, row = gi / S::kRow, c = gi % S::kRow;
+      lds_k[S::k_at(row, c)] = r.k[j];
+      lds_v[S::v_at(row, c)] = r.v[j];
     }
-    if (kSteady || i + NS < n) {
-      int page;
-      next_entry(page, code);
-      load_page(r, k_cache, v_cache, page, Hkv, (code >> kCodeKvhShift) & 255, lane);
-    }
+    if (kSteady || i + NS < n) fetch(r, code);
     __syncthreads();
 #if defined(COPRIS_ATTN_PROBE_NO_COMPUTE)
-    // timing probe: the page is fetched and parked, nothing is computed from it
+    // timing probe: the slot is fetched and parked, nothing is computed from it
     {
       const u32x4 kk0 = lds_k[lane];
       const u32x4 vv0 = lds_v[lane];
@@ -607,14 +670,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     }
 #endif
 
-    // S^T[token][head]: A = K rows (token = lane&15), B = Q^T
+    // S^T[token][head]: A = K rows (token = lane&15), B = Q^T.  In fp32 the four elements of a
+    // granule are four products of depth 4 (the same order of head_dim on both sides).
     f32x4 sc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const bf16x8 kf = __builtin_bit_cast(bf16x8, lds_k[swz_k(head, 4 * kk + b)]);
-      sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[kk], sc, 0, 0, 0);
+    for (int kk = 0; kk < S::kLoads; ++kk) {
+      const u32x4 kf = lds_k[S::k_at(head, 4 * kk + b)];
+      if constexpr (kBf16) {
+        sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf),
+                                                     __builtin_bit_cast(bf16x8, qf[kk]), sc, 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          sc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kf[e]), __uint_as_float(qf[kk][e]), sc, 0, 0, 0);
+      }
     }
-    // this lane: head `head`, tokens 4b..4b+3 of the page
+    // this lane: head `head`, tokens 4b..4b+3 of the slot
     float t[4];
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) t[rr] = sc[rr] * scale_log2e;
@@ -632,73 +703,73 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) p[rr] = __builtin_amdgcn_exp2f(t[rr] - m_new);
     l_run = l_run * alpha + ((p[0] + p[1]) + (p[2] + p[3]));
-    const uint2 pk = make_uint2(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]));
-    const s16x4 pf = __builtin_bit_cast(s16x4, pk);
     if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) o[dt] *= alpha;
+      for (int dt = 0; dt < S::kDt; ++dt) o[dt] *= alpha;
     }
-    // O^T[d][head] += V^T[d][token] P^T[token][head]: A = V^T via the transposing
-    // read (lane supplies row 4b + L/4, columns 16dt + 4(L%4)..+3, L = lane&15)
-    const int vrow = 4 * b + (head >> 2);
-    const char* vbase = reinterpret_cast<const char*>(lds_v) + (head & 1) * 8;
+    // O^T[d][head] += V^T[d][token] P^T[token][head]; rows past the context may hold anything
+    // (NaN) and are zeroed
+    if constexpr (kBf16) {
+      const uint2 pk = make_uint2(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]));
+      const s16x4 pf = __builtin_bit_cast(s16x4, pk);
+      s16x4 pl = {0, 0, 0, 0};
+      if (SPLIT_P)
+        pl = __builtin_bit_cast(s16x4, make_uint2(pack_bf16x2(p[0] - bf16lo_to_f32(pk.x), p[1] - bf16hi_to_f32(pk.x)),
+                                                  pack_bf16x2(p[2] - bf16lo_to_f32(pk.y), p[3] - bf16hi_to_f32(pk.y))));
+      // A = V^T via the transposing read (lane supplies row 4b + L/4, columns
+      // 16dt + 4(L%4)..+3, L = lane&15)
+      const int vrow = 4 * b + (head >> 2);
+      const char* vbase = reinterpret_cast<const char*>(lds_v) + (head & 1) * 8;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) {
-      const char* addr = vbase + swz_v(vrow, 2 * dt + ((head & 3) >> 1)) * 16;
-      s16x4 vf = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-          (__attribute__((address_space(3))) s16x4*)(addr));
-      if (valid < kP) {   // rows past the context may hold anything (NaN): zero them
+      for (int dt = 0; dt < S::kDt; ++dt) {
+        const char* addr = vbase + S::v_at(vrow, 2 * dt + ((head & 3) >> 1)) * 16;
+        s16x4 vf = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) s16x4*)(addr));
+        if (valid < kP) {
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr)
-          vf[rr] = (4 * b + rr < valid) ? vf[rr] : static_cast<short>(0);
+          for (int rr = 0; rr < 4; ++rr)
+            vf[rr] = (4 * b + rr < valid) ? vf[rr] : static_cast<short>(0);
+        }
+        o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf, pf, o[dt], 0, 0, 0);
+        if (SPLIT_P) o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf, pl, o[dt], 0, 0, 0);
       }
-      o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf, pf, o[dt], 0, 0, 0);
+    } else {
+      // k-slot b of product rr is token 4b + rr: the weight is where the score product left it
+      const float* vrow = reinterpret_cast<const float*>(lds_v) + (head & 3);
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+#pragma unroll
+        for (int dt = 0; dt < S::kDt; ++dt) {
+          float vv = vrow[S::v_at(4 * b + rr, 4 * dt + (head >> 2)) * 4];
+          if (valid < kP) vv = 4 * b + rr < valid ? vv : 0.0f;
+          o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv, p[rr], o[dt], 0, 0, 0);
+        }
+      }
     }
-    __syncthreads();   // the next page may overwrite the LDS tiles
+    __syncthreads();   // the next slot may overwrite the LDS tiles
   };
 
-  static_assert(NS == 3, "the page pipeline below is written out for three stages");
-  PageRegs st0, st1, st2;
-  int c0 = 0, c1 = 0, c2 = 0;   // entry words of the slots held in st0..st2
+  SlotRegs<S::kLoads> stage[NS];
+  int code[NS];                    // entry words of the slots held in stage[]
   int i = 0;
-  {
-    int page;
-    next_entry(page, c0);
-    load_page(st0, k_cache, v_cache, page, Hkv, (c0 >> kCodeKvhShift) & 255, lane);
-  }
+  fetch(stage[0], code[0]);
   if (n >= 2 * NS) {
-    {
-      int page;
-      next_entry(page, c1);
-      load_page(st1, k_cache, v_cache, page, Hkv, (c1 >> kCodeKvhShift) & 255, lane);
-    }
-    {
-      int page;
-      next_entry(page, c2);
-      load_page(st2, k_cache, v_cache, page, Hkv, (c2 >> kCodeKvhShift) & 255, lane);
-    }
+#pragma unroll
+    for (int s = 1; s < NS; ++s) fetch(stage[s], code[s]);
     do {   // steady state: every refill exists
-      do_slot(st0, c0, i, std::true_type{});
-      do_slot(st1, c1, i + 1, std::true_type{});
-      do_slot(st2, c2, i + 2, std::true_type{});
+#pragma unroll
+      for (int s = 0; s < NS; ++s) do_slot(stage[s], code[s], i + s, std::true_type{});
       i += NS;
     } while (i + 2 * NS <= n);
   } else {
-    if (1 < n) {
-      int page;
-      next_entry(page, c1);
-      load_page(st1, k_cache, v_cache, page, Hkv, (c1 >> kCodeKvhShift) & 255, lane);
-    }
-    if (2 < n) {
-      int page;
-      next_entry(page, c2);
-      load_page(st2, k_cache, v_cache, page, Hkv, (c2 >> kCodeKvhShift) & 255, lane);
-    }
+#pragma unroll
+    for (int s = 1; s < NS; ++s)
+      if (s < n) fetch(stage[s], code[s]);
   }
-  for (; i < n; i += NS) {   // the last 3..5 slots of the share (or a short share)
-    do_slot(st0, c0, i, std::false_type{});
-    if (i + 1 < n) do_slot(st1, c1, i + 1, std::false_type{});
-    if (i + 2 < n) do_slot(st2, c2, i + 2, std::false_type{});
+  for (; i < n; i += NS) {   // the last slots of the share (or a short share)
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (i + s < n) do_slot(stage[s], code[s], i + s, std::false_type{});
   }
   flush();
 }
@@ -759,16 +830,18 @@ __global__ void attn_merge_kernel(const int32_t* __restrict__ seq_off,
 // touched by the wavefronts a/share .. (a+npg-1)/share; the partial of (wavefront w,
 // segment s) sits at index w + s.  A segment inside one share was stored by its wavefront
 // already; an empty sequence gets its zeros here.
-template <bool PRESCAN>
+// Grid (sequence, kv head, z): slice z takes the query heads z, z + gridDim.z, ... of the group.
+template <typename T, int D, bool PRESCAN>
 __global__ __launch_bounds__(256) void attn_merge_flat_kernel(const int32_t* __restrict__ ctx_len,
                                                               const int32_t* __restrict__ hdr,
                                                               const int32_t* __restrict__ seq_pg,
                                                               const float2* __restrict__ ws_ml,
                                                               const float* __restrict__ ws_acc,
-                                                              uint16_t* __restrict__ out,
+                                                              T* __restrict__ out,
                                                               float* __restrict__ lse, int C, int Hq,
                                                               int Hkv, int g, int max_tokens) {
-  // one workgroup per (sequence, kv head); a thread owns four head_dim indices of one head
+  constexpr int kQuads = D / 4;              // threads across the head_dim, four elements each
+  constexpr int kTeams = 256 / kQuads;
   __shared__ int s_before[256 / kWave], s_all[256 / kWave];
   const int seq = blockIdx.x, kvh = blockIdx.y;
   int share, npg, pg0;
@@ -777,11 +850,11 @@ __global__ __launch_bounds__(256) void attn_merge_flat_kernel(const int32_t* __r
     pg0 = seq_pg[seq];
     npg = seq_pg[seq + 1] - pg0;
   } else {
-    // pages before this sequence and in total, from ctx_len (the same counts the split
+    // pieces before this sequence and in total, from ctx_len (the same counts the split
     // kernel's wavefronts derived their cursors from)
     int before = 0, all = 0;
     for (int i = threadIdx.x; i < C; i += 256) {
-      const int pgs = attn_pages_of(ctx_len, i, max_tokens);
+      const int pgs = attn_pieces_of(ctx_len, i, max_tokens);
       all += pgs;
       before += i < seq ? pgs : 0;
     }
@@ -799,78 +872,174 @@ __global__ __launch_bounds__(256) void attn_merge_flat_kernel(const int32_t* __r
       pg0 += s_before[w];
       pages += s_all[w];
     }
-    const int total = pages * Hkv;
-    share = total > 0 ? (total + kAttnWaves - 1) / kAttnWaves : 1;
-    npg = attn_pages_of(ctx_len, seq, max_tokens);
+    share = attn_share(pages * Hkv);
+    npg = attn_pieces_of(ctx_len, seq, max_tokens);
   }
   const int64_t a = static_cast<int64_t>(pg0) * Hkv + static_cast<int64_t>(kvh) * npg;
   const int seg = seq * Hkv + kvh;
   const int w0 = npg > 0 ? static_cast<int>(a / share) : 0;
   const int n = npg > 0 ? static_cast<int>((a + npg - 1) / share) - w0 + 1 : 0;
   if (n == 1) return;   // stored by the one wavefront that saw it
-  for (int idx = threadIdx.x; idx < g * (kD / 4); idx += 256) {
-    const int h = idx / (kD / 4), d4 = idx - h * (kD / 4);
+
+  // The slice's heads are shared out over the teams of threads: `per_head` teams take the partials
+  // sub, sub + per_head, ... of one head, kBatch of them in flight (one round trip), and their
+  // results are combined in team order.  With a large pool a head has one team and nearly always
+  // one batch; with a small one a long context is cut by many shares, a slice is one head, and
+  // all teams work on it.
+  constexpr int kBatch = 6;
+  __shared__ float4 s_num[kTeams][kQuads];
+  __shared__ float2 s_ml[kTeams];
+  const int team = threadIdx.x / kQuads, d4 = threadIdx.x % kQuads;
+  const int heads = (g - static_cast<int>(blockIdx.z) + static_cast<int>(gridDim.z) - 1) / static_cast<int>(gridDim.z);
+  const int per_head = heads >= kTeams ? 1 : kTeams / heads;
+  const int sub = team % per_head;
+  auto store = [&](int h, float m_star, float denom, const float4& num) __attribute__((always_inline)) {
+    const size_t oh = static_cast<size_t>(seq) * Hq + kvh * g + h;
+    if (n > 0) store_out4(out + oh * D + 4 * d4, num.x / denom, num.y / denom, num.z / denom, num.w / denom);
+    else store_out4(out + oh * D + 4 * d4, 0.0f, 0.0f, 0.0f, 0.0f);
+    if (lse != nullptr && d4 == 0)
+      lse[oh] = n > 0 ? (m_star + __builtin_amdgcn_logf(denom)) * kLn2 : -INFINITY;
+  };
+  for (int h0 = 0; h0 < heads; h0 += kTeams / per_head) {
+    const int hi = h0 + team / per_head;
+    const bool mine = hi < heads && team < kTeams / per_head * per_head;
+    const int h = blockIdx.z + (mine ? hi : 0) * gridDim.z;
     const size_t slot0 = (static_cast<size_t>(w0) + seg) * g + h;   // consecutive wavefronts: stride g
-    float m_star = -INFINITY;
-    float denom = 0.0f;
+    float m_run = -INFINITY, denom = 0.0f;
     float4 num = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    constexpr int kFast = 6;
-    if (n <= kFast) {
-      // the usual case: all partials in flight at once (one round trip), then the same
-      // arithmetic in the same order as the loop below
-      float2 ml[kFast];
-      float4 x[kFast];
+    for (int e0 = mine ? sub : n; e0 < n; e0 += kBatch * per_head) {
+      float2 ml[kBatch];
+      float4 x[kBatch];
 #pragma unroll
-      for (int e = 0; e < kFast; ++e) {
-        const size_t slot = slot0 + static_cast<size_t>(e < n ? e : 0) * g;
-        ml[e] = ws_ml[slot];
-        x[e] = *reinterpret_cast<const float4*>(ws_acc + slot * kD + 4 * d4);
+      for (int u = 0; u < kBatch; ++u) {
+        const int e = e0 + u * per_head;
+        const size_t slot = slot0 + static_cast<size_t>(e < n ? e : e0) * g;
+        ml[u] = ws_ml[slot];
+        x[u] = *reinterpret_cast<const float4*>(ws_acc + slot * D + 4 * d4);
       }
+      float m_new = m_run;
 #pragma unroll
-      for (int e = 0; e < kFast; ++e)
-        if (e < n) m_star = fmaxf(m_star, ml[e].x);
+      for (int u = 0; u < kBatch; ++u)
+        if (e0 + u * per_head < n) m_new = fmaxf(m_new, ml[u].x);
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // 0 on the first batch
+      m_run = m_new;
+      denom *= alpha;
+      num.x *= alpha; num.y *= alpha; num.z *= alpha; num.w *= alpha;
 #pragma unroll
-      for (int e = 0; e < kFast; ++e) {
-        if (e < n) {
-          const float w = __builtin_amdgcn_exp2f(ml[e].x - m_star);
-          denom = fmaf(w, ml[e].y, denom);
-          num.x = fmaf(w, x[e].x, num.x);
-          num.y = fmaf(w, x[e].y, num.y);
-          num.z = fmaf(w, x[e].z, num.z);
-          num.w = fmaf(w, x[e].w, num.w);
+      for (int u = 0; u < kBatch; ++u) {
+        if (e0 + u * per_head < n) {
+          const float w = __builtin_amdgcn_exp2f(ml[u].x - m_new);
+          denom = fmaf(w, ml[u].y, denom);
+          num.x = fmaf(w, x[u].x, num.x);
+          num.y = fmaf(w, x[u].y, num.y);
+          num.z = fmaf(w, x[u].z, num.z);
+          num.w = fmaf(w, x[u].w, num.w);
         }
       }
-    } else {
-      for (int e = 0; e < n; ++e) m_star = fmaxf(m_star, ws_ml[slot0 + static_cast<size_t>(e) * g].x);
-      for (int e = 0; e < n; ++e) {
-        const size_t slot = slot0 + static_cast<size_t>(e) * g;
-        const float2 ml = ws_ml[slot];
-        const float4 x = *reinterpret_cast<const float4*>(ws_acc + slot * kD + 4 * d4);
-        const float w = __builtin_amdgcn_exp2f(ml.x - m_star);
-        denom = fmaf(w, ml.y, denom);
+    }
+    if (per_head == 1) {
+      if (mine) store(h, m_run, denom, num);
+      continue;
+    }
+    if (d4 == 0) s_ml[team] = make_float2(m_run, denom);
+    s_num[team][d4] = num;
+    __syncthreads();
+    if (mine && sub == 0) {
+      const int used = min(per_head, n);          // (a team without a partial has nothing to add)
+      float m_star = -INFINITY;
+      for (int e = 0; e < used; ++e) m_star = fmaxf(m_star, s_ml[team + e].x);
+      denom = 0.0f;
+      num = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      for (int e = 0; e < used; ++e) {
+        const float w = __builtin_amdgcn_exp2f(s_ml[team + e].x - m_star);
+        const float4 x = s_num[team + e][d4];
+        denom = fmaf(w, s_ml[team + e].y, denom);
         num.x = fmaf(w, x.x, num.x);
         num.y = fmaf(w, x.y, num.y);
         num.z = fmaf(w, x.z, num.z);
         num.w = fmaf(w, x.w, num.w);
       }
+      store(h, m_star, denom, num);
     }
-    const size_t oh = static_cast<size_t>(seq) * Hq + kvh * g + h;
-    ushort4 r = make_ushort4(0, 0, 0, 0);
-    if (n > 0) {
-      r.x = f32_to_bf16(num.x / denom);
-      r.y = f32_to_bf16(num.y / denom);
-      r.z = f32_to_bf16(num.z / denom);
-      r.w = f32_to_bf16(num.w / denom);
-    }
-    *reinterpret_cast<ushort4*>(out + oh * kD + 4 * d4) = r;
-    if (lse != nullptr && d4 == 0)
-      lse[oh] = n > 0 ? (m_star + __builtin_amdgcn_logf(denom)) * kLn2 : -INFINITY;
+    __syncthreads();
   }
 }
 
 // --------------------------------------------------------------------------
 // host launcher
 // --------------------------------------------------------------------------
+constexpr int kMergeFill = 1024;   // workgroups of the merge that fill the chip
+
+struct AttnFlatArgs {
+  const void *q, *k_cache, *v_cache;
+  const int32_t *block_table, *ctx_len;
+  int32_t *hdr, *seq_off;
+  int4* start;
+  float2* ws_ml;
+  float* ws_acc;
+  void* out;
+  float* lse;
+  int C, Hq, Hkv, g, page_size, max_pages, max_tokens;
+  float scale_log2e;
+  hipStream_t stream;
+};
+
+template <typename T, int D, int NS, bool PRESCAN>
+static void enqueue_split(const AttnFlatArgs& a, int waves) {
+#define COPRIS_SPLIT(PG, SPLIT_P, LSP)                                                                    \
+  hipLaunchKernelGGL((attn_split_flat_kernel<T, D, PRESCAN, PG, SPLIT_P, NS>), dim3(waves), dim3(64), 0,  \
+                     a.stream, static_cast<const T*>(a.q), static_cast<const u32x4*>(a.k_cache),          \
+                     static_cast<const u32x4*>(a.v_cache), a.block_table, a.ctx_len, a.hdr, a.start,      \
+                     a.ws_ml, a.ws_acc, static_cast<T*>(a.out), a.lse, a.C, a.Hq, a.Hkv, a.g, LSP,        \
+                     a.max_pages, a.max_tokens, a.scale_log2e)
+  constexpr bool kSplitP = sizeof(T) == 2;
+  if (a.page_size == 16) COPRIS_SPLIT(16, kSplitP && D != 128, 0);
+  else if (a.page_size == 8) COPRIS_SPLIT(8, kSplitP, 0);
+  else COPRIS_SPLIT(0, kSplitP, __builtin_ctz(static_cast<unsigned>(a.page_size / kP)));   // page_size divides 512
+#undef COPRIS_SPLIT
+}
+
+template <typename T, int D, int NS>
+static int launch_flat(const AttnFlatArgs& a) {
+  const hipStream_t stream = a.stream;
+  const bool prescan = a.C > kAttnMaxSeqInKernelCursor;
+  if (prescan) {
+    COPRIS_PRE("attn_scan_kernel");
+    hipLaunchKernelGGL(attn_scan_kernel, dim3(1), dim3(kListThreads), 0, stream, a.ctx_len, a.C,
+                       a.max_tokens, a.Hkv, a.hdr, a.seq_off, a.start);
+    COPRIS_POST("attn_scan_kernel");
+  }
+  // no more wavefronts than the longest contexts that the block table admits give shares
+  const int64_t most = (static_cast<int64_t>(a.C) * ((a.max_tokens + kP - 1) / kP) * a.Hkv + kMinShare - 1) / kMinShare;
+  const int waves = static_cast<int>(most < kAttnWaves ? most : kAttnWaves);
+  COPRIS_PRE("attn_split_flat_kernel");
+  if (prescan) {
+    enqueue_split<T, D, NS, true>(a, waves);
+  } else {
+    enqueue_split<T, D, NS, false>(a, waves);
+  }
+  COPRIS_POST("attn_split_flat_kernel");
+  // Small pools: the heads of a group get workgroups of their own, because a long context is then
+  // cut by many shares and its partials are what the merge waits for (64 sequences, 12 / 2 heads,
+  // the longest context in 66 shares: 29 us with one workgroup per segment walking them one
+  // after the other, 6 us here; at 256 sequences, 28 / 4 heads, one per segment: 10 -> 8 us).
+  int z = kMergeFill / (a.C * a.Hkv);
+  z = z < 1 ? 1 : (z < a.g ? z : a.g);
+  const dim3 grid(a.C, a.Hkv, z);
+  COPRIS_PRE("attn_merge_flat_kernel");
+  if (prescan) {
+    hipLaunchKernelGGL((attn_merge_flat_kernel<T, D, true>), grid, dim3(256), 0, stream, a.ctx_len, a.hdr,
+                       a.seq_off, a.ws_ml, a.ws_acc, static_cast<T*>(a.out), a.lse, a.C, a.Hq, a.Hkv, a.g,
+                       a.max_tokens);
+  } else {
+    hipLaunchKernelGGL((attn_merge_flat_kernel<T, D, false>), grid, dim3(256), 0, stream, a.ctx_len, a.hdr,
+                       a.seq_off, a.ws_ml, a.ws_acc, static_cast<T*>(a.out), a.lse, a.C, a.Hq, a.Hkv, a.g,
+                       a.max_tokens);
+  }
+  COPRIS_POST("attn_merge_flat_kernel");
+  return 0;
+}
+
 int launch_decode_attn(const void* q, const void* k_cache, const void* v_cache,
                        const int32_t* block_table, const int32_t* ctx_len, void* out, float* lse,
                        void* workspace, int C, int Hq, int Hkv, int D, int page_size,
@@ -887,45 +1056,16 @@ int launch_decode_attn(const void* q, const void* k_cache, const void* v_cache,
   const int max_tokens = static_cast<int>(max_tokens64);
   const float scale_log2e = scale * kLog2e;
 
-  // the flat slot stream packs the kv head in 8 bits and the sequence in 17
-  const bool tuned = dtype == 1 && D == kD && page_size == kP && Hkv <= 256 && C < kAttnMaxSeqTuned &&
-                     static_cast<int64_t>(C) * max_pages * Hkv < (1ll << 31);
-  if (tuned) {
-    int4* start = reinterpret_cast<int4*>(list);   // kAttnWaves start cursors (the list area is larger)
-    const bool prescan = C > kAttnMaxSeqInKernelCursor;
-    if (prescan) {
-      COPRIS_PRE("attn_scan_kernel");
-      hipLaunchKernelGGL(attn_scan_kernel, dim3(1), dim3(kListThreads), 0, stream, ctx_len, C,
-                         max_tokens, Hkv, hdr, seq_off, start);
-      COPRIS_POST("attn_scan_kernel");
-    }
-    COPRIS_PRE("attn_split_flat_kernel");
-    if (prescan) {
-      hipLaunchKernelGGL((attn_split_flat_kernel<3, true>), dim3(kAttnWaves), dim3(64), 0, stream,
-                         static_cast<const uint16_t*>(q), static_cast<const u32x4*>(k_cache),
-                         static_cast<const u32x4*>(v_cache), block_table, ctx_len, hdr, start, ws_ml,
-                         ws_acc, static_cast<uint16_t*>(out), lse, C, Hq, Hkv, g, max_pages, max_tokens,
-                         scale_log2e);
-    } else {
-      hipLaunchKernelGGL((attn_split_flat_kernel<3, false>), dim3(kAttnWaves), dim3(64), 0, stream,
-                         static_cast<const uint16_t*>(q), static_cast<const u32x4*>(k_cache),
-                         static_cast<const u32x4*>(v_cache), block_table, ctx_len, hdr, start, ws_ml,
-                         ws_acc, static_cast<uint16_t*>(out), lse, C, Hq, Hkv, g, max_pages, max_tokens,
-                         scale_log2e);
-    }
-    COPRIS_POST("attn_split_flat_kernel");
-    COPRIS_PRE("attn_merge_flat_kernel");
-    if (prescan) {
-      hipLaunchKernelGGL(attn_merge_flat_kernel<true>, dim3(C, Hkv), dim3(256), 0, stream, ctx_len, hdr,
-                         seq_off, ws_ml, ws_acc, static_cast<uint16_t*>(out), lse, C, Hq, Hkv, g,
-                         max_tokens);
-    } else {
-      hipLaunchKernelGGL(attn_merge_flat_kernel<false>, dim3(C, Hkv), dim3(256), 0, stream, ctx_len, hdr,
-                         seq_off, ws_ml, ws_acc, static_cast<uint16_t*>(out), lse, C, Hq, Hkv, g,
-                         max_tokens);
-    }
-    COPRIS_POST("attn_merge_flat_kernel");
-    return 0;
+  // The flat slot stream packs the kv head in 8 bits and the sequence in 17.  Pages of 1, 2 or 4
+  // tokens stay with the generic kernels (a slot would gather rows from 4 to 16 pages).
+  const int64_t max_pieces = (max_tokens64 + kP - 1) / kP;
+  const bool flat = (page_size == 8 || page_size % kP == 0) && Hkv <= 256 && C < kAttnMaxSeqTuned &&
+                    static_cast<int64_t>(C) * max_pieces * Hkv < (1ll << 31);
+  if (flat) {
+    AttnFlatArgs a{q, k_cache, v_cache, block_table, ctx_len, hdr, seq_off, reinterpret_cast<int4*>(list),
+                   ws_ml, ws_acc, out, lse, C, Hq, Hkv, g, page_size, max_pages, max_tokens, scale_log2e, stream};
+    if (dtype == 1) return D == 128 ? launch_flat<uint16_t, 128, 3>(a) : launch_flat<uint16_t, 64, 4>(a);
+    return D == 128 ? launch_flat<float, 128, 2>(a) : launch_flat<float, 64, 3>(a);
   }
 
   COPRIS_PRE("attn_worklist_kernel");

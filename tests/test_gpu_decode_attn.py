@@ -51,6 +51,41 @@ def test_generic_path_other_page_size(R):
     _run_case(R, case, W.BF16, "page8")
 
 
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("page", [1, 4, 8, 16, 32, 512])
+def test_every_page_geometry(R, dtype, D, page):
+    # contexts that end before, on and after the middle and the end of a 16-token piece and of a
+    # page, an empty one, and one that many shares cut; unused slots and table entries are poisoned
+    ctx = [1, 7, 8, 9, 15, 16, 17, 24, 25, 0, 31, 32, 33, 500, 513, 5000]
+    case = W.make_small_decode_case(300 + D + page, len(ctx), 6, 2, D, dtype, page, ctx)
+    _run_case(R, case, dtype, f"{dtype} D={D} page={page}")
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(16, 1), (10, 2), (3, 3)])
+@pytest.mark.parametrize("dtype,D", [(W.F32, 64), (W.BF16, 128), (W.BF16, 64)])
+def test_a_context_that_hundreds_of_shares_cut(R, dtype, D, Hq, Hkv):
+    # few sequences: the merge spreads a segment's heads and partials over workgroups and teams
+    # (16, 5 and 1 heads in a group: more heads than teams, a remainder, and all teams on one head)
+    ctx = [12000, 70, 0, 6001]
+    case = W.make_small_decode_case(400 + D + Hq, len(ctx), Hq, Hkv, D, dtype, 16, ctx)
+    _run_case(R, case, dtype, f"{dtype} D={D} {Hq}/{Hkv}")
+
+
+@pytest.mark.parametrize("D,page", [(64, 16), (128, 8), (128, 32)])
+def test_bf16_weights_keep_their_precision(R, D, page):
+    # Outside head_dim 128 / page 16 the weights are not rounded to bf16: what is left is the
+    # result's own rounding, 2^-9 relative at worst for one element and 2^-9 / sqrt(3) in the
+    # 2-norm for uniformly spread mantissas (1.13e-3; up to 1.95e-3 if all mantissas were 1.0).
+    ctx = [700, 1033, 64, 2000]
+    case = W.make_small_decode_case(500 + D + page, len(ctx), 12, 2, D, W.BF16, page, ctx)
+    out, _ = R.run_decode_attn(case, W.BF16)
+    ref, _ = P.oracle_attn(case, W.BF16)
+    exact_rounding = W.bf16_bits_to_f32(W.f32_to_bf16_bits(ref.astype(np.float32)))
+    floor = np.linalg.norm(exact_rounding - ref) / np.linalg.norm(ref)
+    assert np.linalg.norm(out - ref) / np.linalg.norm(ref) <= 1.02 * floor
+
+
 def test_page_permutation_is_bitwise_invariant_and_runs_are_reproducible(R):
     ctx = [1000, 37, 1536, 513]
     case = W.make_small_decode_case(7, 4, 28, 4, 128, W.BF16, 16, ctx)
