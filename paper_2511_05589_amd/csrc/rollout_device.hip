@@ -6,8 +6,7 @@
 //                          advances the slot
 //   traj_gather_kernel     buffer rows -> the packed training batch (Eq. 6: the per-stage
 //                          pieces of a trajectory, concatenated in token order)
-// All of them move a few bytes per slot or per token: plain copies with bounds checks, no
-// tuning beyond coalesced access.
+// All of them move a few bytes per slot or per token: plain copies with bounds checks.
 #include "copris.h"
 #include "copris_device.h"
 #include "copris_internal.h"
@@ -75,31 +74,73 @@ __global__ __launch_bounds__(256) void traj_append_kernel(
   ctx_len[c] += 1;
 }
 
-// One workgroup per trajectory of the batch.
+// A trajectory's tokens are shared out over `parts` workgroups in pieces of kGatherPiece, and
+// where that is more than one a workgroup of its own counts the trajectory's earlier tokens
+// (4 of the 24 bytes per token are read twice for it, which a counter in memory and a launch to
+// clear it would cost more than).  What bounds it is bytes in flight: a thread moves kGatherDeep
+// tokens per round trip to memory.  256 trajectories of 1024..16384 tokens, 2.2 M in all (53 MB):
+// 12 us, where one workgroup per trajectory with one token per thread in flight took 39.
+constexpr int kGatherPiece = 2048;
+constexpr int kGatherDeep = 8;
+static_assert(kGatherPiece == 256 * kGatherDeep, "a piece is one round trip of a workgroup");
+
 __global__ __launch_bounds__(256) void traj_gather_kernel(
     const int32_t* __restrict__ buf_token, const float* __restrict__ buf_logp,
     const int32_t* __restrict__ buf_tag, const int32_t* __restrict__ traj,
     const int32_t* __restrict__ cu_seqlens, int stage, int32_t* __restrict__ tokens_out,
     float* __restrict__ logp_buf_out, float* __restrict__ logp_roll_out,
-    int32_t* __restrict__ split_out, int64_t n_traj, int max_resp) {
+    int32_t* __restrict__ split_out, int64_t n_traj, int max_resp, int parts) {
   __shared__ int s_cnt[256 / kWave];
-  const int b = blockIdx.x;
+  const int per_traj = parts == 1 ? 1 : parts + 1;
+  const int b = blockIdx.x / per_traj, part = blockIdx.x % per_traj;
   const int64_t tr = traj[b];
   const int64_t j0 = cu_seqlens[b];
   int64_t len = static_cast<int64_t>(cu_seqlens[b + 1]) - j0;
   len = len < 0 ? 0 : (len > max_resp ? max_resp : len);
   const bool ok = tr >= 0 && tr < n_traj;
   const float nan = __int_as_float(0x7fc00000);
+  const size_t row = static_cast<size_t>(ok ? tr : 0) * max_resp;
   int earlier_cnt = 0;
-  for (int64_t t = threadIdx.x; t < len; t += 256) {
-    const size_t at = static_cast<size_t>(ok ? tr : 0) * max_resp + t;
-    const bool earlier = ok && buf_tag[at] < stage;
-    const float lp = ok ? buf_logp[at] : nan;
-    tokens_out[j0 + t] = ok ? buf_token[at] : -1;
-    logp_buf_out[j0 + t] = earlier ? lp : nan;
-    logp_roll_out[j0 + t] = earlier ? nan : lp;
-    earlier_cnt += earlier ? 1 : 0;
+  if (part < parts) {
+    for (int64_t t0 = static_cast<int64_t>(part) * kGatherPiece; t0 < len;
+         t0 += static_cast<int64_t>(parts) * kGatherPiece) {
+      int32_t tag[kGatherDeep], tok[kGatherDeep];
+      float lp[kGatherDeep];
+#pragma unroll
+      for (int u = 0; u < kGatherDeep; ++u) {
+        const int64_t t = t0 + u * 256 + threadIdx.x;
+        const size_t at = row + static_cast<size_t>(t < len ? t : 0);
+        tag[u] = buf_tag[at];
+        lp[u] = buf_logp[at];
+        tok[u] = buf_token[at];
+      }
+#pragma unroll
+      for (int u = 0; u < kGatherDeep; ++u) {
+        const int64_t t = t0 + u * 256 + threadIdx.x;
+        if (t < len) {
+          const bool earlier = ok && tag[u] < stage;
+          const float x = ok ? lp[u] : nan;
+          tokens_out[j0 + t] = ok ? tok[u] : -1;
+          logp_buf_out[j0 + t] = earlier ? x : nan;
+          logp_roll_out[j0 + t] = earlier ? nan : x;
+          earlier_cnt += earlier ? 1 : 0;
+        }
+      }
+    }
+  } else if (ok) {
+    for (int64_t t0 = 0; t0 < len; t0 += 2 * kGatherPiece) {
+      int32_t tag[2 * kGatherDeep];
+#pragma unroll
+      for (int u = 0; u < 2 * kGatherDeep; ++u) {
+        const int64_t t = t0 + u * 256 + threadIdx.x;
+        tag[u] = buf_tag[row + static_cast<size_t>(t < len ? t : 0)];
+      }
+#pragma unroll
+      for (int u = 0; u < 2 * kGatherDeep; ++u)
+        earlier_cnt += (t0 + u * 256 + threadIdx.x < len && tag[u] < stage) ? 1 : 0;
+    }
   }
+  if (part != per_traj - 1) return;   // the last one has seen every token
   const int w = wave_sum_i(earlier_cnt);
   if ((threadIdx.x & (kWave - 1)) == 0) s_cnt[threadIdx.x / kWave] = w;
   __syncthreads();
@@ -189,10 +230,17 @@ int copris_traj_gather(const int32_t* buf_token, const float* buf_logp, const in
     return COPRIS_EINVAL;
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   (void)hipGetLastError();
+  // as many workgroups per trajectory as the longest row has pieces, while that fills the chip
+  // (more trajectories than kGatherFill need no splitting)
+  constexpr int kGatherFill = 8192;
+  const int pieces = (max_resp - 1) / copris::kGatherPiece + 1;
+  const int room = kGatherFill / B > 1 ? kGatherFill / B : 1;
+  const int parts = pieces < room ? pieces : room;
+  const unsigned grid = static_cast<unsigned>(B) * static_cast<unsigned>(parts == 1 ? 1 : parts + 1);
   COPRIS_PRE("traj_gather_kernel");
-  hipLaunchKernelGGL(copris::traj_gather_kernel, dim3(B), dim3(256), 0, stream, buf_token, buf_logp,
+  hipLaunchKernelGGL(copris::traj_gather_kernel, dim3(grid), dim3(256), 0, stream, buf_token, buf_logp,
                      buf_tag, traj, cu_seqlens, stage, tokens_out, logp_buf_out, logp_roll_out,
-                     split_out, n_traj, max_resp);
+                     split_out, n_traj, max_resp, parts);
   COPRIS_POST("traj_gather_kernel");
   return COPRIS_OK;
 }

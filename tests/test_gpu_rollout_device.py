@@ -131,6 +131,39 @@ def test_buffer_append_and_concatenation(gpu):
     assert ((tags >= 0).sum(axis=1) == gen).all()
 
 
+@pytest.mark.parametrize("lens", [[0, 1, 255, 256, 257, 2047, 2048, 2049, 4095, 4096, 4097, 9001],   # pieces shared out
+                                  [1] * 3000 + [2049] + [3] * 6000])                                # ... and one workgroup each
+def test_gather_over_piece_boundaries(gpu, lens):
+    # plain numpy of what the call is defined as, with earlier tokens anywhere in a row (the call
+    # counts tags, it does not look for a boundary) and one trajectory outside the buffer
+    torch, binding, runner, dev = gpu
+    rng = np.random.default_rng(len(lens))
+    B, max_resp, stage = len(lens), max(lens) + 5, 4
+    rows = B + 3 if B < 100 else 40
+    tok, tag = rng.integers(0, 999, (rows, max_resp)), rng.integers(2, 6, (rows, max_resp))
+    lp = rng.normal(size=(rows, max_resp)).astype(np.float32)
+    traj = rng.permutation(rows)[:B] if B < 100 else rng.integers(0, rows, B)
+    traj[1] = rows
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    N = int(cu[-1])
+    up = lambda a, t=np.int32: torch.from_numpy(np.ascontiguousarray(a, dtype=t)).to(dev)
+    tokens = torch.full((N,), -7, dtype=torch.int32, device=dev)
+    lb, lr = torch.zeros(N, device=dev), torch.zeros(N, device=dev)
+    split = torch.full((B,), -7, dtype=torch.int32, device=dev)
+    binding.traj_gather(up(tok), up(lp, np.float32), up(tag), up(traj), up(cu), stage, tokens, lb, lr, split)
+    torch.cuda.synchronize()
+    b = np.repeat(np.arange(B), lens)
+    t = np.arange(N) - cu[b]
+    ok = traj[b] < rows
+    at = (np.where(ok, traj[b], 0), t)
+    earlier = ok & (tag[at] < stage)
+    x = np.where(ok, lp[at], np.float32(np.nan))
+    np.testing.assert_array_equal(tokens.cpu().numpy(), np.where(ok, tok[at], -1))
+    np.testing.assert_array_equal(lb.cpu().numpy(), np.where(earlier, x, np.float32(np.nan)))
+    np.testing.assert_array_equal(lr.cpu().numpy(), np.where(earlier, np.float32(np.nan), x))
+    np.testing.assert_array_equal(split.cpu().numpy(), np.bincount(b, weights=earlier, minlength=B).astype(int))
+
+
 def test_empty_calls_enqueue_nothing(gpu):
     torch, binding, runner, dev = gpu
     lib = binding.load_library()
