@@ -141,39 +141,56 @@ def set_launch_hook(fn) -> None:
     lib.copris_set_launch_hook(ctypes.cast(_hook_ref, c_void_p), None)
 
 
-def _ptr(t) -> Optional[int]:
-    return None if t is None else t.data_ptr()
+_torch_dtypes = {}   # name -> torch dtype; filled on first use (torch is not imported with this module)
 
 
-def _expect(t, dtype: Optional[str], name: str, optional: bool = False) -> None:
-    """Host-side check of a tensor argument before its address crosses the C ABI: on the GPU,
-    contiguous, of the expected torch dtype (a name such as "int32"; None = any)."""
+def _dtype(name: str):
+    d = _torch_dtypes.get(name)
+    if d is None:
+        import torch
+        d = _torch_dtypes[name] = getattr(torch, name)
+    return d
+
+
+def _arg(t, dtype: Optional[str], name: str, optional: bool = False) -> Optional[int]:
+    """The device address of a tensor argument, after the host-side checks it must pass before it
+    crosses the C ABI: on the GPU, contiguous, of the expected torch dtype (a name such as "int32";
+    None = any).  A decode step passes some 35 tensors through here, so the way of a good one is
+    three comparisons."""
     if t is None:
         if optional:
-            return
+            return None
         raise TypeError(f"{name}: a device tensor is required")
+    if t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype == _dtype(dtype)):
+        return t.data_ptr()
     if not t.is_cuda:
         raise TypeError(f"{name}: must be a GPU tensor, got device {t.device}")
     if not t.is_contiguous():
         raise TypeError(f"{name}: must be contiguous")
-    if dtype is not None and str(t.dtype) != "torch." + dtype:
-        raise TypeError(f"{name}: expected torch.{dtype}, got {t.dtype}")
+    raise TypeError(f"{name}: expected torch.{dtype}, got {t.dtype}")
 
 
 def _elem(dtype_code: int) -> str:
     return {COPRIS_F32: "float32", COPRIS_BF16: "bfloat16"}.get(int(dtype_code))
 
 
-def _stream(stream, ref=None) -> Optional[int]:
+_raw_stream = None   # device index -> raw handle of torch's current stream
+
+
+def _stream(stream, ref) -> Optional[int]:
     """The raw stream handle (None = the null stream); `ref` is a tensor argument of the call,
     which must live on the stream's device."""
+    global _raw_stream
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream(ref.device if ref is not None else None)
-    if ref is not None and stream.device != ref.device:
+        if _raw_stream is None:
+            import torch
+            # the handle alone: a torch.cuda.Stream object per call costs 2 us
+            _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+                lambda i: torch.cuda.current_stream(i).cuda_stream)
+        return _raw_stream(ref.get_device()) or None
+    if stream.device != ref.device:
         raise TypeError(f"stream on {stream.device} but tensors on {ref.device}")
-    h = stream.cuda_stream
-    return h if h else None
+    return stream.cuda_stream or None
 
 
 def _check(code: int, where: str) -> None:
@@ -189,16 +206,16 @@ def decode_attn(q, k_cache, v_cache, block_table, ctx_len, out, lse, workspace, 
                 dtype: int, stream=None) -> None:
     """copris_decode_attn on device tensors (shapes as in include/copris.h)."""
     e = _elem(dtype)
-    _expect(q, e, "q"); _expect(k_cache, e, "k_cache"); _expect(v_cache, e, "v_cache"); _expect(out, e, "out")
-    _expect(block_table, "int32", "block_table"); _expect(ctx_len, "int32", "ctx_len")
-    _expect(lse, "float32", "lse", optional=True); _expect(workspace, "uint8", "workspace")
+    ptrs = (_arg(q, e, "q"), _arg(k_cache, e, "k_cache"), _arg(v_cache, e, "v_cache"))
+    out_ = _arg(out, e, "out")
+    ptrs += (_arg(block_table, "int32", "block_table"), _arg(ctx_len, "int32", "ctx_len"), out_,
+             _arg(lse, "float32", "lse", optional=True), _arg(workspace, "uint8", "workspace"))
     C, Hq, D = q.shape
     num_pages, Hkv, page_size, _ = k_cache.shape
     max_pages = block_table.shape[1]
     code = load_library().copris_decode_attn(
-        _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(ctx_len), _ptr(out),
-        _ptr(lse), _ptr(workspace), workspace.numel() * workspace.element_size(),
-        C, Hq, Hkv, D, page_size, max_pages, num_pages, float(scale), int(dtype), _stream(stream, q))
+        *ptrs, workspace.numel(), C, Hq, Hkv, D, page_size, max_pages, num_pages, float(scale), int(dtype),
+        _stream(stream, q))
     _check(code, "copris_decode_attn")
 
 
@@ -210,15 +227,15 @@ def lmhead_logprob(hidden, weight, seq_id, step, token, logprob, lse, workspace,
                    temperature: float, dtype: int, stream=None) -> None:
     """copris_lmhead_logprob on device tensors."""
     e = _elem(dtype)
-    _expect(hidden, e, "hidden"); _expect(weight, e, "weight"); _expect(seq_id, "int64", "seq_id")
-    _expect(step, "int32", "step"); _expect(token, "int32", "token"); _expect(logprob, "float32", "logprob")
-    _expect(lse, "float32", "lse", optional=True); _expect(workspace, "uint8", "workspace")
+    ins = (_arg(hidden, e, "hidden"), _arg(weight, e, "weight"), _arg(seq_id, "int64", "seq_id"),
+           _arg(step, "int32", "step"))
+    outs = (_arg(token, "int32", "token"), _arg(logprob, "float32", "logprob"),
+            _arg(lse, "float32", "lse", optional=True), _arg(workspace, "uint8", "workspace"))
     C, H = hidden.shape
     V = weight.shape[0]
     code = load_library().copris_lmhead_logprob(
-        _ptr(hidden), _ptr(weight), _ptr(seq_id), _ptr(step), int(seed) & 0xFFFFFFFFFFFFFFFF,
-        float(temperature), _ptr(token), _ptr(logprob), _ptr(lse), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), C, H, V, int(dtype), _stream(stream, hidden))
+        *ins, int(seed) & 0xFFFFFFFFFFFFFFFF, float(temperature), *outs, workspace.numel(), C, H, V, int(dtype),
+        _stream(stream, hidden))
     _check(code, "copris_lmhead_logprob")
 
 
@@ -226,51 +243,48 @@ def lmhead_logprob_noalloc(hidden, weight, seq_id, step, token, logprob, lse, *,
                            temperature: float, dtype: int, stream=None) -> None:
     """copris_lmhead_logprob_noalloc on device tensors (partials in the library's static array)."""
     e = _elem(dtype)
-    _expect(hidden, e, "hidden"); _expect(weight, e, "weight"); _expect(seq_id, "int64", "seq_id")
-    _expect(step, "int32", "step"); _expect(token, "int32", "token"); _expect(logprob, "float32", "logprob")
-    _expect(lse, "float32", "lse", optional=True)
+    ins = (_arg(hidden, e, "hidden"), _arg(weight, e, "weight"), _arg(seq_id, "int64", "seq_id"),
+           _arg(step, "int32", "step"))
+    outs = (_arg(token, "int32", "token"), _arg(logprob, "float32", "logprob"),
+            _arg(lse, "float32", "lse", optional=True))
     C, H = hidden.shape
     V = weight.shape[0]
     code = load_library().copris_lmhead_logprob_noalloc(
-        _ptr(hidden), _ptr(weight), _ptr(seq_id), _ptr(step), int(seed) & 0xFFFFFFFFFFFFFFFF,
-        float(temperature), _ptr(token), _ptr(logprob), _ptr(lse), C, H, V, int(dtype),
-        _stream(stream, hidden))
+        *ins, int(seed) & 0xFFFFFFFFFFFFFFFF, float(temperature), *outs, C, H, V, int(dtype), _stream(stream, hidden))
     _check(code, "copris_lmhead_logprob_noalloc")
 
 
 def is_ratio(logp_cur, logp_buf, logp_roll, cu_seqlens, split, mask, ratio, ratio_clipped,
              seq_sum, seq_cnt, seq_nclip, *, eps_low: float, eps_high: float, stream=None) -> None:
     """copris_is_ratio on device tensors."""
-    for t, n in ((logp_cur, "logp_cur"), (logp_buf, "logp_buf"), (logp_roll, "logp_roll"), (ratio, "ratio"),
-                 (ratio_clipped, "ratio_clipped"), (seq_sum, "seq_sum")):
-        _expect(t, "float32", n)
-    for t, n in ((cu_seqlens, "cu_seqlens"), (split, "split"), (seq_cnt, "seq_cnt"), (seq_nclip, "seq_nclip")):
-        _expect(t, "int32", n)
-    _expect(mask, "uint8", "mask", optional=True)
+    f32, i32 = "float32", "int32"
+    cur, buf, roll = _arg(logp_cur, f32, "logp_cur"), _arg(logp_buf, f32, "logp_buf"), _arg(logp_roll, f32, "logp_roll")
+    r, rc, ssum = _arg(ratio, f32, "ratio"), _arg(ratio_clipped, f32, "ratio_clipped"), _arg(seq_sum, f32, "seq_sum")
+    cu, sp = _arg(cu_seqlens, i32, "cu_seqlens"), _arg(split, i32, "split")
+    cnt, nclip = _arg(seq_cnt, i32, "seq_cnt"), _arg(seq_nclip, i32, "seq_nclip")
+    m = _arg(mask, "uint8", "mask", optional=True)
     B = cu_seqlens.numel() - 1
     N = logp_cur.numel()
     code = load_library().copris_is_ratio(
-        _ptr(logp_cur), _ptr(logp_buf), _ptr(logp_roll), _ptr(cu_seqlens), _ptr(split), _ptr(mask),
-        float(eps_low), float(eps_high), _ptr(ratio), _ptr(ratio_clipped), _ptr(seq_sum),
-        _ptr(seq_cnt), _ptr(seq_nclip), B, N, _stream(stream, cu_seqlens))
+        cur, buf, roll, cu, sp, m, float(eps_low), float(eps_high), r, rc, ssum, cnt, nclip, B, N,
+        _stream(stream, cu_seqlens))
     _check(code, "copris_is_ratio")
 
 
 def grpo_surrogate(logp_cur, logp_buf, logp_roll, cu_seqlens, split, mask, adv, surr, grad, seq_surr,
                    seq_cnt, objective, *, eps_low: float, eps_high: float, stream=None) -> None:
     """copris_grpo_surrogate on device tensors."""
-    for t, n in ((logp_cur, "logp_cur"), (logp_buf, "logp_buf"), (logp_roll, "logp_roll"), (adv, "adv"),
-                 (surr, "surr"), (grad, "grad"), (seq_surr, "seq_surr"), (objective, "objective")):
-        _expect(t, "float32", n)
-    for t, n in ((cu_seqlens, "cu_seqlens"), (split, "split"), (seq_cnt, "seq_cnt")):
-        _expect(t, "int32", n)
-    _expect(mask, "uint8", "mask", optional=True)
+    f32, i32 = "float32", "int32"
+    cur, buf, roll = _arg(logp_cur, f32, "logp_cur"), _arg(logp_buf, f32, "logp_buf"), _arg(logp_roll, f32, "logp_roll")
+    a, sr, gr = _arg(adv, f32, "adv"), _arg(surr, f32, "surr"), _arg(grad, f32, "grad")
+    ssurr, obj = _arg(seq_surr, f32, "seq_surr"), _arg(objective, f32, "objective")
+    cu, sp, cnt = _arg(cu_seqlens, i32, "cu_seqlens"), _arg(split, i32, "split"), _arg(seq_cnt, i32, "seq_cnt")
+    m = _arg(mask, "uint8", "mask", optional=True)
     B = cu_seqlens.numel() - 1
     N = logp_cur.numel()
     code = load_library().copris_grpo_surrogate(
-        _ptr(logp_cur), _ptr(logp_buf), _ptr(logp_roll), _ptr(cu_seqlens), _ptr(split), _ptr(mask),
-        _ptr(adv), float(eps_low), float(eps_high), _ptr(surr), _ptr(grad), _ptr(seq_surr),
-        _ptr(seq_cnt), _ptr(objective), B, N, _stream(stream, objective))
+        cur, buf, roll, cu, sp, m, a, float(eps_low), float(eps_high), sr, gr, ssurr, cnt, obj, B, N,
+        _stream(stream, objective))
     _check(code, "copris_grpo_surrogate")
 
 
@@ -282,15 +296,13 @@ def lmhead_token_logprob(hidden, weight, tokens, logprob, lse, workspace, *, tem
                          dtype: int, stream=None) -> None:
     """copris_lmhead_token_logprob on device tensors."""
     e = _elem(dtype)
-    _expect(hidden, e, "hidden"); _expect(weight, e, "weight"); _expect(tokens, "int32", "tokens")
-    _expect(logprob, "float32", "logprob"); _expect(lse, "float32", "lse", optional=True)
-    _expect(workspace, "uint8", "workspace")
+    ins = _arg(hidden, e, "hidden"), _arg(weight, e, "weight"), _arg(tokens, "int32", "tokens")
+    outs = (_arg(logprob, "float32", "logprob"), _arg(lse, "float32", "lse", optional=True),
+            _arg(workspace, "uint8", "workspace"))
     M, H = hidden.shape
     V = weight.shape[0]
     code = load_library().copris_lmhead_token_logprob(
-        _ptr(hidden), _ptr(weight), _ptr(tokens), float(temperature), _ptr(logprob), _ptr(lse),
-        _ptr(workspace), workspace.numel() * workspace.element_size(), M, H, V, int(dtype),
-        _stream(stream, hidden))
+        *ins, float(temperature), *outs, workspace.numel(), M, H, V, int(dtype), _stream(stream, hidden))
     _check(code, "copris_lmhead_token_logprob")
 
 
@@ -298,17 +310,16 @@ def prefill_attn(q, k, v, cu_seqlens, block_table, k_cache, v_cache, out, lse, *
                  scale: float, dtype: int, stream=None) -> None:
     """copris_prefill_attn on device tensors (shapes as in include/copris.h)."""
     e = _elem(dtype)
-    for t, n in ((q, "q"), (k, "k"), (v, "v"), (k_cache, "k_cache"), (v_cache, "v_cache"), (out, "out")):
-        _expect(t, e, n)
-    _expect(cu_seqlens, "int32", "cu_seqlens"); _expect(block_table, "int32", "block_table")
-    _expect(lse, "float32", "lse", optional=True)
+    q_, k_, v_ = _arg(q, e, "q"), _arg(k, e, "k"), _arg(v, e, "v")
+    kc, vc, o = _arg(k_cache, e, "k_cache"), _arg(v_cache, e, "v_cache"), _arg(out, e, "out")
+    cu, bt = _arg(cu_seqlens, "int32", "cu_seqlens"), _arg(block_table, "int32", "block_table")
+    l = _arg(lse, "float32", "lse", optional=True)
     T, Hq, D = q.shape
     Hkv = k.shape[1]
     num_pages, _, page_size, _ = k_cache.shape
     B = cu_seqlens.numel() - 1
     code = load_library().copris_prefill_attn(
-        _ptr(q), _ptr(k), _ptr(v), _ptr(cu_seqlens), _ptr(block_table), _ptr(k_cache), _ptr(v_cache),
-        _ptr(out), _ptr(lse), B, T, Hq, Hkv, D, page_size, block_table.shape[1], num_pages,
+        q_, k_, v_, cu, bt, kc, vc, o, l, B, T, Hq, Hkv, D, page_size, block_table.shape[1], num_pages,
         int(max_seqlen), float(scale), int(dtype), _stream(stream, q))
     _check(code, "copris_prefill_attn")
 
@@ -432,51 +443,47 @@ class RolloutManager:
 def rollout_apply(cmds, n_slot_cmds: int, n_page_cmds: int, seq_id, ctx_len, step, block_table, *,
                   stream=None) -> None:
     """copris_rollout_apply on device tensors (cmds: the plan's commands, already on the device)."""
-    _expect(cmds, "int32", "cmds"); _expect(seq_id, "int64", "seq_id")
-    _expect(ctx_len, "int32", "ctx_len"); _expect(step, "int32", "step"); _expect(block_table, "int32", "block_table")
+    cm, sid = _arg(cmds, "int32", "cmds"), _arg(seq_id, "int64", "seq_id")
+    state = _arg(ctx_len, "int32", "ctx_len"), _arg(step, "int32", "step"), _arg(block_table, "int32", "block_table")
     pool, max_pages = block_table.shape
-    code = load_library().copris_rollout_apply(_ptr(cmds), int(n_slot_cmds), int(n_page_cmds), _ptr(seq_id),
-                                               _ptr(ctx_len), _ptr(step), _ptr(block_table), pool, max_pages,
+    code = load_library().copris_rollout_apply(cm, int(n_slot_cmds), int(n_page_cmds), sid, *state, pool, max_pages,
                                                _stream(stream, block_table))
     _check(code, "copris_rollout_apply")
 
 
 def kv_append(k_new, v_new, block_table, ctx_len, k_cache, v_cache, *, dtype: int, stream=None) -> None:
     """copris_kv_append on device tensors."""
-    for t, n in ((k_new, "k_new"), (v_new, "v_new"), (k_cache, "k_cache"), (v_cache, "v_cache")):
-        _expect(t, None, n)
-    _expect(block_table, "int32", "block_table"); _expect(ctx_len, "int32", "ctx_len")
+    kn, vn = _arg(k_new, None, "k_new"), _arg(v_new, None, "v_new")
+    kc, vc = _arg(k_cache, None, "k_cache"), _arg(v_cache, None, "v_cache")
+    bt, ctx = _arg(block_table, "int32", "block_table"), _arg(ctx_len, "int32", "ctx_len")
     C, Hkv, D = k_new.shape
     num_pages, _, page_size, _ = k_cache.shape
-    code = load_library().copris_kv_append(_ptr(k_new), _ptr(v_new), _ptr(block_table), _ptr(ctx_len),
-                                           _ptr(k_cache), _ptr(v_cache), C, Hkv, D, page_size,
-                                           block_table.shape[1], num_pages, int(dtype), _stream(stream, k_cache))
+    code = load_library().copris_kv_append(kn, vn, bt, ctx, kc, vc, C, Hkv, D, page_size, block_table.shape[1],
+                                           num_pages, int(dtype), _stream(stream, k_cache))
     _check(code, "copris_kv_append")
 
 
 def traj_append(token, logprob, seq_id, step, ctx_len, stage: int, buf_token, buf_logp, buf_tag, *,
                 stream=None) -> None:
     """copris_traj_append on device tensors (buffers [n_traj, max_resp])."""
-    _expect(token, "int32", "token"); _expect(logprob, "float32", "logprob"); _expect(seq_id, "int64", "seq_id")
-    _expect(step, "int32", "step"); _expect(ctx_len, "int32", "ctx_len")
-    _expect(buf_token, "int32", "buf_token"); _expect(buf_logp, "float32", "buf_logp"); _expect(buf_tag, "int32", "buf_tag")
+    state = (_arg(token, "int32", "token"), _arg(logprob, "float32", "logprob"), _arg(seq_id, "int64", "seq_id"),
+             _arg(step, "int32", "step"), _arg(ctx_len, "int32", "ctx_len"))
+    bufs = (_arg(buf_token, "int32", "buf_token"), _arg(buf_logp, "float32", "buf_logp"),
+            _arg(buf_tag, "int32", "buf_tag"))
     n_traj, max_resp = buf_token.shape
-    code = load_library().copris_traj_append(_ptr(token), _ptr(logprob), _ptr(seq_id), _ptr(step), _ptr(ctx_len),
-                                             int(stage), _ptr(buf_token), _ptr(buf_logp), _ptr(buf_tag),
-                                             token.numel(), n_traj, max_resp, _stream(stream, buf_token))
+    code = load_library().copris_traj_append(*state, int(stage), *bufs, token.numel(), n_traj, max_resp,
+                                             _stream(stream, buf_token))
     _check(code, "copris_traj_append")
 
 
 def traj_gather(buf_token, buf_logp, buf_tag, traj, cu_seqlens, stage: int, tokens_out, logp_buf_out,
                 logp_roll_out, split_out, *, stream=None) -> None:
     """copris_traj_gather on device tensors."""
-    _expect(buf_token, "int32", "buf_token"); _expect(buf_logp, "float32", "buf_logp"); _expect(buf_tag, "int32", "buf_tag")
-    _expect(traj, "int32", "traj"); _expect(cu_seqlens, "int32", "cu_seqlens"); _expect(tokens_out, "int32", "tokens_out")
-    _expect(logp_buf_out, "float32", "logp_buf_out"); _expect(logp_roll_out, "float32", "logp_roll_out")
-    _expect(split_out, "int32", "split_out")
+    ins = (_arg(buf_token, "int32", "buf_token"), _arg(buf_logp, "float32", "buf_logp"),
+           _arg(buf_tag, "int32", "buf_tag"), _arg(traj, "int32", "traj"), _arg(cu_seqlens, "int32", "cu_seqlens"))
+    outs = (_arg(tokens_out, "int32", "tokens_out"), _arg(logp_buf_out, "float32", "logp_buf_out"),
+            _arg(logp_roll_out, "float32", "logp_roll_out"), _arg(split_out, "int32", "split_out"))
     n_traj, max_resp = buf_token.shape
-    code = load_library().copris_traj_gather(_ptr(buf_token), _ptr(buf_logp), _ptr(buf_tag), _ptr(traj),
-                                             _ptr(cu_seqlens), int(stage), _ptr(tokens_out), _ptr(logp_buf_out),
-                                             _ptr(logp_roll_out), _ptr(split_out), traj.numel(), n_traj, max_resp,
+    code = load_library().copris_traj_gather(*ins, int(stage), *outs, traj.numel(), n_traj, max_resp,
                                              _stream(stream, buf_token))
     _check(code, "copris_traj_gather")
