@@ -218,9 +218,9 @@ int copris_lmhead_logprob(const void* hidden, const void* weight,
  *
  * A shape that needs more partials than the array holds returns COPRIS_EWORKSPACE (the
  * text of copris_last_error_detail() gives the sizes) and enqueues nothing.  The need
- * is C x parts x 20 bytes: for bf16 with H % 64 == 0, parts = min(512 / ceil(C / 256),
- * ceil(V / 128)), at most 2.6 MB for any C up to 200 000; for other shapes parts =
- * ceil(V / 64), e.g. C <= 88 at V = 151 936.
+ * is C x parts x 20 bytes: for bf16 with H % 64 == 0, parts is at most
+ * min(512 / ceil(C / 256), ceil(V / 64)), 2.6 MB for any C up to 200 000; for other shapes
+ * parts = ceil(V / 64), e.g. C <= 88 at V = 151 936.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU
  * (different streams, or threads) race.  Nothing in it needs clearing between calls:
  * every partial a call reads it has written first.

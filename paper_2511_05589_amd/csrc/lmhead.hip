@@ -297,6 +297,30 @@ __device__ __forceinline__ void lm_given_block(const f32x16& acc, LmLaneState& s
   }
 }
 
+// A lane's running state as a partial, combined with the other k-half of the wave (lane ^ 32).
+template <bool GIVEN>
+__device__ __forceinline__ LmPartial lane_partial(const LmLaneState& st) {
+  LmPartial p;
+  p.m = st.m;
+  p.s = st.s;
+  p.z = st.z_best;
+  p.idx = st.idx;
+  // perturbed score z + G with G = -ln(E), E = -ln u = e_best * ln 2
+  if (GIVEN) {
+    p.best = st.idx == 0x7fffffff ? -INFINITY : INFINITY;
+  } else {
+    p.best = st.idx == 0x7fffffff ? -INFINITY : st.z_best - logf(st.e_best * kLn2f);
+  }
+  LmPartial o;
+  o.m = __shfl_xor(p.m, 32, kWave);
+  o.s = __shfl_xor(p.s, 32, kWave);
+  o.best = __shfl_xor(p.best, 32, kWave);
+  o.z = __shfl_xor(p.z, 32, kWave);
+  o.idx = __shfl_xor(p.idx, 32, kWave);
+  combine(p, o);
+  return p;
+}
+
 // ---- memory pipeline of the matrix-core kernel --------------------------------
 // Both operands reach LDS through LDS-direct loads (global_load_lds_dwordx4: each
 // lane's 16 bytes land at base + 16*lane, no registers in between), so the data in
@@ -344,6 +368,7 @@ __device__ __forceinline__ u32x4 lds_read128(uint32_t addr) {
 #define COPRIS_LM_MFMA(fa, fb, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb, c, 0, 0, 0)
 #endif
 
+// (Batches of up to 64 rows mostly take lmhead_skinny_kernel below.)
 // HALVES = 2: 256 batch rows per workgroup (two halves of 128 against every W slab), W ring
 // of two slabs, hidden ring of three units.  HALVES = 1 (C <= 128): only the first half
 // exists, so there is no second half of products, loads and barrier; the hidden ring needs two
@@ -666,24 +691,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   LmPartial(*s_part)[kMfBN / 2] = reinterpret_cast<LmPartial(*)[kMfBN / 2]>(smem);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    LmPartial p;
-    p.m = st[i].m;
-    p.s = st[i].s;
-    p.z = st[i].z_best;
-    p.idx = st[i].idx;
-    // perturbed score z + G with G = -ln(E), E = -ln u = e_best * ln 2
-    if (GIVEN) {
-      p.best = st[i].idx == 0x7fffffff ? -INFINITY : INFINITY;
-    } else {
-      p.best = st[i].idx == 0x7fffffff ? -INFINITY : st[i].z_best - logf(st[i].e_best * kLn2f);
-    }
-    LmPartial o;
-    o.m = __shfl_xor(p.m, 32, kWave);
-    o.s = __shfl_xor(p.s, 32, kWave);
-    o.best = __shfl_xor(p.best, 32, kWave);
-    o.z = __shfl_xor(p.z, 32, kWave);
-    o.idx = __shfl_xor(p.idx, 32, kWave);
-    combine(p, o);
+    LmPartial p = lane_partial<GIVEN>(st[i]);
     if (wm == 1 && kb == 0) s_part[wq][32 * i + l32] = p;
     __syncthreads();
     if (wm == 0 && kb == 0) {
@@ -692,6 +700,292 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       if (c < C) part[static_cast<size_t>(c) * n_parts + blockIdx.x] = p;
     }
     __syncthreads();
+  }
+}
+
+// --------------------------------------------------------------------------
+// matrix-core kernel for at most 64 batch rows.
+//
+// With so few rows the kernel is its W stream, and what counts is that the stream never stops.
+// One workgroup of eight waves per CU takes 32 vocabulary rows per wave against all 32 * NT batch
+// rows: [256 rows][64 k] slabs of W (32 KB) and [32 * NT rows][64 k] slabs of the hidden state,
+// both in rings of four (all of the CU's LDS).  A CU's loads return in the order they were issued,
+// whichever wave issued them, so a hidden slab that is requested later than W but needed sooner
+// would drain the W requests with it: both streams run the same four slabs ahead, and two to three
+// slabs (64 .. 96 KB of W per CU) stay in flight.  Both operands of a slab go to registers before
+// the slab's one barrier, which therefore frees both slots.
+// A workgroup owns a contiguous run of `rows` vocabulary rows, the same for all, in tiles of equal
+// height: the stream ends everywhere at once and asks for the same bytes per slab throughout
+// (128-row tiles dealt out whole leave the last round to a third of the chip).  The rows that a
+// tile lacks to 256 re-read its last row (from the cache) and are masked.
+// The epilogue of a tile is spread over the slabs of the next one, a Philox block (four vocabulary
+// entries of one batch row) at a time: its ~30 vector instructions per entry would otherwise stop
+// the workgroup's loads.
+// --------------------------------------------------------------------------
+template <int N>
+__device__ __forceinline__ void wait_loads() {   // at most N of this wave's loads may still be in flight
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// every LDS read of the slab's operands has arrived
+template <int NT>
+__device__ __forceinline__ void lds_arrived(u32x4 (&a)[4], u32x4 (&b)[4][NT]) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0][0]), "+v"(b[1][0]), "+v"(b[2][0]),
+                 "+v"(b[3][0])::"memory");
+  if constexpr (NT == 2)
+    asm volatile("" : "+v"(b[0][1]), "+v"(b[1][1]), "+v"(b[2][1]), "+v"(b[3][1])::"memory");
+}
+
+// One Philox block of a tile: the accumulators of vocabulary entries vq .. vq+3 (vq % 4 == 0),
+// of which those at or past v_end are masked where the vocabulary (or a tile) ends inside a block.
+__device__ __forceinline__ void lm_sample_quad(const float (&a)[4], LmLaneState& st, int vq, int v_end,
+                                               bool ragged, float inv_temperature, uint32_t step_c, uint32_t sid_lo,
+                                               uint32_t sid_hi, uint32_t key0, uint32_t key1) {
+  float z[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    z[j] = a[j] * inv_temperature;
+    if (ragged && vq + j >= v_end) z[j] = -INFINITY;
+  }
+  const float m_new = fmaxf(st.m, fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
+  if (m_new == -INFINITY) return;
+  const float alpha = __expf(st.m - m_new);
+  st.s *= alpha;
+  st.p_best *= alpha;
+  st.m = m_new;
+  const Philox4 x = philox4x32_10(static_cast<uint32_t>(vq) >> 2, step_c, sid_lo, sid_hi, key0, key1);
+  const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float p = __expf(z[j] - m_new);                            // 0 for masked entries
+    st.s += p;
+    const float e = -__builtin_amdgcn_logf(word_to_uniform(w[j]));   // -log2(u) > 0
+    if (e * st.p_best < st.e_best * p) {                             // (see lm_epilogue_block)
+      st.e_best = e;
+      st.p_best = p;
+      st.z_best = z[j];
+      st.idx = vq + j;
+    }
+  }
+}
+__device__ __forceinline__ void lm_given_quad(const float (&a)[4], LmLaneState& st, int vq, int v_end,
+                                              bool ragged, float inv_temperature, int target) {
+  float z[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    z[j] = a[j] * inv_temperature;
+    if (ragged && vq + j >= v_end) z[j] = -INFINITY;
+  }
+  const float m_new = fmaxf(st.m, fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
+  if (m_new == -INFINITY) return;
+  st.s = st.s * __expf(st.m - m_new) +
+         ((__expf(z[0] - m_new) + __expf(z[1] - m_new)) + (__expf(z[2] - m_new) + __expf(z[3] - m_new)));
+  st.m = m_new;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (target == vq + j && target < v_end) {
+      st.z_best = z[j];
+      st.idx = target;
+    }
+  }
+}
+
+constexpr int kSkMaxRows = 64;
+constexpr int kSkBM = 256;                             // vocabulary rows per tile, at most
+constexpr int kSkMaxGrid = 256;                        // one workgroup per CU
+constexpr int kSkRing = 4;
+constexpr int kSkSlab = kSkBM * kMfBK * 2;             // 32 KB
+constexpr int kSkLds = kSkRing * (kSkSlab + kSkMaxRows * kMfBK * 2);   // 160 KB
+
+template <bool GIVEN, int NT>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void lmhead_skinny_kernel(
+    const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ weight,
+    const int64_t* __restrict__ seq_id, const int32_t* __restrict__ step,
+    const int32_t* __restrict__ target, uint32_t key0, uint32_t key1, float inv_temperature,
+    LmPartial* __restrict__ part, int C, int H, int V, int rows, int height, int n_parts) {
+  constexpr int kHUnit = 32 * NT * kMfBK * 2;          // bytes of a hidden slab
+  constexpr int kHBase = kSkRing * kSkSlab;
+  constexpr int kWLoads = 4;                           // loads per wave and slab: W ...
+  constexpr int kLoads = kWLoads + 1;                  // ... and hidden
+  static_assert(32 * NT <= kSkMaxRows, "rings exceed the workgroup's LDS");
+  __shared__ __attribute__((aligned(1024))) char smem[kSkLds];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, kb = lane >> 5;
+  const int nkd = H / kMfBK;
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
+  const uint32_t pitch = static_cast<uint32_t>(H) * 2u;
+  const int v_begin = blockIdx.x * rows, v_end = min(v_begin + rows, V);   // (v_begin < V: the launcher's grid)
+
+  uint32_t a_off[4], b_off[4];
+#pragma unroll
+  for (int k16 = 0; k16 < 4; ++k16) {
+    a_off[k16] = lm_swz(32 * wave + l32, 2 * k16 + kb) * 16;
+    b_off[k16] = lm_swz(l32, 2 * k16 + kb) * 16;       // a further 32 rows add 4096 bytes
+  }
+
+  // this lane owns batch rows 32*nt + l32; their keys are here before the pipeline starts
+  LmLaneState st[NT];
+  uint32_t step_c[NT], sid_lo[NT], sid_hi[NT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    st[i] = LmLaneState{-INFINITY, 0.0f, INFINITY, 0.0f, 0.0f, 0x7fffffff};
+    const int c = 32 * i + l32;
+    if (GIVEN) {   // step_c holds the row's given token
+      step_c[i] = c < C ? static_cast<uint32_t>(target[c]) : 0xffffffffu;
+      sid_lo[i] = sid_hi[i] = 0;
+    } else {
+      const uint64_t sid = c < C ? static_cast<uint64_t>(seq_id[c]) : 0;
+      step_c[i] = c < C ? static_cast<uint32_t>(step[c]) : 0;
+      sid_lo[i] = static_cast<uint32_t>(sid);
+      sid_hi[i] = static_cast<uint32_t>(sid >> 32);
+    }
+  }
+
+  // ---- loaders: an instruction moves 8 rows x 128 bytes; LDS position 64*chunk + lane holds (row
+  // 8*chunk + lane/8, stored granule lane%8), see lm_swz ((row>>1)&7 = lane>>4, +4 in odd chunks)
+  const uint32_t ld_g = ((lane & 7) ^ (lane >> 4)) * 16;
+  int ld_tile = v_begin, ld_kd = 0, ld_slot = 0;       // cursor of both streams
+  const char* wbase = reinterpret_cast<const char*>(weight);
+  const char* hbase = reinterpret_cast<const char*>(hidden);
+  // W: wave w moves chunks 4w .. 4w+3.  Hidden: chunk w, or w mod 4 where there are only four (two
+  // waves then write the same bytes).
+  auto load = [&](int j) __attribute__((always_inline)) {
+    const uint32_t koff = static_cast<uint32_t>(ld_kd) * (kMfBK * 2) + ld_g;
+    if (j < kWLoads) {
+      const int chunk = kWLoads * wave + j;
+      const int v = min(min(ld_tile + 8 * chunk + (lane >> 3), ld_tile + height - 1), v_end - 1);
+      __builtin_amdgcn_global_load_lds(wbase + (static_cast<uint32_t>(v) * pitch + (koff ^ ((j & 1) * 64))),
+                                       smem + ld_slot * kSkSlab + chunk * 1024, 16, 0, kLmStreamOnce);
+    } else {
+      const int chunk = wave & (4 * NT - 1);
+      const int c = min(8 * chunk + (lane >> 3), C - 1);           // rows past C duplicate the last row (unused)
+      __builtin_amdgcn_global_load_lds(hbase + (static_cast<uint32_t>(c) * pitch + (koff ^ ((chunk & 1) * 64))),
+                                       smem + kHBase + ld_slot * kHUnit + chunk * 1024, 16, 0, 0);
+    }
+  };
+  // Past the run's last slab the loads re-read clamped rows into slots nobody reads any more.
+  auto advance = [&]() __attribute__((always_inline)) {
+    ld_slot = (ld_slot + 1) & (kSkRing - 1);
+    if (++ld_kd == nkd) {
+      ld_kd = 0;
+      ld_tile += height;
+    }
+  };
+  // prologue: the rings are filled; the first slab has landed at the barrier
+  for (int d = 0; d < kSkRing; ++d) {
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) load(j);
+    advance();
+  }
+  wait_loads<(kSkRing - 1) * kLoads>();
+  asm volatile("s_barrier" ::: "memory");
+
+  // the finished tile whose epilogue is under way: its accumulators, first row and end
+  f32x16 done[NT];
+  int done_v0 = v_begin, done_end = v_begin;           // (nothing yet: every entry is masked)
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) done[i][r] = 0.0f;
+  constexpr int kPieces = 4 * NT;
+  auto piece = [&](auto pc) __attribute__((always_inline)) {
+    constexpr int i = decltype(pc)::value / 4, q = decltype(pc)::value % 4;
+    const int vq = done_v0 + 32 * wave + 4 * kb + 8 * q;       // accumulators 4q .. 4q+3 of block i
+    if (32 * i + l32 < C && vq < done_end) {
+      const float z[4] = {done[i][4 * q], done[i][4 * q + 1], done[i][4 * q + 2], done[i][4 * q + 3]};
+      const bool ragged = (done_end & 3) != 0;
+      if (GIVEN) lm_given_quad(z, st[i], vq, done_end, ragged, inv_temperature, static_cast<int>(step_c[i]));
+      else lm_sample_quad(z, st[i], vq, done_end, ragged, inv_temperature, step_c[i], sid_lo[i], sid_hi[i], key0, key1);
+    }
+  };
+  auto pieces = [&](int from, int to) __attribute__((always_inline)) {
+    for (int p = from; p < to; ++p) {
+      switch (p) {
+        case 0: piece(std::integral_constant<int, 0>{}); break;
+        case 1: piece(std::integral_constant<int, 1>{}); break;
+        case 2: piece(std::integral_constant<int, 2>{}); break;
+        case 3: piece(std::integral_constant<int, 3>{}); break;
+        case 4: piece(std::integral_constant<int, 4 % kPieces>{}); break;
+        case 5: piece(std::integral_constant<int, 5 % kPieces>{}); break;
+        case 6: piece(std::integral_constant<int, 6 % kPieces>{}); break;
+        case 7: piece(std::integral_constant<int, 7 % kPieces>{}); break;
+      }
+    }
+  };
+  const int per_slab = (kPieces + nkd - 1) / nkd;
+
+  int slot = 0;
+  for (int v0 = v_begin; v0 < v_end; v0 += height) {
+    f32x16 acc[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.0f;
+    for (int kd = 0; kd < nkd; ++kd) {
+      const uint32_t wb = lds0 + slot * kSkSlab, hb = lds0 + kHBase + slot * kHUnit;
+      slot = (slot + 1) & (kSkRing - 1);
+      u32x4 a[4], b[4][NT];
+#pragma unroll
+      for (int k16 = 0; k16 < 4; ++k16) {
+        a[k16] = lds_read128<0>(wb + a_off[k16]);
+        b[k16][0] = lds_read128<0>(hb + b_off[k16]);
+        if (NT == 2) b[k16][NT - 1] = lds_read128<4096>(hb + b_off[k16]);
+      }
+      lds_arrived(a, b);
+      // the next slab has landed (the two after it may be in flight) ...
+      wait_loads<(kSkRing - 2) * kLoads>();
+      asm volatile("s_barrier" ::: "memory");   // ... for every wave, and all hold this slab's operands
+      // the loads into the freed slot go out between the products
+#pragma unroll
+      for (int m = 0; m < 4 * NT; ++m) {
+        const int k16 = m / NT, nt = m % NT;
+        acc[nt] = COPRIS_LM_MFMA(__builtin_bit_cast(bf16x8, a[k16]), __builtin_bit_cast(bf16x8, b[k16][nt]), acc[nt]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (NT == 1 || m < kLoads) load(m);
+        if (NT == 1 && m == 3) load(4);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      advance();
+      const int first = kd * per_slab;
+      if (first < kPieces) pieces(first, min(first + per_slab, kPieces));
+    }
+#pragma unroll
+    for (int i = 0; i < NT; ++i) done[i] = acc[i];
+    done_v0 = v0;
+    done_end = min(v0 + height, v_end);
+  }
+  // the last tile's epilogue has nothing to hide behind: a block at a time, which leaves the
+  // compiler sixteen entries to interleave
+  const bool tail = done_v0 + 32 * wave + 32 > done_end;
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    if (32 * i + l32 < C) {
+      const int vbase = done_v0 + 32 * wave + 4 * kb;
+      if (GIVEN) {
+        lm_given_block(done[i], st[i], vbase, done_end, tail, inv_temperature, static_cast<int>(step_c[i]));
+      } else {
+        lm_epilogue_block(done[i], st[i], vbase, done_end, tail, inv_temperature, step_c[i], sid_lo[i], sid_hi[i],
+                          key0, key1);
+      }
+    }
+  }
+
+  // lane state -> partial; combine the two k-halves of a wave, then the waves' vocabulary
+  // rows.  The exchange buffer reuses the ring memory: all slabs have been consumed.
+  asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+  LmPartial(*s_part)[32 * NT] = reinterpret_cast<LmPartial(*)[32 * NT]>(smem);
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    LmPartial p = lane_partial<GIVEN>(st[i]);
+    if (kb == 0) s_part[wave][32 * i + l32] = p;
+  }
+  __syncthreads();
+  if (tid < 32 * NT && tid < C) {
+    LmPartial p = s_part[0][tid];
+    for (int w = 1; w < 8; ++w) combine(p, s_part[w][tid]);
+    part[static_cast<size_t>(tid) * n_parts + blockIdx.x] = p;
   }
 }
 
@@ -931,19 +1225,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   LmPartial(*s_part)[64] = reinterpret_cast<LmPartial(*)[64]>(smem);
 #pragma unroll
   for (int nt = 0; nt < 2; ++nt) {
-    LmPartial p;
-    p.m = st[nt].m;
-    p.s = st[nt].s;
-    p.z = st[nt].z_best;
-    p.idx = st[nt].idx;
-    p.best = st[nt].idx == 0x7fffffff ? -INFINITY : INFINITY;
-    LmPartial o;
-    o.m = __shfl_xor(p.m, 32, kWave);
-    o.s = __shfl_xor(p.s, 32, kWave);
-    o.best = __shfl_xor(p.best, 32, kWave);
-    o.z = __shfl_xor(p.z, 32, kWave);
-    o.idx = __shfl_xor(p.idx, 32, kWave);
-    combine(p, o);
+    LmPartial p = lane_partial<true>(st[nt]);
     if (wm == 1 && kb == 0) s_part[wq][32 * nt + l32] = p;
     __syncthreads();
     if (wm == 0 && kb == 0) {
@@ -992,6 +1274,29 @@ static bool lm_use_gemm(int C, int H, int V, int dtype, bool given) {
   return given && C >= kGmMinRows && lm_use_mfma(C, H, V, dtype);
 }
 
+// At most 64 rows: the skinny kernel, unless the vocabulary gives its workgroups fewer than six
+// waves' worth of rows (V < 192 * 256): then half of its waves idle and the 128-row tiles of
+// lmhead_mfma_kernel share the same work out better.  Up to 32 rows it is still the faster one
+// there if the hidden dimension is long.  Whole sampling calls, skinny / 128-row tiles:
+//   C = 64, H = 1536, V = 151936    92.0 / 100.5 us      C = 40, H = 512, V = 60001   23.2 / 24.9
+//   C = 60, H = 1024, V = 30001     25.1 /  23.2         C = 60, H = 512, V = 20001   19.2 / 17.5
+//   C = 22, H = 3584, V = 4096      35.6 /  39.3         C = 22, H = 1024, V = 20011  20.8 / 21.2
+//   C = 20, H = 512, V = 9001       14.6 /  14.4
+static bool lm_use_skinny(int C, int H, int V, int dtype) {
+  return C <= kSkMaxRows && lm_use_mfma(C, H, V, dtype) && (V >= 192 * kSkMaxGrid || (C <= 32 && H >= 1024));
+}
+// Vocabulary rows per workgroup of the skinny kernel: an equal share for the resident workgroups,
+// in whole Philox blocks, but at least kLmTileV (a shorter run is all pipeline start).  Its tiles:
+// as few as cover the run, of equal height.
+static int lm_skinny_height(int rows) {
+  const int tiles = (rows + kSkBM - 1) / kSkBM;
+  return ((rows + tiles - 1) / tiles + 3) & ~3;
+}
+static int lm_skinny_rows(int V) {
+  const int rows = (((V + kSkMaxGrid - 1) / kSkMaxGrid) + 3) & ~3;
+  return rows < kLmTileV ? kLmTileV : rows;
+}
+
 // Partials per row.  Matrix-core kernels: the grid is (parts, blocks of 256 rows) with
 // parts * blocks <= the resident workgroups (512, or 256 for the 256 x 256 kernel) where
 // possible, so that the workgroups that run at the same time walk the same vocabulary tiles
@@ -999,6 +1304,7 @@ static bool lm_use_gemm(int C, int H, int V, int dtype, bool given) {
 // across all of its tiles.
 static int lm_parts(int C, int H, int V, int dtype, bool given) {
   if (!lm_use_mfma(C, H, V, dtype)) return (V + kLmTileV - 1) / kLmTileV;
+  if (lm_use_skinny(C, H, V, dtype)) return (V - 1) / lm_skinny_rows(V) + 1;
   const bool gemm = lm_use_gemm(C, H, V, dtype, given);
   const int bm = gemm ? kGmBM : kMfBM;
   const int n_tiles = (V + bm - 1) / bm;
@@ -1030,6 +1336,19 @@ static int launch_lmhead(const void* hidden, const void* weight, const int64_t* 
                        static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(weight),
                        target, inv_t, part, C, H, V, n_tiles, n_parts);
     COPRIS_POST("lmhead_gemm_given_kernel");
+  } else if (lm_use_skinny(C, H, V, dtype)) {
+    const int rows = lm_skinny_rows(V);
+    COPRIS_PRE("lmhead_skinny_kernel");
+#define COPRIS_LM_SKINNY(G, NT)                                                                          \
+  hipLaunchKernelGGL((lmhead_skinny_kernel<G, NT>), dim3(n_parts), dim3(512), 0, stream,                 \
+                     static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(weight), seq_id, \
+                     step, target, key0, key1, inv_t, part, C, H, V, rows, lm_skinny_height(rows), n_parts)
+    if (given && C <= 32) COPRIS_LM_SKINNY(true, 1);
+    else if (given) COPRIS_LM_SKINNY(true, 2);
+    else if (C <= 32) COPRIS_LM_SKINNY(false, 1);
+    else COPRIS_LM_SKINNY(false, 2);
+#undef COPRIS_LM_SKINNY
+    COPRIS_POST("lmhead_skinny_kernel");
   } else if (lm_use_mfma(C, H, V, dtype)) {
     const int n_tiles = (V + kMfBM - 1) / kMfBM;
     const dim3 grid(n_parts, (C + kMfBN - 1) / kMfBN);

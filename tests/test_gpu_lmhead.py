@@ -38,6 +38,21 @@ def test_small_shapes(R, dtype, C, H, V):
     assert n_exempt <= 2          # expected near-ties: about C / 1000
 
 
+@pytest.mark.parametrize("C,H,V", [(1, 64, 49152), (32, 128, 49153), (33, 64, 50257), (64, 192, 65537),   # one slab per tile and more
+                                   (63, 64, 66001),                # two tiles of unequal fill per workgroup
+                                   (32, 1024, 3), (31, 1024, 65), (5, 1088, 4099),    # fewer rows than a wave, one workgroup and a row
+                                   (65, 64, 49153), (20, 64, 49151)])   # just outside the rule
+def test_few_rows_over_the_whole_vocabulary(R, C, H, V):
+    inp = W.make_small_lmhead_case(C * 11 + V, C, H, V, W.BF16, w_std=0.1)
+    tok, lp, lse = R.run_lmhead_logprob(inp, W.BF16)
+    P.check_lmhead(tok, lp, lse, P.oracle_lmhead(inp, W.BF16), f"{C}x{H}x{V}")
+    # the same rows scored as given tokens, the ends of tiles and runs among them
+    given = np.where(np.arange(C) % 2 == 0, tok, np.minimum(np.arange(C) * 37 % V, V - 1)).astype(np.int32)
+    given[-1] = V - 1
+    lp2, lse2 = R.run_token_logprob(inp["hidden"], inp["weight"], given, 1.0, W.BF16)
+    P.check_token_logprob(lp2, lse2, P.oracle_token_logprob(inp["hidden"], inp["weight"], given, 1.0, W.BF16), f"given {C}x{H}x{V}")
+
+
 def test_zero_weights_token_is_argmax_of_the_noise(R):
     # isolates the Philox counter layout and the uniform -> Gumbel mapping
     C, H, V = 16, 64, 5000
