@@ -124,7 +124,7 @@ int copris_prefill_attn(const void* q, const void* k, const void* v, const int32
   if (!copris::prefill_attn_supported(Hq, Hkv, D, page_size, dtype)) return COPRIS_EUNSUPPORTED;
   (void)hipGetLastError();
   return copris::launch_prefill_attn(q, k, v, cu_seqlens, block_table, k_cache, v_cache, out, lse, B,
-                                     Hq, Hkv, max_pages, max_seqlen, scale,
+                                     T, Hq, Hkv, max_pages, max_seqlen, scale,
                                      static_cast<hipStream_t>(stream));
 }
 

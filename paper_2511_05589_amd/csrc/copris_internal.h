@@ -49,7 +49,7 @@ int launch_decode_attn(const void* q, const void* k_cache, const void* v_cache,
 bool prefill_attn_supported(int Hq, int Hkv, int D, int page_size, int dtype);
 int launch_prefill_attn(const void* q, const void* k, const void* v, const int32_t* cu_seqlens,
                         const int32_t* block_table, void* k_cache, void* v_cache, void* out,
-                        float* lse, int B, int Hq, int Hkv, int max_pages, int max_seqlen,
+                        float* lse, int B, int64_t T, int Hq, int Hkv, int max_pages, int max_seqlen,
                         float scale, hipStream_t stream);
 
 // ---- LM head ----------------------------------------------------------------

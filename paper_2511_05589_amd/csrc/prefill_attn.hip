@@ -3,6 +3,8 @@
 // (Section 4, "Prioritized Resumption": buffered partial trajectories are continued in the
 // next rollout stage; Section 5.3 names their re-prefilling as a cost of high concurrency).
 //
+// (What follows describes a call that fills the chip; smaller ones walk the same steps with several
+// groups of waves per unit: Shape and the split kernels below.)
 // bf16, head_dim 128, page 16.  The unit of work is (query head, tile of 32 query tokens): one
 // wave, the tile as two blocks of 16 queries.  A workgroup is four waves = four consecutive
 // units of one (sequence, kv head, super-tile of T tiles), the units numbered tile-major
@@ -51,23 +53,28 @@ namespace {
 
 constexpr int kD = 128;
 constexpr int kP = 16;
-constexpr int kTileQ = 32;                        // query tokens per workgroup
+constexpr int kTileQ = 32;                        // query tokens per unit
 constexpr int kPageGranules = kP * kD * 2 / 16;   // 256 16-byte granules of K (and of V) per page
 constexpr int kSubs = 2;                          // pages per step
 constexpr int kStepTok = kSubs * kP;              // 32 tokens per step (= kTileQ: a tile's own tokens are one step)
 constexpr int kStepGranules = kSubs * kPageGranules;   // 512 granules of K (and of V) per step
 constexpr int kHalfBytes = kStepGranules * 16;    // 8 KB: a step's K rows (or V rows)
 constexpr int kBufBytes = 2 * kHalfBytes;         // 16 KB: one ring buffer = K rows, then V rows
-constexpr int kRing = 4;                          // ring buffers
-constexpr int kAhead = kRing - 1;                 // a step is requested this many steps before its use
-constexpr int kThreads = 256;                     // four waves = four units; all fetch
-constexpr int kHeadsPerWg = kThreads / 64;
-constexpr int kLoadsPerStep = 2 * kStepGranules / kThreads;   // LDS-direct loads a wave issues per step
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kSlack = 6.0f;   // scores may exceed the softmax reference by 2^kSlack
 constexpr float kBig = 64.0f;    // = 2^kSlack
-static_assert(kLoadsPerStep == 4, "the waits below count four loads per wave and step");
+
+// A workgroup is GROUPS groups of UNITS waves, one unit per wave of a group.
+template <int GROUPS, int UNITS> struct Shape {
+  static constexpr int kUnits = UNITS;
+  static constexpr int kThreads = 64 * GROUPS * UNITS;
+  static constexpr int kRing = GROUPS == 4 ? 2 : 4;        // ring buffers per group
+  static constexpr int kAhead = kRing - 1;                 // a step is requested this many of the group's steps before its use
+  static constexpr int kRows = kStepTok / kUnits;          // K and V rows of a step that a wave fetches
+  static constexpr int kLoads = 2 * kRows / 4;             // ... as LDS-direct loads
+  static constexpr int kLds = GROUPS * kRing * kBufBytes;  // 64 KB (two workgroups per CU) or 128 KB
+};
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   uint32_t r;
@@ -94,15 +101,20 @@ __device__ __forceinline__ s16x4 lds_read_tr16(uint32_t addr) {
   return x;
 }
 
-// (two workgroups per CU: 256 registers per lane)
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_attn_kernel(
-    const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
+template <int N>
+__device__ __forceinline__ void wait_loads() {   // at most N of this wave's loads may still be in flight
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// GROUPS > 1: see the split kernels below.
+template <int GROUPS, int UNITS>
+__device__ __forceinline__ void prefill_attn_body(
+    char* __restrict__ smem, const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
     const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ block_table,
     u32x4* __restrict__ k_cache, u32x4* __restrict__ v_cache, uint16_t* __restrict__ out,
     float* __restrict__ lse, int Hq, int Hkv, int super_tiles, int wgs_per_super, int max_pages,
     float scale_log2e) {
-  __shared__ __attribute__((aligned(1024))) char smem[kRing * kBufBytes];
-
+  using S = Shape<GROUPS, UNITS>;
   const int b = blockIdx.z, kvh = blockIdx.y;
   const int g = Hq / Hkv;
   const int s0 = cu_seqlens[b];
@@ -113,14 +125,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   if (sidx >= n_super) return;
   const int tile0 = (n_super - 1 - sidx) * super_tiles;   // late (long) super-tiles first
   const int units = g * super_tiles;                       // units of a super-tile: u -> (tile0 + u / g, head u % g)
-  if (tile0 + (kHeadsPerWg * wg) / g >= n_tiles) return;   // not even the first unit has a tile
+  if (tile0 + (S::kUnits * wg) / g >= n_tiles) return;   // not even the first unit has a tile
   // the last step of the workgroup: the tile of its last unit that has one
-  const int last_tile = min(tile0 + min(kHeadsPerWg * wg + kHeadsPerWg - 1, units - 1) / g, n_tiles - 1);
+  const int last_tile = min(tile0 + min(S::kUnits * wg + S::kUnits - 1, units - 1) / g, n_tiles - 1);
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = GROUPS == 1 ? wave_id : wave_id % S::kUnits;   // within its group
+  const int grp = GROUPS == 1 ? 0 : wave_id / S::kUnits;
   const int n = lane & 15;        // N index of both products: the query within a block
   const int bq = lane >> 4;       // k-group of the MFMA operand layouts
-  const int unit = kHeadsPerWg * wg + wave;
+  const int unit = S::kUnits * wg + wave;
   const int tile = __builtin_amdgcn_readfirstlane(tile0 + unit / g);   // this wave's tile ...
   const bool computes = unit < units && tile < n_tiles;                // ... if it has one (else the wave only moves data)
   const int head = kvh * g + unit % g;
@@ -129,14 +143,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
   // ---- a tile's own K/V rows go to the sequence's pages, by the workgroup that holds the
   // tile's unit of head 0 (slots past the end of the sequence are left alone) ----
-  for (int i4 = 0; i4 < kHeadsPerWg; ++i4) {
-    const int u = kHeadsPerWg * wg + i4;
+  for (int i4 = 0; i4 < S::kUnits; ++i4) {
+    const int u = S::kUnits * wg + i4;
     const int ut = tile0 + u / g;
     if (u >= units || u % g != 0 || ut >= n_tiles) continue;
     const int32_t* bt = block_table + static_cast<size_t>(b) * max_pages;
 #pragma unroll
-    for (int j = 0; j < 2 * kStepGranules / kThreads; ++j) {
-      const int i = tid + j * kThreads;             // i < 512: K, else V; token (i & 511) >> 4, granule i & 15
+    for (int j = 0; j < 2 * kStepGranules / S::kThreads; ++j) {
+      const int i = tid + j * S::kThreads;             // i < 512: K, else V; token (i & 511) >> 4, granule i & 15
       const int gi = i & (kStepGranules - 1);
       const int tok = ut * kTileQ + (gi >> 4);
       if (tok < len) {
@@ -165,37 +179,38 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
 
   // ---- LDS-direct fetch of one step (32 tokens of K and of V) into a ring buffer ----
-  // A wave moves rows 8*wave .. 8*wave+7 of K and of V: per operand two instructions of four
-  // rows x 256 bytes.  LDS position lane%16 of row 8*wave + 4*j + lane/16 takes the global
+  // A wave moves kRows rows of its group's K and of V: per operand kRows / 4 instructions of four
+  // rows x 256 bytes.  LDS position lane%16 of row kRows*wave + 4*j + lane/16 takes the global
   // granule that the swizzle maps there.  Rows past the end of the sequence re-read its last
   // row (they are masked below); steps past the last one do the same into buffers nobody reads.
-  const int ld_row = 8 * wave + (lane >> 4);                       // + 4*j
+  const int ld_row = S::kRows * wave + (lane >> 4);                // + 4*j
   const size_t row_pitch = static_cast<size_t>(Hkv) * (kD * 2);
   const char* kbase = reinterpret_cast<const char*>(k) + (static_cast<size_t>(s0) * Hkv + kvh) * (kD * 2);
   const char* vbase = reinterpret_cast<const char*>(v) + (static_cast<size_t>(s0) * Hkv + kvh) * (kD * 2);
-  uint32_t ld_gk[2], ld_gv[2];                                     // byte offset of the lane's granule in its row
-  uint32_t ld_ok[2], ld_ov[2];                                     // ... and in a whole step, for steps that need no clamp
+  uint32_t ld_gk[S::kRows / 4], ld_gv[S::kRows / 4];                                     // byte offset of the lane's granule in its row
+  uint32_t ld_ok[S::kRows / 4], ld_ov[S::kRows / 4];                                     // ... and in a whole step, for steps that need no clamp
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
+  for (int j = 0; j < S::kRows / 4; ++j) {
     const int row = ld_row + 4 * j;
     ld_gk[j] = static_cast<uint32_t>((lane & 15) ^ (row & 15)) * 16;
     ld_gv[j] = static_cast<uint32_t>((lane & 15) ^ ((row & 7) << 1)) * 16;
     ld_ok[j] = static_cast<uint32_t>(row) * static_cast<uint32_t>(row_pitch) + ld_gk[j];
     ld_ov[j] = static_cast<uint32_t>(row) * static_cast<uint32_t>(row_pitch) + ld_gv[j];
   }
+  // (The groups' steps alternate: a group has every GROUPS-th buffer of the ring.)
   auto fetch = [&](int step) __attribute__((always_inline)) {
-    char* dst = smem + (step & (kRing - 1)) * kBufBytes + (8 * wave) * 256;
+    char* dst = smem + (step & (GROUPS * S::kRing - 1)) * kBufBytes + (S::kRows * wave) * 256;
     if (step * kStepTok + kStepTok <= len) {
       // a whole step inside the sequence: one address for the wave plus the lane's fixed offset
       const size_t so = static_cast<size_t>(step) * kStepTok * row_pitch;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < S::kRows / 4; ++j) {
         __builtin_amdgcn_global_load_lds(kbase + so + ld_ok[j], dst + j * 1024, 16, 0, 0);
         __builtin_amdgcn_global_load_lds(vbase + so + ld_ov[j], dst + kHalfBytes + j * 1024, 16, 0, 0);
       }
     } else {
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int j = 0; j < S::kRows / 4; ++j) {
         const int tok = min(step * kStepTok + ld_row + 4 * j, len - 1);
         const size_t ro = static_cast<size_t>(tok) * row_pitch;
         __builtin_amdgcn_global_load_lds(kbase + (ro + ld_gk[j]), dst + j * 1024, 16, 0, 0);
@@ -220,21 +235,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
   for (int i = 0; i < 16; ++i) o[i >> 3][i & 7] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-  // A wave's loads complete in issue order, four per step: once at most 4*(kAhead-1) are
-  // outstanding, the step after the current one has landed.
-#pragma unroll
-  for (int st = 0; st < kAhead; ++st) fetch(st);
-  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(4 * (kAhead - 1)) : "memory");
-
-  // one step.  diag = true: the tile's own tokens (causal mask, end of the sequence).
-  // active = false: a step after the wave's own tile (another wave of the workgroup still
-  // needs the rows), or a wave without a unit: it fetches and waits with the others.
-  auto do_step = [&](const int step, const bool active, auto diag) __attribute__((always_inline)) {
+  // One step from the buffer at LDS offset boff.  diag = true: the tile's own tokens (causal mask,
+  // end of the sequence).
+  auto compute = [&](const int step, const uint32_t boff, auto diag) __attribute__((always_inline)) {
     constexpr bool kDiag = decltype(diag)::value;
-    const uint32_t boff = static_cast<uint32_t>(step & (kRing - 1)) * kBufBytes;
-    fetch(step + kAhead);          // into the buffer of step-1, which every wave left at the last barrier
-
-    if (active) {
+    {
       // Scores of the two pages: K rows as the A operand (token = lane & 15), read once for
       // both query blocks.  This lane: query n of each block, tokens 4*bq .. 4*bq+3 of each page.
       // A block whose queries all lie before a page's tokens is fully masked there: its
@@ -365,18 +370,75 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         }
       }
     }
-    // the next step has landed, for every wave; all are done with this step's buffer
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(4 * (kAhead - 1)) : "memory");
   };
+
   const int my_last = computes ? tile : -1;
-  int step = 0;
-  for (; step < my_last; ++step) do_step(step, true, std::false_type{});
-  if (computes) {
-    do_step(tile, true, std::true_type{});
-    step = tile + 1;
+  // A wave's loads complete in issue order: once at most those of kAhead - 1 steps are
+  // outstanding, its group's next step has landed.
+  auto wait_next = [&]() __attribute__((always_inline)) {
+    wait_loads<S::kLoads*(S::kAhead - 1)>();
+    asm volatile("s_barrier" ::: "memory");
+  };
+#pragma unroll
+  for (int st = 0; st < S::kAhead; ++st) fetch(GROUPS * st + grp);
+  wait_next();
+
+  // active = false: a step after the wave's own tile (another wave of the workgroup still
+  // needs the rows), or a wave without a unit: it fetches and waits with the others.
+  auto do_step = [&](const int step, const bool active, auto diag) __attribute__((always_inline)) {
+    fetch(step + GROUPS * S::kAhead);   // into the buffer of the group's last step, which every wave left at the last barrier
+    if (active) compute(step, static_cast<uint32_t>(step & (GROUPS * S::kRing - 1)) * kBufBytes, diag);
+    wait_next();                        // ... for every wave; all are done with this step's buffer
+  };
+  int step = grp;
+  for (; step < my_last; step += GROUPS) do_step(step, true, std::false_type{});
+  if (step == my_last) {
+    do_step(step, true, std::true_type{});
+    step += GROUPS;
   }
-  for (; step <= last_tile; ++step) do_step(step, false, std::false_type{});
+  // (every group passes the same number of barriers)
+  for (; step < (last_tile / GROUPS + 1) * GROUPS; step += GROUPS) do_step(step, false, std::false_type{});
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (the loads past the last step land before the LDS is given back)
+
+  if constexpr (GROUPS > 1) {
+    // the first group takes the softmax states of the others over; a wave of theirs without a step
+    // has m = -inf and weighs 0 (the first group has seen token 0, so the common reference is finite)
+    constexpr int kState = 16 * 64 * 16 + 2 * 64 * 8;          // bytes per wave: O, then (m, l)
+    static_assert((GROUPS - 1) * UNITS * kState <= S::kLds, "the states do not fit the rings");
+    __syncthreads();                       // every load has landed and every buffer has been read
+    if (grp > 0) {
+      char* mine = smem + ((grp - 1) * S::kUnits + wave) * kState;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        reinterpret_cast<float4*>(mine)[i * 64 + lane] =
+            make_float4(o[i >> 3][i & 7][0], o[i >> 3][i & 7][1], o[i >> 3][i & 7][2], o[i >> 3][i & 7][3]);
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb)
+        reinterpret_cast<float2*>(mine + 16 * 64 * 16)[nb * 64 + lane] = make_float2(m_run[nb], l_run[nb]);
+    }
+    __syncthreads();
+    if (grp > 0 || !computes) return;
+#pragma unroll
+    for (int og = 1; og < GROUPS; ++og) {
+      const char* other = smem + ((og - 1) * S::kUnits + wave) * kState;
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb) {
+        const float2 ml = reinterpret_cast<const float2*>(other + 16 * 64 * 16)[nb * 64 + lane];
+        const float m_all = fmaxf(m_run[nb], ml.x);
+        const float w0 = __builtin_amdgcn_exp2f(m_run[nb] - m_all), w1 = __builtin_amdgcn_exp2f(ml.x - m_all);
+        m_run[nb] = m_all;
+        l_run[nb] = w0 * l_run[nb] + w1 * ml.y;
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) {
+          const float4 y = reinterpret_cast<const float4*>(other)[(8 * nb + dt) * 64 + lane];
+          o[nb][dt][0] = w0 * o[nb][dt][0] + w1 * y.x;
+          o[nb][dt][1] = w0 * o[nb][dt][1] + w1 * y.y;
+          o[nb][dt][2] = w0 * o[nb][dt][2] + w1 * y.z;
+          o[nb][dt][3] = w0 * o[nb][dt][3] + w1 * y.w;
+        }
+      }
+    }
+  }
 
   // normalise and store: lane (n, bq) owns d = 16*dt + 4*bq + r of query n
 #pragma unroll
@@ -400,6 +462,38 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
 }
 
+// (two workgroups per CU: 256 registers per lane)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_attn_kernel(
+    const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
+    const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ block_table,
+    u32x4* __restrict__ k_cache, u32x4* __restrict__ v_cache, uint16_t* __restrict__ out,
+    float* __restrict__ lse, int Hq, int Hkv, int super_tiles, int wgs_per_super, int max_pages,
+    float scale_log2e) {
+  __shared__ __attribute__((aligned(1024))) char smem[Shape<1, 4>::kLds];
+  prefill_attn_body<1, 4>(smem, q, k, v, cu_seqlens, block_table, k_cache, v_cache, out, lse, Hq, Hkv, super_tiles,
+                           wgs_per_super, max_pages, scale_log2e);
+}
+
+// The same for calls that do not fill the chip.  What counts there is the longest chain of steps
+// (0.65 us each), so the waves of a workgroup are several groups on the same units: group i takes the
+// steps i, i + GROUPS, ... from a ring of its own, and the softmax states are combined at the end.
+#define COPRIS_PREFILL_SPLIT(NAME, GROUPS, UNITS)                                                      \
+  __global__ __launch_bounds__((Shape<GROUPS, UNITS>::kThreads))                                       \
+  __attribute__((amdgpu_waves_per_eu(1, 2))) void NAME(                                                \
+      const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,        \
+      const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ block_table,                 \
+      u32x4* __restrict__ k_cache, u32x4* __restrict__ v_cache, uint16_t* __restrict__ out,            \
+      float* __restrict__ lse, int Hq, int Hkv, int super_tiles, int wgs_per_super, int max_pages,     \
+      float scale_log2e) {                                                                             \
+    __shared__ __attribute__((aligned(1024))) char smem[Shape<GROUPS, UNITS>::kLds];                   \
+    prefill_attn_body<GROUPS, UNITS>(smem, q, k, v, cu_seqlens, block_table, k_cache, v_cache, out,    \
+                                     lse, Hq, Hkv, super_tiles, wgs_per_super, max_pages, scale_log2e); \
+  }
+COPRIS_PREFILL_SPLIT(prefill_attn_split4x1_kernel, 4, 1)
+COPRIS_PREFILL_SPLIT(prefill_attn_split2x2_kernel, 2, 2)
+COPRIS_PREFILL_SPLIT(prefill_attn_split2x4_kernel, 2, 4)
+#undef COPRIS_PREFILL_SPLIT
+
 }  // namespace
 
 bool prefill_attn_supported(int Hq, int Hkv, int D, int page_size, int dtype) {
@@ -410,23 +504,46 @@ bool prefill_attn_supported(int Hq, int Hkv, int D, int page_size, int dtype) {
 
 int launch_prefill_attn(const void* q, const void* k, const void* v, const int32_t* cu_seqlens,
                         const int32_t* block_table, void* k_cache, void* v_cache, void* out,
-                        float* lse, int B, int Hq, int Hkv, int max_pages, int max_seqlen,
+                        float* lse, int B, int64_t T, int Hq, int Hkv, int max_pages, int max_seqlen,
                         float scale, hipStream_t stream) {
   const int g = Hq / Hkv;
-  // super-tile of T tiles: the smallest T for which g * T units fill whole workgroups
-  const int gcd4 = (g % 4 == 0) ? 4 : (g % 2 == 0 ? 2 : 1);
-  const int super_tiles = kHeadsPerWg / gcd4;
-  const int wgs_per_super = g * super_tiles / kHeadsPerWg;
-  const int n_tiles_max = (max_seqlen + kTileQ - 1) / kTileQ;
-  const dim3 grid(((n_tiles_max + super_tiles - 1) / super_tiles) * wgs_per_super, Hkv, B);
   const float scale_log2e = scale * kLog2e;
-  COPRIS_PRE("prefill_attn_kernel");
-  hipLaunchKernelGGL(prefill_attn_kernel, grid, dim3(kThreads), 0, stream,
-                     static_cast<const uint16_t*>(q), static_cast<const u32x4*>(k),
-                     static_cast<const u32x4*>(v), cu_seqlens, block_table,
-                     static_cast<u32x4*>(k_cache), static_cast<u32x4*>(v_cache),
-                     static_cast<uint16_t*>(out), lse, Hq, Hkv, super_tiles, wgs_per_super, max_pages, scale_log2e);
-  COPRIS_POST("prefill_attn_kernel");
+  const int n_tiles_max = (max_seqlen + kTileQ - 1) / kTileQ;
+  // Which shape: as many groups per unit as the chip has room for.  `units` (query head, tile) is at
+  // most what the sequences have; one workgroup of a split kernel fits a CU.
+  //   4 groups, 1 unit    units <= 256                     1 x 600 tokens, 12 heads     17.6 -> 13.2 us
+  //   2 groups, 2 units   units <= 512                     356 + 942 tokens, 12 heads   24.9 -> 21.4
+  //   2 groups, 4 units   units <= 1024, or twice that     1 x 915 tokens, 28 heads     25.4 -> 22.9
+  //                       with nearly all tokens in one    1 x 4003 tokens, 12 heads    86.9 -> 65.6
+  //                       sequence (one long chain)
+  // Beyond, the workgroups that do not fit at once cost more than the shorter chains give
+  // (3 sequences of 303 .. 1211 tokens, 28 heads, 1876 units: 36 us whole, 40 in two groups).
+  const int64_t units = (T / kTileQ + B) * Hq;
+  const bool one_chain = T <= max_seqlen + max_seqlen / 4;
+  const bool split4 = units <= 256, split2 = units <= 512, split2x4 = units <= (one_chain ? 2048 : 1024);
+  const int per_wg = split4 ? 1 : (split2 ? 2 : 4);     // units
+  // super-tile of T tiles: the smallest T for which g * T units fill whole workgroups
+  const int gcd = g % per_wg == 0 ? per_wg : (g % 2 == 0 && per_wg > 2 ? 2 : 1);
+  const int super_tiles = per_wg / gcd;
+  const int wgs_per_super = g * super_tiles / per_wg;
+  const dim3 grid(((n_tiles_max + super_tiles - 1) / super_tiles) * wgs_per_super, Hkv, B);
+#define COPRIS_PREFILL(KERNEL, THREADS)                                                                     \
+  COPRIS_PRE(#KERNEL);                                                                                      \
+  hipLaunchKernelGGL(KERNEL, grid, dim3(THREADS), 0, stream, static_cast<const uint16_t*>(q),              \
+                     static_cast<const u32x4*>(k), static_cast<const u32x4*>(v), cu_seqlens, block_table,   \
+                     static_cast<u32x4*>(k_cache), static_cast<u32x4*>(v_cache), static_cast<uint16_t*>(out), \
+                     lse, Hq, Hkv, super_tiles, wgs_per_super, max_pages, scale_log2e);                     \
+  COPRIS_POST(#KERNEL)
+  if (split4) {
+    COPRIS_PREFILL(prefill_attn_split4x1_kernel, 256);
+  } else if (split2) {
+    COPRIS_PREFILL(prefill_attn_split2x2_kernel, 256);
+  } else if (split2x4) {
+    COPRIS_PREFILL(prefill_attn_split2x4_kernel, 512);
+  } else {
+    COPRIS_PREFILL(prefill_attn_kernel, 256);
+  }
+#undef COPRIS_PREFILL
   return 0;
 }
 

@@ -50,6 +50,29 @@ def test_empty_sequences_among_others_and_a_loose_length_bound(R, Hq, Hkv):
     np.testing.assert_array_equal(R.out_to_f32(d.v_cache), ref_vc)
 
 
+@pytest.mark.parametrize("most", [256, 512, 1024, 3000])
+@pytest.mark.parametrize("Hq,Hkv", [(28, 4), (12, 2), (8, 8), (8, 1), (6, 2), (5, 1)])
+def test_every_workgroup_shape(R, Hq, Hkv, most):
+    # the call picks its workgroup shape by the number of units (query head, tile) that T and B
+    # admit: fill up to just below each bound with lengths around the tile, page and step boundaries
+    rng = np.random.default_rng(Hq * 7 + most)
+    units = lambda ls: (sum(ls) // 32 + len(ls)) * Hq
+    lens = [33] if units([33]) <= most else [1]
+    while True:
+        n = int(rng.choice([1, 16, 31, 32, 33, 64, 65, 97, 129, 200, 333]))
+        if units(lens + [n]) > most:
+            break
+        lens.append(n)
+    b = W.make_prefill_case(600 + Hq + most, lens, Hq, Hkv, 128, W.BF16)
+    _check_all(R, b, f"{Hq}/{Hkv} up to {most} units")
+
+
+@pytest.mark.parametrize("Hq,Hkv,lens", [(28, 4, [1500]), (6, 2, [2049, 0, 300]), (14, 2, [1, 3000])])
+def test_one_long_chain(R, Hq, Hkv, lens):
+    b = W.make_prefill_case(700 + Hq, lens, Hq, Hkv, 128, W.BF16)
+    _check_all(R, b, f"{Hq}/{Hkv} {lens}")
+
+
 def test_seeded_random_group_sizes_and_lengths(R):
     # every supported group size against lengths around the page, block, tile and super-tile
     # boundaries, a few sequences per case (the workgroup <-> (head, tile) mapping differs with
