@@ -352,6 +352,21 @@ __device__ __forceinline__ u32x4 lds_read128(uint32_t addr) {
 // (Waits on these reads are inline "s_waitcnt lgkmcnt(N)" statements that tie the operands
 // which must have arrived, so that no use can be scheduled above the wait.)
 
+template <int N>
+__device__ __forceinline__ void wait_loads() {   // at most N of this wave's loads may still be in flight
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// two k-steps' hidden operands have arrived, N LDS reads may still be under way
+template <int N, int NT>
+__device__ __forceinline__ void lds_wait_b(u32x4 (&p)[NT], u32x4 (&q)[NT]) {
+  if constexpr (NT == 2) {
+    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(p[0]), "+v"(p[1]), "+v"(q[0]), "+v"(q[1]) : "n"(N) : "memory");
+  } else {
+    asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(p[0]), "+v"(q[0]) : "n"(N) : "memory");
+  }
+}
+
 // Timing probes (never defined in the product build; `python -m paper_2511_05589_amd.build
 // --define NAME --out other.so` builds one, bench.py --lib times it; the results of such a
 // build are wrong by design, every access stays in bounds and every loop ends):
@@ -370,21 +385,27 @@ __device__ __forceinline__ u32x4 lds_read128(uint32_t addr) {
 
 // (Batches of up to 64 rows mostly take lmhead_skinny_kernel below.)
 // HALVES = 2: 256 batch rows per workgroup (two halves of 128 against every W slab), W ring
-// of two slabs, hidden ring of three units.  HALVES = 1 (C <= 128): only the first half
+// of two slabs, hidden ring of three units; NT1 = 1: the second half has only 64 rows (192 in all).
+// HALVES = 1 (C <= 128): only the first half
 // exists, so there is no second half of products, loads and barrier; the hidden ring needs two
 // units and the W ring gets three slabs (a slab is requested two slabs ahead).
-template <bool GIVEN, int HALVES>
+template <bool GIVEN, int HALVES, int NT1>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void lmhead_mfma_kernel(
     const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ weight,
     const int64_t* __restrict__ seq_id, const int32_t* __restrict__ step,
     const int32_t* __restrict__ target, uint32_t key0, uint32_t key1, float inv_temperature,
-    LmPartial* __restrict__ part, int C, int H, int V, int n_tiles, int n_parts) {
+    LmPartial* __restrict__ part, int C, int H, int V, int block_rows, int n_tiles, int n_parts) {
   __shared__ __attribute__((aligned(1024))) char smem[kMfLds];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wq = wave & 1;     // vocabulary half; 64-row block of a batch half
   const int l32 = lane & 31, kb = lane >> 5;
-  const int c0 = blockIdx.y * kMfBN;
+  // this workgroup's batch rows, and its place among those that share the tiles out: odd row
+  // blocks count from the end, so that the CU whose workgroup of one block has a tile more gets one
+  // with a tile less of the next
+  const int c0 = blockIdx.y * block_rows, c_end = min(C, c0 + block_rows);
+  // (n_parts = gridDim.x; with one tile each the blocks share it through the L2)
+  const int place = (blockIdx.y & 1) && n_tiles > n_parts ? n_parts - 1 - blockIdx.x : blockIdx.x;
   const int nkd = H / kMfBK;                   // slabs per tile
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
   const uint32_t pitch = static_cast<uint32_t>(H) * 2u;
@@ -394,15 +415,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   static_assert(kHBase + kRingH * kSlab <= kMfLds, "rings exceed the workgroup's LDS");
 
   // operand read offsets inside a slab / unit (bytes); it / nt add 32 rows = 4096 bytes
-  uint32_t a_off[4], b_off[4];
+  uint32_t a_off[4], b_off[4], b1_off[4];
 #pragma unroll
   for (int k16 = 0; k16 < 4; ++k16) {
     a_off[k16] = lm_swz(64 * wm + l32, 2 * k16 + kb) * 16;
     b_off[k16] = lm_swz(64 * wq + l32, 2 * k16 + kb) * 16;
+    b1_off[k16] = lm_swz(32 * NT1 * wq + l32, 2 * k16 + kb) * 16;   // second half
   }
 
   // ---- loader cursors (wave-uniform) ----
-  const int my_tiles = blockIdx.x < n_tiles ? (n_tiles - 1 - blockIdx.x) / gridDim.x + 1 : 0;
+  const int my_tiles = place < n_tiles ? (n_tiles - 1 - place) / gridDim.x + 1 : 0;
   const int total = my_tiles * nkd;            // W slabs this workgroup consumes (hidden units: 2x)
   // Every wave moves a quarter of every W slab and of every hidden unit: rows 32*wave ..
   // 32*wave+31, four instructions of 8 rows x 128 bytes.  LDS position 64*chunk + lane of a
@@ -411,7 +433,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // ones, i.e. bit 6 of the byte offset flips for odd j.
   const int ld_row = 32 * wave + (lane >> 3);                // + 8*j
   const uint32_t ld_g = ((lane & 7) ^ (lane >> 4)) * 16;
-  int w_tile = blockIdx.x, w_kd = 0, w_ring = 0;             // W cursor (tile, slab) and ring slot
+  int w_tile = place, w_kd = 0, w_ring = 0;             // W cursor (tile, slab) and ring slot
   int h_n = 0, h_kd = 0, h_ring = 0;                         // hidden units issued so far (half = h_n & 1), slab, slot
   const char* wbase = reinterpret_cast<const char*>(weight);
   const char* hbase = reinterpret_cast<const char*>(hidden);
@@ -440,10 +462,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       w_tile += gridDim.x;
     }
   };
-  auto h_load = [&](int j) __attribute__((always_inline)) {
-    char* dst = smem + kHBase + h_ring * kSlab + (4 * wave + j) * 1024;
+  // (a second half of 64 rows is two loads per wave, rows 16*wave ..)
+  auto h_load = [&](int j, auto halfc) __attribute__((always_inline)) {
+    constexpr int kHalf = decltype(halfc)::value, kPer = kHalf == 1 ? 2 * NT1 : 4;
+    char* dst = smem + kHBase + h_ring * kSlab + (kPer * wave + j) * 1024;
     const uint32_t koff = static_cast<uint32_t>(h_kd) * (kMfBK * 2) + ld_g;
-    const int c = min(c0 + (HALVES == 2 ? 128 * (h_n & 1) : 0) + ld_row + 8 * j, C - 1);
+    // (128 * kHalf from the unit counter where registers are short: as a constant it makes the rows'
+    // eight addresses loop invariants, which do not fit)
+    const int first = HALVES == 2 && NT1 == 2 ? 128 * (h_n & 1) : 128 * kHalf;
+    const int c = min(c0 + first + (kPer == 4 ? ld_row : 16 * wave + (lane >> 3)) + 8 * j, C - 1);
 #if !defined(COPRIS_LM_PROBE_NO_H_LOADS)
     __builtin_amdgcn_global_load_lds(hbase + (static_cast<uint32_t>(c) * pitch + (koff ^ ((j & 1) * 64))), dst,
                                      16, 0, 0);
@@ -461,27 +488,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int j = 0; j < 4; ++j) w_load(j);
     w_advance();
   };
-  auto issue_h = [&]() __attribute__((always_inline)) {
+  using Half0 = std::integral_constant<int, 0>;
+  using Half1 = std::integral_constant<int, 1>;
+  auto issue_h = [&](auto halfc) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) h_load(j);
+    for (int j = 0; j < (decltype(halfc)::value == 1 ? 2 * NT1 : 4); ++j) h_load(j, halfc);
     h_advance();
   };
+  // batch row of state i (2*half + nt) of this lane
+  auto state_row = [&](int i) __attribute__((always_inline)) {
+    return c0 + 128 * (i >> 1) + (i >> 1 ? 32 * NT1 : 64) * wq + 32 * (i & 1) + l32;
+  };
 
-  // this lane owns batch rows c0 + 128*half + 64*wq + 32*nt + l32 (state index 2*half + nt);
-  // their stream keys stay in registers (a global load inside the tile loop would drain
+  // this lane owns the batch rows state_row(2*half + nt); their stream keys stay in registers (a global load inside the tile loop would drain
   // the prefetch queue)
-  LmLaneState st[4];
-  uint32_t step_c[4], sid_lo[4], sid_hi[4];
+  constexpr int kStates = HALVES == 1 ? 2 : 2 + NT1;
+  LmLaneState st[kStates];
+  uint32_t step_c[kStates], sid_lo[kStates], sid_hi[kStates];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < kStates; ++i) {
     st[i] = LmLaneState{-INFINITY, 0.0f, INFINITY, 0.0f, 0.0f, 0x7fffffff};
-    const int c = c0 + 128 * (i >> 1) + 64 * wq + 32 * (i & 1) + l32;
+    const int c = state_row(i);
     if (GIVEN) {   // step_c holds the row's given token
-      step_c[i] = c < C ? static_cast<uint32_t>(target[c]) : 0xffffffffu;
+      step_c[i] = c < c_end ? static_cast<uint32_t>(target[c]) : 0xffffffffu;
       sid_lo[i] = sid_hi[i] = 0;
     } else {
-      const uint64_t sid = c < C ? static_cast<uint64_t>(seq_id[c]) : 0;
-      step_c[i] = c < C ? static_cast<uint32_t>(step[c]) : 0;
+      const uint64_t sid = c < c_end ? static_cast<uint64_t>(seq_id[c]) : 0;
+      step_c[i] = c < c_end ? static_cast<uint32_t>(step[c]) : 0;
       sid_lo[i] = static_cast<uint32_t>(sid);
       sid_hi[i] = static_cast<uint32_t>(sid >> 32);
     }
@@ -489,7 +522,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // prologue = the loads of "slabs -2 and -1".  A wave's loads complete in issue order, and
   // that order is, per slab d: hidden (d+1, half 0), W(d+2) | hidden (d+1, half 1).  So at the
-  // top of slab d the wave may leave its newest eight loads (W(d+1), hidden (d, 1)) in flight
+  // top of slab d the wave may leave its newest loads (W(d+1), four, and hidden (d, 1)) in flight
   // and knows hidden (d, 0) has landed; at mid-slab it may leave the eight issued since the
   // top and knows W(d+1) and hidden (d, 1) have.
   // (HALVES = 1: per slab d hidden (d+1), W(d+3); at the top of slab d the newest four loads,
@@ -498,13 +531,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (HALVES == 2) {
       issue_w();
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // W(0): the first slab reads it before any barrier of the loop
-      issue_h();
+      issue_h(Half0{});
       issue_w();
-      issue_h();
+      issue_h(Half1{});
     } else {
       issue_w();
       issue_w();
-      issue_h();
+      issue_h(Half0{});
       issue_w();
       asm volatile("s_waitcnt vmcnt(12)" ::: "memory");  // W(0)
     }
@@ -512,7 +545,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   asm volatile("s_barrier" ::: "memory");
 
   int ring = 0, hring = 0;                     // W / hidden ring slots being consumed
-  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+  for (int tile = place; tile < n_tiles; tile += gridDim.x) {
     const int v0 = tile * kMfBM;
     f32x16 acc[2][2][2];                       // [batch half][it][nt]
 #pragma unroll
@@ -561,7 +594,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
               const int q = 4 * grp + (m >> 1);                                   // 0 .. 7
               __builtin_amdgcn_sched_barrier(0);
               if (q < 4) {
-                h_load(q);
+                h_load(q, Half0{});
                 if (q == 3) h_advance();
               } else {
                 w_load(q - 4);
@@ -591,86 +624,85 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                    : "+v"(a[0][0]), "+v"(a[0][1]), "+v"(a[1][0]), "+v"(a[1][1]), "+v"(a[2][0]),
                      "+v"(a[2][1]), "+v"(a[3][0]), "+v"(a[3][1])::"memory");
       // ---- top: hidden unit (d, half 0) has landed ----
-      asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+      wait_loads<4 + 2 * NT1>();
       asm volatile("s_barrier" ::: "memory");   // ... for every wave; all are done with slab d-1
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
+      auto half_slab = [&](auto halfc) __attribute__((always_inline)) {
+        constexpr int half = decltype(halfc)::value, kNt = half == 1 ? NT1 : 2;
         if (half == 1) {
           // ---- middle: W(d+1) and hidden unit (d, half 1) have landed ----
-          asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+          wait_loads<8>();
           asm volatile("s_barrier" ::: "memory");             // all are done with unit (d, half 0)
         }
         const uint32_t hb = lds0 + kHBase + hring * kSlab;
         hring = hring + 1 == kRingH ? 0 : hring + 1;
-        // all eight hidden operands of the half at once, then sixteen products in two groups
-        // of eight: one wait per eight products instead of one per four
-        u32x4 b[4][2];
+        // all hidden operands of the half at once, then its products in two groups of eight (of
+        // four where the half has 64 rows): one wait per group instead of one per four
+        u32x4 b[4][kNt];
 #pragma unroll
         for (int k16 = 0; k16 < 4; ++k16) {
-          b[k16][0] = lds_read128<0>(hb + b_off[k16]);
-          b[k16][1] = lds_read128<4096>(hb + b_off[k16]);
+          b[k16][0] = lds_read128<0>(hb + (half == 1 && NT1 == 1 ? b1_off[k16] : b_off[k16]));
+          if constexpr (kNt == 2) b[k16][1] = lds_read128<4096>(hb + (half == 1 && NT1 == 1 ? b1_off[k16] : b_off[k16]));
         }
 #pragma unroll
         for (int grp = 0; grp < 2; ++grp) {
-          if (grp == 0) {
-            asm volatile("s_waitcnt lgkmcnt(4)" : "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[1][0]), "+v"(b[1][1])::"memory");
-          } else {
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(b[2][0]), "+v"(b[2][1]), "+v"(b[3][0]), "+v"(b[3][1])::"memory");
-          }
+          if (grp == 0) lds_wait_b<2 * kNt>(b[0], b[1]);
+          else lds_wait_b<0>(b[2], b[3]);
 #pragma unroll
-          for (int m = 0; m < 8; ++m) {
-            const int k16 = 2 * grp + (m >> 2), it = (m >> 1) & 1;
+          for (int m = 0; m < 4 * kNt; ++m) {
+            const int k16 = 2 * grp + m / (2 * kNt), it = m / kNt % 2, nt = m % kNt;
             const bf16x8 fa = __builtin_bit_cast(bf16x8, a[k16][it]);
-            const bf16x8 fb = __builtin_bit_cast(bf16x8, b[k16][m & 1]);
-            acc[half][it][m & 1] = COPRIS_LM_MFMA(fa, fb, acc[half][it][m & 1]);
-            // The twelve loads a wave issues per slab go out one at a time between the
-            // products.  Issued in a bunch they keep every wave of the CU at the issue stage
-            // while the address unit works through them, and the matrix pipes idle meanwhile;
-            // spread out they cost the products nothing.  First half: hidden (d+1, half 0) (its
-            // slot is free since the top barrier), then W(d+2) (likewise); second half: hidden
-            // (d+1, half 1) (the middle barrier has freed the slot of (d, half 0)).  Past the
-            // last slab the loads re-read clamped rows into ring slots nobody reads any more.
+            const bf16x8 fb = __builtin_bit_cast(bf16x8, b[k16][nt]);
+            acc[half][it][nt] = COPRIS_LM_MFMA(fa, fb, acc[half][it][nt]);
+            // The loads a wave issues per slab go out one at a time between the products.  Issued
+            // in a bunch they keep every wave of the CU at the issue stage while the address unit
+            // works through them, and the matrix pipes idle meanwhile; spread out they cost the
+            // products nothing.  First half: hidden (d+1, half 0) (its slot is free since the top
+            // barrier), then W(d+2) (likewise); second half: hidden (d+1, half 1) (the middle
+            // barrier has freed the slot of (d, half 0)).  Past the last slab the loads re-read
+            // clamped rows into ring slots nobody reads any more.
             if (half == 0 && (m & 1)) {
               const int q = 4 * grp + (m >> 1);                                   // 0 .. 7
               __builtin_amdgcn_sched_barrier(0);
               if (q < 4) {
-                h_load(q);
+                h_load(q, Half0{});
                 if (q == 3) h_advance();
               } else {
                 w_load(q - 4);
                 if (q == 7) w_advance();
               }
               __builtin_amdgcn_sched_barrier(0);
-            } else if (half == 1 && (m == 1 || m == 5)) {
-              const int q = 2 * grp + (m >> 2);                                   // 0 .. 3
+            } else if (half == 1 && m % 4 == 1) {
+              const int q = kNt * grp + (m >> 2);                                 // 0 .. 2 * NT1 - 1
               __builtin_amdgcn_sched_barrier(0);
-              h_load(q);
-              if (q == 3) h_advance();
+              h_load(q, Half1{});
+              if (q == 2 * NT1 - 1) h_advance();
               __builtin_amdgcn_sched_barrier(0);
             }
           }
         }
-      }
+      };
+      half_slab(Half0{});
+      half_slab(Half1{});
     }
 
     const bool tail = v0 + kMfBM > V;   // only the last tile can hold rows past V
     // written out per batch block: the unrolled body is too large for the unroll pragma
     auto epilogue = [&](auto ic) __attribute__((always_inline)) {
       constexpr int i = decltype(ic)::value;       // state index = 2*half + nt
-      const int c = c0 + 128 * (i >> 1) + 64 * wq + 32 * (i & 1) + l32;
+      const int c = state_row(i);
 #if defined(COPRIS_LM_PROBE_NO_EPILOGUE)
-      if (c < C) {   // keep the accumulators alive, nothing else
+      if (c < c_end) {   // keep the accumulators alive, nothing else
         st[i].s += acc[i >> 1][0][i & 1][0] + acc[i >> 1][1][i & 1][15];
         st[i].m = 0.0f;
         st[i].idx = v0;
       } else
 #endif
-      if (c < C && GIVEN) {
+      if (c < c_end && GIVEN) {
         lm_given_block(acc[i >> 1][0][i & 1], st[i], v0 + 64 * wm + 4 * kb, V, tail, inv_temperature,
                        static_cast<int>(step_c[i]));
         lm_given_block(acc[i >> 1][1][i & 1], st[i], v0 + 64 * wm + 32 + 4 * kb, V, tail,
                        inv_temperature, static_cast<int>(step_c[i]));
-      } else if (c < C) {
+      } else if (c < c_end) {
         lm_epilogue_block(acc[i >> 1][0][i & 1], st[i], v0 + 64 * wm + 4 * kb, V, tail,
                           inv_temperature, step_c[i], sid_lo[i], sid_hi[i], key0, key1);
         lm_epilogue_block(acc[i >> 1][1][i & 1], st[i], v0 + 64 * wm + 32 + 4 * kb, V, tail,
@@ -679,9 +711,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     };
     epilogue(std::integral_constant<int, 0>{});
     epilogue(std::integral_constant<int, 1>{});
-    if (HALVES == 2) {
+    if constexpr (HALVES == 2) {
       epilogue(std::integral_constant<int, 2>{});
-      epilogue(std::integral_constant<int, 3>{});
+      if constexpr (NT1 == 2) epilogue(std::integral_constant<int, 3>{});
     }
   }
 
@@ -690,14 +722,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
   LmPartial(*s_part)[kMfBN / 2] = reinterpret_cast<LmPartial(*)[kMfBN / 2]>(smem);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < kStates; ++i) {
     LmPartial p = lane_partial<GIVEN>(st[i]);
     if (wm == 1 && kb == 0) s_part[wq][32 * i + l32] = p;
     __syncthreads();
     if (wm == 0 && kb == 0) {
       combine(p, s_part[wq][32 * i + l32]);
-      const int c = c0 + 128 * (i >> 1) + 64 * wq + 32 * (i & 1) + l32;
-      if (c < C) part[static_cast<size_t>(c) * n_parts + blockIdx.x] = p;
+      const int c = state_row(i);
+      if (c < c_end) part[static_cast<size_t>(c) * n_parts + blockIdx.x] = p;
     }
     __syncthreads();
   }
@@ -722,11 +754,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // entries of one batch row) at a time: its ~30 vector instructions per entry would otherwise stop
 // the workgroup's loads.
 // --------------------------------------------------------------------------
-template <int N>
-__device__ __forceinline__ void wait_loads() {   // at most N of this wave's loads may still be in flight
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 // every LDS read of the slab's operands has arrived
 template <int NT>
 __device__ __forceinline__ void lds_arrived(u32x4 (&a)[4], u32x4 (&b)[4][NT]) {
@@ -1353,15 +1380,25 @@ static int launch_lmhead(const void* hidden, const void* weight, const int64_t* 
     const int n_tiles = (V + kMfBM - 1) / kMfBM;
     const dim3 grid(n_parts, (C + kMfBN - 1) / kMfBN);
     COPRIS_PRE("lmhead_mfma_kernel");
-#define COPRIS_LM_MFMA_LAUNCH(G, HV)                                                                   \
-  hipLaunchKernelGGL((lmhead_mfma_kernel<G, HV>), grid, dim3(256), 0, stream,                            \
+#define COPRIS_LM_MFMA_LAUNCH(G, HV, NT1)                                                                \
+  hipLaunchKernelGGL((lmhead_mfma_kernel<G, HV, NT1>), grid, dim3(256), 0, stream,                        \
                      static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(weight), seq_id, \
-                     step, target, key0, key1, inv_t, part, C, H, V, n_tiles, n_parts)
-    const bool one_half = C <= kMfBN / 2;      // only the first 128 batch rows exist
-    if (given && one_half) COPRIS_LM_MFMA_LAUNCH(true, 1);
-    else if (given) COPRIS_LM_MFMA_LAUNCH(true, 2);
-    else if (one_half) COPRIS_LM_MFMA_LAUNCH(false, 1);
-    else COPRIS_LM_MFMA_LAUNCH(false, 2);
+                     step, target, key0, key1, inv_t, part, C, H, V, block_rows, n_tiles, n_parts)
+    // The row blocks share the rows evenly; a block computes 128, 192 or 256.  (C = 301: two blocks
+    // of 192 instead of 256, and their odd tiles dealt from opposite ends: 132 -> 128 us per call;
+    // C = 160, H = 3584: 285 -> 257; M = 320 given tokens,
+    // H = 2048, V = 100000: 229 -> 204.  Both are bound by the depth of their W stream, some 1.8 us per slab.)
+    const int block_rows = ((C + static_cast<int>(grid.y) - 1) / static_cast<int>(grid.y) + 31) & ~31;
+    const int width = block_rows <= 128 ? 128 : (block_rows <= 192 ? 192 : 256);
+    if (given) {
+      if (width == 128) COPRIS_LM_MFMA_LAUNCH(true, 1, 2);
+      else if (width == 192) COPRIS_LM_MFMA_LAUNCH(true, 2, 1);
+      else COPRIS_LM_MFMA_LAUNCH(true, 2, 2);
+    } else {
+      if (width == 128) COPRIS_LM_MFMA_LAUNCH(false, 1, 2);
+      else if (width == 192) COPRIS_LM_MFMA_LAUNCH(false, 2, 1);
+      else COPRIS_LM_MFMA_LAUNCH(false, 2, 2);
+    }
 #undef COPRIS_LM_MFMA_LAUNCH
     COPRIS_POST("lmhead_mfma_kernel");
   } else {

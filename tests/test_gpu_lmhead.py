@@ -53,6 +53,20 @@ def test_few_rows_over_the_whole_vocabulary(R, C, H, V):
     P.check_token_logprob(lp2, lse2, P.oracle_token_logprob(inp["hidden"], inp["weight"], given, 1.0, W.BF16), f"given {C}x{H}x{V}")
 
 
+@pytest.mark.parametrize("C", [65, 128, 129, 160, 192, 193, 257, 301, 320, 383, 384, 385, 520])
+def test_row_blocks_of_every_width(R, C):
+    # row blocks of 128, 192 and 256, one, two and three of them, with the rows shared evenly; more
+    # tiles than workgroups per block in the larger ones (the odd block deals them from the end)
+    H, V = 64, 40000 if C > 256 else 9001
+    inp = W.make_small_lmhead_case(C * 13, C, H, V, W.BF16, w_std=0.1)
+    tok, lp, lse = R.run_lmhead_logprob(inp, W.BF16)
+    P.check_lmhead(tok, lp, lse, P.oracle_lmhead(inp, W.BF16), f"{C}x{H}x{V}")
+    if C < 384:
+        lp2, lse2 = R.run_token_logprob(inp["hidden"], inp["weight"], tok, 1.0, W.BF16)
+        np.testing.assert_allclose(lp2, lp, atol=2e-5)
+        np.testing.assert_allclose(lse2, lse, atol=2e-5)
+
+
 def test_zero_weights_token_is_argmax_of_the_noise(R):
     # isolates the Philox counter layout and the uniform -> Gumbel mapping
     C, H, V = 16, 64, 5000
