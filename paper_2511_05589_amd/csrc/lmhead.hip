@@ -92,45 +92,53 @@ __device__ __forceinline__ LmPartial empty_partial() {
 }
 
 // --------------------------------------------------------------------------
-// generic kernel (fp32 or bf16, vector ALU): wave w of a workgroup owns batch rows
+// generic kernel (bf16 whose hidden size the matrix-core kernels do not take; vector ALU): wave w of a workgroup owns batch rows
 // 4w..4w+3 of the 16-row block, lane l owns vocabulary row tile*64 + l.
 // --------------------------------------------------------------------------
-template <typename T> struct WVec;
-template <> struct WVec<float> {
-  static constexpr int N = 4;
-  static __device__ __forceinline__ void load(const float* p, float (&x)[8]) {
-    const float4 v = *reinterpret_cast<const float4*>(p);
-    x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-  }
-  static __device__ __forceinline__ float one(const float* p) { return *p; }
-};
-template <> struct WVec<uint16_t> {
-  static constexpr int N = 8;
-  static __device__ __forceinline__ void load(const uint16_t* p, float (&x)[8]) {
-    const uint4 v = *reinterpret_cast<const uint4*>(p);
-    x[0] = bf16lo_to_f32(v.x); x[1] = bf16hi_to_f32(v.x);
-    x[2] = bf16lo_to_f32(v.y); x[3] = bf16hi_to_f32(v.y);
-    x[4] = bf16lo_to_f32(v.z); x[5] = bf16hi_to_f32(v.z);
-    x[6] = bf16lo_to_f32(v.w); x[7] = bf16hi_to_f32(v.w);
-  }
-  static __device__ __forceinline__ float one(const uint16_t* p) { return bf16_to_f32(*p); }
-};
+__device__ __forceinline__ void load_bf16x8(const uint16_t* p, float (&x)[8]) {
+  const uint4 v = *reinterpret_cast<const uint4*>(p);
+  x[0] = bf16lo_to_f32(v.x); x[1] = bf16hi_to_f32(v.x);
+  x[2] = bf16lo_to_f32(v.y); x[3] = bf16hi_to_f32(v.y);
+  x[4] = bf16lo_to_f32(v.z); x[5] = bf16hi_to_f32(v.z);
+  x[6] = bf16lo_to_f32(v.w); x[7] = bf16hi_to_f32(v.w);
+}
 
-// GIVEN: no sampling; the partial that holds vocabulary entry target[c] carries its logit
-// (best = +inf marks it, so the same combine picks it up).
-template <typename T, bool GIVEN>
+// Logit z of vocabulary entry v of batch row c as a partial.  GIVEN: no sampling; the partial that
+// holds vocabulary entry target[c] carries its logit (best = +inf marks it, so the same combine
+// picks it up).
+template <bool GIVEN>
+__device__ __forceinline__ LmPartial tile_partial(float z, int v, int c, const int64_t* seq_id, const int32_t* step,
+                                                  const int32_t* target, uint32_t key0, uint32_t key1) {
+  if (GIVEN) {
+    const bool hit = v == target[c];
+    LmPartial p;
+    p.m = z;
+    p.s = 1.0f;
+    p.z = z;
+    p.best = hit ? INFINITY : -INFINITY;
+    p.idx = hit ? v : 0x7fffffff;
+    return p;
+  }
+  const uint64_t sid = static_cast<uint64_t>(seq_id[c]);
+  const Philox4 x = philox4x32_10(static_cast<uint32_t>(v) >> 2, static_cast<uint32_t>(step[c]),
+                                  static_cast<uint32_t>(sid), static_cast<uint32_t>(sid >> 32), key0, key1);
+  const int sel = v & 3;
+  const uint32_t word = sel == 0 ? x.x : (sel == 1 ? x.y : (sel == 2 ? x.z : x.w));
+  return logit_partial(z, v, word);
+}
+
+template <bool GIVEN>
 __global__ __launch_bounds__(256) void lmhead_generic_kernel(
-    const T* __restrict__ hidden, const T* __restrict__ weight, const int64_t* __restrict__ seq_id,
+    const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ weight, const int64_t* __restrict__ seq_id,
     const int32_t* __restrict__ step, const int32_t* __restrict__ target, uint32_t key0,
     uint32_t key1, float inv_temperature, LmPartial* __restrict__ part, int C, int H, int V,
     int n_tiles) {
-  constexpr int NV = WVec<T>::N;
   __shared__ float s_h[kLmTileC][kLmBK];
   const int tile = blockIdx.x, cb = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int v = tile * kLmTileV + lane;
   const bool v_ok = v < V;
-  const T* wrow = weight + static_cast<size_t>(v_ok ? v : 0) * H;
+  const uint16_t* wrow = weight + static_cast<size_t>(v_ok ? v : 0) * H;
   float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 
   for (int k0 = 0; k0 < H; k0 += kLmBK) {
@@ -139,15 +147,15 @@ __global__ __launch_bounds__(256) void lmhead_generic_kernel(
     for (int e = tid; e < kLmTileC * kn; e += 256) {
       const int r = e / kn, k = e - r * kn;
       const int c = cb * kLmTileC + r;
-      s_h[r][k] = c < C ? WVec<T>::one(hidden + static_cast<size_t>(c) * H + k0 + k) : 0.0f;
+      s_h[r][k] = c < C ? bf16_to_f32(hidden[static_cast<size_t>(c) * H + k0 + k]) : 0.0f;
     }
     __syncthreads();
     if (v_ok) {
-      for (int k = 0; k < kn; k += NV) {
+      for (int k = 0; k < kn; k += 8) {
         float x[8];
-        WVec<T>::load(wrow + k0 + k, x);
+        load_bf16x8(wrow + k0 + k, x);
 #pragma unroll
-        for (int j = 0; j < NV; ++j) {
+        for (int j = 0; j < 8; ++j) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) acc[r] = fmaf(s_h[4 * wave + r][k + j], x[j], acc[r]);
         }
@@ -160,23 +168,91 @@ __global__ __launch_bounds__(256) void lmhead_generic_kernel(
     const int c = cb * kLmTileC + 4 * wave + r;
     if (c >= C) continue;   // uniform across the wave
     LmPartial p = empty_partial();
-    if (v_ok && GIVEN) {
-      const float z = acc[r] * inv_temperature;
-      const bool hit = v == target[c];
-      p.m = z;
-      p.s = 1.0f;
-      p.z = z;
-      p.best = hit ? INFINITY : -INFINITY;
-      p.idx = hit ? v : 0x7fffffff;
-    } else if (v_ok) {
-      const uint64_t sid = static_cast<uint64_t>(seq_id[c]);
-      const Philox4 x = philox4x32_10(static_cast<uint32_t>(v) >> 2, static_cast<uint32_t>(step[c]),
-                                      static_cast<uint32_t>(sid), static_cast<uint32_t>(sid >> 32),
-                                      key0, key1);
-      const int sel = v & 3;
-      const uint32_t word = sel == 0 ? x.x : (sel == 1 ? x.y : (sel == 2 ? x.z : x.w));
-      p = logit_partial(acc[r] * inv_temperature, v, word);
+    if (v_ok) p = tile_partial<GIVEN>(acc[r] * inv_temperature, v, c, seq_id, step, target, key0, key1);
+    p = wave_combine(p);
+    if (lane == 0) part[static_cast<size_t>(c) * n_tiles + tile] = p;
+  }
+}
+
+// --------------------------------------------------------------------------
+// fp32 kernel: full-precision matrix products (mfma 16x16x4 fp32).
+//
+// A workgroup of 16 waves takes 64 vocabulary rows (one partial per batch row, as in the generic
+// kernel) against 16 * NB batch rows: four vocabulary groups of 16 rows x four quarters of the hidden
+// dimension.  Lane (i, b) of a product holds element b of row i, so a lane fetches 16-byte granules
+// 4j + b of its vocabulary row and of its batch rows and feeds four products with each; the operands
+// come straight from memory, kDeep granules of each in flight.  The quarters' sums are added in
+// order, and then every wave forms the partials of NB batch rows with one vocabulary entry per lane.
+// Small shapes are bound by the chain of latencies (16 products deep per quarter here, where a wave
+// of the vector-ALU kernel walked the whole hidden dimension with four entries in flight):
+// whole calls, C = 8, H = 256, V = 1024: 20.4 -> 10.8 us; C = 64, H = 1024, V = 32768: 283 -> 100;
+// C = 2, H = 3584, V = 100000: 1020 -> 272.
+// --------------------------------------------------------------------------
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kF32Threads = 1024;
+
+template <bool GIVEN, int NB>
+__global__ __launch_bounds__(kF32Threads) void lmhead_f32_kernel(
+    const float* __restrict__ hidden, const float* __restrict__ weight, const int64_t* __restrict__ seq_id,
+    const int32_t* __restrict__ step, const int32_t* __restrict__ target, uint32_t key0, uint32_t key1,
+    float inv_temperature, LmPartial* __restrict__ part, int C, int H, int V, int n_tiles) {
+  constexpr int kPitch = kLmTileV + 4;
+  constexpr int kDeep = NB == 1 ? 4 : 2;
+  __shared__ __attribute__((aligned(16))) float s_z[4][16 * NB][kPitch];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int vg = wave & 3, kq = wave >> 2;             // vocabulary group, quarter of the hidden dimension
+  const int n = lane & 15, b = lane >> 4;
+  const int tile = blockIdx.x, c0 = blockIdx.y * 16 * NB;
+  const int granules = H / 4;                          // of a row
+  const int steps = (granules + 3) / 4;                // four granules (16 elements) of a row per step
+  const int j0 = steps * kq / 4, j1 = steps * (kq + 1) / 4;
+  const float4* wrow = reinterpret_cast<const float4*>(weight + static_cast<size_t>(min(tile * kLmTileV + 16 * vg + n, V - 1)) * H);
+  const float4* hrow[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+    hrow[i] = reinterpret_cast<const float4*>(hidden + static_cast<size_t>(min(c0 + 16 * i + n, C - 1)) * H);
+  f32x4 acc[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  for (int j = j0; j < j1; j += kDeep) {
+    float4 x[kDeep], y[kDeep][NB];
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u) {
+      const int gr = 4 * (j + u) + b, at = gr < granules ? gr : 0;
+      x[u] = wrow[at];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) y[u][i] = hrow[i][at];
     }
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u) {
+      // past the quarter or the row: nothing (both sides zero, so that no infinity meets a zero)
+      const bool in = j + u < j1 && 4 * (j + u) + b < granules;
+      if (!in) x[u] = zero;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const float4 h = in ? y[u][i] : zero;
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u].x, h.x, acc[i], 0, 0, 0);
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u].y, h.y, acc[i], 0, 0, 0);
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u].z, h.z, acc[i], 0, 0, 0);
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u].w, h.w, acc[i], 0, 0, 0);
+      }
+    }
+  }
+  // lane (n, b): vocabulary rows 16*vg + 4b .. +3 of batch row 16*i + n
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+    *reinterpret_cast<float4*>(&s_z[kq][16 * i + n][16 * vg + 4 * b]) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+  __syncthreads();
+  const int v = tile * kLmTileV + lane;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int c = c0 + 16 * i + wave;
+    if (c >= C) continue;   // uniform across the wave
+    const float dot = ((s_z[0][16 * i + wave][lane] + s_z[1][16 * i + wave][lane]) + s_z[2][16 * i + wave][lane]) +
+                      s_z[3][16 * i + wave][lane];
+    LmPartial p = empty_partial();
+    if (v < V) p = tile_partial<GIVEN>(dot * inv_temperature, v, c, seq_id, step, target, key0, key1);
     p = wave_combine(p);
     if (lane == 0) part[static_cast<size_t>(c) * n_tiles + tile] = p;
   }
@@ -1401,17 +1477,29 @@ static int launch_lmhead(const void* hidden, const void* weight, const int64_t* 
     }
 #undef COPRIS_LM_MFMA_LAUNCH
     COPRIS_POST("lmhead_mfma_kernel");
+  } else if (dtype == 0) {
+    // (up to 16 rows the second half of a 32-row block would be padding)
+    COPRIS_PRE("lmhead_f32_kernel");
+#define COPRIS_LM_F32(G, NB)                                                                              \
+  hipLaunchKernelGGL((lmhead_f32_kernel<G, NB>), dim3(n_parts, (C + 16 * NB - 1) / (16 * NB)),            \
+                     dim3(kF32Threads), 0, stream, static_cast<const float*>(hidden),                     \
+                     static_cast<const float*>(weight), seq_id, step, target, key0, key1, inv_t, part, C, \
+                     H, V, n_parts)
+    if (given && C <= 16) COPRIS_LM_F32(true, 1);
+    else if (given) COPRIS_LM_F32(true, 2);
+    else if (C <= 16) COPRIS_LM_F32(false, 1);
+    else COPRIS_LM_F32(false, 2);
+#undef COPRIS_LM_F32
+    COPRIS_POST("lmhead_f32_kernel");
   } else {
     const dim3 grid(n_parts, (C + kLmTileC - 1) / kLmTileC);
-#define COPRIS_LM_GENERIC(T, G)                                                                   \
-  hipLaunchKernelGGL((lmhead_generic_kernel<T, G>), grid, dim3(256), 0, stream,                   \
-                     static_cast<const T*>(hidden), static_cast<const T*>(weight), seq_id, step,  \
+#define COPRIS_LM_GENERIC(G)                                                                      \
+  hipLaunchKernelGGL((lmhead_generic_kernel<G>), grid, dim3(256), 0, stream,            \
+                     static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(weight), seq_id, step,  \
                      target, key0, key1, inv_t, part, C, H, V, n_parts)
     COPRIS_PRE("lmhead_generic_kernel");
-    if (dtype == 0 && given) COPRIS_LM_GENERIC(float, true);
-    else if (dtype == 0) COPRIS_LM_GENERIC(float, false);
-    else if (given) COPRIS_LM_GENERIC(uint16_t, true);
-    else COPRIS_LM_GENERIC(uint16_t, false);
+    if (given) COPRIS_LM_GENERIC(true);
+    else COPRIS_LM_GENERIC(false);
 #undef COPRIS_LM_GENERIC
     COPRIS_POST("lmhead_generic_kernel");
   }

@@ -67,6 +67,17 @@ def test_row_blocks_of_every_width(R, C):
         np.testing.assert_allclose(lse2, lse, atol=2e-5)
 
 
+@pytest.mark.parametrize("C,H,V", [(1, 4, 3), (16, 60, 64), (17, 68, 65), (32, 132, 63), (33, 1028, 129), (8, 12, 4000)])
+def test_fp32_ends_of_rows_and_quarters(R, C, H, V):
+    # hidden sizes that leave a quarter, a step or part of a granule group empty
+    inp = W.make_small_lmhead_case(C * 17 + H, C, H, V, W.F32, w_std=0.2)
+    tok, lp, lse = R.run_lmhead_logprob(inp, W.F32)
+    P.check_lmhead(tok, lp, lse, P.oracle_lmhead(inp, W.F32), f"f32 {C}x{H}x{V}")
+    given = (np.arange(C) * 31 % V).astype(np.int32)
+    lp2, lse2 = R.run_token_logprob(inp["hidden"], inp["weight"], given, 1.0, W.F32)
+    P.check_token_logprob(lp2, lse2, P.oracle_token_logprob(inp["hidden"], inp["weight"], given, 1.0, W.F32), f"f32 given {C}x{H}x{V}")
+
+
 def test_zero_weights_token_is_argmax_of_the_noise(R):
     # isolates the Philox counter layout and the uniform -> Gumbel mapping
     C, H, V = 16, 64, 5000
