@@ -841,7 +841,8 @@ __global__ __launch_bounds__(256) void attn_merge_flat_kernel(const int32_t* __r
                                                               float* __restrict__ lse, int C, int Hq,
                                                               int Hkv, int g, int max_tokens) {
   constexpr int kQuads = D / 4;              // threads across the head_dim, four elements each
-  constexpr int kTeams = 256 / kQuads;
+  constexpr int kTeams = 256 / kQuads;       // at most
+  const int threads = blockDim.x, teams = threads / kQuads;
   __shared__ int s_before[256 / kWave], s_all[256 / kWave];
   const int seq = blockIdx.x, kvh = blockIdx.y;
   int share, npg, pg0;
@@ -853,7 +854,7 @@ __global__ __launch_bounds__(256) void attn_merge_flat_kernel(const int32_t* __r
     // pieces before this sequence and in total, from ctx_len (the same counts the split
     // kernel's wavefronts derived their cursors from)
     int before = 0, all = 0;
-    for (int i = threadIdx.x; i < C; i += 256) {
+    for (int i = threadIdx.x; i < C; i += threads) {
       const int pgs = attn_pieces_of(ctx_len, i, max_tokens);
       all += pgs;
       before += i < seq ? pgs : 0;
@@ -867,8 +868,7 @@ __global__ __launch_bounds__(256) void attn_merge_flat_kernel(const int32_t* __r
     __syncthreads();
     pg0 = 0;
     int pages = 0;
-#pragma unroll
-    for (int w = 0; w < 256 / kWave; ++w) {
+    for (int w = 0; w < threads / kWave; ++w) {
       pg0 += s_before[w];
       pages += s_all[w];
     }
@@ -891,7 +891,7 @@ __global__ __launch_bounds__(256) void attn_merge_flat_kernel(const int32_t* __r
   __shared__ float2 s_ml[kTeams];
   const int team = threadIdx.x / kQuads, d4 = threadIdx.x % kQuads;
   const int heads = (g - static_cast<int>(blockIdx.z) + static_cast<int>(gridDim.z) - 1) / static_cast<int>(gridDim.z);
-  const int per_head = heads >= kTeams ? 1 : kTeams / heads;
+  const int per_head = n <= kBatch || heads >= teams ? 1 : teams / heads;   // (one round trip needs one team)
   const int sub = team % per_head;
   auto store = [&](int h, float m_star, float denom, const float4& num) __attribute__((always_inline)) {
     const size_t oh = static_cast<size_t>(seq) * Hq + kvh * g + h;
@@ -900,9 +900,9 @@ __global__ __launch_bounds__(256) void attn_merge_flat_kernel(const int32_t* __r
     if (lse != nullptr && d4 == 0)
       lse[oh] = n > 0 ? (m_star + __builtin_amdgcn_logf(denom)) * kLn2 : -INFINITY;
   };
-  for (int h0 = 0; h0 < heads; h0 += kTeams / per_head) {
+  for (int h0 = 0; h0 < heads; h0 += teams / per_head) {
     const int hi = h0 + team / per_head;
-    const bool mine = hi < heads && team < kTeams / per_head * per_head;
+    const bool mine = hi < heads && team < teams / per_head * per_head;
     const int h = blockIdx.z + (mine ? hi : 0) * gridDim.z;
     const size_t slot0 = (static_cast<size_t>(w0) + seg) * g + h;   // consecutive wavefronts: stride g
     float m_run = -INFINITY, denom = 0.0f;
@@ -992,8 +992,16 @@ static void enqueue_split(const AttnFlatArgs& a, int waves) {
                      static_cast<const u32x4*>(a.v_cache), a.block_table, a.ctx_len, a.hdr, a.start,      \
                      a.ws_ml, a.ws_acc, static_cast<T*>(a.out), a.lse, a.C, a.Hq, a.Hkv, a.g, LSP,        \
                      a.max_pages, a.max_tokens, a.scale_log2e)
+  // Rounded weights stay where they always were, at head_dim 128 / page 16, and there only in
+  // pools whose table admits more than kSplitSlots slots.  (A share's largest weight is exactly 1;
+  // below that size a share used to be one to three slots, so that shares of four alone would round
+  // more of them: 1.9e-3 -> 2.1e-3 against 64 bits.  What the second product costs: 64 sequences,
+  // 12 / 2 heads 33.8 -> 34.3 us, 256 sequences, 28 / 4 heads 313.3 -> 314.6.)
+  constexpr int64_t kSplitSlots = 16 * kAttnWaves;
   constexpr bool kSplitP = sizeof(T) == 2;
-  if (a.page_size == 16) COPRIS_SPLIT(16, kSplitP && D != 128, 0);
+  const bool small = static_cast<int64_t>(a.C) * ((a.max_tokens + kP - 1) / kP) * a.Hkv <= kSplitSlots;
+  if (a.page_size == 16 && D == 128 && !small) COPRIS_SPLIT(16, false, 0);
+  else if (a.page_size == 16) COPRIS_SPLIT(16, kSplitP, 0);
   else if (a.page_size == 8) COPRIS_SPLIT(8, kSplitP, 0);
   else COPRIS_SPLIT(0, kSplitP, __builtin_ctz(static_cast<unsigned>(a.page_size / kP)));   // page_size divides 512
 #undef COPRIS_SPLIT
@@ -1025,14 +1033,17 @@ static int launch_flat(const AttnFlatArgs& a) {
   // after the other, 6 us here; at 256 sequences, 28 / 4 heads, one per segment: 10 -> 8 us).
   int z = kMergeFill / (a.C * a.Hkv);
   z = z < 1 ? 1 : (z < a.g ? z : a.g);
+  // one team of threads per head is enough for a large pool, and its workgroups start sooner
+  const int one_team = (a.g * (D / 4) + kWave - 1) / kWave * kWave;
+  const int threads = z > 1 || one_team > 256 ? 256 : one_team;
   const dim3 grid(a.C, a.Hkv, z);
   COPRIS_PRE("attn_merge_flat_kernel");
   if (prescan) {
-    hipLaunchKernelGGL((attn_merge_flat_kernel<T, D, true>), grid, dim3(256), 0, stream, a.ctx_len, a.hdr,
+    hipLaunchKernelGGL((attn_merge_flat_kernel<T, D, true>), grid, dim3(threads), 0, stream, a.ctx_len, a.hdr,
                        a.seq_off, a.ws_ml, a.ws_acc, static_cast<T*>(a.out), a.lse, a.C, a.Hq, a.Hkv, a.g,
                        a.max_tokens);
   } else {
-    hipLaunchKernelGGL((attn_merge_flat_kernel<T, D, false>), grid, dim3(256), 0, stream, a.ctx_len, a.hdr,
+    hipLaunchKernelGGL((attn_merge_flat_kernel<T, D, false>), grid, dim3(threads), 0, stream, a.ctx_len, a.hdr,
                        a.seq_off, a.ws_ml, a.ws_acc, static_cast<T*>(a.out), a.lse, a.C, a.Hq, a.Hkv, a.g,
                        a.max_tokens);
   }

@@ -72,9 +72,9 @@ def test_a_context_that_hundreds_of_shares_cut(R, dtype, D, Hq, Hkv):
     _run_case(R, case, dtype, f"{dtype} D={D} {Hq}/{Hkv}")
 
 
-@pytest.mark.parametrize("D,page", [(64, 16), (128, 8), (128, 32)])
+@pytest.mark.parametrize("D,page", [(64, 16), (128, 8), (128, 32), (128, 16)])
 def test_bf16_weights_keep_their_precision(R, D, page):
-    # Outside head_dim 128 / page 16 the weights are not rounded to bf16: what is left is the
+    # Outside large pools of head_dim 128 / page 16 the weights are not rounded to bf16: what is left is the
     # result's own rounding, 2^-9 relative at worst for one element and 2^-9 / sqrt(3) in the
     # 2-norm for uniformly spread mantissas (1.13e-3; up to 1.95e-3 if all mantissas were 1.0).
     ctx = [700, 1033, 64, 2000]
