@@ -1128,15 +1128,15 @@ template <bool W_DEEP>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void lmhead_gemm_given_kernel(
     const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ weight,
     const int32_t* __restrict__ target, float inv_temperature, LmPartial* __restrict__ part, int C,
-    int H, int V, int n_tiles, int n_parts) {
+    int H, int V, int lane_units, int n_parts) {
   __shared__ __attribute__((aligned(1024))) char smem[kGmLds];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 2, wq = wave & 3;     // 128-row vocabulary half; 64-row batch block
+  const int wm = wave >> 2, wq = wave & 3;     // vocabulary rows 64*rb + 32*wm ..; 64-row batch block
   const int l32 = lane & 31, kb = lane >> 5;
-  // grid = (row blocks, tile lanes): consecutive workgroups (which the dispatcher deals out
+  // grid = (row blocks, vocabulary lanes): consecutive workgroups (which the dispatcher deals out
   // to the XCDs in turn) differ in the row block, so one XCD's L2 sees few row blocks
-  const int lane_id = blockIdx.y, n_lanes = gridDim.y;
+  const int lane_id = blockIdx.y;
   const int c0 = blockIdx.x * kGmBN;
   const int nkd = H / kMfBK;
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
@@ -1145,11 +1145,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr int kWSlots = W_DEEP ? 3 : 2, kHSlots = W_DEEP ? 2 : 3;
   constexpr int kHBase = kWSlots * kGmSlab;
 
-  // operand read offsets inside a slab (bytes); each further 32-row block adds 4096
+  // A lane owns a contiguous run of lane_units * 64 vocabulary rows, the same for all (the last
+  // one's may be shorter): whole tiles, then one of one to three row blocks of 64 where they are left.
+  // Dealt out as whole tiles the last round would run as long as any other: 2.5 rounds instead of 3
+  // at M = 2000, V = 20011 and 9.5 instead of 10 at M = 777, V = 151936.
+  const int v_begin = lane_id * lane_units * 64, v_end = min(v_begin + lane_units * 64, V);
+
+  // operand read offsets inside a slab (bytes); each further row block of W adds 64 rows = 8192
+  // bytes, of the hidden state 32 rows = 4096
   uint32_t a_off[4], b_off[4];
 #pragma unroll
   for (int k16 = 0; k16 < 4; ++k16) {
-    a_off[k16] = lm_swz(128 * wm + l32, 2 * k16 + kb) * 16;
+    a_off[k16] = lm_swz(32 * wm + l32, 2 * k16 + kb) * 16;
     b_off[k16] = lm_swz(64 * wq + l32, 2 * k16 + kb) * 16;
   }
 
@@ -1157,11 +1164,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // four instructions of 8 rows x 128 bytes; LDS position 64*chunk + lane holds (row
   // 8*chunk + lane/8, stored granule lane%8) and the lane fetches the global granule the
   // swizzle maps there ((row>>1)&7 = lane>>4 for even chunks, +4 for odd ones).
-  const int my_tiles = (n_tiles - 1 - lane_id) / n_lanes + 1;
-  const int total = my_tiles * nkd;            // slabs this workgroup consumes
+  const int total = (v_end - v_begin + kGmBM - 1) / kGmBM * nkd;   // slabs this workgroup consumes
   const int ld_row = 32 * wave + (lane >> 3);
   const uint32_t ld_g = ((lane & 7) ^ (lane >> 4)) * 16;
-  int w_tile = lane_id, w_kd = 0, w_slot = 0;
+  int w_row = v_begin, w_kd = 0, w_slot = 0;
   int h_kd = 0, h_slot = 0;
   const char* wbase = reinterpret_cast<const char*>(weight);
   const char* hbase = reinterpret_cast<const char*>(hidden);
@@ -1169,7 +1175,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   auto w_load = [&](int j) __attribute__((always_inline)) {
     char* dst = smem + w_slot * kGmSlab + (4 * wave + j) * 1024;
     const uint32_t koff = static_cast<uint32_t>(w_kd) * (kMfBK * 2) + ld_g;
-    const int v = min(w_tile * kGmBM + ld_row + 8 * j, V - 1);   // rows past V re-read the last row (masked later)
+    const int v = min(w_row + ld_row + 8 * j, v_end - 1);   // rows past the run re-read its last row (masked or skipped later)
     __builtin_amdgcn_global_load_lds(wbase + (static_cast<uint32_t>(v) * pitch + (koff ^ ((j & 1) * 64))), dst,
                                      16, 0, 0);
   };
@@ -1177,7 +1183,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     w_slot = w_slot + 1 == kWSlots ? 0 : w_slot + 1;
     if (++w_kd == nkd) {
       w_kd = 0;
-      w_tile += n_lanes;
+      w_row += kGmBM;
     }
   };
   auto h_load = [&](int j) __attribute__((always_inline)) {
@@ -1235,9 +1241,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   auto read_operands = [&](auto bufc, auto k16c) __attribute__((always_inline)) {
     constexpr int buf = decltype(bufc)::value, k16 = decltype(k16c)::value;
     a[buf][0] = lds_read128<0>(wb + a_off[k16]);
-    a[buf][1] = lds_read128<4096>(wb + a_off[k16]);
-    a[buf][2] = lds_read128<8192>(wb + a_off[k16]);
-    a[buf][3] = lds_read128<12288>(wb + a_off[k16]);
+    a[buf][1] = lds_read128<8192>(wb + a_off[k16]);
+    a[buf][2] = lds_read128<16384>(wb + a_off[k16]);
+    a[buf][3] = lds_read128<24576>(wb + a_off[k16]);
     b[buf][0] = lds_read128<0>(hb + b_off[k16]);
     b[buf][1] = lds_read128<4096>(hb + b_off[k16]);
   };
@@ -1248,24 +1254,27 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   read_operands(I0{}, I0{});
 
   int d = 0;
-  for (int tile = lane_id; tile < n_tiles; tile += n_lanes) {
-    const int v0 = tile * kGmBM;
+  for (int v0 = v_begin; v0 < v_end; v0 += kGmBM) {
+    const int blocks = min(4, (v_end - v0 + 63) / 64);     // row blocks of the tile
     f32x16 acc[4][2];
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i >> 1][i & 1][r] = 0.0f;
-    // eight products from operand buffer `buf`; if `issue`, loads FIRST and FIRST+1 of the
-    // open set go out after the second and the sixth of them
-    auto products = [&](auto bufc, auto firstc, const bool issue) __attribute__((always_inline)) {
+    // eight products from operand buffer `buf` (two per row block); if `issue`, loads FIRST and
+    // FIRST+1 of the open set go out after the second and the sixth of them
+    auto products = [&](auto fullc, auto bufc, auto firstc, const bool issue) __attribute__((always_inline)) {
+      constexpr bool kFull = decltype(fullc)::value;
       constexpr int buf = decltype(bufc)::value, kFirst = decltype(firstc)::value;
       const bf16x8 fb0 = __builtin_bit_cast(bf16x8, b[buf][0]);
       const bf16x8 fb1 = __builtin_bit_cast(bf16x8, b[buf][1]);
 #pragma unroll
       for (int rb = 0; rb < 4; ++rb) {
         const bf16x8 fa = __builtin_bit_cast(bf16x8, a[buf][rb]);
-        acc[rb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb0, acc[rb][0], 0, 0, 0);
-        acc[rb][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb1, acc[rb][1], 0, 0, 0);
+        if (kFull || rb < blocks) {
+          acc[rb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb0, acc[rb][0], 0, 0, 0);
+          acc[rb][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb1, acc[rb][1], 0, 0, 0);
+        }
         if (rb == 0 || rb == 2) {
           __builtin_amdgcn_sched_barrier(0);
           if (issue) load_one(kFirst + (rb >> 1));
@@ -1278,16 +1287,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     using L4 = std::integral_constant<int, 4>;
     using L6 = std::integral_constant<int, 6>;
 
+    auto slabs = [&](auto fullc) __attribute__((always_inline)) {
     for (int kd = 0; kd < nkd; ++kd, ++d) {
       read_operands(I1{}, I1{});
       lds_wait6<6>(a[0], b[0]);
-      products(I0{}, L2{}, true);
+      products(fullc, I0{}, L2{}, true);
       read_operands(I0{}, I2{});
       lds_wait6<6>(a[1], b[1]);
-      products(I1{}, L4{}, true);
+      products(fullc, I1{}, L4{}, true);
       read_operands(I1{}, I3{});
       lds_wait6<6>(a[0], b[0]);
-      products(I0{}, L6{}, true);
+      products(fullc, I0{}, L6{}, true);
       // every LDS read of slab d is complete; the other operand buffer is tied as well so
       // that the products just issued from it stay above this wait
       asm volatile("s_waitcnt lgkmcnt(0)"
@@ -1306,18 +1316,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         hb = lds0 + kHBase + hslot * kGmSlab;
         read_operands(I0{}, I0{});                // first operands of slab d+1, under the products below
       }
-      products(I1{}, L0{}, more);                 // with the first two loads into the slots of slab d
+      products(fullc, I1{}, L0{}, more);                 // with the first two loads into the slots of slab d
     }
+    };
+    if (blocks == 4) slabs(std::true_type{});
+    else slabs(std::false_type{});
 
-    const bool tail = v0 + kGmBM > V;   // only the last tile can hold rows past V
+    const bool tail = v0 + kGmBM > v_end;   // only a run's last tile can hold rows past it
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
       const int c = c0 + 64 * wq + 32 * nt + l32;
       if (c < C) {
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb)
-          lm_given_block(acc[rb][nt], st[nt], v0 + 128 * wm + 32 * rb + 4 * kb, V, tail, inv_temperature,
-                         tgt[nt]);
+          if (rb < blocks)
+            lm_given_block(acc[rb][nt], st[nt], v0 + 64 * rb + 32 * wm + 4 * kb, v_end, tail, inv_temperature,
+                           tgt[nt]);
       }
     }
   }
@@ -1400,6 +1414,14 @@ static int lm_skinny_rows(int V) {
   return rows < kLmTileV ? kLmTileV : rows;
 }
 
+// Vocabulary rows per lane of the 256 x 256 kernel, in blocks of 64: an equal share for as many lanes
+// as there are CUs for every row block.
+static int lm_gemm_lane_units(int C, int V) {
+  const int blocks = (C + kGmBN - 1) / kGmBN, units = (V - 1) / 64 + 1;
+  const int lanes = kGmMaxGrid / blocks < 1 ? 1 : kGmMaxGrid / blocks;
+  return (units + lanes - 1) / lanes;
+}
+
 // Partials per row.  Matrix-core kernels: the grid is (parts, blocks of 256 rows) with
 // parts * blocks <= the resident workgroups (512, or 256 for the 256 x 256 kernel) where
 // possible, so that the workgroups that run at the same time walk the same vocabulary tiles
@@ -1408,11 +1430,10 @@ static int lm_skinny_rows(int V) {
 static int lm_parts(int C, int H, int V, int dtype, bool given) {
   if (!lm_use_mfma(C, H, V, dtype)) return (V + kLmTileV - 1) / kLmTileV;
   if (lm_use_skinny(C, H, V, dtype)) return (V - 1) / lm_skinny_rows(V) + 1;
-  const bool gemm = lm_use_gemm(C, H, V, dtype, given);
-  const int bm = gemm ? kGmBM : kMfBM;
-  const int n_tiles = (V + bm - 1) / bm;
+  if (lm_use_gemm(C, H, V, dtype, given)) return (V - 1) / (64 * lm_gemm_lane_units(C, V)) + 1;
+  const int n_tiles = (V + kMfBM - 1) / kMfBM;
   const int blocks = (C + kMfBN - 1) / kMfBN;
-  int parts = (gemm ? kGmMaxGrid : kMfMaxGrid) / blocks;
+  int parts = kMfMaxGrid / blocks;
   parts = parts < 1 ? 1 : parts;
   return parts < n_tiles ? parts : n_tiles;
 }
@@ -1432,12 +1453,11 @@ static int launch_lmhead(const void* hidden, const void* weight, const int64_t* 
   const bool given = target != nullptr;
   const int n_parts = lm_parts(C, H, V, dtype, given);
   if (lm_use_gemm(C, H, V, dtype, given)) {
-    const int n_tiles = (V + kGmBM - 1) / kGmBM;
     const dim3 grid((C + kGmBN - 1) / kGmBN, n_parts);
     COPRIS_PRE("lmhead_gemm_given_kernel");
     hipLaunchKernelGGL(lmhead_gemm_given_kernel<true>, grid, dim3(512), 0, stream,
                        static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(weight),
-                       target, inv_t, part, C, H, V, n_tiles, n_parts);
+                       target, inv_t, part, C, H, V, lm_gemm_lane_units(C, V), n_parts);
     COPRIS_POST("lmhead_gemm_given_kernel");
   } else if (lm_use_skinny(C, H, V, dtype)) {
     const int rows = lm_skinny_rows(V);

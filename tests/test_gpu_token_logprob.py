@@ -41,6 +41,15 @@ def test_small_shapes(R, dtype, M, H, V):
     P.check_token_logprob(lp, lse, P.oracle_token_logprob(h, w, tok, 1.0, dtype), f"{dtype} {M}x{H}x{V}")
 
 
+@pytest.mark.parametrize("M,H,V", [(1300, 64, 13000), (1300, 128, 14011), (1300, 64, 18000),   # a whole tile and 1, 2, 3 row blocks per lane
+                                   (384, 64, 1), (385, 192, 65), (600, 64, 8193),            # one row, one block and a row, blocks only
+                                   (3000, 64, 21505)])                                       # several tiles, a last lane of one block
+def test_runs_that_end_inside_a_tile(R, M, H, V):
+    h, w, tok = _case(M * 5 + V, M, H, V, W.BF16)
+    lp, lse = R.run_token_logprob(h, w, tok, 1.0, W.BF16)
+    P.check_token_logprob(lp, lse, P.oracle_token_logprob(h, w, tok, 1.0, W.BF16), f"{M}x{H}x{V}")
+
+
 def test_temperature(R):
     h, w, tok = _case(5, 48, 256, 3000, W.BF16, w_std=0.1)
     lp, lse = R.run_token_logprob(h, w, tok, 0.6, W.BF16)
