@@ -1481,7 +1481,7 @@ static int launch_lmhead(const void* hidden, const void* weight, const int64_t* 
                      static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(weight), seq_id, \
                      step, target, key0, key1, inv_t, part, C, H, V, block_rows, n_tiles, n_parts)
     // The row blocks share the rows evenly; a block computes 128, 192 or 256.  (C = 301: two blocks
-    // of 192 instead of 256, and their odd tiles dealt from opposite ends: 132 -> 128 us per call;
+    // of 192 instead of 256, and their odd tiles dealt from opposite ends: 132 -> 124 us per call;
     // C = 160, H = 3584: 285 -> 257; M = 320 given tokens,
     // H = 2048, V = 100000: 229 -> 204.  Both are bound by the depth of their W stream, some 1.8 us per slab.)
     const int block_rows = ((C + static_cast<int>(grid.y) - 1) / static_cast<int>(grid.y) + 31) & ~31;
