@@ -374,6 +374,18 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return r;
 }
 
+// A weight (0 or 2^-126 .. 1) as the sum of two bf16 numbers: its first 8 significant bits, and the rest rounded to 8
+// bits (2^-16 of the weight at worst).  Neither part is negative, and the rest of a weight above 0 is raised to at
+// least 2^-126, so that an infinite value times both parts is that infinity (0 x infinity and the difference of two
+// would be NaN).
+__device__ __forceinline__ uint32_t cut_bf16x2(float lo, float hi) {
+  return (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u);
+}
+__device__ __forceinline__ float rest_of_cut(float p) {
+  const float rest = p - __uint_as_float(__float_as_uint(p) & 0xffff0000u);
+  return fmaxf(rest, fminf(p, 0x1p-126f));
+}
+
 __device__ __forceinline__ void store_out4(uint16_t* p, float a, float b, float c, float d) {
   *reinterpret_cast<ushort4*>(p) = make_ushort4(f32_to_bf16(a), f32_to_bf16(b), f32_to_bf16(c), f32_to_bf16(d));
 }
@@ -494,9 +506,9 @@ constexpr int kAttnMaxSeqTuned = 1 << 17;
 constexpr int kAttnMaxSeqInKernelCursor = 4096;
 
 // PG, tokens per page: 16 (a slot is a page's slab), 8 (a slot is two pages) or 0 (16 << lsp).
-// SPLIT_P (bf16): the weights enter the value product as two bf16 numbers, the rounded weight
-// and what the rounding left over, instead of as the rounded weight alone.  Without it their
-// rounding is as large as the result's own: error against 64 bits 2.1e-3 instead of 1.7e-3.
+// SPLIT_P (bf16): the weights enter the value product as two bf16 numbers (cut_bf16x2 and
+// rest_of_cut) instead of as the rounded weight alone.  Without it their rounding is as large as
+// the result's own: error against 64 bits 2.1e-3 instead of 1.7e-3.
 // Two wavefronts per SIMD, except for slots of 16 KB (fp32, head_dim 128): their two stages
 // need more registers than half the file holds.
 template <typename T, int D> constexpr int kFlatWavesPerSimd = sizeof(T) * D > 256 ? 1 : 2;
@@ -710,12 +722,14 @@ __attribute__((amdgpu_waves_per_eu(kFlatWavesPerSimd<T, D>, kFlatWavesPerSimd<T,
     // O^T[d][head] += V^T[d][token] P^T[token][head]; rows past the context may hold anything
     // (NaN) and are zeroed
     if constexpr (kBf16) {
-      const uint2 pk = make_uint2(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]));
-      const s16x4 pf = __builtin_bit_cast(s16x4, pk);
-      s16x4 pl = {0, 0, 0, 0};
-      if (SPLIT_P)
-        pl = __builtin_bit_cast(s16x4, make_uint2(pack_bf16x2(p[0] - bf16lo_to_f32(pk.x), p[1] - bf16hi_to_f32(pk.x)),
-                                                  pack_bf16x2(p[2] - bf16lo_to_f32(pk.y), p[3] - bf16hi_to_f32(pk.y))));
+      s16x4 pf, pl = {0, 0, 0, 0};
+      if (SPLIT_P) {
+        pf = __builtin_bit_cast(s16x4, make_uint2(cut_bf16x2(p[0], p[1]), cut_bf16x2(p[2], p[3])));
+        pl = __builtin_bit_cast(s16x4, make_uint2(pack_bf16x2(rest_of_cut(p[0]), rest_of_cut(p[1])),
+                                                  pack_bf16x2(rest_of_cut(p[2]), rest_of_cut(p[3]))));
+      } else {
+        pf = __builtin_bit_cast(s16x4, make_uint2(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3])));
+      }
       // A = V^T via the transposing read (lane supplies row 4b + L/4, columns
       // 16dt + 4(L%4)..+3, L = lane&15)
       const int vrow = 4 * b + (head >> 2);

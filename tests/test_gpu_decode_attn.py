@@ -86,6 +86,28 @@ def test_bf16_weights_keep_their_precision(R, D, page):
     assert np.linalg.norm(out - ref) / np.linalg.norm(ref) <= 1.02 * floor
 
 
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("D,page", [(64, 16), (128, 8), (128, 32), (128, 16)])
+def test_infinite_values_reach_the_result(R, D, page, dtype):
+    # an infinite V element inside a context makes its head_dim index infinite (weights are above
+    # 0 here), whatever the form in which the weights enter the value product; every other index
+    # stays what it was
+    case = W.make_small_decode_case(9, 3, 12, 2, D, dtype, page, [700, 16, 1033])
+    ref, ref_lse = P.oracle_attn(case, dtype)
+    v = case["v_cache"].copy()
+    hit = np.zeros(ref.shape, dtype=np.float64)
+    for seq, n in ((0, 700), (2, 1033)):
+        for i, t in enumerate(range(0, n, 23)):         # an index of its own for each: no two infinities meet
+            page_id, d = case["block_table"][seq, t // page], i % D
+            x = W.to_f32(v[page_id], dtype)
+            x[:, t % page, d] = np.inf if i % 2 else -np.inf
+            v[page_id] = W.to_storage(x, dtype)
+            hit[seq, :, d] = np.inf if i % 2 else -np.inf
+    out, lse = R.run_decode_attn(dict(case, v_cache=v), dtype)
+    np.testing.assert_array_equal(out[hit != 0], hit[hit != 0])
+    P.check_attn(np.where(hit != 0, ref, out), lse, ref, ref_lse, dtype, f"{dtype} D={D} page={page}")
+
+
 def test_page_permutation_is_bitwise_invariant_and_runs_are_reproducible(R):
     ctx = [1000, 37, 1536, 513]
     case = W.make_small_decode_case(7, 4, 28, 4, 128, W.BF16, 16, ctx)
