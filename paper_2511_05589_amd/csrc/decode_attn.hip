@@ -25,7 +25,7 @@
 // cores with the TOKENS (scores) or the head dimension (values) as the 16-row M side and
 // the 16-padded group of query heads as the N side (bf16, head_dim 128):
 //     S^T[token][head] = K_slot[token][:] . Q[head][:]          4 x mfma 16x16x32
-//     O^T[d][head]    += V_slot^T[d][token] . P^T[token][head]  8 x mfma 16x16x16
+//     O^T[d][head]    += V_slot^T[d][token] . P^T[token][head]  2 x 8 x mfma 16x16x16
 // With that orientation the score tile leaves the first product already in the register
 // layout the second one wants for P^T, and every per-head softmax quantity (max, sum,
 // rescale factor) lives in the lane that owns the head.  A slot's K (and V) is one
@@ -379,11 +379,11 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // least 2^-126, so that an infinite value times both parts is that infinity (0 x infinity and the difference of two
 // would be NaN).
 __device__ __forceinline__ uint32_t cut_bf16x2(float lo, float hi) {
-  return (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u);
+  return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);   // the upper halves
 }
 __device__ __forceinline__ float rest_of_cut(float p) {
-  const float rest = p - __uint_as_float(__float_as_uint(p) & 0xffff0000u);
-  return fmaxf(rest, fminf(p, 0x1p-126f));
+  const float rest = p - __uint_as_float(__float_as_uint(p) & 0xffff0000u);   // 0 <= rest <= p
+  return __builtin_amdgcn_fmed3f(rest, 0x1p-126f, p);
 }
 
 __device__ __forceinline__ void store_out4(uint16_t* p, float a, float b, float c, float d) {
@@ -506,13 +506,16 @@ constexpr int kAttnMaxSeqTuned = 1 << 17;
 constexpr int kAttnMaxSeqInKernelCursor = 4096;
 
 // PG, tokens per page: 16 (a slot is a page's slab), 8 (a slot is two pages) or 0 (16 << lsp).
-// SPLIT_P (bf16): the weights enter the value product as two bf16 numbers (cut_bf16x2 and
-// rest_of_cut) instead of as the rounded weight alone.  Without it their rounding is as large as
-// the result's own: error against 64 bits 2.1e-3 instead of 1.7e-3.
+// bf16: the weights enter the value product as two bf16 numbers (cut_bf16x2 and rest_of_cut).
+// As one rounded number each their rounding is as large as the result's own: error against 64 bits
+// 2.1e-3 instead of 1.7e-3.  The second product costs pools of long contexts 0.3 .. 0.9 % (256 sequences
+// of 2500 tokens, 28 / 4 heads: 224.3 -> 225.7 us; shorter ones 1 .. 2 %).  It is not left out anywhere:
+// a rule on what the block table could hold gave other bits, and the larger error, to the same contexts in
+// a wider table, and a branch on the pool's slots cost as much in the loop as it saved.
 // Two wavefronts per SIMD, except for slots of 16 KB (fp32, head_dim 128): their two stages
 // need more registers than half the file holds.
 template <typename T, int D> constexpr int kFlatWavesPerSimd = sizeof(T) * D > 256 ? 1 : 2;
-template <typename T, int D, bool PRESCAN, int PG, bool SPLIT_P, int NS>
+template <typename T, int D, bool PRESCAN, int PG, int NS>
 __global__ __launch_bounds__(64)
 __attribute__((amdgpu_waves_per_eu(kFlatWavesPerSimd<T, D>, kFlatWavesPerSimd<T, D>))) void attn_split_flat_kernel(
     const T* __restrict__ q, const u32x4* __restrict__ k_cache,
@@ -722,14 +725,9 @@ __attribute__((amdgpu_waves_per_eu(kFlatWavesPerSimd<T, D>, kFlatWavesPerSimd<T,
     // O^T[d][head] += V^T[d][token] P^T[token][head]; rows past the context may hold anything
     // (NaN) and are zeroed
     if constexpr (kBf16) {
-      s16x4 pf, pl = {0, 0, 0, 0};
-      if (SPLIT_P) {
-        pf = __builtin_bit_cast(s16x4, make_uint2(cut_bf16x2(p[0], p[1]), cut_bf16x2(p[2], p[3])));
-        pl = __builtin_bit_cast(s16x4, make_uint2(pack_bf16x2(rest_of_cut(p[0]), rest_of_cut(p[1])),
-                                                  pack_bf16x2(rest_of_cut(p[2]), rest_of_cut(p[3]))));
-      } else {
-        pf = __builtin_bit_cast(s16x4, make_uint2(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3])));
-      }
+      const s16x4 ph = __builtin_bit_cast(s16x4, make_uint2(cut_bf16x2(p[0], p[1]), cut_bf16x2(p[2], p[3])));
+      const s16x4 pl = __builtin_bit_cast(s16x4, make_uint2(pack_bf16x2(rest_of_cut(p[0]), rest_of_cut(p[1])),
+                                                            pack_bf16x2(rest_of_cut(p[2]), rest_of_cut(p[3]))));
       // A = V^T via the transposing read (lane supplies row 4b + L/4, columns
       // 16dt + 4(L%4)..+3, L = lane&15)
       const int vrow = 4 * b + (head >> 2);
@@ -744,8 +742,8 @@ __attribute__((amdgpu_waves_per_eu(kFlatWavesPerSimd<T, D>, kFlatWavesPerSimd<T,
           for (int rr = 0; rr < 4; ++rr)
             vf[rr] = (4 * b + rr < valid) ? vf[rr] : static_cast<short>(0);
         }
-        o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf, pf, o[dt], 0, 0, 0);
-        if (SPLIT_P) o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf, pl, o[dt], 0, 0, 0);
+        o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf, ph, o[dt], 0, 0, 0);
+        o[dt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf, pl, o[dt], 0, 0, 0);
       }
     } else {
       // k-slot b of product rr is token 4b + rr: the weight is where the score product left it
@@ -1000,24 +998,15 @@ struct AttnFlatArgs {
 
 template <typename T, int D, int NS, bool PRESCAN>
 static void enqueue_split(const AttnFlatArgs& a, int waves) {
-#define COPRIS_SPLIT(PG, SPLIT_P, LSP)                                                                    \
-  hipLaunchKernelGGL((attn_split_flat_kernel<T, D, PRESCAN, PG, SPLIT_P, NS>), dim3(waves), dim3(64), 0,  \
+#define COPRIS_SPLIT(PG, LSP)                                                                             \
+  hipLaunchKernelGGL((attn_split_flat_kernel<T, D, PRESCAN, PG, NS>), dim3(waves), dim3(64), 0,           \
                      a.stream, static_cast<const T*>(a.q), static_cast<const u32x4*>(a.k_cache),          \
                      static_cast<const u32x4*>(a.v_cache), a.block_table, a.ctx_len, a.hdr, a.start,      \
                      a.ws_ml, a.ws_acc, static_cast<T*>(a.out), a.lse, a.C, a.Hq, a.Hkv, a.g, LSP,        \
                      a.max_pages, a.max_tokens, a.scale_log2e)
-  // Rounded weights stay where they always were, at head_dim 128 / page 16, and there only in
-  // pools whose table admits more than kSplitSlots slots.  (A share's largest weight is exactly 1;
-  // below that size a share used to be one to three slots, so that shares of four alone would round
-  // more of them: 1.9e-3 -> 2.1e-3 against 64 bits.  What the second product costs: 64 sequences,
-  // 12 / 2 heads 33.8 -> 34.3 us, 256 sequences, 28 / 4 heads 313.3 -> 314.6.)
-  constexpr int64_t kSplitSlots = 16 * kAttnWaves;
-  constexpr bool kSplitP = sizeof(T) == 2;
-  const bool small = static_cast<int64_t>(a.C) * ((a.max_tokens + kP - 1) / kP) * a.Hkv <= kSplitSlots;
-  if (a.page_size == 16 && D == 128 && !small) COPRIS_SPLIT(16, false, 0);
-  else if (a.page_size == 16) COPRIS_SPLIT(16, kSplitP, 0);
-  else if (a.page_size == 8) COPRIS_SPLIT(8, kSplitP, 0);
-  else COPRIS_SPLIT(0, kSplitP, __builtin_ctz(static_cast<unsigned>(a.page_size / kP)));   // page_size divides 512
+  if (a.page_size == 16) COPRIS_SPLIT(16, 0);
+  else if (a.page_size == 8) COPRIS_SPLIT(8, 0);
+  else COPRIS_SPLIT(0, __builtin_ctz(static_cast<unsigned>(a.page_size / kP)));   // page_size divides 512
 #undef COPRIS_SPLIT
 }
 

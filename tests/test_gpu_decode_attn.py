@@ -72,18 +72,31 @@ def test_a_context_that_hundreds_of_shares_cut(R, dtype, D, Hq, Hkv):
     _run_case(R, case, dtype, f"{dtype} D={D} {Hq}/{Hkv}")
 
 
-@pytest.mark.parametrize("D,page", [(64, 16), (128, 8), (128, 32), (128, 16)])
-def test_bf16_weights_keep_their_precision(R, D, page):
-    # Outside large pools of head_dim 128 / page 16 the weights are not rounded to bf16: what is left is the
+@pytest.mark.parametrize("D,page,max_pages", [(64, 16, None), (128, 8, None), (128, 32, None), (128, 16, None),
+                                              (128, 16, 4200), (64, 8, 9000)])     # tables for far longer contexts
+def test_bf16_weights_keep_their_precision(R, D, page, max_pages):
+    # The weights are not rounded to bf16: what is left is the
     # result's own rounding, 2^-9 relative at worst for one element and 2^-9 / sqrt(3) in the
     # 2-norm for uniformly spread mantissas (1.13e-3; up to 1.95e-3 if all mantissas were 1.0).
     ctx = [700, 1033, 64, 2000]
-    case = W.make_small_decode_case(500 + D + page, len(ctx), 12, 2, D, W.BF16, page, ctx)
+    case = W.make_small_decode_case(500 + D + page, len(ctx), 12, 2, D, W.BF16, page, ctx, max_pages=max_pages)
     out, _ = R.run_decode_attn(case, W.BF16)
     ref, _ = P.oracle_attn(case, W.BF16)
     exact_rounding = W.bf16_bits_to_f32(W.f32_to_bf16_bits(ref.astype(np.float32)))
     floor = np.linalg.norm(exact_rounding - ref) / np.linalg.norm(ref)
     assert np.linalg.norm(out - ref) / np.linalg.norm(ref) <= 1.02 * floor
+
+
+@pytest.mark.parametrize("dtype,D,page", [(W.BF16, 128, 16), (W.BF16, 64, 8), (W.F32, 128, 32)])
+def test_the_width_of_the_block_table_changes_no_bit(R, dtype, D, page):
+    ctx = list(range(1, 641, 10))
+    case = W.make_small_decode_case(77, len(ctx), 12, 2, D, dtype, page, ctx)
+    out, lse = R.run_decode_attn(case, dtype)
+    wide = np.full((len(ctx), 10000 // page), -1, dtype=np.int32)
+    wide[:, :case["block_table"].shape[1]] = case["block_table"]
+    out2, lse2 = R.run_decode_attn(dict(case, block_table=wide), dtype)
+    np.testing.assert_array_equal(out, out2)
+    np.testing.assert_array_equal(lse, lse2)
 
 
 @pytest.mark.parametrize("dtype", [W.F32, W.BF16])
