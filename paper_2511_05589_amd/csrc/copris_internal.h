@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "launch_rules.h"
+
 namespace copris {
 
 // Checks hipGetLastError() after a launch; on failure records "<kernel>: <hip error>" for
@@ -26,11 +28,10 @@ constexpr int kErrLaunch = -4;   // COPRIS_ELAUNCH
 // ---- decode attention -------------------------------------------------------
 constexpr int kAttnChunkTokens = 512;   // split-K granularity along the context
 constexpr int kAttnMaxGroup = 16;       // query heads per kv head, at most
-constexpr int kAttnWaves = 256 * 8;     // persistent wavefronts of the tuned split kernel (8 per CU)
 
 // Workspace carve-up (byte offsets from a 256-byte aligned base).
 struct AttnWorkspace {
-  size_t hdr;       // int32[64]:  [0] number of (seq, chunk) entries, [1] work counter
+  size_t hdr;       // int32[64]:  [0] number of (seq, chunk) entries / slots, [1] work counter / slots per wavefront
   size_t seq_off;   // int32[C+1]: first list entry (generic path) / prefix of 16-token pieces (tuned path) of every sequence
   size_t list;      // int2[]: (seq, chunk) items (generic path) / int4 start cursor per wavefront (tuned path)
   size_t ml;        // float2[max_list*Hkv*g]: running max (log2 domain) and sum of weights

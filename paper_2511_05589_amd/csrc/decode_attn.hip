@@ -302,28 +302,21 @@ template <typename T, int D> struct Slab {
 //   start[w] = {sequence, kv head, piece index, pieces of that sequence} of slot w*share
 //              (sequence = -1: no slots for this wavefront).
 
-// Slots per wavefront: an equal share, but no less than kMinShare: a shorter share makes more
-// partials to merge than its wavefront saves in time.  Whole call, one sequence of 8192 tokens,
-// 12 / 2 heads: 21.4 us with shares of 1, 16.1 of 2, 14.1 of 4, 16.0 of 8; pools of 16 and more
-// sequences have longer shares anyway.
-constexpr int kMinShare = 4;
-__device__ __forceinline__ int attn_share(int total) {
-  return max((total + kAttnWaves - 1) / kAttnWaves, kMinShare);
-}
-
 __global__ __launch_bounds__(kListThreads) void attn_scan_kernel(
     const int32_t* __restrict__ ctx_len, int C, int max_tokens, int Hkv, int32_t* __restrict__ hdr,
     int32_t* __restrict__ seq_pg, int4* __restrict__ start) {
   __shared__ int s_wave[kListThreads / kWave];
-  __shared__ int s_carry;
+  __shared__ int s_carry, s_longest;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  if (tid == 0) s_carry = 0;
+  if (tid == 0) s_carry = s_longest = 0;
   __syncthreads();
+  int longest = 0;
   for (int base = 0; base < C; base += kListThreads) {
     const int i = base + tid;
     int n = i < C ? ctx_len[i] : 0;
     n = n < 0 ? 0 : (n > max_tokens ? max_tokens : n);
     const int npg = (n + kP - 1) / kP;
+    longest = max(longest, npg);
     int incl = npg;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
@@ -339,9 +332,11 @@ __global__ __launch_bounds__(kListThreads) void attn_scan_kernel(
     if (tid == kListThreads - 1) s_carry = before + incl;
     __syncthreads();
   }
+  atomicMax(&s_longest, longest);
+  __syncthreads();
   const int pages = s_carry;
   const int total = pages * Hkv;
-  const int share = attn_share(total);
+  const int share = attn_share(total, s_longest);
   if (tid == 0) {
     seq_pg[C] = pages;
     hdr[0] = total;
@@ -440,15 +435,20 @@ __device__ __forceinline__ int4 attn_derive_cursor(const int32_t* __restrict__ c
   // no second round trip to memory
   constexpr int kReg = 8;
   int reg[kReg];
-  int mine = 0;
+  int mine = 0, longest = 0;
   if (chunk <= kReg) {
 #pragma unroll
     for (int j = 0; j < kReg; ++j) {
       reg[j] = i0 + j < i1 ? attn_pieces_of(ctx_len, i0 + j, max_tokens) : 0;
       mine += reg[j];
+      longest = max(longest, reg[j]);
     }
   } else {
-    for (int i = i0; i < i1; ++i) mine += attn_pieces_of(ctx_len, i, max_tokens);
+    for (int i = i0; i < i1; ++i) {
+      const int npg = attn_pieces_of(ctx_len, i, max_tokens);
+      mine += npg;
+      longest = max(longest, npg);
+    }
   }
   int incl = mine;
 #pragma unroll
@@ -458,7 +458,11 @@ __device__ __forceinline__ int4 attn_derive_cursor(const int32_t* __restrict__ c
   }
   const int pages = __shfl(incl, kWave - 1, kWave);
   total = pages * Hkv;
-  share = attn_share(total);
+  // (of the longest context the rule asks only which of its two bounds it exceeds)
+  const bool over2 = __builtin_amdgcn_ballot_w64(longest > 2 * kAttnShort) != 0;
+  const bool over1 = __builtin_amdgcn_ballot_w64(longest > kAttnShort) != 0;
+  longest = over2 ? 2 * kAttnShort + 1 : (over1 ? kAttnShort + 1 : 0);
+  share = attn_share(total, longest);
   const int64_t slot = static_cast<int64_t>(w) * share;
   int4 st = make_int4(-1, 0, 0, 0);
   if (slot >= total) return st;
@@ -520,7 +524,7 @@ __global__ __launch_bounds__(64)
 __attribute__((amdgpu_waves_per_eu(kFlatWavesPerSimd<T, D>, kFlatWavesPerSimd<T, D>))) void attn_split_flat_kernel(
     const T* __restrict__ q, const u32x4* __restrict__ k_cache,
     const u32x4* __restrict__ v_cache, const int32_t* __restrict__ block_table,
-    const int32_t* __restrict__ ctx_len, const int32_t* __restrict__ hdr,
+    const int32_t* __restrict__ ctx_len, int32_t* __restrict__ hdr,
     const int4* __restrict__ start, float2* __restrict__ ws_ml, float* __restrict__ ws_acc,
     T* __restrict__ out, float* __restrict__ lse, int C, int Hq, int Hkv, int g, int lsp_,
     int max_pages, int max_tokens, float scale_log2e) {
@@ -547,6 +551,7 @@ __attribute__((amdgpu_waves_per_eu(kFlatWavesPerSimd<T, D>, kFlatWavesPerSimd<T,
     st.w = __builtin_amdgcn_readfirstlane(st.w);
     total = __builtin_amdgcn_readfirstlane(total);
     share = __builtin_amdgcn_readfirstlane(share);
+    if (wv == 0 && lane == 0) hdr[1] = share;   // the merge reads it
   }
   if (st.x < 0) return;
   const int64_t first = static_cast<int64_t>(wv) * share;
@@ -855,36 +860,23 @@ __global__ __launch_bounds__(256) void attn_merge_flat_kernel(const int32_t* __r
   constexpr int kQuads = D / 4;              // threads across the head_dim, four elements each
   constexpr int kTeams = 256 / kQuads;       // at most
   const int threads = blockDim.x, teams = threads / kQuads;
-  __shared__ int s_before[256 / kWave], s_all[256 / kWave];
+  __shared__ int s_before[256 / kWave];
   const int seq = blockIdx.x, kvh = blockIdx.y;
-  int share, npg, pg0;
+  const int share = hdr[1];
+  int npg, pg0;
   if (PRESCAN) {
-    share = hdr[1];
     pg0 = seq_pg[seq];
     npg = seq_pg[seq + 1] - pg0;
   } else {
-    // pieces before this sequence and in total, from ctx_len (the same counts the split
-    // kernel's wavefronts derived their cursors from)
-    int before = 0, all = 0;
-    for (int i = threadIdx.x; i < C; i += threads) {
-      const int pgs = attn_pieces_of(ctx_len, i, max_tokens);
-      all += pgs;
-      before += i < seq ? pgs : 0;
-    }
+    // pieces before this sequence, from ctx_len (the same counts the split kernel's wavefronts
+    // derived their cursors from)
+    int before = 0;
+    for (int i = threadIdx.x; i < seq; i += threads) before += attn_pieces_of(ctx_len, i, max_tokens);
     before = wave_sum_i(before);
-    all = wave_sum_i(all);
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-      s_before[threadIdx.x / kWave] = before;
-      s_all[threadIdx.x / kWave] = all;
-    }
+    if ((threadIdx.x & (kWave - 1)) == 0) s_before[threadIdx.x / kWave] = before;
     __syncthreads();
     pg0 = 0;
-    int pages = 0;
-    for (int w = 0; w < threads / kWave; ++w) {
-      pg0 += s_before[w];
-      pages += s_all[w];
-    }
-    share = attn_share(pages * Hkv);
+    for (int w = 0; w < threads / kWave; ++w) pg0 += s_before[w];
     npg = attn_pieces_of(ctx_len, seq, max_tokens);
   }
   const int64_t a = static_cast<int64_t>(pg0) * Hkv + static_cast<int64_t>(kvh) * npg;
@@ -1020,9 +1012,8 @@ static int launch_flat(const AttnFlatArgs& a) {
                        a.max_tokens, a.Hkv, a.hdr, a.seq_off, a.start);
     COPRIS_POST("attn_scan_kernel");
   }
-  // no more wavefronts than the longest contexts that the block table admits give shares
-  const int64_t most = (static_cast<int64_t>(a.C) * ((a.max_tokens + kP - 1) / kP) * a.Hkv + kMinShare - 1) / kMinShare;
-  const int waves = static_cast<int>(most < kAttnWaves ? most : kAttnWaves);
+  // no more wavefronts than the contexts that the block table admits can have shares
+  const int waves = attn_most_waves(static_cast<int64_t>(a.C) * ((a.max_tokens + kP - 1) / kP) * a.Hkv);
   COPRIS_PRE("attn_split_flat_kernel");
   if (prescan) {
     enqueue_split<T, D, NS, true>(a, waves);

@@ -62,6 +62,15 @@ def test_every_page_geometry(R, dtype, D, page):
     _run_case(R, case, dtype, f"{dtype} D={D} page={page}")
 
 
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("ctx", [[5] * 200 + [56 * 16], [16] * 257, [33] * 512, [33] * 513,    # 256 / 257 and 1536 / 1539 slots
+                                 [1024, 1, 0], [100, 1025], [2048, 9], [16, 2049],               # 64 / 65 and 128 / 129 pieces
+                                 [47] * 2048, [47] * 2049])                                      # 6144 / 6147 slots
+def test_pools_around_the_share_steps(R, dtype, ctx):
+    case = W.make_small_decode_case(800 + len(ctx), len(ctx), 2, 1, 64, dtype, 16, ctx)
+    _run_case(R, case, dtype, f"{dtype} {len(ctx)} sequences")
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(16, 1), (10, 2), (3, 3)])
 @pytest.mark.parametrize("dtype,D", [(W.F32, 64), (W.BF16, 128), (W.BF16, 64)])
 def test_a_context_that_hundreds_of_shares_cut(R, dtype, D, Hq, Hkv):
