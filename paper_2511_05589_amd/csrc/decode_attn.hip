@@ -303,8 +303,8 @@ template <typename T, int D> struct Slab {
 //              (sequence = -1: no slots for this wavefront).
 
 __global__ __launch_bounds__(kListThreads) void attn_scan_kernel(
-    const int32_t* __restrict__ ctx_len, int C, int max_tokens, int Hkv, int32_t* __restrict__ hdr,
-    int32_t* __restrict__ seq_pg, int4* __restrict__ start) {
+    const int32_t* __restrict__ ctx_len, int C, int max_tokens, int Hkv, int group,
+    int32_t* __restrict__ hdr, int32_t* __restrict__ seq_pg, int4* __restrict__ start) {
   __shared__ int s_wave[kListThreads / kWave];
   __shared__ int s_carry, s_longest;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(kListThreads) void attn_scan_kernel(
   __syncthreads();
   const int pages = s_carry;
   const int total = pages * Hkv;
-  const int share = attn_share(total, s_longest);
+  const int share = attn_share(total, s_longest, group);
   if (tid == 0) {
     seq_pg[C] = pages;
     hdr[0] = total;
@@ -426,8 +426,8 @@ __device__ __forceinline__ int attn_pieces_of(const int32_t* __restrict__ ctx_le
 // lane whose range holds the slot walks its (at most `chunk`) sequences.  Returns the
 // cursor in every lane ({-1,..}: no slot for this wavefront) and total / share by reference.
 __device__ __forceinline__ int4 attn_derive_cursor(const int32_t* __restrict__ ctx_len, int C,
-                                                   int max_tokens, int Hkv, int w, int& total,
-                                                   int& share) {
+                                                   int max_tokens, int Hkv, int group, int w,
+                                                   int& total, int& share) {
   const int lane = threadIdx.x & (kWave - 1);
   const int chunk = (C + kWave - 1) / kWave;
   const int i0 = min(lane * chunk, C), i1 = min(i0 + chunk, C);
@@ -462,7 +462,7 @@ __device__ __forceinline__ int4 attn_derive_cursor(const int32_t* __restrict__ c
   const bool over2 = __builtin_amdgcn_ballot_w64(longest > 2 * kAttnShort) != 0;
   const bool over1 = __builtin_amdgcn_ballot_w64(longest > kAttnShort) != 0;
   longest = over2 ? 2 * kAttnShort + 1 : (over1 ? kAttnShort + 1 : 0);
-  share = attn_share(total, longest);
+  share = attn_share(total, longest, group);
   const int64_t slot = static_cast<int64_t>(w) * share;
   int4 st = make_int4(-1, 0, 0, 0);
   if (slot >= total) return st;
@@ -544,7 +544,7 @@ __attribute__((amdgpu_waves_per_eu(kFlatWavesPerSimd<T, D>, kFlatWavesPerSimd<T,
     share = hdr[1];
     st = start[wv];
   } else {
-    st = attn_derive_cursor(ctx_len, C, max_tokens, Hkv, wv, total, share);
+    st = attn_derive_cursor(ctx_len, C, max_tokens, Hkv, g, wv, total, share);
     st.x = __builtin_amdgcn_readfirstlane(st.x);
     st.y = __builtin_amdgcn_readfirstlane(st.y);
     st.z = __builtin_amdgcn_readfirstlane(st.z);
@@ -1009,11 +1009,11 @@ static int launch_flat(const AttnFlatArgs& a) {
   if (prescan) {
     COPRIS_PRE("attn_scan_kernel");
     hipLaunchKernelGGL(attn_scan_kernel, dim3(1), dim3(kListThreads), 0, stream, a.ctx_len, a.C,
-                       a.max_tokens, a.Hkv, a.hdr, a.seq_off, a.start);
+                       a.max_tokens, a.Hkv, a.g, a.hdr, a.seq_off, a.start);
     COPRIS_POST("attn_scan_kernel");
   }
   // no more wavefronts than the contexts that the block table admits can have shares
-  const int waves = attn_most_waves(static_cast<int64_t>(a.C) * ((a.max_tokens + kP - 1) / kP) * a.Hkv);
+  const int waves = attn_most_waves(static_cast<int64_t>(a.C) * ((a.max_tokens + kP - 1) / kP) * a.Hkv, a.g);
   COPRIS_PRE("attn_split_flat_kernel");
   if (prescan) {
     enqueue_split<T, D, NS, true>(a, waves);

@@ -29,16 +29,21 @@ constexpr int kAttnWaves = 256 * 8;     // persistent wavefronts of the flat spl
 //   1 sequence x 3000 tokens,   28 / 4 heads   (752 slots)    13.9 / 11.6 / 11.8
 //   1 sequence x 9000 tokens,   12 / 2 heads  (1126 slots)    22.2 / 15.9 / 13.9
 //   8 sequences x 3000 tokens,  16 / 1 heads  (1504 slots)    21.3 / 14.8 / 13.4
+//   128 sequences x 64 tokens,  8 / 8 heads   (4096 slots)       - / 13.7 / 16.0
+// The last line: with one query head per kv head (group = 1) the partials are small, and merging them
+// costs less than the chain of slots up to more slots.
 constexpr int kAttnMinShare = 4;       // where there are slots for it; 8 is slower again (1 x 8192 tokens, 12 / 2 heads: 14.1 -> 16.0)
-constexpr int kAttnSmall = 1536, kAttnShort = 64;
-COPRIS_RULE int attn_share(int total, int longest) {
-  if (total > (kAttnMinShare - 1) * kAttnWaves) return total / kAttnWaves + (total % kAttnWaves != 0);
-  if (total > kAttnSmall || longest > 2 * kAttnShort) return kAttnMinShare;
+constexpr int kAttnShort = 64;
+COPRIS_RULE int attn_small(int group) { return group == 1 ? 4096 : 1536; }
+COPRIS_RULE int attn_share(int total, int longest, int group) {
+  const int equal = total / kAttnWaves + (total % kAttnWaves != 0);
+  if (equal >= kAttnMinShare) return equal;
+  if (total > attn_small(group) || longest > 2 * kAttnShort) return kAttnMinShare;
   return total > 256 || longest > kAttnShort ? 2 : 1;
 }
 // Wavefronts that a pool whose block table admits `capacity` slots needs at most.
-COPRIS_RULE int attn_most_waves(int64_t capacity) {
-  const int64_t in_fours = (capacity + kAttnMinShare - 1) / kAttnMinShare, in_twos = kAttnSmall / 2;
+COPRIS_RULE int attn_most_waves(int64_t capacity, int group) {
+  const int64_t in_fours = (capacity + kAttnMinShare - 1) / kAttnMinShare, in_twos = attn_small(group) / 2;
   if (capacity <= in_twos) return static_cast<int>(capacity);
   return static_cast<int>(in_fours > kAttnWaves ? kAttnWaves : (in_fours > in_twos ? in_fours : in_twos));
 }

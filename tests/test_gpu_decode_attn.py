@@ -65,10 +65,11 @@ def test_every_page_geometry(R, dtype, D, page):
 @pytest.mark.parametrize("dtype", [W.F32, W.BF16])
 @pytest.mark.parametrize("ctx", [[5] * 200 + [56 * 16], [16] * 257, [33] * 512, [33] * 513,    # 256 / 257 and 1536 / 1539 slots
                                  [1024, 1, 0], [100, 1025], [2048, 9], [16, 2049],               # 64 / 65 and 128 / 129 pieces
-                                 [47] * 2048, [47] * 2049])                                      # 6144 / 6147 slots
+                                 [47] * 2048, [47] * 2049, [17] * 2048, [17] * 2049])           # 6144 / 6147 and 4096 / 4098 slots
 def test_pools_around_the_share_steps(R, dtype, ctx):
-    case = W.make_small_decode_case(800 + len(ctx), len(ctx), 2, 1, 64, dtype, 16, ctx)
-    _run_case(R, case, dtype, f"{dtype} {len(ctx)} sequences")
+    for Hq in (2, 1):
+        case = W.make_small_decode_case(800 + len(ctx), len(ctx), Hq, 1, 64, dtype, 16, ctx)
+        _run_case(R, case, dtype, f"{dtype} {len(ctx)} sequences {Hq} heads")
 
 
 @pytest.mark.parametrize("Hq,Hkv", [(16, 1), (10, 2), (3, 3)])

@@ -25,9 +25,9 @@ int main() {
   while (std::scanf("%31s", name) == 1) {
     long long a[8] = {};
     if (!std::strcmp(name, "share")) {
-      std::scanf("%lld %lld %lld", a, a + 1, a + 2);
-      const int total = static_cast<int>(a[0]), longest = static_cast<int>(a[1]);
-      std::printf("%d %d\n", attn_share(total, longest), attn_most_waves(a[2]));
+      std::scanf("%lld %lld %lld %lld", a, a + 1, a + 2, a + 3);
+      const int total = static_cast<int>(a[0]), longest = static_cast<int>(a[1]), group = static_cast<int>(a[3]);
+      std::printf("%d %d\n", attn_share(total, longest, group), attn_most_waves(a[2], group));
     }
   }
 }
@@ -41,11 +41,12 @@ int main() {
     return ask
 
 
-def test_attention_shares(rules):
-    totals = sorted({0, 1, 2, 256, 257, 1536, 1537, 2047, 2048, 2049, 6144, 6145, 8192, 8193, 100000, 2**31 - 1}
+@pytest.mark.parametrize("group", [1, 2, 16])
+def test_attention_shares(rules, group):
+    totals = sorted({0, 1, 2, 256, 257, 1536, 1537, 2047, 2048, 2049, 4096, 4097, 6144, 6145, 8192, 8193, 100000, 2**31 - 1}
                     | {int(1.37 ** k) for k in range(1, 60)})
     cases = [(t, l) for t in totals for l in (0, 1, 4, 64, 65, 128, 129, 2048, 10**6) if l <= t]
-    for (t, l), (s, _) in zip(cases, rules([f"share {t} {l} 1" for t, l in cases])):
+    for (t, l), (s, _) in zip(cases, rules([f"share {t} {l} 1 {group}" for t, l in cases])):
         equal = -(-t // WAVES)
         assert 1 <= s and s * WAVES >= t, (t, l, s)                     # the wavefronts cover the slots
         assert s == equal if equal >= 4 else equal <= s <= 4, (t, l, s)
@@ -54,12 +55,13 @@ def test_attention_shares(rules):
         assert s >= 4 or l <= 64 * s, (t, l, s)                         # partials of a context
 
 
-def test_attention_launches_enough_wavefronts(rules):
+@pytest.mark.parametrize("group", [1, 2, 16])
+def test_attention_launches_enough_wavefronts(rules, group):
     # for every pool that a table of some capacity admits
     totals = list(range(1, 9000)) + [10**5, 10**7, 2**31 - 1]
-    caps = [1, 2, 255, 256, 257, 600, 767, 768, 769, 1535, 1536, 1537, 3071, 3072, 3073, 6144, 6145, 8192, 8193, 10**5, 2**31 - 1]
-    most = {c: m for c, (_, m) in zip(caps, rules([f"share 1 1 {c}" for c in caps]))}
-    need = [-(-t // s) for t, (s, _) in zip(totals, rules([f"share {t} 1 1" for t in totals]))]
+    caps = [1, 2, 255, 256, 257, 600, 767, 768, 769, 1535, 1536, 1537, 2047, 2048, 2049, 3071, 3072, 3073, 4096, 4097, 6144, 6145, 8192, 8193, 10**5, 2**31 - 1]
+    most = {c: m for c, (_, m) in zip(caps, rules([f"share 1 1 {c} {group}" for c in caps]))}
+    need = [-(-t // s) for t, (s, _) in zip(totals, rules([f"share {t} 1 1 {group}" for t in totals]))]
     for c in caps:
         worst = max(n for t, n in zip(totals, need) if t <= c)
         assert worst <= most[c] <= WAVES, (c, worst, most[c])
