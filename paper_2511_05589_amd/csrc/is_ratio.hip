@@ -17,9 +17,14 @@ constexpr int kIsThreads = 1024;
 // The outputs are stored non-temporally (the next reader is another pass); the inputs are read
 // through the caches, because the gather that packs the batch, or the ratio call before the
 // surrogate, has just written or read them: 256 trajectories, gather + ratio + surrogate 39.3 ->
-// 36.9 us (plain stores as well: 40.4).  (The builtins take native vector types.)
+// 36.9 us (plain stores as well: 40.4).  (Native vector types: the builtin takes no others, and a
+// load of a struct of four floats is taken apart where a branch beside it loads single floats, which
+// cost one trajectory of 16384 tokens 5.7 -> 7.4 us.)
 typedef float is_f32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ float4 load4(const float* p) {
+  const is_f32x4 v = *reinterpret_cast<const is_f32x4*>(p);
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
 __device__ __forceinline__ void store_stream4(float* p, const float4& x) {
   const is_f32x4 v = {x.x, x.y, x.z, x.w};
   __builtin_nontemporal_store(v, reinterpret_cast<is_f32x4*>(p));
