@@ -7,6 +7,8 @@
 //   traj_gather_kernel     buffer rows -> the packed training batch (Eq. 6: the per-stage
 //                          pieces of a trajectory, concatenated in token order)
 // All of them move a few bytes per slot or per token: plain copies with bounds checks.
+#include <type_traits>
+
 #include "copris.h"
 #include "copris_device.h"
 #include "copris_internal.h"
@@ -75,11 +77,13 @@ __global__ __launch_bounds__(256) void traj_append_kernel(
 }
 
 // A trajectory's tokens are shared out over `parts` workgroups in pieces of kGatherPiece, and
-// where that is more than one a workgroup of its own counts the trajectory's earlier tokens
+// a trajectory of more than one piece has its earlier tokens counted by a workgroup of its own
 // (4 of the 24 bytes per token are read twice for it, which a counter in memory and a launch to
 // clear it would cost more than).  What bounds it is bytes in flight: a thread moves kGatherDeep
-// tokens per round trip to memory.  256 trajectories of 1024..16384 tokens, 2.2 M in all (53 MB):
-// 12 us, where one workgroup per trajectory with one token per thread in flight took 39.
+// tokens per round trip to memory, and fewer where the piece is short, because a load without a
+// token is a request all the same.  256 trajectories of 1024..16384 tokens, 2.2 M in all (53 MB):
+// 12 us, where one workgroup per trajectory with one token per thread in flight took 39; 20000
+// trajectories of 1..50 tokens: 16.8 us, 26.5 with eight loads per thread in every piece.
 constexpr int kGatherPiece = 2048;
 constexpr int kGatherDeep = 8;
 static_assert(kGatherPiece == 256 * kGatherDeep, "a piece is one round trip of a workgroup");
@@ -91,56 +95,65 @@ __global__ __launch_bounds__(256) void traj_gather_kernel(
     float* __restrict__ logp_buf_out, float* __restrict__ logp_roll_out,
     int32_t* __restrict__ split_out, int64_t n_traj, int max_resp, int parts) {
   __shared__ int s_cnt[256 / kWave];
-  const int per_traj = parts == 1 ? 1 : parts + 1;
-  const int b = blockIdx.x / per_traj, part = blockIdx.x % per_traj;
+  const int b = blockIdx.x, part = blockIdx.y;
   const int64_t tr = traj[b];
   const int64_t j0 = cu_seqlens[b];
-  int64_t len = static_cast<int64_t>(cu_seqlens[b + 1]) - j0;
-  len = len < 0 ? 0 : (len > max_resp ? max_resp : len);
+  const int64_t len64 = static_cast<int64_t>(cu_seqlens[b + 1]) - j0;
+  const uint32_t len = len64 < 0 ? 0 : static_cast<uint32_t>(len64 > max_resp ? max_resp : len64);
   const bool ok = tr >= 0 && tr < n_traj;
   const float nan = __int_as_float(0x7fc00000);
   const size_t row = static_cast<size_t>(ok ? tr : 0) * max_resp;
   int earlier_cnt = 0;
+  const bool one_piece = parts == 1 || len <= kGatherPiece;   // its first workgroup sees every token
   if (part < parts) {
-    for (int64_t t0 = static_cast<int64_t>(part) * kGatherPiece; t0 < len;
-         t0 += static_cast<int64_t>(parts) * kGatherPiece) {
-      int32_t tag[kGatherDeep], tok[kGatherDeep];
-      float lp[kGatherDeep];
+    // DEEP * 256 tokens from t0 on (past the end: nothing, or token 0 in their place where there are
+    // several loads, which a branch would put one behind the other)
+    auto copy = [&](uint32_t t0, auto deep) __attribute__((always_inline)) {
+      constexpr int DEEP = decltype(deep)::value;
+      if (DEEP == 1 && t0 + threadIdx.x >= len) return;
+      int32_t tag[DEEP], tok[DEEP];
+      float lp[DEEP];
 #pragma unroll
-      for (int u = 0; u < kGatherDeep; ++u) {
-        const int64_t t = t0 + u * 256 + threadIdx.x;
-        const size_t at = row + static_cast<size_t>(t < len ? t : 0);
-        tag[u] = buf_tag[at];
-        lp[u] = buf_logp[at];
-        tok[u] = buf_token[at];
+      for (int u = 0; u < DEEP; ++u) {
+        const uint32_t t = t0 + u * 256 + threadIdx.x, at = t < len ? t : 0;
+        tag[u] = (buf_tag + row)[at];
+        lp[u] = (buf_logp + row)[at];
+        tok[u] = (buf_token + row)[at];
       }
 #pragma unroll
-      for (int u = 0; u < kGatherDeep; ++u) {
-        const int64_t t = t0 + u * 256 + threadIdx.x;
+      for (int u = 0; u < DEEP; ++u) {
+        const uint32_t t = t0 + u * 256 + threadIdx.x;
         if (t < len) {
           const bool earlier = ok && tag[u] < stage;
           const float x = ok ? lp[u] : nan;
-          tokens_out[j0 + t] = ok ? tok[u] : -1;
-          logp_buf_out[j0 + t] = earlier ? x : nan;
-          logp_roll_out[j0 + t] = earlier ? nan : x;
+          (tokens_out + j0)[t] = ok ? tok[u] : -1;
+          (logp_buf_out + j0)[t] = earlier ? x : nan;
+          (logp_roll_out + j0)[t] = earlier ? nan : x;
           earlier_cnt += earlier ? 1 : 0;
         }
       }
+    };
+    for (uint32_t t0 = part * kGatherPiece; t0 < len; t0 += static_cast<uint32_t>(parts) * kGatherPiece) {
+      const uint32_t left = len - t0;              // (the same for the whole workgroup)
+      if (left <= 256) copy(t0, std::integral_constant<int, 1>{});
+      else if (left <= 512) copy(t0, std::integral_constant<int, 2>{});
+      else if (left <= 1024) copy(t0, std::integral_constant<int, 4>{});
+      else copy(t0, std::integral_constant<int, kGatherDeep>{});
     }
-  } else if (ok) {
-    for (int64_t t0 = 0; t0 < len; t0 += 2 * kGatherPiece) {
+  } else if (ok && !one_piece) {
+    for (uint32_t t0 = 0; t0 < len; t0 += 2 * kGatherPiece) {
       int32_t tag[2 * kGatherDeep];
 #pragma unroll
       for (int u = 0; u < 2 * kGatherDeep; ++u) {
-        const int64_t t = t0 + u * 256 + threadIdx.x;
-        tag[u] = buf_tag[row + static_cast<size_t>(t < len ? t : 0)];
+        const uint32_t t = t0 + u * 256 + threadIdx.x;
+        tag[u] = (buf_tag + row)[t < len ? t : 0];
       }
 #pragma unroll
       for (int u = 0; u < 2 * kGatherDeep; ++u)
         earlier_cnt += (t0 + u * 256 + threadIdx.x < len && tag[u] < stage) ? 1 : 0;
     }
   }
-  if (part != per_traj - 1) return;   // the last one has seen every token
+  if (part != (one_piece ? 0 : parts)) return;   // this one has seen every token
   const int w = wave_sum_i(earlier_cnt);
   if ((threadIdx.x & (kWave - 1)) == 0) s_cnt[threadIdx.x / kWave] = w;
   __syncthreads();
@@ -230,15 +243,17 @@ int copris_traj_gather(const int32_t* buf_token, const float* buf_logp, const in
     return COPRIS_EINVAL;
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   (void)hipGetLastError();
-  // as many workgroups per trajectory as the longest row has pieces, while that fills the chip
-  // (more trajectories than kGatherFill need no splitting)
-  constexpr int kGatherFill = 8192;
+  // as many workgroups per trajectory as the longest row has pieces, while that fills the chip (eight
+  // workgroups per CU; the rows of a buffer may be far longer than the batch's trajectories, and a
+  // workgroup without a token costs its launch: 1000 trajectories of 10..100 tokens in rows of 8192
+  // 2.9 us with one each, 3.2 with three, 6.2 with nine)
+  constexpr int kGatherFill = 2048;
   const int pieces = (max_resp - 1) / copris::kGatherPiece + 1;
   const int room = kGatherFill / B > 1 ? kGatherFill / B : 1;
   const int parts = pieces < room ? pieces : room;
-  const unsigned grid = static_cast<unsigned>(B) * static_cast<unsigned>(parts == 1 ? 1 : parts + 1);
+  const dim3 grid(B, parts == 1 ? 1 : parts + 1);
   COPRIS_PRE("traj_gather_kernel");
-  hipLaunchKernelGGL(copris::traj_gather_kernel, dim3(grid), dim3(256), 0, stream, buf_token, buf_logp,
+  hipLaunchKernelGGL(copris::traj_gather_kernel, grid, dim3(256), 0, stream, buf_token, buf_logp,
                      buf_tag, traj, cu_seqlens, stage, tokens_out, logp_buf_out, logp_roll_out,
                      split_out, n_traj, max_resp, parts);
   COPRIS_POST("traj_gather_kernel");
