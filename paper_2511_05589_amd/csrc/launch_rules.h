@@ -48,4 +48,36 @@ COPRIS_RULE int attn_most_waves(int64_t capacity, int group) {
   return static_cast<int>(in_fours > kAttnWaves ? kAttnWaves : (in_fours > in_twos ? in_fours : in_twos));
 }
 
+// LM head, 65 rows and more (sampling, or fewer given tokens than the 256 x 256 kernel takes): batch rows
+// per row block.  The blocks share the rows evenly where that makes them narrower, 192 columns (or
+// 128) multiplied instead of 256.  Where it does not, evenly shared rows only leave the last block's
+// waves as long an epilogue as the others', so the blocks are full and the last one takes the rest.
+// Whole sampling calls in us, blocks of 256 / shared evenly:
+//   C = 301, H = 2048, V = 50257   130.0 / 121.8      C = 400, H = 2048, V = 50257   139.3 / 146.4
+//   C = 384, H = 1024, V = 32000    49.2 /  46.4      C = 580, H = 2048, V = 12800    66.7 /  72.3
+//   C = 160, H = 3584, V = 33000   101.1 /  94.0      C = 400, H = 1024, V = 32000    51.5 /  53.2
+COPRIS_RULE int lm_row_blocks(int C) { return (C + 255) / 256; }
+COPRIS_RULE int lm_block_rows(int C) {
+  const int blocks = lm_row_blocks(C), even = ((C + blocks - 1) / blocks + 31) & ~31;
+  return even <= 192 ? even : 256;
+}
+// Columns that a block multiplies: 128, 192 or 256.
+COPRIS_RULE int lm_block_width(int C) {
+  const int rows = lm_block_rows(C);
+  return rows <= 128 ? 128 : (rows <= 192 ? 192 : 256);
+}
+
+// Two row blocks of 256 workgroups each: workgroups i of both share a CU, and workgroup p takes the
+// tiles p, p + 256, ...  Where at most half of the places have a tile more than the rest, the second block
+// counts its places from the end (place = i ^ flip), so that no CU has two workgroups with the tile more.
+// Where more have it, some CUs get two anyway, and the blocks no longer read the same rows of W at the same
+// time: C = 301, H = 2048, dealt alike / from both ends: V = 33000 (2 of 256 places) 114.1 / 100.9 us,
+// V = 100000 (14) 236.7 / 222.2, V = 40000 (57) 117.0 / 106.5, V = 50257 (137) 122.4 / 126.3,
+// V = 151936 (163) 313.2 / 315.4, V = 65000 (252) 133.9 / 136.4.  With more row blocks other workgroups
+// meet: C = 768, H = 1024, V = 32000 83.6 / 90.7.
+COPRIS_RULE int lm_second_block_flip(int C, int n_tiles, int n_parts) {
+  const int more = n_tiles % n_parts;
+  return lm_row_blocks(C) == 2 && n_parts == 256 && more > 0 && more <= 128 ? 255 : 0;
+}
+
 }  // namespace copris

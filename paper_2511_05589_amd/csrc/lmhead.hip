@@ -470,18 +470,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ weight,
     const int64_t* __restrict__ seq_id, const int32_t* __restrict__ step,
     const int32_t* __restrict__ target, uint32_t key0, uint32_t key1, float inv_temperature,
-    LmPartial* __restrict__ part, int C, int H, int V, int block_rows, int n_tiles, int n_parts) {
+    LmPartial* __restrict__ part, int C, int H, int V, int block_rows, int n_tiles, int n_parts, int flip) {
   __shared__ __attribute__((aligned(1024))) char smem[kMfLds];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wq = wave & 1;     // vocabulary half; 64-row block of a batch half
   const int l32 = lane & 31, kb = lane >> 5;
-  // this workgroup's batch rows, and its place among those that share the tiles out: odd row
-  // blocks count from the end, so that the CU whose workgroup of one block has a tile more gets one
-  // with a tile less of the next
+  // this workgroup's batch rows, and its place among those that share the tiles out (flip: see
+  // lm_second_block_flip; with one tile each the blocks share it through the L2)
   const int c0 = blockIdx.y * block_rows, c_end = min(C, c0 + block_rows);
-  // (n_parts = gridDim.x; with one tile each the blocks share it through the L2)
-  const int place = (blockIdx.y & 1) && n_tiles > n_parts ? n_parts - 1 - blockIdx.x : blockIdx.x;
+  const int place = blockIdx.x ^ (blockIdx.y * flip);
   const int nkd = H / kMfBK;                   // slabs per tile
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
   const uint32_t pitch = static_cast<uint32_t>(H) * 2u;
@@ -1432,8 +1430,7 @@ static int lm_parts(int C, int H, int V, int dtype, bool given) {
   if (lm_use_skinny(C, H, V, dtype)) return (V - 1) / lm_skinny_rows(V) + 1;
   if (lm_use_gemm(C, H, V, dtype, given)) return (V - 1) / (64 * lm_gemm_lane_units(C, V)) + 1;
   const int n_tiles = (V + kMfBM - 1) / kMfBM;
-  const int blocks = (C + kMfBN - 1) / kMfBN;
-  int parts = kMfMaxGrid / blocks;
+  int parts = kMfMaxGrid / lm_row_blocks(C);
   parts = parts < 1 ? 1 : parts;
   return parts < n_tiles ? parts : n_tiles;
 }
@@ -1474,18 +1471,14 @@ static int launch_lmhead(const void* hidden, const void* weight, const int64_t* 
     COPRIS_POST("lmhead_skinny_kernel");
   } else if (lm_use_mfma(C, H, V, dtype)) {
     const int n_tiles = (V + kMfBM - 1) / kMfBM;
-    const dim3 grid(n_parts, (C + kMfBN - 1) / kMfBN);
+    const dim3 grid(n_parts, lm_row_blocks(C));
     COPRIS_PRE("lmhead_mfma_kernel");
 #define COPRIS_LM_MFMA_LAUNCH(G, HV, NT1)                                                                \
   hipLaunchKernelGGL((lmhead_mfma_kernel<G, HV, NT1>), grid, dim3(256), 0, stream,                        \
                      static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(weight), seq_id, \
-                     step, target, key0, key1, inv_t, part, C, H, V, block_rows, n_tiles, n_parts)
-    // The row blocks share the rows evenly; a block computes 128, 192 or 256.  (C = 301: two blocks
-    // of 192 instead of 256, and their odd tiles dealt from opposite ends: 132 -> 124 us per call;
-    // C = 160, H = 3584: 285 -> 257; M = 320 given tokens,
-    // H = 2048, V = 100000: 229 -> 204.  Both are bound by the depth of their W stream, some 1.8 us per slab.)
-    const int block_rows = ((C + static_cast<int>(grid.y) - 1) / static_cast<int>(grid.y) + 31) & ~31;
-    const int width = block_rows <= 128 ? 128 : (block_rows <= 192 ? 192 : 256);
+                     step, target, key0, key1, inv_t, part, C, H, V, block_rows, n_tiles, n_parts, flip)
+    const int block_rows = lm_block_rows(C), width = lm_block_width(C);
+    const int flip = lm_second_block_flip(C, n_tiles, n_parts);
     if (given) {
       if (width == 128) COPRIS_LM_MFMA_LAUNCH(true, 1, 2);
       else if (width == 192) COPRIS_LM_MFMA_LAUNCH(true, 2, 1);

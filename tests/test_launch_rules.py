@@ -29,6 +29,15 @@ int main() {
       const int total = static_cast<int>(a[0]), longest = static_cast<int>(a[1]), group = static_cast<int>(a[3]);
       std::printf("%d %d\n", attn_share(total, longest, group), attn_most_waves(a[2], group));
     }
+    if (!std::strcmp(name, "rows")) {
+      std::scanf("%lld", a);
+      const int C = static_cast<int>(a[0]);
+      std::printf("%d %d %d\n", lm_row_blocks(C), lm_block_rows(C), lm_block_width(C));
+    }
+    if (!std::strcmp(name, "flip")) {
+      std::scanf("%lld %lld %lld", a, a + 1, a + 2);
+      std::printf("%d\n", lm_second_block_flip(static_cast<int>(a[0]), static_cast<int>(a[1]), static_cast<int>(a[2])));
+    }
   }
 }
 ''')
@@ -65,3 +74,39 @@ def test_attention_launches_enough_wavefronts(rules, group):
     for c in caps:
         worst = max(n for t, n in zip(totals, need) if t <= c)
         assert worst <= most[c] <= WAVES, (c, worst, most[c])
+
+
+def _longest_epilogue(rows, width):
+    """32-row states of the wave of a row block that has most: of each half of 128 rows (the second half of a
+    192-wide block has 64) a wave has one run of 64 (32) rows."""
+    second = 32 if width == 192 else 64
+    runs = [[(0, 64), (128, 128 + second)], [(64, 128), (128 + second, 128 + 2 * second)]]
+    return max(sum(max(0, -(-(min(rows, hi) - lo) // 32)) for lo, hi in w if lo < width) for w in runs)
+
+
+def test_row_blocks(rules):
+    Cs = list(range(1, 2100)) + [4096, 100001]
+    for C, (blocks, rows, width) in zip(Cs, rules([f"rows {C}" for C in Cs])):
+        assert (blocks - 1) * rows < C <= blocks * rows, C               # no block is empty, none too short
+        assert width in (128, 192, 256) and rows <= width, C
+        last = C - (blocks - 1) * rows
+        if width == 256:
+            # nothing is saved by sharing the rows: no wave of the last block is longer for it
+            whole = C - (blocks - 1) * 256
+            assert _longest_epilogue(last, 256) <= _longest_epilogue(whole, 256), C
+        elif blocks > 1:
+            assert width < 256 and rows % 32 == 0, C
+
+
+def test_the_second_row_block_counts_from_the_end_where_that_evens_the_load(rules):
+    cases = [(C, -(-V // 128)) for C in (129, 256, 257, 301, 384, 512, 513, 900) for V in range(1000, 160000, 997)]
+    parts = [min(512 // -(-C // 256), t) for C, t in cases]
+    for (C, t), n, (flip,) in zip(cases, parts, rules([f"flip {C} {t} {n}" for (C, t), n in zip(cases, parts)])):
+        assert flip in (0, 255), (C, t)
+        if flip:
+            assert 256 < C <= 512 and n == 256 and t > n, (C, t)
+            tiles = [-(-(t - p) // n) for p in range(n)]                 # of place p
+            both = [tiles[i] + tiles[i ^ flip] for i in range(n)]        # of the two workgroups that share a CU
+            assert max(both) - min(both) <= 1, (C, t)
+        elif 256 < C <= 512 and t > 256:
+            assert t % 256 == 0 or t % 256 > 128, (C, t)
