@@ -80,4 +80,29 @@ COPRIS_RULE int lm_second_block_flip(int C, int n_tiles, int n_parts) {
   return lm_row_blocks(C) == 2 && n_parts == 256 && more > 0 && more <= 128 ? 255 : 0;
 }
 
+// LM head, at most 64 rows: whether the skinny kernel (256 workgroups, an equal run of vocabulary rows
+// each) is faster than the tiles of 128 vocabulary rows.  It is where its stream of W is long enough to
+// hide the start and the last epilogue, which are longer than the tiles': with more than 32 rows twice as
+// long.  The tiles have 512 workgroups, so one round of them up to V = 65536; beyond, their second round is
+// as long as the first one.  Up to V = 32768 the tiles are at most one per CU and lose nothing to rounds.
+// Time of the tiles over that of the skinny kernel (sampling; C = 32 / C = 64 where two are given):
+//               V = 5003   20000   40000       50257         60001         75000        100000        151936
+//   H =   64        0.88    0.88    0.91   0.91 / 0.87   0.92 / 0.89   0.93 / 0.92   0.95 / 0.93   0.94 / 0.93
+//   H =  256        0.89    0.91    0.97   0.96 / 0.90   1.01 / 0.98   1.00 / 0.97   1.10 / 1.05   1.08 / 1.02
+//   H =  512        0.93    0.95    1.06   1.07 / 0.97   1.07 / 0.99   1.10 / 1.03   1.15 / 1.08   1.12 / 1.05
+//   H = 1024        0.95    0.97    1.15   1.12 / 1.06   1.06 / 1.03   1.15 / 1.09   1.14 / 1.16   1.09 / 1.12
+//   H = 2048        1.03    1.01    1.12   1.04 / 1.03   1.00 / 1.00   1.23 / 1.22   1.28 / 1.33   1.09 / 1.12
+// (up to 8 rows sampled, V = 5003, H = 1024: 1.02 .. 1.06; H = 1792: 1.10)
+constexpr int kSkMaxRows = 64;
+COPRIS_RULE bool lm_skinny_pays(int C, int H, int V, bool given) {
+  const int64_t elements = static_cast<int64_t>(H) * V;
+  if (C > kSkMaxRows) return false;
+  if (V < 192 * 256) {                 // (fewer than six waves' worth of rows per workgroup)
+    if (C > 32) return false;
+    return H >= (V > 32768 || (C <= 8 && !given) ? 1024 : 1792);
+  }
+  if (C <= 32) return H >= 192 && elements >= 15000000;
+  return H >= 256 && elements >= (V > 65536 ? 25000000 : 38000000);
+}
+
 }  // namespace copris

@@ -892,7 +892,6 @@ __device__ __forceinline__ void lm_given_quad(const float (&a)[4], LmLaneState& 
   }
 }
 
-constexpr int kSkMaxRows = 64;
 constexpr int kSkBM = 256;                             // vocabulary rows per tile, at most
 constexpr int kSkMaxGrid = 256;                        // one workgroup per CU
 constexpr int kSkRing = 4;
@@ -1389,16 +1388,9 @@ static bool lm_use_gemm(int C, int H, int V, int dtype, bool given) {
   return given && C >= kGmMinRows && lm_use_mfma(C, H, V, dtype);
 }
 
-// At most 64 rows: the skinny kernel, unless the vocabulary gives its workgroups fewer than six
-// waves' worth of rows (V < 192 * 256): then half of its waves idle and the 128-row tiles of
-// lmhead_mfma_kernel share the same work out better.  Up to 32 rows it is still the faster one
-// there if the hidden dimension is long.  Whole sampling calls, skinny / 128-row tiles:
-//   C = 64, H = 1536, V = 151936    92.0 / 100.5 us      C = 40, H = 512, V = 60001   23.2 / 24.9
-//   C = 60, H = 1024, V = 30001     25.1 /  23.2         C = 60, H = 512, V = 20001   19.2 / 17.5
-//   C = 22, H = 3584, V = 4096      35.6 /  39.3         C = 22, H = 1024, V = 20011  20.8 / 21.2
-//   C = 20, H = 512, V = 9001       14.6 /  14.4
-static bool lm_use_skinny(int C, int H, int V, int dtype) {
-  return C <= kSkMaxRows && lm_use_mfma(C, H, V, dtype) && (V >= 192 * kSkMaxGrid || (C <= 32 && H >= 1024));
+// At most 64 rows: the skinny kernel, where it pays.
+static bool lm_use_skinny(int C, int H, int V, int dtype, bool given) {
+  return lm_use_mfma(C, H, V, dtype) && lm_skinny_pays(C, H, V, given);
 }
 // Vocabulary rows per workgroup of the skinny kernel: an equal share for the resident workgroups,
 // in whole Philox blocks, but at least kLmTileV (a shorter run is all pipeline start).  Its tiles:
@@ -1427,7 +1419,7 @@ static int lm_gemm_lane_units(int C, int V) {
 // across all of its tiles.
 static int lm_parts(int C, int H, int V, int dtype, bool given) {
   if (!lm_use_mfma(C, H, V, dtype)) return (V + kLmTileV - 1) / kLmTileV;
-  if (lm_use_skinny(C, H, V, dtype)) return (V - 1) / lm_skinny_rows(V) + 1;
+  if (lm_use_skinny(C, H, V, dtype, given)) return (V - 1) / lm_skinny_rows(V) + 1;
   if (lm_use_gemm(C, H, V, dtype, given)) return (V - 1) / (64 * lm_gemm_lane_units(C, V)) + 1;
   const int n_tiles = (V + kMfBM - 1) / kMfBM;
   int parts = kMfMaxGrid / lm_row_blocks(C);
@@ -1456,7 +1448,7 @@ static int launch_lmhead(const void* hidden, const void* weight, const int64_t* 
                        static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(weight),
                        target, inv_t, part, C, H, V, lm_gemm_lane_units(C, V), n_parts);
     COPRIS_POST("lmhead_gemm_given_kernel");
-  } else if (lm_use_skinny(C, H, V, dtype)) {
+  } else if (lm_use_skinny(C, H, V, dtype, given)) {
     const int rows = lm_skinny_rows(V);
     COPRIS_PRE("lmhead_skinny_kernel");
 #define COPRIS_LM_SKINNY(G, NT)                                                                          \

@@ -38,10 +38,14 @@ def test_small_shapes(R, dtype, C, H, V):
     assert n_exempt <= 2          # expected near-ties: about C / 1000
 
 
-@pytest.mark.parametrize("C,H,V", [(1, 64, 49152), (32, 128, 49153), (33, 64, 50257), (64, 192, 65537),   # one slab per tile and more
-                                   (63, 64, 66001),                # two tiles of unequal fill per workgroup
+@pytest.mark.parametrize("C,H,V", [(1, 64, 49152), (32, 128, 49153), (33, 64, 50257), (64, 192, 65537), (63, 64, 66001),   # too short a hidden state
                                    (32, 1024, 3), (31, 1024, 65), (5, 1088, 4099),    # fewer rows than a wave, one workgroup and a row
-                                   (65, 64, 49153), (20, 64, 49151)])   # just outside the rule
+                                   (65, 64, 49153), (20, 64, 49151),                  # just outside the rule
+                                   # the skinny kernel: three slabs per tile and more, tiles of equal and unequal fill, a
+                                   # vocabulary that ends inside a Philox block
+                                   (32, 192, 78125), (1, 320, 49152), (31, 320, 49153), (32, 1024, 32769), (33, 384, 65537),
+                                   (64, 256, 97657), (63, 384, 66001), (64, 832, 49155),
+                                   (8, 1024, 3), (17, 1792, 3), (31, 1856, 65), (5, 1792, 4099)])
 def test_few_rows_over_the_whole_vocabulary(R, C, H, V):
     inp = W.make_small_lmhead_case(C * 11 + V, C, H, V, W.BF16, w_std=0.1)
     tok, lp, lse = R.run_lmhead_logprob(inp, W.BF16)

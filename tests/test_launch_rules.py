@@ -34,6 +34,10 @@ int main() {
       const int C = static_cast<int>(a[0]);
       std::printf("%d %d %d\n", lm_row_blocks(C), lm_block_rows(C), lm_block_width(C));
     }
+    if (!std::strcmp(name, "skinny")) {
+      std::scanf("%lld %lld %lld %lld", a, a + 1, a + 2, a + 3);
+      std::printf("%d\n", lm_skinny_pays(static_cast<int>(a[0]), static_cast<int>(a[1]), static_cast<int>(a[2]), a[3] != 0));
+    }
     if (!std::strcmp(name, "flip")) {
       std::scanf("%lld %lld %lld", a, a + 1, a + 2);
       std::printf("%d\n", lm_second_block_flip(static_cast<int>(a[0]), static_cast<int>(a[1]), static_cast<int>(a[2])));
@@ -110,3 +114,18 @@ def test_the_second_row_block_counts_from_the_end_where_that_evens_the_load(rule
             assert max(both) - min(both) <= 1, (C, t)
         elif 256 < C <= 512 and t > 256:
             assert t % 256 == 0 or t % 256 > 128, (C, t)
+
+
+# (rows, hidden size, vocabulary): measured faster with the skinny kernel / with tiles of 128 rows, sampling
+SKINNY = [(1, 1024, 1000), (8, 1536, 5003), (20, 1792, 5003), (32, 2048, 300), (32, 1024, 33000), (32, 1536, 45000),
+          (20, 384, 60001), (32, 256, 100000), (32, 192, 100000), (64, 1536, 151936), (64, 768, 50257), (64, 512, 75000),
+          (33, 256, 100000), (64, 3584, 2**31 // 3584)]
+TILES = [(65, 1536, 151936), (32, 1024, 5003), (20, 1024, 20000), (33, 3584, 5003), (32, 64, 151936), (20, 128, 100000),
+         (32, 256, 50257), (64, 256, 50257), (64, 512, 50257), (64, 192, 151936), (48, 256, 75000), (33, 64, 151936)]
+
+
+def test_few_rows(rules):
+    got = rules([f"skinny {c} {h} {v} 0" for c, h, v in SKINNY + TILES])
+    assert got == [[1]] * len(SKINNY) + [[0]] * len(TILES)
+    # given tokens: the same but for the few sampled rows of a short vocabulary
+    assert rules(["skinny 1 1024 1000 1", "skinny 1 1792 1000 1", "skinny 64 1536 151936 1"]) == [[0], [1], [1]]
