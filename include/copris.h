@@ -158,7 +158,11 @@ int copris_decode_attn(const void* q, const void* k_cache, const void* v_cache,
  *   block_table [B, max_pages] int32, entries >= ceil(len_b / P) ignored
  *   k_cache, v_cache [num_pages, Hkv, P, D] dtype, written
  *   out  [T, Hq, D]  dtype        lse [T, Hq] fp32 or NULL
- *   max_seqlen  an upper bound of the sequence lengths (sizes the launch)
+ *   max_seqlen  an upper bound of the sequence lengths (sizes the launch: a loose one costs time)
+ *
+ * Every call gives the same bits for the same arguments.  B, T, Hq and max_seqlen decide how the keys of a
+ * query are shared out and summed, so a sequence's out and lse may differ in their last bits between
+ * batches, or with another max_seqlen; the pages do not.
  *
  * No workspace.  Compiled for dtype = COPRIS_BF16, D = 128, page_size = 16 and
  * Hq / Hkv <= 8; anything else returns COPRIS_EUNSUPPORTED.

@@ -105,4 +105,40 @@ COPRIS_RULE bool lm_skinny_pays(int C, int H, int V, bool given) {
   return H >= 256 && elements >= (V > 65536 ? 25000000 : 38000000);
 }
 
+// Re-prefill attention: workgroup shapes, as groups of waves per unit x units (query head, tile of 32
+// queries).  A workgroup of several groups takes a CU for itself and shortens the chain of steps that the
+// longest sequence makes; whole ones (one group, four units, two workgroups per CU) have the throughput.
+// What is known of the sequences is their number B, their tokens T and a bound of their lengths:
+//   units     at most (T / 32 + B) * Hq; launched for the bound are tiles(bound) * B * Hq
+//   steps     of the longest chain: of the bound, if it can be a length (bound <= T, or one sequence); a
+//             looser one says nothing, and the longest is at least T / B long
+// A shape of several groups is taken where the chip has room for its workgroups, one per CU, those that are
+// launched for nothing among them (they end at once, but the others are then placed behind them); and two
+// groups of four units also beyond while the chain is long for the units: 36 units per step (24 of many).
+// Where more than 100 units per step of the chain (250 of a chain that is known, one sequence) are launched for
+// nothing, whole workgroups lose least.
+// Whole call in us, whole / 4 x 1 / 2 x 2 / 2 x 4:
+//   600 tokens, 12 / 2 heads (228 units)              17.4 / 12.8 / 15.0 / 16.4
+//   2 x 700 tokens, 8 / 8 heads (360)                 22.1 / 24.8 / 18.5 / 18.6
+//   926 + 439 tokens, 8 / 8 heads (352, 464 launched) 26.7 / 24.3 / 20.9 / 22.4
+//   2 x 1000 tokens, 8 / 8 heads, bound 2000 (512, 1008 launched)
+//                                                     28.4 / 34.1 / 42.1 / 23.8
+//   4000 tokens, 12 / 2 heads (1512)                  85.7 /   -  /   -  / 61.9
+//   1500 + 200 + 100 tokens, 28 / 4 heads (1652)      47.8 /   -  /   -  / 39.6
+//   2000 tokens, 28 / 4 heads (1764)                  52.9 /   -  /   -  / 55.4
+//   4 x 900 tokens, 12 / 2 heads (1392)               31.5 /   -  /   -  / 33.7
+//   8 x 200 tokens, 12 / 2 heads (696)                11.1 /   -  / 16.8 / 12.1
+//   30 x 60 tokens, 12 / 2 heads, bound 4096          45.0 / 99.0 / 76.3 / 81.0
+//   2 x 500 tokens, 8 / 8 heads, bound 8192           27.2 / 30.2 / 30.4 / 33.4
+enum PrefillShape { kPrefillWhole, kPrefill4x1, kPrefill2x2, kPrefill2x4 };
+COPRIS_RULE PrefillShape prefill_shape(int B, int64_t T, int Hq, int max_seqlen) {
+  const int64_t units = (T / 32 + B) * Hq;
+  const int64_t launched = ((static_cast<int64_t>(max_seqlen) + 31) / 32) * B * Hq;
+  const int64_t chain = max_seqlen <= T ? max_seqlen : (B == 1 ? T : T / B), steps = (chain + 31) / 32;
+  if (launched - units > (B == 1 ? 250 : 100) * steps) return kPrefillWhole;
+  if (units <= 256 && launched <= 512) return kPrefill4x1;
+  if (units <= 512 && (launched <= 600 || 5 * launched <= 8 * units)) return kPrefill2x2;
+  return units <= 2048 && units <= (units <= 1728 ? 36 : 24) * steps ? kPrefill2x4 : kPrefillWhole;
+}
+
 }  // namespace copris

@@ -508,20 +508,9 @@ int launch_prefill_attn(const void* q, const void* k, const void* v, const int32
                         float scale, hipStream_t stream) {
   const int g = Hq / Hkv;
   const float scale_log2e = scale * kLog2e;
-  const int n_tiles_max = (max_seqlen + kTileQ - 1) / kTileQ;
-  // Which shape: as many groups per unit as the chip has room for.  `units` (query head, tile) is at
-  // most what the sequences have; one workgroup of a split kernel fits a CU.
-  //   4 groups, 1 unit    units <= 256                     1 x 600 tokens, 12 heads     17.6 -> 13.2 us
-  //   2 groups, 2 units   units <= 512                     356 + 942 tokens, 12 heads   24.9 -> 21.4
-  //   2 groups, 4 units   units <= 1024, or twice that     1 x 915 tokens, 28 heads     25.4 -> 22.9
-  //                       with nearly all tokens in one    1 x 4003 tokens, 12 heads    86.9 -> 65.6
-  //                       sequence (one long chain)
-  // Beyond, the workgroups that do not fit at once cost more than the shorter chains give
-  // (3 sequences of 303 .. 1211 tokens, 28 heads, 1876 units: 36 us whole, 40 in two groups).
-  const int64_t units = (T / kTileQ + B) * Hq;
-  const bool one_chain = T <= max_seqlen + max_seqlen / 4;
-  const bool split4 = units <= 256, split2 = units <= 512, split2x4 = units <= (one_chain ? 2048 : 1024);
-  const int per_wg = split4 ? 1 : (split2 ? 2 : 4);     // units
+  const int n_tiles_max = (max_seqlen - 1) / kTileQ + 1;
+  const PrefillShape shape = prefill_shape(B, T, Hq, max_seqlen);
+  const int per_wg = shape == kPrefill4x1 ? 1 : (shape == kPrefill2x2 ? 2 : 4);     // units
   // super-tile of T tiles: the smallest T for which g * T units fill whole workgroups
   const int gcd = g % per_wg == 0 ? per_wg : (g % 2 == 0 && per_wg > 2 ? 2 : 1);
   const int super_tiles = per_wg / gcd;
@@ -534,11 +523,11 @@ int launch_prefill_attn(const void* q, const void* k, const void* v, const int32
                      static_cast<u32x4*>(k_cache), static_cast<u32x4*>(v_cache), static_cast<uint16_t*>(out), \
                      lse, Hq, Hkv, super_tiles, wgs_per_super, max_pages, scale_log2e);                     \
   COPRIS_POST(#KERNEL)
-  if (split4) {
+  if (shape == kPrefill4x1) {
     COPRIS_PREFILL(prefill_attn_split4x1_kernel, 256);
-  } else if (split2) {
+  } else if (shape == kPrefill2x2) {
     COPRIS_PREFILL(prefill_attn_split2x2_kernel, 256);
-  } else if (split2x4) {
+  } else if (shape == kPrefill2x4) {
     COPRIS_PREFILL(prefill_attn_split2x4_kernel, 512);
   } else {
     COPRIS_PREFILL(prefill_attn_kernel, 256);

@@ -67,6 +67,44 @@ def test_every_workgroup_shape(R, Hq, Hkv, most):
     _check_all(R, b, f"{Hq}/{Hkv} up to {most} units")
 
 
+def _kernels_of(R, d):
+    from paper_2511_05589_amd import binding
+    names = []
+    binding.set_launch_hook(lambda kernel, phase, stream, user: names.append(kernel.decode()) if phase == 0 else None)
+    try:
+        d.run()
+    finally:
+        binding.set_launch_hook(None)
+    return names
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(28, 4), (12, 2), (8, 8), (8, 1), (6, 2), (5, 1)])
+def test_each_workgroup_shape_is_taken(R, Hq, Hkv):
+    # by the units that the lengths make (see csrc/launch_rules.h); ragged ends, a second sequence
+    n4, n2 = 32 * (240 // Hq - 1) - 3, 32 * (300 // Hq) - 3
+    for name, lens in (("prefill_attn_split4x1_kernel", [n4]), ("prefill_attn_split2x2_kernel", [n2, n2 // 2 + 1]),
+                       ("prefill_attn_split2x4_kernel", [32 * (700 // Hq) + 5, 33]),
+                       ("prefill_attn_kernel", [200] * (1 + 900 // (7 * Hq)))):
+        b = W.make_prefill_case(800 + Hq, lens, Hq, Hkv, 128, W.BF16)
+        assert _kernels_of(R, R.stage_prefill_attn(b, W.BF16)) == [name], lens
+        _check_all(R, b, f"{Hq}/{Hkv} {name}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,lens,bound", [(12, 2, [60] * 30, 4096), (12, 2, [330] * 6, 8192), (8, 8, [500, 500], 8192)])
+def test_a_loose_length_bound_takes_whole_workgroups(R, Hq, Hkv, lens, bound):
+    b = W.make_prefill_case(900 + Hq, lens, Hq, Hkv, 128, W.BF16)
+    b["block_table"] = np.concatenate([b["block_table"], np.full((len(lens), bound // 16), -1, np.int32)], axis=1)
+    d = R.stage_prefill_attn(b, W.BF16)
+    d.max_seqlen = bound
+    assert _kernels_of(R, d) == ["prefill_attn_kernel"]
+    import torch
+    torch.cuda.synchronize()
+    ref_out, ref_lse, ref_kc, ref_vc = P.oracle_prefill(b, W.BF16)
+    P.check_attn(R.out_to_f32(d.out), d.lse.cpu().numpy(), ref_out, ref_lse, W.BF16, "loose bound")
+    np.testing.assert_array_equal(R.out_to_f32(d.k_cache), ref_kc)
+    np.testing.assert_array_equal(R.out_to_f32(d.v_cache), ref_vc)
+
+
 @pytest.mark.parametrize("Hq,Hkv,lens", [(28, 4, [1500]), (6, 2, [2049, 0, 300]), (14, 2, [1, 3000])])
 def test_one_long_chain(R, Hq, Hkv, lens):
     b = W.make_prefill_case(700 + Hq, lens, Hq, Hkv, 128, W.BF16)

@@ -38,6 +38,10 @@ int main() {
       std::scanf("%lld %lld %lld %lld", a, a + 1, a + 2, a + 3);
       std::printf("%d\n", lm_skinny_pays(static_cast<int>(a[0]), static_cast<int>(a[1]), static_cast<int>(a[2]), a[3] != 0));
     }
+    if (!std::strcmp(name, "prefill")) {
+      std::scanf("%lld %lld %lld %lld", a, a + 1, a + 2, a + 3);
+      std::printf("%d\n", prefill_shape(static_cast<int>(a[0]), a[1], static_cast<int>(a[2]), static_cast<int>(a[3])));
+    }
     if (!std::strcmp(name, "flip")) {
       std::scanf("%lld %lld %lld", a, a + 1, a + 2);
       std::printf("%d\n", lm_second_block_flip(static_cast<int>(a[0]), static_cast<int>(a[1]), static_cast<int>(a[2])));
@@ -129,3 +133,23 @@ def test_few_rows(rules):
     assert got == [[1]] * len(SKINNY) + [[0]] * len(TILES)
     # given tokens: the same but for the few sampled rows of a short vocabulary
     assert rules(["skinny 1 1024 1000 1", "skinny 1 1792 1000 1", "skinny 64 1536 151936 1"]) == [[0], [1], [1]]
+
+
+WHOLE, S4X1, S2X2, S2X4 = range(4)
+# (lengths, query heads, length bound or None for the longest length): the shape measured fastest, or within 3 % of it
+PREFILL = [([600], 12, None, S4X1), ([285], 28, None, S4X1), ([1000], 8, None, S4X1),
+           ([1000], 12, None, S2X2), ([700, 700], 8, None, S2X2), ([942, 356], 12, None, S2X2), ([400] * 4, 8, None, S2X2),
+           ([1000], 28, None, S2X4), ([4000], 12, None, S2X4), ([1500, 200, 100], 28, None, S2X4), ([3000] + [100] * 5, 12, None, S2X4),
+           ([2000], 28, None, WHOLE), ([330] * 6, 28, None, WHOLE), ([200] * 8, 12, None, WHOLE), ([100] * 16, 12, None, WHOLE),
+           ([900] * 4, 12, None, WHOLE), ([1200] + [30] * 10, 28, None, WHOLE),
+           # bounds that no sequence can have, or that few have: whole workgroups cost least for nothing
+           ([60] * 30, 12, 4096, WHOLE), ([330] * 6, 12, 8192, WHOLE), ([500, 500], 8, 8192, WHOLE), ([200] * 8, 28, 8192, WHOLE),
+           ([1000, 1000], 8, 8192, WHOLE), ([100] * 16, 6, 4096, WHOLE),
+           # one sequence: the bound is not needed to know the chain
+           ([1000], 12, 1024, S2X2), ([2000], 12, 2**31 - 1, WHOLE), ([16384] * 16, 28, 2**31 - 1, WHOLE)]
+
+
+def test_prefill_shapes(rules):
+    ask = [f"prefill {len(l)} {sum(l)} {h} {b or max(l)}" for l, h, b, _ in PREFILL]
+    assert [g for g, in rules(ask)] == [s for *_, s in PREFILL]
+    assert rules([f"prefill 65535 {2**31 - 1} 256 {2**31 - 1}", "prefill 1 1 1 1"]) == [[WHOLE], [S4X1]]
