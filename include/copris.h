@@ -253,7 +253,8 @@ int copris_lmhead_logprob_noalloc(const void* hidden, const void* weight,
  *
  *   hidden  [M, H] dtype       weight [V, H] dtype (row v = vocabulary entry v)
  *   tokens  [M] int32          logprob [M] fp32 out     lse [M] fp32 out or NULL
- *   workspace  at least copris_lmhead_token_logprob_workspace_bytes() bytes, 256-byte aligned
+ *   workspace  at least copris_lmhead_token_logprob_workspace_bytes() bytes, 256-byte aligned;
+ *              one that serves M positions serves fewer too
  *
  * Requires temperature > 0, H % 8 == 0 for bf16 (H % 4 == 0 for fp32), V < 2^31.
  * ------------------------------------------------------------------------ */

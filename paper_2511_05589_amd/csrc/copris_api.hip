@@ -198,7 +198,7 @@ int copris_lmhead_token_logprob(const void* hidden, const void* weight, const in
       (lse && !aligned16(lse)))
     return COPRIS_EINVAL;
   if (!aligned256(workspace) ||
-      workspace_bytes < copris_lmhead_token_logprob_workspace_bytes(M, H, V, dtype))
+      workspace_bytes < copris::lm_token_workspace_need(M, H, V, dtype))
     return COPRIS_EWORKSPACE;
   (void)hipGetLastError();
   return copris::launch_lmhead_token_logprob(hidden, weight, tokens, temperature, logprob, lse,

@@ -61,7 +61,8 @@ struct LmWorkspace {
 };
 LmWorkspace lm_workspace_layout(int C, int H, int V);
 
-size_t lm_token_workspace_bytes(int M, int H, int V, int dtype);
+size_t lm_token_workspace_bytes(int M, int H, int V, int dtype);   // enough for up to M positions
+size_t lm_token_workspace_need(int M, int H, int V, int dtype);    // of a call with M positions
 int launch_lmhead_token_logprob(const void* hidden, const void* weight, const int32_t* tokens,
                                 float temperature, float* logprob, float* lse, void* workspace,
                                 int M, int H, int V, int dtype, hipStream_t stream);

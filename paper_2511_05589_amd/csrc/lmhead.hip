@@ -1427,8 +1427,24 @@ static int lm_parts(int C, int H, int V, int dtype, bool given) {
   return parts < n_tiles ? parts : n_tiles;
 }
 
-size_t lm_token_workspace_bytes(int M, int H, int V, int dtype) {
+size_t lm_token_workspace_need(int M, int H, int V, int dtype) {
   return align256(static_cast<size_t>(M) * lm_parts(M, H, V, dtype, true) * sizeof(LmPartial));
+}
+
+// What M positions need, or any smaller number: fewer rows may be cut into more parts, and a program
+// sizes its workspace for its largest micro-batch.
+size_t lm_token_workspace_bytes(int M, int H, int V, int dtype) {
+  size_t most = lm_token_workspace_need(M, H, V, dtype);
+  if (!lm_use_mfma(M, H, V, dtype)) return most;   // (a part per 64 vocabulary rows: as many as there can be)
+  // the parts per row are constant between these numbers of rows
+  const int ends[] = {8, 32, kSkMaxRows, kGmMinRows - 1};
+  for (int m : ends)
+    if (m < M && lm_token_workspace_need(m, H, V, dtype) > most) most = lm_token_workspace_need(m, H, V, dtype);
+  for (int64_t m = kMfBN; m < M; m += kMfBN) {
+    const size_t need = lm_token_workspace_need(static_cast<int>(m), H, V, dtype);
+    if (need > most) most = need;
+  }
+  return most;
 }
 
 // Both modes: target == nullptr samples (seq_id / step / seed), else scores the given tokens.

@@ -56,6 +56,15 @@ def test_workspace_queries_are_host_only_and_monotone(lib):
     assert binding.lmhead_logprob_workspace_bytes(256, 3584, 0) == 0
 
 
+@pytest.mark.parametrize("H,V", [(512, 5000), (64, 8193), (1536, 20000), (3584, 151936), (96, 5000)])
+def test_a_token_logprob_workspace_serves_every_smaller_batch(lib, H, V):
+    Ms = list(range(1, 1100)) + list(range(1100, 9000, 61))
+    for dtype in (binding.COPRIS_BF16, binding.COPRIS_F32):
+        q = [binding.lmhead_token_logprob_workspace_bytes(M, H, V, dtype) for M in Ms]
+        assert all(a <= b for a, b in zip(q, q[1:]))
+        assert q[0] >= 20 and all(x % 256 == 0 for x in q)
+
+
 def test_bad_arguments_are_rejected_before_any_launch(lib):
     # null pointers / bad scalars return COPRIS_EINVAL without touching a device
     r = lib.copris_decode_attn(None, None, None, None, None, None, None, None, 0,
