@@ -101,8 +101,8 @@ void copris_set_launch_hook(copris_launch_hook_fn hook, void* user);
  * of the whole pool, per kv head, form one stream that is cut into equal shares, one per
  * wavefront, and the parts of a sequence are combined in a fixed order; smaller pages split
  * every context into 512-token chunks, combined in chunk order.  Either way the partition
- * depends on ctx_len only: results are bitwise reproducible and do not depend on the
- * physical page order.
+ * depends on ctx_len and the head counts only: results are bitwise reproducible and depend neither
+ * on the physical page order nor on the width of the block table.
  *
  *   q           [C, Hq, D]                      dtype
  *   k_cache     [num_pages, Hkv, page_size, D]  dtype; RoPE already applied
@@ -223,8 +223,8 @@ int copris_lmhead_logprob(const void* hidden, const void* weight,
  * A shape that needs more partials than the array holds returns COPRIS_EWORKSPACE (the
  * text of copris_last_error_detail() gives the sizes) and enqueues nothing.  The need
  * is C x parts x 20 bytes: for bf16 with H % 64 == 0, parts is at most
- * min(512 / ceil(C / 256), ceil(V / 64)), 2.6 MB for any C up to 200 000; for other shapes
- * parts = ceil(V / 64), e.g. C <= 88 at V = 151 936.
+ * max(1, min(512 / ceil(C / 256), ceil(V / 64))), i.e. 2.6 MB for any C up to 131 072 and 20 x C bytes
+ * beyond (209 715 rows fill the array); for other shapes parts = ceil(V / 64), e.g. C <= 88 at V = 151 936.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU
  * (different streams, or threads) race.  Nothing in it needs clearing between calls:
  * every partial a call reads it has written first.

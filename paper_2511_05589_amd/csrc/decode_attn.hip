@@ -31,8 +31,8 @@
 // rescale factor) lives in the lane that owns the head.  A slot's K (and V) is one
 // contiguous run (two when a page holds 8 tokens): it is fetched with fully coalesced 16-byte
 // loads, parked in LDS with an XOR swizzle, and read back in MFMA operand layout (V through the
-// transposing LDS read).  fp32 takes the same walk with mfma 16x16x4 in full fp32 (32 products
-// per 16 of head_dim and slot: the matrix pipes stay ahead of HBM).
+// transposing LDS read).  fp32 takes the same walk with mfma 16x16x4 in full fp32 (8 products
+// per 16 of head_dim and slot, half of them for the scores).
 // Measured (whole call, 64 sequences, mean context 1949): bf16, head_dim 64, 16 / 4 heads,
 // 129 MB of K and V: 32 us, where the vector-ALU kernels took 370; fp32, head_dim 128, 12 / 2
 // heads, 256 MB: 64 us.
@@ -517,7 +517,7 @@ constexpr int kAttnMaxSeqInKernelCursor = 4096;
 // a rule on what the block table could hold gave other bits, and the larger error, to the same contexts in
 // a wider table, and a branch on the pool's slots cost as much in the loop as it saved.
 // Two wavefronts per SIMD, except for slots of 16 KB (fp32, head_dim 128): their two stages
-// need more registers than half the file holds.
+// need more registers than half the file holds, so half of the wavefronts wait for the others.
 template <typename T, int D> constexpr int kFlatWavesPerSimd = sizeof(T) * D > 256 ? 1 : 2;
 template <typename T, int D, bool PRESCAN, int PG, int NS>
 __global__ __launch_bounds__(64)

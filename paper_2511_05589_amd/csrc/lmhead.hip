@@ -92,8 +92,8 @@ __device__ __forceinline__ LmPartial empty_partial() {
 }
 
 // --------------------------------------------------------------------------
-// generic kernel (bf16 whose hidden size the matrix-core kernels do not take; vector ALU): wave w of a workgroup owns batch rows
-// 4w..4w+3 of the 16-row block, lane l owns vocabulary row tile*64 + l.
+// generic kernel (bf16 whose hidden size the matrix-core kernels do not take; vector ALU): wave w of
+// a workgroup owns batch rows 4w..4w+3 of the 16-row block, lane l owns vocabulary row tile*64 + l.
 // --------------------------------------------------------------------------
 __device__ __forceinline__ void load_bf16x8(const uint16_t* p, float (&x)[8]) {
   const uint4 v = *reinterpret_cast<const uint4*>(p);
@@ -1107,9 +1107,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 constexpr int kGmBM = 256;                          // vocabulary rows per tile
 constexpr int kGmBN = 256;                          // batch rows per workgroup
 constexpr int kGmSlab = 256 * kMfBK * 2;            // 32 KB
-constexpr int kGmNW = 3;                            // W ring slabs
-constexpr int kGmHRing = kGmNW * kGmSlab;           // hidden ring (2 slabs) starts here
-constexpr int kGmLds = kGmHRing + 2 * kGmSlab;      // 160 KB
+constexpr int kGmNW = 3;                            // W ring slabs (issued three ahead)
+constexpr int kGmNH = 2;                            // hidden ring slabs
+constexpr int kGmHRing = kGmNW * kGmSlab;           // the hidden ring starts here
+constexpr int kGmLds = kGmHRing + kGmNH * kGmSlab;  // 160 KB
 constexpr int kGmMaxGrid = 256;                     // one workgroup per CU
 constexpr int kGmMinRows = 384;                     // below this the 128-row kernel is used
 
@@ -1121,7 +1122,6 @@ __device__ __forceinline__ void lds_wait6(u32x4 (&a)[4], u32x4 (&b)[2]) {
                : "memory");
 }
 
-template <bool W_DEEP>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void lmhead_gemm_given_kernel(
     const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ weight,
     const int32_t* __restrict__ target, float inv_temperature, LmPartial* __restrict__ part, int C,
@@ -1138,9 +1138,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int nkd = H / kMfBK;
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
   const uint32_t pitch = static_cast<uint32_t>(H) * 2u;
-  // the deep stream (three slots, issued three slabs ahead) and the shallow one (two slots)
-  constexpr int kWSlots = W_DEEP ? 3 : 2, kHSlots = W_DEEP ? 2 : 3;
-  constexpr int kHBase = kWSlots * kGmSlab;
 
   // A lane owns a contiguous run of lane_units * 64 vocabulary rows, the same for all (the last
   // one's may be shorter): whole tiles, then one of one to three row blocks of 64 where they are left.
@@ -1177,29 +1174,27 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                                      16, 0, 0);
   };
   auto w_advance = [&]() __attribute__((always_inline)) {
-    w_slot = w_slot + 1 == kWSlots ? 0 : w_slot + 1;
+    w_slot = w_slot + 1 == kGmNW ? 0 : w_slot + 1;
     if (++w_kd == nkd) {
       w_kd = 0;
       w_row += kGmBM;
     }
   };
   auto h_load = [&](int j) __attribute__((always_inline)) {
-    char* dst = smem + kHBase + h_slot * kGmSlab + (4 * wave + j) * 1024;
+    char* dst = smem + kGmHRing + h_slot * kGmSlab + (4 * wave + j) * 1024;
     const uint32_t koff = static_cast<uint32_t>(h_kd) * (kMfBK * 2) + ld_g;
     const int c = min(c0 + ld_row + 8 * j, C - 1);               // rows past C duplicate the last row (unused)
     __builtin_amdgcn_global_load_lds(hbase + (static_cast<uint32_t>(c) * pitch + (koff ^ ((j & 1) * 64))), dst,
                                      16, 0, 0);
   };
   auto h_advance = [&]() __attribute__((always_inline)) {
-    h_slot = h_slot + 1 == kHSlots ? 0 : h_slot + 1;
+    h_slot = h_slot + 1 == kGmNH ? 0 : h_slot + 1;
     if (++h_kd == nkd) h_kd = 0;
   };
-  // Load k (0..7) of the set a barrier opens: the shallow stream's slab first, then the deep
-  // one's.  Past the workgroup's last slab the loads re-read clamped rows into ring slots
+  // Load k (0..7) of the set a barrier opens: the hidden slab first, then the W slab.  Past the workgroup's last slab the loads re-read clamped rows into ring slots
   // nobody reads any more, so none of them needs a condition.
   auto load_one = [&](int k) __attribute__((always_inline)) {
-    const bool is_h = W_DEEP ? k < 4 : k >= 4;
-    if (is_h) {
+    if (k < 4) {
       h_load(k & 3);
       if ((k & 3) == 3) h_advance();
     } else {
@@ -1219,22 +1214,22 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     tgt[nt] = c < C ? target[c] : -1;
   }
 
-  // prologue: slab 0 of both streams and slab 1 of the deep one land; then the steady order
-  // begins - after the barrier that ends slab d, the shallow stream's slab d+2 and the deep
-  // one's slab d+3 go out, one load at a time between the matrix products of the next 32
+  // prologue: slab 0 of both streams and slab 1 of W land; then the steady order
+  // begins - after the barrier that ends slab d, the hidden slab d+2 and the W
+  // slab d+3 go out, one load at a time between the matrix products of the next 32
   // (issued in a bunch they keep all eight waves at the issue stage while the address unit
   // works through them, and the matrix pipes idle).  The first two loads of the set that the
   // prologue's barrier opens go out here, the other six with the products of slab 0.
-  for (int k = 0; k < 4; ++k) load_one(k);          // shallow slab 0
-  for (int k = 4; k < 8; ++k) load_one(k);          // deep slab 0
-  for (int k = 4; k < 8; ++k) load_one(k);          // deep slab 1
+  for (int k = 0; k < 4; ++k) load_one(k);          // hidden slab 0
+  for (int k = 4; k < 8; ++k) load_one(k);          // W slab 0
+  for (int k = 4; k < 8; ++k) load_one(k);          // W slab 1
   asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
   load_one(0);
   load_one(1);
 
   u32x4 a[2][4], b[2][2];
   int wslot = 0, hslot = 0;                     // ring slots of the slab being consumed
-  uint32_t wb = lds0, hb = lds0 + kHBase;
+  uint32_t wb = lds0, hb = lds0 + kGmHRing;
   auto read_operands = [&](auto bufc, auto k16c) __attribute__((always_inline)) {
     constexpr int buf = decltype(bufc)::value, k16 = decltype(k16c)::value;
     a[buf][0] = lds_read128<0>(wb + a_off[k16]);
@@ -1303,14 +1298,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                      "+v"(b[0][0]), "+v"(b[0][1])::"memory");
       const bool more = d + 1 < total;
       if (more) {
-        // slab d+1 has landed (this wave's part: only the deep stream's slab d+2, the newest
+        // slab d+1 has landed (this wave's part: only W slab d+2, the newest
         // four loads, is younger) ...
         asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
         asm volatile("s_barrier" ::: "memory");   // ... for every wave, and all are done reading slab d
-        wslot = wslot + 1 == kWSlots ? 0 : wslot + 1;
-        hslot = hslot + 1 == kHSlots ? 0 : hslot + 1;
+        wslot = wslot + 1 == kGmNW ? 0 : wslot + 1;
+        hslot = hslot + 1 == kGmNH ? 0 : hslot + 1;
         wb = lds0 + wslot * kGmSlab;
-        hb = lds0 + kHBase + hslot * kGmSlab;
+        hb = lds0 + kGmHRing + hslot * kGmSlab;
         read_operands(I0{}, I0{});                // first operands of slab d+1, under the products below
       }
       products(fullc, I1{}, L0{}, more);                 // with the first two loads into the slots of slab d
@@ -1460,7 +1455,7 @@ static int launch_lmhead(const void* hidden, const void* weight, const int64_t* 
   if (lm_use_gemm(C, H, V, dtype, given)) {
     const dim3 grid((C + kGmBN - 1) / kGmBN, n_parts);
     COPRIS_PRE("lmhead_gemm_given_kernel");
-    hipLaunchKernelGGL(lmhead_gemm_given_kernel<true>, grid, dim3(512), 0, stream,
+    hipLaunchKernelGGL(lmhead_gemm_given_kernel, grid, dim3(512), 0, stream,
                        static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(weight),
                        target, inv_t, part, C, H, V, lm_gemm_lane_units(C, V), n_parts);
     COPRIS_POST("lmhead_gemm_given_kernel");

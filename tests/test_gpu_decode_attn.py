@@ -45,10 +45,12 @@ def test_zero_length_and_wide_block_table(R):
     assert (out[0] == 0).all() and (out[2] == 0).all()
 
 
-def test_generic_path_other_page_size(R):
+@pytest.mark.parametrize("page", [8, 4])
+def test_other_page_sizes(R, page):
+    # two pages to a slot of the slot stream, and the vector-ALU kernels
     ctx = [3, 64, 65, 700]
-    case = W.make_small_decode_case(6, 4, 6, 2, 64, W.BF16, 8, ctx)
-    _run_case(R, case, W.BF16, "page8")
+    case = W.make_small_decode_case(6, 4, 6, 2, 64, W.BF16, page, ctx)
+    _run_case(R, case, W.BF16, f"page{page}")
 
 
 @pytest.mark.parametrize("dtype", [W.F32, W.BF16])
@@ -182,6 +184,18 @@ def test_thousands_of_sequences(R):
     ctx = rng.integers(0, 34, size=4500).tolist()
     case = W.make_small_decode_case(23, len(ctx), 6, 2, 128, W.BF16, 16, ctx)
     _run_case(R, case, W.BF16, "4500 sequences")
+
+
+@pytest.mark.parametrize("dtype", [W.F32, W.BF16])
+@pytest.mark.parametrize("D,page", [(64, 8), (64, 16), (64, 32), (128, 8), (128, 32), (128, 16), (64, 4)])
+def test_thousands_of_sequences_of_every_geometry(R, dtype, D, page):
+    # the cursors from the scan kernel (page 4: the vector-ALU kernels); a context that shares cut, and
+    # contexts that end on either side of a page and of a piece
+    rng = np.random.default_rng(5)
+    ctx = rng.integers(0, 20, size=4100)
+    ctx[[0, 7, 2000, 4099]] = [31, 300, 1000, 33]
+    case = W.make_small_decode_case(24 + D + page, len(ctx), 2, 1, D, dtype, page, ctx.tolist())
+    _run_case(R, case, dtype, f"{dtype} D={D} page={page} 4100 sequences")
 
 
 def test_large_scores_do_not_overflow(R):
