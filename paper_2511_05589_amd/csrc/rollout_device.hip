@@ -77,16 +77,18 @@ __global__ __launch_bounds__(256) void traj_append_kernel(
 }
 
 // A trajectory's tokens are shared out over `parts` workgroups in pieces of kGatherPiece, and
-// a trajectory of more than one piece has its earlier tokens counted by a workgroup of its own
+// where that is more than one a workgroup of its own counts a longer trajectory's earlier tokens
 // (4 of the 24 bytes per token are read twice for it, which a counter in memory and a launch to
-// clear it would cost more than).  What bounds it is bytes in flight: a thread moves kGatherDeep
+// clear it would cost more than; up to kGatherCounted tokens the one that moves them counts them).
+// What bounds it is bytes in flight: a thread moves kGatherDeep
 // tokens per round trip to memory, and fewer where the piece is short, because a load without a
 // token is a request all the same.  256 trajectories of 1024..16384 tokens, 2.2 M in all (53 MB):
 // 12 us, where one workgroup per trajectory with one token per thread in flight took 39; 20000
 // trajectories of 1..50 tokens: 16.8 us, 26.5 with eight loads per thread in every piece.
 constexpr int kGatherPiece = 2048;
 constexpr int kGatherDeep = 8;
-static_assert(kGatherPiece == 256 * kGatherDeep, "a piece is one round trip of a workgroup");
+constexpr int kGatherCounted = 1024;
+static_assert(kGatherPiece == 256 * kGatherDeep && kGatherCounted <= kGatherPiece, "a piece is one round trip of a workgroup");
 
 __global__ __launch_bounds__(256) void traj_gather_kernel(
     const int32_t* __restrict__ buf_token, const float* __restrict__ buf_logp,
@@ -104,7 +106,7 @@ __global__ __launch_bounds__(256) void traj_gather_kernel(
   const float nan = __int_as_float(0x7fc00000);
   const size_t row = static_cast<size_t>(ok ? tr : 0) * max_resp;
   int earlier_cnt = 0;
-  const bool one_piece = parts == 1 || len <= kGatherPiece;   // its first workgroup sees every token
+  const bool counted = parts == 1 || len <= kGatherCounted;   // by the workgroup that moves the tokens
   if (part < parts) {
     // DEEP * 256 tokens from t0 on (past the end: nothing, or token 0 in their place where there are
     // several loads, which a branch would put one behind the other)
@@ -137,10 +139,9 @@ __global__ __launch_bounds__(256) void traj_gather_kernel(
       const uint32_t left = len - t0;              // (the same for the whole workgroup)
       if (left <= 256) copy(t0, std::integral_constant<int, 1>{});
       else if (left <= 512) copy(t0, std::integral_constant<int, 2>{});
-      else if (left <= 1024) copy(t0, std::integral_constant<int, 4>{});
       else copy(t0, std::integral_constant<int, kGatherDeep>{});
     }
-  } else if (ok && !one_piece) {
+  } else if (ok && !counted) {
     for (uint32_t t0 = 0; t0 < len; t0 += 2 * kGatherPiece) {
       int32_t tag[2 * kGatherDeep];
 #pragma unroll
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(256) void traj_gather_kernel(
         earlier_cnt += (t0 + u * 256 + threadIdx.x < len && tag[u] < stage) ? 1 : 0;
     }
   }
-  if (part != (one_piece ? 0 : parts)) return;   // this one has seen every token
+  if (part != (counted ? 0 : parts)) return;   // this one has seen every token
   const int w = wave_sum_i(earlier_cnt);
   if ((threadIdx.x & (kWave - 1)) == 0) s_cnt[threadIdx.x / kWave] = w;
   __syncthreads();

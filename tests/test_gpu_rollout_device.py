@@ -133,7 +133,7 @@ def test_buffer_append_and_concatenation(gpu):
 
 @pytest.mark.parametrize("lens", [[0, 1, 255, 256, 257, 2047, 2048, 2049, 4095, 4096, 4097, 9001],   # pieces shared out
                                   [1] * 3000 + [2049] + [3] * 6000,                                 # ... and one workgroup each
-                                  [511, 512, 513, 1023, 1024, 1025, 2560, 2561, 3073, 5000],        # 1, 2, 4 and 8 tokens per thread
+                                  [511, 512, 513, 1023, 1024, 1025, 2560, 2561, 3073, 5000],        # 1, 2 and 8 tokens per thread, counted with and apart
                                   [300] * 700 + [2048, 2049, 4500] + [2100] * 400])                 # two workgroups, and one that counts
 def test_gather_over_piece_boundaries(gpu, lens):
     # plain numpy of what the call is defined as, with earlier tokens anywhere in a row (the call
