@@ -59,8 +59,9 @@ def test_few_rows_over_the_whole_vocabulary(R, C, H, V):
 
 @pytest.mark.parametrize("C", [65, 128, 129, 160, 192, 193, 257, 301, 320, 383, 384, 385, 520])
 def test_row_blocks_of_every_width(R, C):
-    # row blocks of 128, 192 and 256, one, two and three of them, with the rows shared evenly; more
-    # tiles than workgroups per block in the larger ones (the odd block deals them from the end)
+    # row blocks of 128, 192 and 256, one, two and three of them, the rows shared evenly or the last block
+    # with the rest; more tiles than workgroups per block in the larger ones (57 of 256 places have one
+    # more: with two blocks the second deals them from the end)
     H, V = 64, 40000 if C > 256 else 9001
     inp = W.make_small_lmhead_case(C * 13, C, H, V, W.BF16, w_std=0.1)
     tok, lp, lse = R.run_lmhead_logprob(inp, W.BF16)

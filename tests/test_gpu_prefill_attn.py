@@ -53,8 +53,9 @@ def test_empty_sequences_among_others_and_a_loose_length_bound(R, Hq, Hkv):
 @pytest.mark.parametrize("most", [256, 512, 1024, 3000])
 @pytest.mark.parametrize("Hq,Hkv", [(28, 4), (12, 2), (8, 8), (8, 1), (6, 2), (5, 1)])
 def test_every_workgroup_shape(R, Hq, Hkv, most):
-    # the call picks its workgroup shape by the number of units (query head, tile) that T and B
-    # admit: fill up to just below each bound with lengths around the tile, page and step boundaries
+    # batches of ever more units (query head, tile), just below the bounds at which workgroup shapes
+    # change, with lengths around the tile, page and step boundaries (which shape each takes depends on
+    # the lengths too: test_each_workgroup_shape_is_taken asks for every one of them)
     rng = np.random.default_rng(Hq * 7 + most)
     units = lambda ls: (sum(ls) // 32 + len(ls)) * Hq
     lens = [33] if units([33]) <= most else [1]
