@@ -289,16 +289,27 @@ constexpr int kMfBK = 64;        // hidden-dim slab (128 bytes of a row)
 constexpr int kMfMaxGrid = 512;  // persistent workgroups along the vocabulary (2 per CU)
 constexpr float kLn2f = 0.6931471805599453f, kLog2ef = 1.4426950408889634f;
 
-// Exponentials and the running maximum are in units of log2: an entry's is accumulator * scale with
-// scale = log2(e) / temperature, and exp(z - m) = exp2(fma(accumulator, scale, -m)) is two instructions.  m is the
-// rounded product; that is no error, because the sum is formed against the same m.
+// The running maximum is an accumulator, and exp(z - m) = exp2((accumulator - maximum) * scale) with
+// scale = log2(e) / temperature: three instructions, whose rounding is relative to the distance from the maximum.  The
+// maximum's own exponential is 1 and its logit rounds like the chosen one's, so that a row's log-prob is never above 0.
+// (exp2(fma(accumulator, scale, -maximum * scale)) is one instruction fewer, but then the rounding of scale counts by the
+// size of the logits: a log-prob was 3e-6 off for logits around 30 at temperature 0.55, now 1e-6; up to 3e-5 above 0 at
+// temperature 0.1 where one token has all the weight, now 0.  Whole calls before / now, in us: C = 256, H = 3584,
+// V = 151936 300.5 / 298.0; C = 301, H = 2048, V = 50257 85.0 / 85.0; 8192 given tokens 6496 / 6466.)
 struct LmLaneState {
-  float m, s;        // running max (units of log2) and sum of exp2(accumulator * scale - m)
+  float m, s;        // running max (an accumulator) and sum of the exponentials
   float l_best;      // log2(u) of the current best candidate (-inf: none yet)
   float p_best;      // its exponential
   float a_best;      // its accumulator
   int idx;
 };
+
+// log2(e) / temperature, finite where 1 / temperature is
+__device__ __forceinline__ float lm_scale(float inv_temperature) {
+  constexpr float kLog2eLo = 1.92596299e-8f;     // log2(e) - kLog2ef
+  return fminf(__builtin_fmaf(inv_temperature, kLog2ef, inv_temperature * kLog2eLo), 3.402823466e38f);
+}
+__device__ __forceinline__ float lm_exp(float a, float m, float scale) { return __builtin_amdgcn_exp2f((a - m) * scale); }
 
 // LDS position (in 16-byte granules) of granule g (0..7) of row `row` of a [rows][64]
 // bf16 slab.  Sixteen lanes that read one granule column of sixteen consecutive rows
@@ -313,10 +324,10 @@ __device__ __forceinline__ void lm_mask_block(f32x16& acc, int vbase, int V) {
     if (vbase + 8 * (r >> 2) + (r & 3) >= V) acc[r] = -INFINITY;
 }
 
-// The sampler: 24 vector instructions per entry (of a Philox block's 95, 18 are 64-bit multiplications and 19
+// The sampler: 25 vector instructions per entry (of a Philox block's 95, 18 are 64-bit multiplications and 19
 // three-input exclusive ors).  It is bound by their number: two waves of a SIMD issue one each in turn.  35 instructions
 // (exclusive ors by pairs, the uniform through a conversion, the temperature and the base of the exponential
-// multiplied apart, a mask test per entry) took 171 cycles per entry and SIMD where nothing else ran; whole calls
+// multiplied apart, a mask test per entry) against 24 (see above) took 171 cycles per entry and SIMD where nothing else ran; whole calls
 // C = 64, H = 1536, V = 151936 92 -> 89.5 us, C = 301, H = 2048, V = 50257 118.4 -> 115.4,
 // C = 256, H = 3584, V = 151936 302.5 -> 299.1.
 __device__ __forceinline__ void lm_epilogue_block(f32x16& acc, LmLaneState& st, int vbase, int V, bool tail,
@@ -326,9 +337,9 @@ __device__ __forceinline__ void lm_epilogue_block(f32x16& acc, LmLaneState& st, 
   float am = acc[0];
 #pragma unroll
   for (int r = 1; r < 16; ++r) am = fmaxf(am, acc[r]);
-  const float m_new = fmaxf(st.m, am * scale);
+  const float m_new = fmaxf(st.m, am);
   if (m_new == -INFINITY) return;            // nothing valid seen so far (vocabulary tail)
-  const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);  // 0 on the first block (m = -inf)
+  const float alpha = lm_exp(st.m, m_new, scale);  // 0 on the first block (m = -inf)
   st.s *= alpha;
   st.p_best *= alpha;
   st.m = m_new;
@@ -339,7 +350,7 @@ __device__ __forceinline__ void lm_epilogue_block(f32x16& acc, LmLaneState& st, 
     const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[4 * q + j], scale, -m_new));   // 0 for masked entries
+      const float p = lm_exp(acc[4 * q + j], m_new, scale);   // 0 for masked entries
       st.s += p;
       const float l = __builtin_amdgcn_logf(word_to_uniform(w[j]));   // log2(u) < 0
       // strictly better only: on an exact tie the earlier (lower) index stays
@@ -361,13 +372,13 @@ __device__ __forceinline__ void lm_given_block(f32x16& acc, LmLaneState& st, int
   float am = acc[0];
 #pragma unroll
   for (int r = 1; r < 16; ++r) am = fmaxf(am, acc[r]);
-  const float m_new = fmaxf(st.m, am * scale);
+  const float m_new = fmaxf(st.m, am);
   if (m_new == -INFINITY) return;
-  st.s *= __builtin_amdgcn_exp2f(st.m - m_new);
+  st.s *= lm_exp(st.m, m_new, scale);
   st.m = m_new;
   float s = 0.0f;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) s += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r], scale, -m_new));
+  for (int r = 0; r < 16; ++r) s += lm_exp(acc[r], m_new, scale);
   st.s += s;
   const int d = target - vbase;                  // entry vbase + 8q + j sits in accumulator 4q + j
   if (d >= 0 && d < 32 && (d & 4) == 0 && target < V) {
@@ -383,11 +394,8 @@ __device__ __forceinline__ void lm_given_block(f32x16& acc, LmLaneState& st, int
 template <bool GIVEN>
 __device__ __forceinline__ LmPartial lane_partial(const LmLaneState& st, float inv_temperature) {
   LmPartial p;
-  // the maximum in natural units, and the sum against the rounded one: m - log2(e) * p.m to 48 bits
-  constexpr float kLog2eLo = 1.92596299e-8f;     // log2(e) - kLog2ef
-  p.m = st.m * kLn2f;
-  const float back = p.m * kLog2ef, rest = __builtin_fmaf(p.m, kLog2ef, -back) + p.m * kLog2eLo;
-  p.s = st.m == -INFINITY ? 0.0f : st.s * __builtin_amdgcn_exp2f((st.m - back) - rest);
+  p.m = st.m * inv_temperature;
+  p.s = st.s;
   p.z = st.a_best * inv_temperature;
   p.idx = st.idx;
   // perturbed score z + G with G = -ln(E), E = -ln u = -l_best * ln 2
@@ -482,7 +490,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     LmPartial* __restrict__ part, int C, int H, int V, int block_rows, int n_tiles, int n_parts, int flip) {
   __shared__ __attribute__((aligned(1024))) char smem[kMfLds];
   const int tid = threadIdx.x, lane = tid & 63;
-  const float scale = inv_temperature * kLog2ef;   // (rounded once, the same for every entry)
+  const float scale = lm_scale(inv_temperature);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wq = wave & 1;     // vocabulary half; 64-row block of a batch half
   const int l32 = lane & 31, kb = lane >> 5;
@@ -855,9 +863,9 @@ __device__ __forceinline__ void lm_sample_quad(float (&a)[4], LmLaneState& st, i
     for (int j = 0; j < 4; ++j)
       if (vq + j >= v_end) a[j] = -INFINITY;
   }
-  const float m_new = fmaxf(st.m, fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])) * scale);
+  const float m_new = fmaxf(st.m, fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])));
   if (m_new == -INFINITY) return;
-  const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
+  const float alpha = lm_exp(st.m, m_new, scale);
   st.s *= alpha;
   st.p_best *= alpha;
   st.m = m_new;
@@ -865,7 +873,7 @@ __device__ __forceinline__ void lm_sample_quad(float (&a)[4], LmLaneState& st, i
   const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(a[j], scale, -m_new));   // 0 for masked entries
+    const float p = lm_exp(a[j], m_new, scale);                     // 0 for masked entries
     st.s += p;
     const float l = __builtin_amdgcn_logf(word_to_uniform(w[j]));   // log2(u) < 0
     if (l * st.p_best > st.l_best * p) {                            // (see lm_epilogue_block)
@@ -883,12 +891,12 @@ __device__ __forceinline__ void lm_given_quad(float (&a)[4], LmLaneState& st, in
     for (int j = 0; j < 4; ++j)
       if (vq + j >= v_end) a[j] = -INFINITY;
   }
-  const float m_new = fmaxf(st.m, fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])) * scale);
+  const float m_new = fmaxf(st.m, fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])));
   if (m_new == -INFINITY) return;
   float p[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) p[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(a[j], scale, -m_new));
-  st.s = st.s * __builtin_amdgcn_exp2f(st.m - m_new) + ((p[0] + p[1]) + (p[2] + p[3]));
+  for (int j = 0; j < 4; ++j) p[j] = lm_exp(a[j], m_new, scale);
+  st.s = st.s * lm_exp(st.m, m_new, scale) + ((p[0] + p[1]) + (p[2] + p[3]));
   st.m = m_new;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -918,7 +926,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   static_assert(32 * NT <= kSkMaxRows, "rings exceed the workgroup's LDS");
   __shared__ __attribute__((aligned(1024))) char smem[kSkLds];
   const int tid = threadIdx.x, lane = tid & 63;
-  const float scale = inv_temperature * kLog2ef;   // (rounded once, the same for every entry)
+  const float scale = lm_scale(inv_temperature);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, kb = lane >> 5;
   const int nkd = H / kMfBK;
@@ -1135,7 +1143,7 @@ __device__ __forceinline__ void lm_gemm_given_body(
     const int32_t* __restrict__ target, float inv_temperature, LmPartial* __restrict__ part, int c0, int C, int H, int V,
     int lane_id, int lane_units, int n_parts) {
   const int tid = threadIdx.x, lane = tid & 63;
-  const float scale = inv_temperature * kLog2ef;   // (rounded once, the same for every entry)
+  const float scale = lm_scale(inv_temperature);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wq = wave & 3;     // vocabulary rows 64*rb + 32*wm ..; 64-row batch block
   const int l32 = lane & 31, kb = lane >> 5;
@@ -1467,7 +1475,7 @@ __device__ __forceinline__ void lm_run_body(
     int lane_rows, int n_parts) {
   constexpr int NT = S::kNT, GN = S::kGN, GPK = NT / GN;
   const int tid = threadIdx.x, lane = tid & 63;
-  const float scale = inv_temperature * kLog2ef;   // (rounded once, the same for every entry)
+  const float scale = lm_scale(inv_temperature);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, kb = lane >> 5;
   const int nkd = H / kMfBK;

@@ -146,6 +146,73 @@ def test_log_sum_exp_has_no_bias(R, C):
     assert abs((lse.astype(np.float64) - P.oracle_lmhead(inp, W.BF16)["lse"]).mean()) <= 4 * 2.8e-7 / math.sqrt(C) + 5e-8
 
 
+# (C, H, V): together these reach every kernel, sampling and with given tokens (rows of 128 .. 320, the skinny one, the
+# 256 x 256 one with a last block of another width and without, the generic one)
+EVERY_KERNEL = [(48, 384, 65537), (20, 64, 5003), (200, 64, 20011), (200, 128, 8195), (150, 64, 8195), (300, 64, 3001), (320, 1024, 33001),
+                (400, 64, 20011), (448, 64, 20011), (5, 72, 260)]
+
+
+def _scored(R, hidden, weight, temperature):
+    """tokens, log-probs, log-sum-exps of a sampling call, and the latter two of its tokens as given ones (stored operands)"""
+    C, V = len(hidden), len(weight)
+    inp = dict(hidden=hidden, weight=weight, seq_id=np.arange(C, dtype=np.int64), step=np.zeros(C, np.int32), seed=5,
+               temperature=temperature, C=C, H=hidden.shape[1], V=V, dtype=W.BF16)
+    tok, lp, lse = R.run_lmhead_logprob(inp, W.BF16)
+    assert ((0 <= tok) & (tok < V)).all()
+    return tok, (lp, lse), R.run_token_logprob(hidden, weight, tok, temperature, W.BF16)
+
+
+@pytest.mark.parametrize("C,H,V", EVERY_KERNEL + [(5, 64, 1), (200, 64, 1), (300, 64, 1), (400, 64, 1)])
+def test_a_peaked_row_has_no_positive_log_prob(R, C, H, V):
+    # one logit of lo .. 2 * lo, the others noise around 0: the log-prob is -ln(1 + less than 70000 e^-35), so 0 up to the
+    # rounding of a sum near 1 and of its logarithm.  The last two are near the end of fp32's range.
+    rng = np.random.default_rng(C + V)
+    noise, peak = rng.standard_normal(V), V // 3
+    for T, lo, amp in ((1.0, 40.0, 1.0), (0.6, 40.0, 1.0), (0.1, 40.0, 1.0), (1.0, 1.5e38, 1.0), (3.5e-39, 0.5, 0.0)):
+        hidden, weight = np.zeros((C, H), np.float32), np.zeros((V, H), np.float32)
+        hidden[:, 0] = lo * (1 + np.arange(C) % 128 / 128)
+        hidden[:, 1] = 1
+        weight[:, 1] = amp * T * noise
+        weight[peak] = 0
+        weight[peak, 0] = 1
+        hidden = W.to_storage(hidden, W.BF16)
+        tok, *scored = _scored(R, hidden, W.to_storage(weight, W.BF16), T)
+        assert (tok == peak).all()
+        z = W.to_f32(hidden, W.BF16)[:, 0] * (np.float32(1) / np.float32(T))
+        for lp, lse in scored:
+            assert (lp <= 0).all() and (lp >= -1e-6).all(), (T, lo, lp.min(), lp.max())
+            np.testing.assert_allclose(lse, z, rtol=3e-7)
+
+
+@pytest.mark.parametrize("C,H,V", EVERY_KERNEL)
+def test_log_probs_have_no_bias_at_any_temperature(R, C, H, V):
+    # Logits whose fp32 sums are exact (small whole numbers over a power of two), deviation 3 to 5 around 20, so that what
+    # differs from the 64-bit log-prob is the rounding of the temperature, of the exponentials and of the results.
+    rng = np.random.default_rng(C * 3 + H)
+    hidden, weight = (rng.integers(-4, 5, size=(n, H), dtype=np.int8).astype(np.float32) for n in (C, V))
+    weight /= 2.0 ** round(math.log2(6.67 * math.sqrt(H) / 4))
+    hidden[:, 0], weight[:, 0] = 4, 5
+    logits = (hidden @ weight.T).astype(np.float64)
+    hidden, weight = W.to_storage(hidden, W.BF16), W.to_storage(weight, W.BF16)
+    for T in (0.1, 0.55, 0.6, 1.0, 1.05, 1.1):
+        tok, *scored = _scored(R, hidden, weight, T)
+        z = logits / float(np.float32(T))
+        m = z.max(axis=1, keepdims=True)
+        p = np.exp(z - m)
+        s = p.sum(axis=1)
+        lse, chosen, mean = m[:, 0] + np.log(s), z[np.arange(C), tok], (p * z).sum(axis=1) / s
+        # 1 / T and log2(e) / T are off by up to 2^-24 of a logit's distance from the mean one; the chosen logit and the
+        # maximum are rounded to 24 bits, and so is the result (ulp / sqrt(12) each, four deviations of the rows' mean);
+        # 1e-7 for the hardware's exponential and logarithm
+        ulp = lambda x: 2.0 ** (np.ceil(np.log2(np.abs(x).max())) - 24)  # noqa: E731
+        bound = (2.0 ** -24 * (np.abs(chosen - mean) + (m[:, 0] - mean)).mean() + 1e-7
+                 + 4 * math.sqrt((2 * ulp(m) ** 2 + ulp(chosen - lse) ** 2) / 12 / C))
+        for what, (lp, _) in zip(("sampled", "given"), scored):
+            bias = (lp - (chosen - lse)).mean()
+            print(f"{what} {C}x{H}x{V} T={T}: bias {bias:+.2e}, bound {bound:.2e}", flush=True)
+            assert abs(bias) <= bound, (what, T, bias, bound)
+
+
 def test_bitwise_reproducible(R):
     inp = W.make_small_lmhead_case(10, 40, 512, 7000, W.BF16)
     a, b = R.run_lmhead_logprob(inp, W.BF16), R.run_lmhead_logprob(inp, W.BF16)
