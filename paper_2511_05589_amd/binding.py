@@ -8,13 +8,13 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from ctypes import c_char_p, c_float, c_int, c_int64, c_size_t, c_uint64, c_void_p
 from typing import Optional
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 # COPRIS_LIB selects another build of the library (e.g. one with host sanitizers)
 LIB_PATH = os.environ.get("COPRIS_LIB") or os.path.join(_PKG_DIR, "libcopris.so")
-ARGS_PATH = os.path.join(_PKG_DIR, "_args.so")
 
 COPRIS_OK = 0
 COPRIS_EINVAL = -1
@@ -88,7 +88,8 @@ SIGNATURES.update({
 _lib = None
 _raw_stream = None
 # The native way of a good call (csrc/py_args.cpp), bound to _lib's entry points: it returns the call's code, or None
-# where the arguments are for the Python checks to look at.  None until the library is loaded.
+# where the arguments are for the Python checks to look at.  None until the library is loaded, and where the module is
+# not there or not of this PyTorch: every call then goes the Python way.
 _args = None
 
 
@@ -119,16 +120,25 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
         fn.restype = res
         fn.argtypes = args
     native = _native_args()
-    native.bind(tuple(ctypes.cast(getattr(lib, name), c_void_p).value for name in native.entry_points), _current_stream())
+    if native is not None:
+        native.bind(tuple(ctypes.cast(getattr(lib, name), c_void_p).value for name in native.entry_points),
+                    _current_stream())
     _lib, _args = lib, native
     return lib
 
 
 def _native_args():
-    if not os.path.exists(ARGS_PATH):
-        raise FileNotFoundError(f"{ARGS_PATH} not found: build it with `python -m paper_2511_05589_amd.build`")
-    from . import _args as native
-    return native
+    import torch
+    try:
+        from . import _args as native
+        if native.built_for == torch.__version__:
+            return native
+        why = f"it was built for PyTorch {native.built_for}, this is {torch.__version__}"
+    except ImportError as e:
+        why = str(e)
+    warnings.warn(f"the binding's argument module (_args.so) cannot be used, calls are marshalled by ctypes: {why}; build it "
+                  "with `python -m paper_2511_05589_amd.build`", RuntimeWarning, stacklevel=3)
+    return None
 
 
 def _current_stream():

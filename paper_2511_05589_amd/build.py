@@ -53,7 +53,8 @@ def args_command() -> list:
     inc = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
            sysconfig.get_paths()["include"], os.path.join(os.path.dirname(PKG_DIR), "include")]
     return ([os.environ.get("CXX") or shutil.which("g++") or "c++", "-std=c++17", "-O2", "-fPIC", "-shared",
-             "-fvisibility=hidden", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+             "-fvisibility=hidden", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+             f'-DCOPRIS_TORCH_VERSION="{torch.__version__}"']
             + [x for i in inc for x in ("-isystem", i)]
             + [os.path.join(CSRC, "py_args.cpp"), "-o", ARGS_PATH, "-L", os.path.join(root, "lib"),
                "-ltorch_python", "-ltorch_cpu", "-lc10"])
@@ -61,7 +62,7 @@ def args_command() -> list:
 
 def build(verbose: bool = False, lib_path: str = LIB_PATH, extra_flags=()) -> str:
     """Compile every HIP source for gfx950 (one hipcc process per file, side by side) and
-    link the shared library; beside it the binding's argument module."""
+    link the shared library; beside it the binding's argument module, without which the binding works too."""
     hipcc = hipcc_path()
     os.makedirs(OBJ_DIR, exist_ok=True)
     tag = os.path.splitext(os.path.basename(lib_path))[0]
@@ -70,10 +71,15 @@ def build(verbose: bool = False, lib_path: str = LIB_PATH, extra_flags=()) -> st
     with ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, os.cpu_count() or 1)) as pool:
         jobs = [pool.submit(_run, [hipcc] + flags + ["-c", os.path.join(CSRC, s), "-o", o], verbose)
                 for s, o in zip(SOURCES, objs)]
-        if lib_path == LIB_PATH:
-            jobs.append(pool.submit(_run, args_command(), verbose))
+        args = pool.submit(lambda: _run(args_command(), verbose))
         for j in jobs:
             j.result()
+        try:
+            args.result()
+        except (ImportError, RuntimeError, OSError) as e:   # no host compiler, or no headers of Python's or PyTorch's
+            if os.path.exists(ARGS_PATH):
+                os.unlink(ARGS_PATH)           # (an older one need not fit the library)
+            print(f"{ARGS_PATH} was not built, calls will be marshalled by ctypes: {e}", file=sys.stderr)
     _run([hipcc, "--offload-arch=gfx950", "-fPIC", "-shared", "-o", lib_path] + list(extra_flags) + objs,
          verbose)
     if lib_path == LIB_PATH:

@@ -215,5 +215,7 @@ PyMODINIT_FUNC PyInit__args(void) {
   if (!names) return nullptr;
   for (int i = 0; i < kEntries; ++i) PyTuple_SET_ITEM(names, i, PyUnicode_FromString(kNames[i]));
   if (PyModule_AddObject(m, "entry_points", names) != 0) return nullptr;
+  // a tensor is read by its C++ layout, which is that of one PyTorch version
+  if (PyModule_AddStringConstant(m, "built_for", COPRIS_TORCH_VERSION) != 0) return nullptr;
   return m;
 }

@@ -1,13 +1,16 @@
 """The binding's native way of a call (csrc/py_args.cpp) hands the C entry points what the Python way hands them, and
 leaves every other call to it.  Nothing is launched: the entry points are replaced by recorders."""
 import ctypes
+import os
+import subprocess
+import sys
 import types
 
 import numpy as np
 import pytest
 import torch
 
-from paper_2511_05589_amd import binding
+from paper_2511_05589_amd import binding, build
 
 F32, BF16, I32, I64, U8 = torch.float32, torch.bfloat16, torch.int32, torch.int64, torch.uint8
 
@@ -89,6 +92,53 @@ def test_host_tensors_are_left_to_python(name):
     assert getattr(binding._args, fn.__name__)(*pos, *kw.values(), None) is None
     with pytest.raises(TypeError, match="must be a GPU tensor"):
         fn(*pos, **kw)
+
+
+# a process in which the module is MODULE (None: it cannot be imported): the library, the manager and the checks work
+WITHOUT = """
+import sys, types, warnings
+sys.modules["paper_2511_05589_amd._args"] = MODULE
+from paper_2511_05589_amd import binding
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    binding.load_library()
+    binding.load_library()
+assert [w.category for w in seen] == [RuntimeWarning] and "ctypes" in str(seen[0].message), seen
+assert binding._args is None and binding.version()
+from tests import test_binding_args as t
+for fn, pos, kw in t.cases("cpu").values():
+    try:
+        fn(*pos, **kw)
+    except TypeError as e:
+        assert "must be a GPU tensor" in str(e)
+    else:
+        raise AssertionError(fn)
+"""
+
+
+@pytest.mark.parametrize("module", ["None", "types.SimpleNamespace(built_for='another version')"])
+def test_every_call_goes_the_python_way_without_the_module(module):
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    done = subprocess.run([sys.executable, "-c", WITHOUT.replace("MODULE", module)], cwd=root, capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0, done.stderr
+
+
+def test_build_makes_the_module_beside_every_library_and_does_without_it(monkeypatch, tmp_path, capsys):
+    ran, old = [], tmp_path / "_args.so"
+    compiles = lambda cmd: any(str(c).endswith("py_args.cpp") for c in cmd)  # noqa: E731
+    monkeypatch.setattr(build, "ARGS_PATH", str(old))
+    monkeypatch.setattr(build, "_run", lambda cmd, verbose: ran.append(cmd))
+    other = str(tmp_path / "other.so")
+    assert build.build(lib_path=other) == other
+    assert sum(compiles(c) for c in ran) == 1
+
+    def no_headers(cmd, verbose):
+        if compiles(cmd):
+            raise RuntimeError("g++ failed:\nPython.h: No such file or directory")
+    monkeypatch.setattr(build, "_run", no_headers)
+    old.write_bytes(b"of an older build")
+    assert build.build(lib_path=other) == other
+    assert not old.exists() and "Python.h" in capsys.readouterr().err
 
 
 @pytest.mark.gpu
