@@ -13,6 +13,11 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <cxxabi.h>
+
+#include <optional>
+#include <tuple>
+
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "copris.h"
@@ -98,82 +103,91 @@ struct Args {
   }
 };
 
-// The call itself, with the interpreter's lock given up as ctypes does: a launch can wait for room in the queue.
-// (Nothing may be thrown while it is given up; a C entry point throws nothing.)
-template <typename F, typename... A> int invoke(F* f, A... a) noexcept {
-  PyThreadState* state = PyEval_SaveThread();
-  const int code = f(a...);
-  PyEval_RestoreThread(state);
-  return code;
-}
-#define INVOKE(e, f, ...) invoke(reinterpret_cast<decltype(&f)>(g_entry[e]), __VA_ARGS__)
+// The checked arguments of one entry point, as it takes them.
+template <typename F> struct Ready;
+template <typename... P> struct Ready<int(P...)> {
+  Entry entry;
+  std::tuple<P...> values;
+  int operator()() const { return std::apply(reinterpret_cast<int (*)(P...)>(g_entry[entry]), values); }
+};
+#define READY(e, f, ...) Ready<decltype(f)>{e, {__VA_ARGS__}}
 
-int rollout_apply(const Args& a) {
-  return INVOKE(kApply, copris_rollout_apply, a.i32(0), a.integer(1), a.integer(2), a.i64(3), a.i32(4), a.i32(5),
-                a.i32(6), a.size32(6, 0, 2), a.size32(6, 1, 2), a.stream(6));
+auto rollout_apply(const Args& a) {
+  return READY(kApply, copris_rollout_apply, a.i32(0), a.integer(1), a.integer(2), a.i64(3), a.i32(4), a.i32(5),
+               a.i32(6), a.size32(6, 0, 2), a.size32(6, 1, 2), a.stream(6));
 }
-int kv_append(const Args& a) {
-  return INVOKE(kAppend, copris_kv_append, a.data(0), a.data(1), a.i32(2), a.i32(3), a.data(4), a.data(5),
-                a.size32(0, 0, 3), a.size32(0, 1, 3), a.size32(0, 2, 3), a.size32(4, 2, 4), a.size32(2, 1, 2),
-                a.size(4, 0, 4), a.integer(6), a.stream(4));
+auto kv_append(const Args& a) {
+  return READY(kAppend, copris_kv_append, a.data(0), a.data(1), a.i32(2), a.i32(3), a.data(4), a.data(5),
+               a.size32(0, 0, 3), a.size32(0, 1, 3), a.size32(0, 2, 3), a.size32(4, 2, 4), a.size32(2, 1, 2),
+               a.size(4, 0, 4), a.integer(6), a.stream(4));
 }
-int traj_append(const Args& a) {
-  return INVOKE(kTrajAppend, copris_traj_append, a.i32(0), a.f32(1), a.i64(2), a.i32(3), a.i32(4), a.integer(5),
-                a.i32(6), a.f32(7), a.i32(8), Args::narrow(a.numel(0)), a.size(6, 0, 2), a.size32(6, 1, 2),
-                a.stream(6));
+auto traj_append(const Args& a) {
+  return READY(kTrajAppend, copris_traj_append, a.i32(0), a.f32(1), a.i64(2), a.i32(3), a.i32(4), a.integer(5),
+               a.i32(6), a.f32(7), a.i32(8), Args::narrow(a.numel(0)), a.size(6, 0, 2), a.size32(6, 1, 2),
+               a.stream(6));
 }
-int traj_gather(const Args& a) {
-  return INVOKE(kGather, copris_traj_gather, a.i32(0), a.f32(1), a.i32(2), a.i32(3), a.i32(4), a.integer(5), a.i32(6),
-                a.f32(7), a.f32(8), a.i32(9), Args::narrow(a.numel(3)), a.size(0, 0, 2), a.size32(0, 1, 2),
-                a.stream(0));
+auto traj_gather(const Args& a) {
+  return READY(kGather, copris_traj_gather, a.i32(0), a.f32(1), a.i32(2), a.i32(3), a.i32(4), a.integer(5), a.i32(6),
+               a.f32(7), a.f32(8), a.i32(9), Args::narrow(a.numel(3)), a.size(0, 0, 2), a.size32(0, 1, 2),
+               a.stream(0));
 }
-int decode_attn(const Args& a) {   // ..., workspace, scale, dtype, stream
+auto decode_attn(const Args& a) {   // ..., workspace, scale, dtype, stream
   const at::ScalarType e = a.element(9);
-  return INVOKE(kDecode, copris_decode_attn, a.data(0, e), a.data(1, e), a.data(2, e), a.i32(3), a.i32(4),
-                a.data(5, e), a.optional<float>(6, at::kFloat), a.data(7, at::kByte), a.numel(7), a.size32(0, 0, 3),
-                a.size32(0, 1, 3), a.size32(1, 1, 4), a.size32(0, 2, 3), a.size32(1, 2, 4), a.size32(3, 1, 2),
-                a.size(1, 0, 4), a.number(8), a.integer(9), a.stream(0));
+  return READY(kDecode, copris_decode_attn, a.data(0, e), a.data(1, e), a.data(2, e), a.i32(3), a.i32(4),
+               a.data(5, e), a.optional<float>(6, at::kFloat), a.data(7, at::kByte), a.numel(7), a.size32(0, 0, 3),
+               a.size32(0, 1, 3), a.size32(1, 1, 4), a.size32(0, 2, 3), a.size32(1, 2, 4), a.size32(3, 1, 2),
+               a.size(1, 0, 4), a.number(8), a.integer(9), a.stream(0));
 }
-int prefill_attn(const Args& a) {   // ..., lse, max_seqlen, scale, dtype, stream
+auto prefill_attn(const Args& a) {   // ..., lse, max_seqlen, scale, dtype, stream
   const at::ScalarType e = a.element(11);
-  return INVOKE(kPrefill, copris_prefill_attn, a.data(0, e), a.data(1, e), a.data(2, e), a.i32(3), a.i32(4),
-                a.data(5, e), a.data(6, e), a.data(7, e), a.optional<float>(8, at::kFloat),
-                Args::narrow(a.numel(3) - 1), a.size(0, 0, 3), a.size32(0, 1, 3), a.size32(1, 1, 3),
-                a.size32(0, 2, 3), a.size32(5, 2, 4), a.size32(4, 1, 2), a.size(5, 0, 4), a.integer(9), a.number(10),
-                a.integer(11), a.stream(0));
+  return READY(kPrefill, copris_prefill_attn, a.data(0, e), a.data(1, e), a.data(2, e), a.i32(3), a.i32(4),
+               a.data(5, e), a.data(6, e), a.data(7, e), a.optional<float>(8, at::kFloat),
+               Args::narrow(a.numel(3) - 1), a.size(0, 0, 3), a.size32(0, 1, 3), a.size32(1, 1, 3),
+               a.size32(0, 2, 3), a.size32(5, 2, 4), a.size32(4, 1, 2), a.size(5, 0, 4), a.integer(9), a.number(10),
+               a.integer(11), a.stream(0));
 }
-int lmhead_logprob(const Args& a) {   // ..., workspace, seed, temperature, dtype, stream
+auto lmhead_logprob(const Args& a) {   // ..., workspace, seed, temperature, dtype, stream
   const at::ScalarType e = a.element(10);
-  return INVOKE(kSample, copris_lmhead_logprob, a.data(0, e), a.data(1, e), a.i64(2), a.i32(3), a.seed(8),
-                a.number(9), a.i32(4), a.f32(5), a.optional<float>(6, at::kFloat), a.data(7, at::kByte), a.numel(7),
-                a.size32(0, 0, 2), a.size32(0, 1, 2), a.size32(1, 0, 2), a.integer(10), a.stream(0));
+  return READY(kSample, copris_lmhead_logprob, a.data(0, e), a.data(1, e), a.i64(2), a.i32(3), a.seed(8),
+               a.number(9), a.i32(4), a.f32(5), a.optional<float>(6, at::kFloat), a.data(7, at::kByte), a.numel(7),
+               a.size32(0, 0, 2), a.size32(0, 1, 2), a.size32(1, 0, 2), a.integer(10), a.stream(0));
 }
-int lmhead_token_logprob(const Args& a) {   // ..., workspace, temperature, dtype, stream
+auto lmhead_token_logprob(const Args& a) {   // ..., workspace, temperature, dtype, stream
   const at::ScalarType e = a.element(7);
-  return INVOKE(kGiven, copris_lmhead_token_logprob, a.data(0, e), a.data(1, e), a.i32(2), a.number(6), a.f32(3),
-                a.optional<float>(4, at::kFloat), a.data(5, at::kByte), a.numel(5), a.size32(0, 0, 2),
-                a.size32(0, 1, 2), a.size32(1, 0, 2), a.integer(7), a.stream(0));
+  return READY(kGiven, copris_lmhead_token_logprob, a.data(0, e), a.data(1, e), a.i32(2), a.number(6), a.f32(3),
+               a.optional<float>(4, at::kFloat), a.data(5, at::kByte), a.numel(5), a.size32(0, 0, 2),
+               a.size32(0, 1, 2), a.size32(1, 0, 2), a.integer(7), a.stream(0));
 }
-int is_ratio(const Args& a) {   // ..., seq_nclip, eps_low, eps_high, stream
-  return INVOKE(kRatio, copris_is_ratio, a.f32(0), a.f32(1), a.f32(2), a.i32(3), a.i32(4),
-                a.optional<uint8_t>(5, at::kByte), a.number(11), a.number(12), a.f32(6), a.f32(7), a.f32(8), a.i32(9),
-                a.i32(10), Args::narrow(a.numel(3) - 1), a.numel(0), a.stream(3));
+auto is_ratio(const Args& a) {   // ..., seq_nclip, eps_low, eps_high, stream
+  return READY(kRatio, copris_is_ratio, a.f32(0), a.f32(1), a.f32(2), a.i32(3), a.i32(4),
+               a.optional<uint8_t>(5, at::kByte), a.number(11), a.number(12), a.f32(6), a.f32(7), a.f32(8), a.i32(9),
+               a.i32(10), Args::narrow(a.numel(3) - 1), a.numel(0), a.stream(3));
 }
-int grpo_surrogate(const Args& a) {   // ..., objective, eps_low, eps_high, stream
-  return INVOKE(kSurrogate, copris_grpo_surrogate, a.f32(0), a.f32(1), a.f32(2), a.i32(3), a.i32(4),
-                a.optional<uint8_t>(5, at::kByte), a.f32(6), a.number(12), a.number(13), a.f32(7), a.f32(8), a.f32(9),
-                a.i32(10), a.f32(11), Args::narrow(a.numel(3) - 1), a.numel(0), a.stream(11));
+auto grpo_surrogate(const Args& a) {   // ..., objective, eps_low, eps_high, stream
+  return READY(kSurrogate, copris_grpo_surrogate, a.f32(0), a.f32(1), a.f32(2), a.i32(3), a.i32(4),
+               a.optional<uint8_t>(5, at::kByte), a.f32(6), a.number(12), a.number(13), a.f32(7), a.f32(8), a.f32(9),
+               a.i32(10), a.f32(11), Args::narrow(a.numel(3) - 1), a.numel(0), a.stream(11));
 }
 
-template <int (*CALL)(const Args&), Py_ssize_t N>
+// The call itself is made with the interpreter's lock given up, as ctypes does: a launch can wait for room in the queue.
+// Asking for the lock again, Python ends a daemon's thread if the interpreter is ending, by unwinding its stack: no frame
+// from here on is noexcept or catches that.
+template <auto PREPARE, Py_ssize_t N>
 PyObject* call(PyObject*, PyObject* const* v, Py_ssize_t n) {
   if (n != N || g_raw_stream == nullptr) Py_RETURN_NONE;
+  std::optional<decltype(PREPARE(Args{v, n}))> ready;
   try {
-    return PyLong_FromLong(CALL(Args{v, n}));
+    ready.emplace(PREPARE(Args{v, n}));
+  } catch (abi::__forced_unwind&) {   // (the stream's look-up may run Python code)
+    throw;
   } catch (...) {   // (no exception of torch's leaves this module either)
     PyErr_Clear();
     Py_RETURN_NONE;
   }
+  PyThreadState* state = PyEval_SaveThread();
+  const int code = (*ready)();        // (a C entry point throws nothing)
+  PyEval_RestoreThread(state);
+  return PyLong_FromLong(code);
 }
 
 // bind(addresses of kNames, raw_stream)

@@ -141,6 +141,57 @@ def test_build_makes_the_module_beside_every_library_and_does_without_it(monkeyp
     assert not old.exists() and "Python.h" in capsys.readouterr().err
 
 
+# the module taking host tensors, and an entry point that is under way while the interpreter ends: the thread in it is a
+# daemon's, which Python ends where it asks for the interpreter's lock again
+SLOW_ENTRY = """
+#include <unistd.h>
+extern "C" __attribute__((visibility("default"))) int slow_entry(...) { usleep(400000); return 0; }
+"""
+ENDING = """
+import ctypes, importlib.machinery, importlib.util, sys, threading, time, torch
+from tests import test_binding_args as t
+path = sys.argv[1]
+loader = importlib.machinery.ExtensionFileLoader("_args", path)
+args = importlib.util.module_from_spec(importlib.util.spec_from_loader("_args", loader))
+loader.exec_module(args)
+slow = ctypes.cast(ctypes.CDLL(path).slow_entry, ctypes.c_void_p).value
+stream = lambda device: time.sleep(WAIT) or 0
+args.bind((slow,) * len(args.entry_points), stream)
+_, pos, kw = t.cases("cpu")["copris_kv_append"]
+assert args.kv_append(*pos, *kw.values(), None) == 0
+
+class Late:                      # goes when the interpreter is ending, and gives up the lock meanwhile
+    def __del__(self, sleep=time.sleep):
+        sleep(1)
+
+sys.late = Late()
+threading.Thread(target=args.kv_append, args=(*pos, *kw.values(), None), daemon=True).start()
+time.sleep(0.1)
+"""
+
+
+@pytest.fixture(scope="module")
+def host_module(tmp_path_factory):
+    with open(os.path.join(build.CSRC, "py_args.cpp")) as f:
+        source = f.read()
+    assert source.count("t.is_cuda()") == 1
+    at = tmp_path_factory.mktemp("args")
+    copy, module = str(at / "py_args.cpp"), str(at / "_args.so")
+    with open(copy, "w") as f:
+        f.write(source.replace("t.is_cuda()", "t.is_cpu()") + SLOW_ENTRY)
+    swap = {os.path.join(build.CSRC, "py_args.cpp"): copy, build.ARGS_PATH: module, "-O2": "-O1"}
+    subprocess.run([swap.get(c, c) for c in build.args_command()], check=True, capture_output=True)
+    return module
+
+
+@pytest.mark.parametrize("wait", [0, 0.4])   # in the entry point; in the look-up of the stream before it
+def test_a_thread_inside_a_call_when_the_interpreter_ends(host_module, wait):
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    done = subprocess.run([sys.executable, "-c", ENDING.replace("WAIT", str(wait)), host_module], cwd=root, capture_output=True, text=True,
+                          timeout=120)
+    assert done.returncode == 0, (done.returncode, done.stderr)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", NAMES)
 def test_same_arguments_by_both_ways(name, recorded):
