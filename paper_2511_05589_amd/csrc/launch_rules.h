@@ -242,11 +242,19 @@ COPRIS_RULE PrefillShape prefill_shape(int B, int64_t T, int Hq, int max_seqlen)
   if (units <= 512 && (launched <= 600 || 5 * launched <= 8 * units)) return kPrefill2x2;
   return units <= 2048 && units <= (units <= 1728 ? 36 : 24) * steps ? kPrefill2x4 : kPrefillWhole;
 }
-// Whether a workgroup of two units has twice two groups (eight waves, two per SIMD) instead of two.  A step then
-// takes 1.0 us instead of 0.85 and the chain has half as many; up to 12 steps the larger combination eats the gain.
-// Whole call in us, twice 2 x 2 / 2 x 2:
-//   942 + 356 tokens, 12 / 2 heads   17.4 / 20.2      1200 tokens, 12 / 2 heads   18.6 / 23.1      300 tokens, 28 / 4  11.2 / 11.2
-//   2 x 1000 tokens, 8 / 8 heads     19.7 / 22.1      2500 tokens, 6 / 2 heads    29.2 / 39.7      5 x 400 of 6 / 2    18.3 / 17.2
-COPRIS_RULE bool prefill_twice(int B, int64_t T, int max_seqlen) { return prefill_chain(B, T, max_seqlen) > 12 * 32; }
+// Whether a workgroup of two units has twice two groups (eight waves, two per SIMD) instead of two.  A step of four groups
+// takes longer and there are half as many, so that what is gained grows with the chain; what the larger combination costs
+// does not.  Up to 24 steps it costs as much or more.  Where every unit has rows of its own to copy to the pages (one
+// query head per kv head), twice the waves copy them and that line lies at 18 steps.
+// Whole call in us, twice 2 x 2 / 2 x 2, for chains of
+//              13           16           19 .. 20     22           24           26           28 .. 31     38           57           79
+//   6 / 2      11.7 / 10.9  12.3 / 11.8  13.0 / 12.7  13.8 / 13.6  14.5 / 14.4  15.1 / 15.1  15.4 / 15.7   -           22.4 / 24.6  28.5 / 32.1
+//   7 / 1      11.6 / 10.7  12.4 / 11.7  13.1 / 12.7  13.8 / 13.6  14.5 / 14.5  14.9 / 14.9  15.8 / 16.1  17.8 / 18.6  22.5 / 24.7
+//   12 / 2     11.4 / 10.5   -           13.7 / 13.3  14.0 / 13.6  14.4 / 14.3  15.1 / 15.1  15.6 / 15.8  18.2 / 19.0
+//   8 / 8      12.7 / 12.8, 19.4 / 19.0  15.9 / 16.1  15.5 / 16.1  16.3 / 17.1  16.1 / 17.1  17.4 / 18.0  19.4 / 20.3  25.3 / 26.7
+// (five sequences of 400 tokens, 6 / 2 heads; 200 .. 400 tokens x 6, 8 / 1 heads 17.0 / 13.9; 8 / 8 heads 19.4 / 19.0)
+COPRIS_RULE bool prefill_twice(int B, int64_t T, int group, int max_seqlen) {
+  return (prefill_chain(B, T, max_seqlen) + 31) / 32 > (group == 1 ? 18 : 24);
+}
 
 }  // namespace copris

@@ -545,7 +545,7 @@ int launch_prefill_attn(const void* q, const void* k, const void* v, const int32
   if (shape == kPrefill4x1) {
     COPRIS_PREFILL(prefill_attn_split4x1_kernel, 256);
   } else if (shape == kPrefill2x2) {
-    COPRIS_PREFILL(prefill_attn_split2x2_kernel, prefill_twice(B, T, max_seqlen) ? 512 : 256);
+    COPRIS_PREFILL(prefill_attn_split2x2_kernel, prefill_twice(B, T, g, max_seqlen) ? 512 : 256);
   } else if (shape == kPrefill2x4) {
     COPRIS_PREFILL(prefill_attn_split2x4_kernel, 512);
   } else {

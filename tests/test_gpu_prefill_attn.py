@@ -4,6 +4,7 @@ import pytest
 
 from paper_2511_05589_amd import workloads as W
 from tests import parity as P
+from tests.test_launch_rules import FOUR_GROUPS, TWO_GROUPS
 
 pytestmark = pytest.mark.gpu
 
@@ -112,9 +113,10 @@ def test_one_long_chain(R, Hq, Hkv, lens):
     _check_all(R, b, f"{Hq}/{Hkv} {lens}")
 
 
-@pytest.mark.parametrize("Hq,Hkv,lens", [(28, 4, [384]), (28, 4, [385]), (8, 8, [1000, 31]), (12, 2, [800, 480]), (7, 1, [1300, 700]), (5, 1, [1500, 0, 1400])])
+@pytest.mark.parametrize("Hq,Hkv,lens", FOUR_GROUPS + TWO_GROUPS)
 def test_two_units_in_four_groups(R, Hq, Hkv, lens):
-    # chains of 12 and of 13 steps, groups with fewer steps than others and without any, a second sequence of one step
+    # (which of them are in four groups: test_prefill_groups_of_two_units)  chains of 12, 13, 18, 19, 24 and 25 steps, groups with
+    # fewer steps than others and without any, a second sequence of one step
     b = W.make_prefill_case(750 + Hq + len(lens), lens, Hq, Hkv, 128, W.BF16)
     assert _kernels_of(R, R.stage_prefill_attn(b, W.BF16)) == ["prefill_attn_split2x2_kernel"]
     _check_all(R, b, f"{Hq}/{Hkv} {lens}")

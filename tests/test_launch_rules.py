@@ -42,6 +42,10 @@ int main() {
       std::scanf("%lld %lld %lld %lld", a, a + 1, a + 2, a + 3);
       std::printf("%d\n", prefill_shape(static_cast<int>(a[0]), a[1], static_cast<int>(a[2]), static_cast<int>(a[3])));
     }
+    if (!std::strcmp(name, "twice")) {
+      std::scanf("%lld %lld %lld %lld", a, a + 1, a + 2, a + 3);
+      std::printf("%d\n", prefill_twice(static_cast<int>(a[0]), a[1], static_cast<int>(a[2]), static_cast<int>(a[3])));
+    }
     if (!std::strcmp(name, "run")) {
       std::scanf("%lld %lld %lld %lld", a, a + 1, a + 2, a + 3);
       const int C = static_cast<int>(a[0]), V = static_cast<int>(a[2]);
@@ -164,6 +168,22 @@ def test_prefill_shapes(rules):
     ask = [f"prefill {len(l)} {sum(l)} {h} {b or max(l)}" for l, h, b, _ in PREFILL]
     assert [g for g, in rules(ask)] == [s for *_, s in PREFILL]
     assert rules([f"prefill 65535 {2**31 - 1} 256 {2**31 - 1}", "prefill 1 1 1 1"]) == [[WHOLE], [S4X1]]
+
+
+# (query heads, kv heads, lengths): two units per workgroup, in four groups of waves or in two
+FOUR_GROUPS = [(8, 8, [1000, 31]), (12, 2, [800, 480]), (7, 1, [1300, 700]), (5, 1, [1500, 0, 1400]), (12, 2, [769]), (8, 8, [577, 577]),
+               (6, 2, [1000, 1000]), (12, 2, [942, 356]), (8, 8, [600, 600, 600])]
+TWO_GROUPS = [(28, 4, [384]), (28, 4, [385]), (12, 2, [768]), (8, 8, [576, 576]), (6, 2, [400] * 5), (8, 1, [400, 400, 300, 300, 200, 200]),
+              (8, 8, [400, 400, 300, 300, 200, 200]), (7, 1, [600] * 3), (28, 4, [300])]
+
+
+def test_prefill_groups_of_two_units(rules):
+    cases = FOUR_GROUPS + TWO_GROUPS
+    assert rules([f"prefill {len(l)} {sum(l)} {q} {max(l)}" for q, _, l in cases]) == [[S2X2]] * len(cases)
+    got = rules([f"twice {len(l)} {sum(l)} {q // kv} {max(l)}" for q, kv, l in cases])
+    assert got == [[1]] * len(FOUR_GROUPS) + [[0]] * len(TWO_GROUPS)
+    # a bound that no sequence can have says nothing of the chain
+    assert rules(["twice 2 800 6 8192", "twice 1 800 6 8192", "twice 65535 2147483647 1 2147483647"]) == [[0], [1], [1]]
 
 
 def test_run_kernel_shapes(rules):
