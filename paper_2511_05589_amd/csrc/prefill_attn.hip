@@ -106,8 +106,17 @@ __device__ __forceinline__ void wait_loads() {   // at most N of this wave's loa
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Copying a tile's own K and V rows to the pages.  Late: where there are several groups of one or two units, those that
+// hand their states over copy while the first one combines them (whole calls 3 - 6 % shorter than with the copy before
+// the steps).  The others copy before their steps, either a row and its page's number at a time, or with all of a thread's
+// rows requested first.  Workgroups of two groups of four units copy row by row: late, up to four tiles' rows take longer than the
+// combination (8 / 8 heads, 600 x 3 tokens, bound 1200: 18.3 us late, 17.3 row by row; 12 / 2 heads, 1500 + 1400 tokens 29.0 /
+// 28.5).  Whole workgroups request all rows first where they have several tiles of their own, with one to three query
+// heads per kv head (8 / 8 heads, 450 x 8 tokens 22.6 us row by row, 20.4; 12 / 2 heads, 50 x 24 tokens 8.0 / 8.3).
+enum CopyRows { kRowByRow, kAllFirst, kLate };
+
 // GROUPS > 1: see the split kernels below.
-template <int GROUPS, int UNITS>
+template <int GROUPS, int UNITS, CopyRows COPY>
 __device__ __forceinline__ void prefill_attn_body(
     char* __restrict__ smem, const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
     const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ block_table,
@@ -169,9 +178,26 @@ __device__ __forceinline__ void prefill_attn_body(
       }
     }
   };
-  // (whole workgroups before their steps; where there are several groups, those that hand their states over copy while
-  // the first one combines them)
-  if (GROUPS == 1) copy_rows(tid, std::integral_constant<int, S::kThreads>{});
+  if constexpr (COPY == kAllFirst) copy_rows(tid, std::integral_constant<int, S::kThreads>{});
+  if constexpr (COPY == kRowByRow) {
+    for (int i4 = 0; i4 < S::kUnits; ++i4) {
+      const int u = S::kUnits * wg + i4;
+      const int ut = tile0 + u / g;
+      if (u >= units || u % g != 0 || ut >= n_tiles) continue;
+      const int32_t* bt = block_table + static_cast<size_t>(b) * max_pages;
+#pragma unroll
+      for (int j = 0; j < 2 * kStepGranules / S::kThreads; ++j) {
+        const int i = tid + j * S::kThreads, gi = i & (kStepGranules - 1);
+        const int tok = ut * kTileQ + (gi >> 4);
+        if (tok < len) {
+          const size_t src = (static_cast<size_t>(s0 + tok) * Hkv + kvh) * (kD * 2 / 16) + (gi & 15);
+          const size_t dst = (static_cast<size_t>(bt[tok / kP]) * Hkv + kvh) * kPageGranules + (gi & (kPageGranules - 1));
+          if (i < kStepGranules) k_cache[dst] = k[src];
+          else v_cache[dst] = v[src];
+        }
+      }
+    }
+  }
 
   // Q^T operands: lane (n, bq) holds Q[query n of block nb][32*kk + 8*bq .. +8]; queries past
   // the end of the sequence are zero
@@ -428,7 +454,7 @@ __device__ __forceinline__ void prefill_attn_body(
         reinterpret_cast<float2*>(mine + 16 * 64 * 16)[nb * 64 + lane] = make_float2(m_run[nb], l_run[nb]);
     }
     __syncthreads();
-    if (grp > 0) copy_rows(tid - 64 * UNITS, std::integral_constant<int, 64 * UNITS * (GROUPS - 1)>{});
+    if (COPY == kLate && grp > 0) copy_rows(tid - 64 * UNITS, std::integral_constant<int, 64 * UNITS * (GROUPS - 1)>{});
     if (grp > 0 || !computes) return;
 #pragma unroll
     for (int og = 1; og < GROUPS; ++og) {
@@ -475,6 +501,7 @@ __device__ __forceinline__ void prefill_attn_body(
 }
 
 // (two workgroups per CU: 256 registers per lane)
+template <CopyRows COPY>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_attn_kernel(
     const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
     const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ block_table,
@@ -482,7 +509,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     float* __restrict__ lse, int Hq, int Hkv, int super_tiles, int wgs_per_super, int max_pages,
     float scale_log2e) {
   __shared__ __attribute__((aligned(1024))) char smem[Shape<1, 4>::kLds];
-  prefill_attn_body<1, 4>(smem, q, k, v, cu_seqlens, block_table, k_cache, v_cache, out, lse, Hq, Hkv, super_tiles,
+  prefill_attn_body<1, 4, COPY>(smem, q, k, v, cu_seqlens, block_table, k_cache, v_cache, out, lse, Hq, Hkv, super_tiles,
                            wgs_per_super, max_pages, scale_log2e);
 }
 
@@ -491,7 +518,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // steps i, i + GROUPS, ... from a ring of its own, and the softmax states are combined at the end.
 // TWICE: with twice the threads a workgroup has twice the groups, each with half the ring (942 + 356 tokens, 12 / 2 heads:
 // 15 steps of two groups 20.7 us, 8 steps of four 17.1; see prefill_twice).
-#define COPRIS_PREFILL_SPLIT(NAME, GROUPS, UNITS, TWICE)                                                \
+#define COPRIS_PREFILL_SPLIT(NAME, GROUPS, UNITS, TWICE, COPY)                                          \
   __global__ __launch_bounds__((TWICE * Shape<GROUPS, UNITS>::kThreads))                               \
   __attribute__((amdgpu_waves_per_eu(1, 2))) void NAME(                                                \
       const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,        \
@@ -502,15 +529,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ __attribute__((aligned(1024))) char smem[Shape<GROUPS, UNITS>::kLds];                   \
     static_assert(Shape<TWICE * GROUPS, UNITS>::kLds == Shape<GROUPS, UNITS>::kLds, "one LDS for both");  \
     if (TWICE == 1 || blockDim.x == Shape<GROUPS, UNITS>::kThreads)                                    \
-      prefill_attn_body<GROUPS, UNITS>(smem, q, k, v, cu_seqlens, block_table, k_cache, v_cache, out,  \
+      prefill_attn_body<GROUPS, UNITS, COPY>(smem, q, k, v, cu_seqlens, block_table, k_cache, v_cache, out,  \
                                        lse, Hq, Hkv, super_tiles, wgs_per_super, max_pages, scale_log2e); \
     else                                                                                               \
-      prefill_attn_body<TWICE * GROUPS, UNITS>(smem, q, k, v, cu_seqlens, block_table, k_cache, v_cache, out, \
+      prefill_attn_body<TWICE * GROUPS, UNITS, COPY>(smem, q, k, v, cu_seqlens, block_table, k_cache, v_cache, out, \
                                                lse, Hq, Hkv, super_tiles, wgs_per_super, max_pages, scale_log2e); \
   }
-COPRIS_PREFILL_SPLIT(prefill_attn_split4x1_kernel, 4, 1, 1)
-COPRIS_PREFILL_SPLIT(prefill_attn_split2x2_kernel, 2, 2, 2)   // two groups, or with twice the threads four (prefill_twice)
-COPRIS_PREFILL_SPLIT(prefill_attn_split2x4_kernel, 2, 4, 1)
+COPRIS_PREFILL_SPLIT(prefill_attn_split4x1_kernel, 4, 1, 1, kLate)
+COPRIS_PREFILL_SPLIT(prefill_attn_split2x2_kernel, 2, 2, 2, kLate)   // two groups, or with twice the threads four (prefill_twice)
+COPRIS_PREFILL_SPLIT(prefill_attn_split2x4_kernel, 2, 4, 1, kRowByRow)
 #undef COPRIS_PREFILL_SPLIT
 
 }  // namespace
@@ -535,9 +562,9 @@ int launch_prefill_attn(const void* q, const void* k, const void* v, const int32
   const int super_tiles = per_wg / gcd;
   const int wgs_per_super = g * super_tiles / per_wg;
   const dim3 grid(((n_tiles_max + super_tiles - 1) / super_tiles) * wgs_per_super, Hkv, B);
-#define COPRIS_PREFILL(KERNEL, THREADS)                                                                     \
+#define COPRIS_PREFILL(KERNEL, THREADS, ...)                                                                \
   COPRIS_PRE(#KERNEL);                                                                                      \
-  hipLaunchKernelGGL(KERNEL, grid, dim3(THREADS), 0, stream, static_cast<const uint16_t*>(q),              \
+  hipLaunchKernelGGL((KERNEL __VA_ARGS__), grid, dim3(THREADS), 0, stream, static_cast<const uint16_t*>(q),              \
                      static_cast<const u32x4*>(k), static_cast<const u32x4*>(v), cu_seqlens, block_table,   \
                      static_cast<u32x4*>(k_cache), static_cast<u32x4*>(v_cache), static_cast<uint16_t*>(out), \
                      lse, Hq, Hkv, super_tiles, wgs_per_super, max_pages, scale_log2e);                     \
@@ -549,7 +576,11 @@ int launch_prefill_attn(const void* q, const void* k, const void* v, const int32
   } else if (shape == kPrefill2x4) {
     COPRIS_PREFILL(prefill_attn_split2x4_kernel, 512);
   } else {
-    COPRIS_PREFILL(prefill_attn_kernel, 256);
+    if (g < 4) {
+      COPRIS_PREFILL(prefill_attn_kernel, 256, <kAllFirst>);
+    } else {
+      COPRIS_PREFILL(prefill_attn_kernel, 256, <kRowByRow>);
+    }
   }
 #undef COPRIS_PREFILL
   return 0;
