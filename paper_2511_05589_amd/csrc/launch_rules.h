@@ -109,41 +109,61 @@ COPRIS_RULE bool lm_skinny_pays(int C, int H, int V, bool given) {
 // vocabulary rows, nothing beside a tile's sampler), or 0 where the tiles of 128 rows (two workgroups per CU, one's sampler
 // beside the other's products) are as fast.
 // 257 .. 320 rows fit one block of 320, which reads W once and multiplies no 384 or 512 columns: the run kernel, unless H
-// is short for the sampler of a tile or V for its 256 workgroups; then it takes two blocks of 160.
+// is short for the sampler of a tile or V for its 256 workgroups; then it takes two blocks of 160, or none.
 // Up to 256 rows the products are as many either way, and what decides is the rounds.  The tiles' 512 places are
 // filled unevenly where V is more than half a round (32768) beyond a whole number of rounds: some CUs have two
 // tiles, some one, and each takes as long as it does alone; the run kernel's tiles are then more than half full.  Where V is little beyond a
 // whole round the run kernel's last tile is nearly empty instead.
-// Time of the tiles over that of the run kernel, sampling (given tokens lie within 0.05 of it):
-//   one block, C = 100 / 192 / 256         V = 33500          50257          65000          70000         105000         130000
-//   H = 1024                          1.12 1.12 1.09  1.08 1.05 1.01  0.94 1.01 0.98  1.01 0.94 0.91  1.01 0.98 0.96  0.92 0.96 0.96
-//   H = 2048                          1.22 1.22 1.13  1.04 1.07 1.05  0.97 0.96 1.04  1.06 0.96 0.99  1.22 1.09 1.06  0.92 0.91 0.96
-//   H = 3584                          1.34 1.22 1.16  1.14 1.11 1.09  1.08 1.09 1.08  1.07 1.03 1.01  1.16 1.09 1.07  1.05 1.07 1.05
-//   C = 300, 320 / 2 x 160 columns         V = 16000     20000     33500     50257     70000     90000    130000
-//   H = 768                               0.74 1.04 0.91 1.15 1.06 1.04  1.03 1.01 0.93 1.02 1.00 1.01 1.13 1.02
-//   H = 1536                              0.78 1.01 1.06 1.26 1.20 1.07  1.26 1.08 1.07 1.05 1.22 1.13 1.29 1.09
-//   H = 2560                              0.81 0.99 1.18 1.32 1.33 1.13  1.38 1.15 1.18 1.09 1.35 1.15 1.41 1.13
-//   two blocks, 2 x 192 / 2 x 256 (C = 384 / 512): V = 20000 1.04 .. 1.21 / 1.04 .. 1.17 for H = 512 .. 3584; V >= 32000
-//   1.05 .. 1.09 / 1.02 .. 1.06 at H = 3584, 0.90 .. 1.03 below; C = 640, 2 x 320: 1.04 .. 1.22 at H = 2048, V >= 20000, 1.11 ..
-//   1.27 at 3584, 0.95 .. 1.14 at 1024
-//   V <= 12000, C = 150 / 192 / 220 / 256, H <= 1024: 1.02 .. 1.10 / 1.01 .. 1.06 / 1.11 .. 1.19 / 1.05 .. 1.13 (the run kernel
-//   has twice the workgroups; given tokens 0.95 .. 1.04)
+// Time of the run kernel over that of the tiles (both with what they share as it is now), sampling / given tokens:
+//   C = 65 .. 256    V = 33500          45000          50257          56000          60000
+//   H =  768   100   0.93 0.90  0.99 0.99  1.00 0.98  1.00 1.00  1.03 1.02     192  0.95 0.91  0.97 0.95  0.98 0.98  0.95 0.98  1.04 1.05
+//   H = 1024   128   0.89 0.85  0.98 0.98  1.03 1.02  1.02 1.07  1.09 1.10     192  0.89 0.86  0.94 0.90  0.99 0.92  0.98 0.99  1.02 0.98
+//   H = 1280   128   0.83 0.77  0.89 0.84  0.92 0.87  0.94 0.90  0.97 0.92     230  0.88 0.84  0.92 0.88  0.94 0.91  0.94 0.91  0.96 0.93
+//   H = 2048   100   0.83 0.80  0.95 0.95  0.97 0.96  1.00 0.99  1.01 1.00     256  0.87 0.86  0.89 0.90  0.91 0.90  0.91 0.93  0.92 0.94
+//   H = 3584   100   0.73 0.73  0.80 0.85  0.84 0.82  0.88 0.87  0.91 0.90     256  0.82 0.82  0.85 0.89  0.87 0.87  0.87 0.89  0.90 0.89
+//   V = 98305 .. 110000: H = 1536 .. 1792 0.88 .. 0.98 / 0.82 .. 0.94, but sampling with 256 rows 1.00 .. 1.05; H = 2048 0.94 .. 1.04 / 0.90 .. 1.03,
+//   H >= 3072 (.. 131072) 0.80 .. 0.99 / 0.77 .. 0.98; 160 columns, H >= 3072, V = 66000 .. 151936 0.89 .. 0.98 / 0.86 .. 0.95
+//   V <= 10000, sampling, 129 .. 256 rows: H = 64 1.00 .. 1.03, above 192 rows 0.88 .. 0.99; H = 256 0.91 .. 1.01; H = 512 .. 1024 0.87 .. 1.02
+//   (.. 12288 0.90 .. 1.00; H = 64 .. 256 0.96 .. 1.08)
+//   C = 257 .. 320   V <= 5000     10000, 15000    17000 .. 24000   28000 .. 30000   33000 .. 50257   65000          66000 .. 100000
+//   H =  384         0.95 .. 0.99  1.02 .. 1.04    0.92 .. 1.04     0.97 .. 1.05     0.93 .. 1.06    1.06 .. 1.09   0.99 .. 1.08
+//   H =  512         0.90 .. 0.98  0.99 .. 1.00    0.88 .. 0.98     0.95 .. 1.03     0.89 .. 1.02    1.04 .. 1.09   0.96 .. 1.05
+//     given          0.95 .. 1.03  1.03 .. 1.07    0.87 .. 0.96     0.99 .. 1.05     0.93 .. 1.01    1.07 .. 1.08   0.96 .. 1.01
+//   H =  768         0.94 .. 0.99  1.01 .. 1.03    0.88 .. 0.97     0.95 .. 1.01     0.92 .. 1.00    1.03           0.98 .. 1.04
+//     given          0.95 .. 1.02  1.07 .. 1.09    0.84 .. 0.94     0.94 .. 1.01     0.90 .. 0.95    0.97 .. 1.00   0.91 .. 0.98
+//   H = 1024         0.96 .. 0.98  0.99 .. 1.00    0.83 .. 0.90     0.94 .. 1.03     0.87 .. 0.96    0.86 .. 0.89   0.88 .. 1.03
+//   H = 1536         0.99 .. 1.00  1.01 .. 1.07    0.79 .. 0.90     0.90 .. 0.96     0.79 .. 0.88    0.78 .. 0.79   0.81 .. 0.95
+//   H = 3584         0.94 .. 0.99  0.98 .. 1.02    0.72 .. 0.82     0.84 .. 1.00     0.69 .. 0.80    0.71 .. 0.72   0.73 .. 0.86
+//     (V = 13238 1.11: a block of 160 leaves four waves idle in a tile of at most 128 rows)
+//     given          0.95 .. 1.02  1.00 .. 1.03    0.70 .. 0.79     0.82 .. 0.99     0.65 .. 0.76    0.63 .. 0.69   0.69 .. 0.82
+//   (one block of 320 against two of 160, over the tiles: H = 1536, V = 33500 1.20 / 1.07, V = 90000 1.22 / 1.13, V = 20000 1.06 / 1.26)
+//   C = 321 .. 512, sampling, V = 16385 .. 27000: H = 896 .. 1792 0.81 .. 1.02, H = 512 1.00 .. 1.11 at 400 rows; V = 28000 .. 30000: up to 384 rows
+//   0.95 .. 1.09, more 0.91 .. 1.03; H >= 3072 0.76 .. 1.01 at every V above 16384
+//   C = 577 .. 640, sampling, H >= 2048: 0.65 .. 1.01.  513 .. 576 rows are three row blocks of 192 to the tiles, whose 170 workgroups each
+//   have whole rounds up to V = 21760, 43520, 87040: V = 22000 .. 32700 0.69 .. 0.87, V = 33000 .. 43500 1.00 .. 1.13, V = 20000 .. 21700 0.99 .. 1.13,
+//   above 43520: H = 2048 0.91 .. 1.11 (above 87040 0.91 .. 1.03), H >= 2560 0.84 .. 0.98
 COPRIS_RULE int lm_run_width(int C, int H, int V, bool given) {
   const bool long_rows = H >= 3072;
   if (C <= kSkMaxRows || C > 640 || (given && C >= 384)) return 0;
+  if (C > 576) return H >= 2048 && V >= 20000 ? 320 : 0;
+  if (C > 512) return H >= 2048 && ((V > 21760 && V <= 32768) || (V > 43520 && H >= 2560) || V > 87040) ? 320 : 0;
   if (C > 320) {
-    const bool pays = C > 512 ? H >= 2048 && V >= 20000 : V > 16384 && (long_rows || (H >= 512 && V <= 30000));
-    return !pays ? 0 : (C <= 384 ? 192 : (C <= 512 ? 256 : 320));
+    const bool pays = V > 16384 && (long_rows || (H >= 896 && V <= (C <= 384 ? 27000 : 30000)));
+    return !pays ? 0 : (C <= 384 ? 192 : 256);
   }
   if (C > 256) {
-    if (H >= 1024 && V > (H >= 2048 ? 28672 : 32768) && (H >= 1536 || V <= 65536 || V > 84000)) return 320;
-    return H >= 768 || V <= 100000 ? 160 : 0;
+    if (V <= 16384) return !given && H >= 512 && V <= (H >= 2048 ? 10240 : 5000) ? 160 : 0;
+    if (H < 1024) return given ? (H >= 640 ? 160 : 0) : (H >= 512 && V <= 52000 ? 160 : 0);
+    return V > (H >= 2048 ? 28672 : 32768) && (H >= 1536 || V <= 65536 || V > 84000) ? 320 : 160;
   }
   const int width = C <= 128 ? 128 : (C <= 160 ? 160 : (C <= 192 ? 192 : 256));
-  if (V <= 12288) return !given && C > 128 && H <= 1024 ? width : 0;
+  if (V <= 12288) return !given && C > 128 && H <= 1024 && (H >= 512 || V <= 10000) && (H >= 256 || C > 192) ? width : 0;
   bool pays = false;
-  if (V > 32768 && V <= 65536) pays = H >= 768 && (V <= 60000 || long_rows);
-  if (V > 98304 && V <= 131072) pays = long_rows || (H >= 1536 && V <= 110000);
+  if (V > 32768 && V <= 65536) {
+    const int most = long_rows ? 65536 : (H >= 1280 || C > 192 ? 60000 : (C > 128 ? 53000 : 44000));
+    pays = H >= 768 && V <= most;
+  }
+  if (V > 98304 && V <= 131072) pays = long_rows || (H >= (given || C <= 192 ? 1536 : 2048) && V <= 110000);
   if (width == 160 && V > 65536) pays = pays || long_rows;
   return pays ? width : 0;
 }

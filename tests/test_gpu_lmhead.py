@@ -7,6 +7,7 @@ import pytest
 from oracle import copris_oracle as O
 from paper_2511_05589_amd import workloads as W
 from tests import parity as P
+from tests.test_launch_rules import RUNS
 
 pytestmark = pytest.mark.gpu
 
@@ -72,13 +73,13 @@ def test_row_blocks_of_every_width(R, C):
         np.testing.assert_allclose(lse2, lse, atol=2e-5)
 
 
-@pytest.mark.parametrize("C,H,V", [(65, 768, 32769), (128, 1024, 45003), (160, 768, 33001), (129, 3072, 32770), (192, 768, 40001),
+@pytest.mark.parametrize("C,H,V", sorted({(65, 768, 32769), (128, 1024, 45003), (160, 768, 33001), (129, 3072, 32770), (192, 768, 40001),
                                    (193, 768, 32771), (256, 768, 50257), (150, 64, 3), (256, 64, 12288), (200, 128, 8195),
                                    # two tiles per workgroup, the last of at most 128 rows and of more
                                    (130, 3072, 98307), (200, 1536, 98313), (250, 1536, 109999), (90, 3072, 120001),
                                    # 320 columns (one tile, two), two blocks of 160 (one slab per tile; more tiles), of 192, 256 and 320
                                    (257, 1024, 33001), (320, 1536, 65539), (301, 1024, 84003), (258, 64, 50257), (320, 64, 3),
-                                   (321, 512, 16385), (384, 512, 20003), (385, 512, 16387), (512, 512, 20001), (600, 2048, 20001)])
+                                   (321, 512, 16385), (384, 512, 20003), (385, 512, 16387), (512, 512, 20001), (600, 2048, 20001), *RUNS}))
 def test_runs_of_vocabulary_rows(R, C, H, V):
     inp = W.make_small_lmhead_case(C * 19 + V, C, H, V, W.BF16, w_std=0.1)
     tok, lp, lse = R.run_lmhead_logprob(inp, W.BF16)
@@ -148,7 +149,7 @@ def test_log_sum_exp_has_no_bias(R, C):
 
 # (C, H, V): together these reach every kernel, sampling and with given tokens (rows of 128 .. 320, the skinny one, the
 # 256 x 256 one with a last block of another width and without, the generic one)
-EVERY_KERNEL = [(48, 384, 65537), (20, 64, 5003), (200, 64, 20011), (200, 128, 8195), (150, 64, 8195), (300, 64, 3001), (320, 1024, 33001),
+EVERY_KERNEL = [(48, 384, 65537), (20, 64, 5003), (200, 64, 20011), (200, 128, 8195), (150, 512, 8195), (300, 512, 3001), (320, 1024, 33001),
                 (400, 64, 20011), (448, 64, 20011), (5, 72, 260)]
 
 

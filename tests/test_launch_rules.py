@@ -186,7 +186,22 @@ def test_prefill_groups_of_two_units(rules):
     assert rules(["twice 2 800 6 8192", "twice 1 800 6 8192", "twice 65535 2147483647 1 2147483647"]) == [[0], [1], [1]]
 
 
+# (rows, hidden size, vocabulary) of sampling calls: the run kernel's row blocks of every width and number; H = 64 is one
+# slab per tile, the others end in tiles of every fill
+RUNS = [(65, 768, 32769), (128, 1024, 43003), (160, 768, 33001), (129, 3072, 32770), (192, 768, 40001), (193, 768, 32771), (256, 768, 50257),
+        (150, 512, 3), (256, 64, 10000), (200, 128, 8195), (130, 3072, 98307), (200, 2048, 98313), (250, 3072, 109999), (90, 3072, 120001),
+        (257, 1024, 33001), (320, 1536, 65539), (301, 1024, 84003), (258, 512, 50257), (320, 512, 3), (321, 896, 16385), (384, 896, 20003),
+        (385, 896, 16387), (512, 896, 20001), (600, 2048, 20001), (520, 2048, 22001)]
+# measured faster, or as fast, with tiles of 128 rows
+NO_RUNS = [(257, 64, 17000, 0), (320, 384, 66000, 0), (274, 64, 17397, 1), (300, 512, 65000, 0), (300, 512, 10000, 0), (300, 1024, 10000, 1), (300, 512, 5000, 1),
+           (300, 1536, 15000, 0), (128, 1024, 50257, 0), (128, 1024, 56000, 1), (150, 1024, 59000, 0), (192, 896, 60000, 1), (256, 1536, 100000, 0),
+           (192, 64, 5000, 0), (256, 64, 12288, 0), (548, 2048, 38000, 0), (548, 2048, 66000, 0), (548, 3584, 42000, 0), (513, 3584, 20000, 0),
+           (400, 640, 17000, 0), (384, 1024, 30000, 0), (320, 3584, 13238, 0)]
+
+
 def test_run_kernel_shapes(rules):
+    assert all(w for w, _ in rules([f"run {c} {h} {v} 0" for c, h, v in RUNS]))
+    assert rules(["run %d %d %d %d" % x for x in NO_RUNS]) == [[0, 0]] * len(NO_RUNS)
     cases = [(C, H, V, g) for C in (1, 64, 65, 100, 128, 129, 160, 161, 192, 193, 256, 257, 301, 320, 321, 383, 384, 385, 512, 513,
                                     640, 641, 5000)
              for H in (64, 512, 768, 1024, 1536, 2048, 3072, 3584, 8192)
@@ -205,7 +220,7 @@ def test_run_kernel_shapes(rules):
         assert rows % 4 == 0 and parts * blocks <= 256 and parts <= -(-V // 64)
     want = {(301, 2048, 50257, 0): 320, (301, 512, 20000, 0): 160, (256, 3584, 151936, 0): 0, (256, 3584, 50257, 0): 256,
             (100, 1024, 40000, 1): 128, (100, 256, 40000, 0): 0, (150, 3584, 151936, 0): 160, (200, 512, 5000, 0): 256,
-            (200, 512, 5000, 1): 0, (384, 3584, 50257, 0): 192, (384, 3584, 50257, 1): 0, (600, 3584, 50257, 0): 320}
+            (200, 512, 5000, 1): 0, (548, 2048, 30000, 0): 320, (548, 3584, 50257, 0): 320, (300, 768, 80000, 1): 160, (384, 3584, 50257, 0): 192, (384, 3584, 50257, 1): 0, (600, 3584, 50257, 0): 320}
     for k, (width, _) in zip(want, rules(["run %d %d %d %d" % k for k in want])):
         assert width == want[k], k
 
