@@ -184,8 +184,17 @@ COPRIS_RULE int lm_run_rows(int C, int V, int width) {
 // M = 690 0.98 .. 1.03; not taken.)  The last block's lanes are then as many as make it finish with the others, by the
 // time of a whole tile relative to one of 256 columns: 0.6, 0.65 and 1.25, where the mixtures were fastest among
 // weights in steps of 0.1; a run of r rows takes its whole tiles and a part of one for the rest.
-// Full blocks only / mixed, in us: M = 777, H = 1536, V = 151936 420 / 365, H = 2048, V = 50257 200 / 171; M = 513 315 / 271;
-// M = 400 228 / 211; M = 600 325 / 305, H = 1024, V = 100000 154 / 135; M = 1290 625 / 585; M = 2100, H = 3584 2050 / 1930.
+// The estimate leaves out the start of a lane and the end of its tiles, so it is not enough by itself (time of the mixture
+// over that of full blocks only; M = 390 .. 8200, H = 64 .. 3584, V = 5003 .. 151936):
+//   lanes of one tile, before                             0.91 .. 1.17
+//   of two, and still two                                 0.92 .. 1.19; one then 0.71 .. 1.01, but 160 columns with H = 64 1.05
+//   more, 128 or 160 columns, estimated gain 3 % and more 0.77 .. 1.03
+//   more, 320 columns: H = 64 1.09 .. 1.49, H = 256 0.94 .. 1.25; H = 512 from 16 % on 0.90 .. 1.00, else 0.93 .. 1.13;
+//     H = 768 and 1024 from 7 % on 0.87 .. 1.02, else 0.97 .. 1.04, but with three or four tiles that become fewer 0.84 .. 0.99;
+//     H >= 2048 0.77 .. 1.02
+// (900 drawn calls of M = 385 .. 4250: at most 1.05, 1.00 in the middle.)
+// Full blocks only / mixed, in us: M = 777, H = 2048, V = 151936 543 / 459, H = 3584, V = 20011 139 / 113; M = 390, H = 3584, V = 100000
+// 358 / 288; M = 600, H = 256, V = 75000 43.7 / 38.7; M = 1600, H = 2048, V = 20011 136 / 124; M = 2100, H = 3584, V = 151936 2037 / 1926.
 struct LmGivenPlan {
   int full, lanes, lane_units;         // row blocks of 256, lanes of each, 64-row blocks of the vocabulary per lane
   int width, rest_lanes, rest_rows;    // columns of the last block (0: there is none), its lanes and vocabulary rows per lane
@@ -200,7 +209,7 @@ COPRIS_RULE int64_t lm_rest_cost(int rows, int width) {
   const int left = rows % 256;
   return rows / 256 * whole + (left == 0 ? 0 : (width == 128 && left <= 128 ? whole * 7 / 10 : whole));
 }
-COPRIS_RULE LmGivenPlan lm_given_plan(int M, int V) {
+COPRIS_RULE LmGivenPlan lm_given_plan(int M, int H, int V) {
   const int blocks = (M - 1) / 256 + 1, units = (V - 1) / 64 + 1, last = M - (blocks - 1) * 256;
   LmGivenPlan p = {blocks, 1, 0, 0, 0, 0};
   const int even = kLmCUs / blocks < 1 ? 1 : kLmCUs / blocks;
@@ -209,19 +218,24 @@ COPRIS_RULE LmGivenPlan lm_given_plan(int M, int V) {
   if (last > 160 || blocks > 64) return p;
   const int width = last <= 64 ? 320 : (last <= 128 ? 128 : 160);
   const int full = width == 320 ? blocks - 2 : blocks - 1;
-  int64_t best = lm_full_cost(p.lane_units) * 97;     // (a mixture has to gain three per cent)
+  LmGivenPlan mixed = p;
+  int64_t best = lm_full_cost(p.lane_units);
   for (int lanes = even; lanes * full < kLmCUs; ++lanes) {
     const int lane_units = (units + lanes - 1) / lanes, used = (units - 1) / lane_units + 1;
     const int left = kLmCUs - full * used;
     int rows = ((V - 1) / left + 4) & ~3;
     if (rows < kLmTileV) rows = kLmTileV;
-    const int64_t a = lm_full_cost(lane_units), b = lm_rest_cost(rows, width), cost = 100 * (a > b ? a : b);
+    const int64_t a = lm_full_cost(lane_units), b = lm_rest_cost(rows, width), cost = a > b ? a : b;
     if (cost < best) {
       best = cost;
-      p = {full, used, lane_units, width, (V - 1) / rows + 1, rows};
+      mixed = {full, used, lane_units, width, (V - 1) / rows + 1, rows};
     }
   }
-  return p;
+  const bool fewer_tiles = (mixed.lane_units + 3) / 4 < (p.lane_units + 3) / 4;
+  if (p.lane_units <= 8 && (!fewer_tiles || (width == 160 && H < 256))) return p;
+  int percent = 97;
+  if (width == 320) percent = H < 512 ? 0 : (H < 768 ? 84 : (H >= 2048 || (H >= 1024 && fewer_tiles && p.lane_units <= 16) ? 97 : 93));
+  return 100 * best < percent * lm_full_cost(p.lane_units) ? mixed : p;
 }
 
 // Re-prefill attention: workgroup shapes, as groups of waves per unit x units (query head, tile of 32

@@ -1870,7 +1870,7 @@ static int lm_parts(int C, int H, int V, int dtype, bool given) {
   if (const int width = lm_use_run(C, H, V, dtype, given)) return (V - 1) / lm_run_rows(C, V, width) + 1;
   if (lm_use_skinny(C, H, V, dtype, given)) return (V - 1) / lm_skinny_rows(V) + 1;
   if (lm_use_gemm(C, H, V, dtype, given)) {
-    const LmGivenPlan p = lm_given_plan(C, V);
+    const LmGivenPlan p = lm_given_plan(C, H, V);
     return p.lanes > p.rest_lanes ? p.lanes : p.rest_lanes;
   }
   const int n_tiles = (V + kMfBM - 1) / kMfBM;
@@ -1933,7 +1933,7 @@ static int launch_lmhead(const void* hidden, const void* weight, const int64_t* 
 #undef COPRIS_LM_RUN
     COPRIS_POST("lmhead_run_kernel");
   } else if (lm_use_gemm(C, H, V, dtype, given)) {
-    const LmGivenPlan p = lm_given_plan(C, V);
+    const LmGivenPlan p = lm_given_plan(C, H, V);
     if (p.width == 0) {
       COPRIS_PRE("lmhead_gemm_given_kernel");
       hipLaunchKernelGGL(lmhead_gemm_given_kernel, dim3(p.full, p.lanes), dim3(512), 0, stream,

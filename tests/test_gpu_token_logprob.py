@@ -6,6 +6,7 @@ import pytest
 
 from paper_2511_05589_amd import workloads as W
 from tests import parity as P
+from tests.test_launch_rules import MIXED
 
 pytestmark = pytest.mark.gpu
 
@@ -51,9 +52,9 @@ def test_runs_that_end_inside_a_tile(R, M, H, V):
 
 
 @pytest.mark.parametrize("M,H,V", [(400, 64, 20011), (400, 128, 32771), (416, 64, 20011), (513, 192, 24001), (576, 64, 50257),
-                                   (600, 64, 24001), (1050, 64, 20011)])
+                                   (600, 64, 24001), (1050, 64, 20011), *MIXED])
 def test_a_last_row_block_of_another_width(R, M, H, V):
-    # 128, 160 and 320 columns, a few rows of the last block and all of them
+    # (MIXED) 128, 160 and 320 columns, a few rows of the last block and all of them; full blocks only
     h, w, tok = _case(M * 7 + V, M, H, V, W.BF16, w_std=0.1)
     tok[-1], tok[-2] = 0, V - 1
     lp, lse = R.run_token_logprob(h, w, tok, 1.0, W.BF16)
