@@ -53,9 +53,10 @@ COPRIS_RULE int attn_most_waves(int64_t capacity, int group) {
 // 128) multiplied instead of 256.  Where it does not, evenly shared rows only leave the last block's
 // waves as long an epilogue as the others', so the blocks are full and the last one takes the rest.
 // Whole sampling calls in us, blocks of 256 / shared evenly:
-//   C = 301, H = 2048, V = 50257   130.0 / 121.8      C = 400, H = 2048, V = 50257   139.3 / 146.4
-//   C = 384, H = 1024, V = 32000    49.2 /  46.4      C = 580, H = 2048, V = 12800    66.7 /  72.3
-//   C = 160, H = 3584, V = 33000   101.1 /  94.0      C = 400, H = 1024, V = 32000    51.5 /  53.2
+//   C = 330, H = 2048, V = 50257   130.3 / 116.8      C = 400, H = 2048, V = 50257   139.3 / 146.4
+//   C = 384, H = 1024, V = 40000    66.5 /  59.6      C = 580, H = 2048, V = 12800    66.7 /  72.3
+//   C = 160, H = 3584, V = 30000    68.1 /  57.2      C = 400, H = 1024, V = 32000    51.5 /  53.2
+//   C = 160, H = 2048, V = 151936  169.5 / 153.3      C = 540, H = 1024, V = 40000    85.9 /  73.5
 COPRIS_RULE int lm_row_blocks(int C) { return (C + 255) / 256; }
 COPRIS_RULE int lm_block_rows(int C) {
   const int blocks = lm_row_blocks(C), even = ((C + blocks - 1) / blocks + 31) & ~31;
@@ -71,10 +72,10 @@ COPRIS_RULE int lm_block_width(int C) {
 // tiles p, p + 256, ...  Where at most half of the places have a tile more than the rest, the second block
 // counts its places from the end (place = i ^ flip), so that no CU has two workgroups with the tile more.
 // Where more have it, some CUs get two anyway, and the blocks no longer read the same rows of W at the same
-// time: C = 301, H = 2048, dealt alike / from both ends: V = 33000 (2 of 256 places) 114.1 / 100.9 us,
-// V = 100000 (14) 236.7 / 222.2, V = 40000 (57) 117.0 / 106.5, V = 50257 (137) 122.4 / 126.3,
-// V = 151936 (163) 313.2 / 315.4, V = 65000 (252) 133.9 / 136.4.  With more row blocks other workgroups
-// meet: C = 768, H = 1024, V = 32000 83.6 / 90.7.
+// time: C = 330, H = 2048, dealt alike / from both ends: V = 33000 (2 of 256 places) 110.3 / 99.2 us,
+// V = 100000 (14) 224.6 / 210.9, V = 40000 (57) 112.3 / 101.0, V = 45000 (96) 114.1 / 103.8, V = 50257 (137) 117.7 / 121.6,
+// V = 151936 (163) 294.9 / 298.7, V = 65000 (252) 126.6 / 129.9.  (H = 512 and C = 400, 512 alike; given tokens with H = 256 gain nothing: 23.1
+// from both ends, 22.0.)  With more row blocks other workgroups meet: C = 768, H = 1024, V = 32000 83.6 / 90.7.
 COPRIS_RULE int lm_second_block_flip(int C, int n_tiles, int n_parts) {
   const int more = n_tiles % n_parts;
   return lm_row_blocks(C) == 2 && n_parts == 256 && more > 0 && more <= 128 ? 255 : 0;
@@ -250,19 +251,22 @@ COPRIS_RULE LmGivenPlan lm_given_plan(int M, int H, int V) {
 // groups of four units also beyond while the chain is long for the units: 36 units per step (24 of many).
 // Where more than 100 units per step of the chain (250 of a chain that is known, one sequence) are launched for
 // nothing, whole workgroups lose least.
-// Whole call in us, whole / 4 x 1 / 2 x 2 (two groups only, see prefill_twice) / 2 x 4:
-//   600 tokens, 12 / 2 heads (228 units)              17.4 / 12.8 / 15.0 / 16.4
-//   2 x 700 tokens, 8 / 8 heads (360)                 22.1 / 24.8 / 18.5 / 18.6
-//   926 + 439 tokens, 8 / 8 heads (352, 464 launched) 26.7 / 24.3 / 20.9 / 22.4
+// Whole call in us, whole / 4 x 1 / 2 x 2 (two or four groups, by prefill_twice) / 2 x 4:
+//   600 tokens, 12 / 2 heads (228 units)              17.2 / 12.4 / 12.5 / 16.3
+//   2 x 700 tokens, 8 / 8 heads (360)                 20.5 / 23.2 / 15.5 / 18.2
+//   926 + 439 tokens, 8 / 8 heads (352, 464 launched) 25.2 / 22.5 / 17.6 / 21.9
 //   2 x 1000 tokens, 8 / 8 heads, bound 2000 (512, 1008 launched)
-//                                                     28.4 / 34.1 / 42.1 / 23.8
-//   4000 tokens, 12 / 2 heads (1512)                  85.7 /   -  /   -  / 61.9
-//   1500 + 200 + 100 tokens, 28 / 4 heads (1652)      47.8 /   -  /   -  / 39.6
-//   2000 tokens, 28 / 4 heads (1764)                  52.9 /   -  /   -  / 55.4
-//   4 x 900 tokens, 12 / 2 heads (1392)               31.5 /   -  /   -  / 33.7
-//   8 x 200 tokens, 12 / 2 heads (696)                11.1 /   -  / 16.8 / 12.1
-//   30 x 60 tokens, 12 / 2 heads, bound 4096          45.0 / 99.0 / 76.3 / 81.0
-//   2 x 500 tokens, 8 / 8 heads, bound 8192           27.2 / 30.2 / 30.4 / 33.4
+//                                                     26.9 / 32.3 / 31.5 / 23.1
+//   4000 tokens, 12 / 2 heads (1512)                  84.6 /   -  / 77.4 / 62.1
+//   1500 + 200 + 100 tokens, 28 / 4 heads (1652)      46.9 /   -  / 51.4 / 39.4
+//   2000 tokens, 28 / 4 heads (1764)                  52.4 /   -  / 62.8 / 55.3
+//   4 x 900 tokens, 12 / 2 heads (1392)               31.0 /   -  / 38.8 / 33.5
+//   8 x 200 tokens, 12 / 2 heads (696)                10.7 / 22.2 / 15.1 / 11.8
+//   30 x 60 tokens, 12 / 2 heads, bound 4096          44.4 / 93.3 / 73.5 / 80.3
+//   2 x 500 tokens, 8 / 8 heads, bound 8192           26.2 / 28.5 / 28.0 / 33.5
+// The line at 512 units is where two groups of two units and two of four cross; with four groups it lies higher where the
+// chain is long: 2 x 700 tokens, 12 / 2 heads (540) 15.1 / 18.0, 1500 + 1400, 6 / 2 (552) 22.1 / 28.3, 2500, 8 / 1 (632) 29.0 / 40.5,
+// 5000, 6 / 2 (942) 57.8 / 72.6, but 1000 tokens, 28 / 4 heads (896) 28.0 / 22.6.
 COPRIS_RULE int64_t prefill_chain(int B, int64_t T, int max_seqlen) {
   return max_seqlen <= T ? max_seqlen : (B == 1 ? T : T / B);
 }
@@ -277,8 +281,8 @@ COPRIS_RULE PrefillShape prefill_shape(int B, int64_t T, int Hq, int max_seqlen)
   return units <= 2048 && units <= (units <= 1728 ? 36 : 24) * steps ? kPrefill2x4 : kPrefillWhole;
 }
 // Whether a workgroup of two units has twice two groups (eight waves, two per SIMD) instead of two.  A step of four groups
-// takes longer and there are half as many, so that what is gained grows with the chain; what the larger combination costs
-// does not.  Up to 24 steps it costs as much or more.  Where every unit has rows of its own to copy to the pages (one
+// takes 1.1 us instead of 0.7 and there are half as many, so that what is gained grows with the chain; what the larger
+// combination costs does not.  Up to 24 steps it costs as much or more.  Where every unit has rows of its own to copy to the pages (one
 // query head per kv head), twice the waves copy them and that line lies at 18 steps.
 // Whole call in us, twice 2 x 2 / 2 x 2, for chains of
 //              13           16           19 .. 20     22           24           26           28 .. 31     38           57           79

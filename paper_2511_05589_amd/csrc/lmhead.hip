@@ -324,7 +324,7 @@ __device__ __forceinline__ void lm_mask_block(f32x16& acc, int vbase, int V) {
     if (vbase + 8 * (r >> 2) + (r & 3) >= V) acc[r] = -INFINITY;
 }
 
-// The sampler: 25 vector instructions per entry (of a Philox block's 95, 18 are 64-bit multiplications and 19
+// The sampler: 25 vector instructions per entry (of a Philox block's 99, 18 are 64-bit multiplications and 19
 // three-input exclusive ors).  It is bound by their number: two waves of a SIMD issue one each in turn.  35 instructions
 // (exclusive ors by pairs, the uniform through a conversion, the temperature and the base of the exponential
 // multiplied apart, a mask test per entry) against 24 (see above) took 171 cycles per entry and SIMD where nothing else ran; whole calls
@@ -1387,10 +1387,10 @@ __device__ __forceinline__ void lm_gemm_given_body(
 // columns (SPLIT; 0.7 of a whole tile's time, 1.1 with four idle waves).
 // The sampler follows a tile's last slab; the rows' states stay in the lanes where registers allow it, else
 // they go to one thread per batch row through the slot of the tile's last hidden slab.
-// Whole sampling calls in us, before (tiles of 128 rows) / now:
-//   C = 301, H = 2048, V = 50257    121.7 /  87.0       C = 320, H = 3584, V = 151936   499.7 / 365.3
-//   C = 160, H = 3584, V =  45000    96.7 /  78.6       C = 100, H = 3584, V =  50257    83.4 /  71.3
-//   C = 256, H = 2048, V =  50257    79.9 /  76.3       C = 300, H = 2560, V =  20000    77.2 /  58.5
+// Whole sampling calls in us, tiles of 128 rows / run kernel:
+//   C = 280, H = 2048, V = 50257    113.3 /  85.1       C = 320, H = 3584, V = 151936   485.4 / 352.3
+//   C = 160, H = 3584, V =  45000    98.5 /  75.2       C = 100, H = 3584, V =  50257    83.2 /  69.8
+//   C = 256, H = 2048, V =  50257    79.9 /  72.4       C = 320, H = 1536, V =  20000    50.0 /  40.4
 // --------------------------------------------------------------------------
 constexpr int kRunBM = 256;                           // vocabulary rows per tile, 32 per wave
 constexpr int kRunSlab = kRunBM * kMfBK * 2;          // 32 KB: a slab of W

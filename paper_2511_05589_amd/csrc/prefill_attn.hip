@@ -514,10 +514,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // The same for calls that do not fill the chip.  What counts there is the longest chain of steps
-// (0.65 .. 1 us each), so the waves of a workgroup are several groups on the same units: group i takes the
+// (0.7 us each; 1.1 where two waves share a SIMD), so the waves of a workgroup are several groups on the same units: group i takes the
 // steps i, i + GROUPS, ... from a ring of its own, and the softmax states are combined at the end.
-// TWICE: with twice the threads a workgroup has twice the groups, each with half the ring (942 + 356 tokens, 12 / 2 heads:
-// 15 steps of two groups 20.7 us, 8 steps of four 17.1; see prefill_twice).
+// TWICE: with twice the threads a workgroup has twice the groups, each with half the ring (2500 tokens, 6 / 2 heads: 40
+// steps of two groups 32.1 us, 20 of four 28.5; 942 + 356 tokens, 12 / 2 heads: 15 of two 16.4, 8 of four 16.2; see prefill_twice).
 #define COPRIS_PREFILL_SPLIT(NAME, GROUPS, UNITS, TWICE, COPY)                                          \
   __global__ __launch_bounds__((TWICE * Shape<GROUPS, UNITS>::kThreads))                               \
   __attribute__((amdgpu_waves_per_eu(1, 2))) void NAME(                                                \

@@ -203,3 +203,15 @@ def oracle_prefill_rows(b, dtype, seq_tok, kc, vc):
     rows = cu[seqs] + toks
     out, lse = O.decode_attn(q[rows], kc, vc, np.asarray(b["block_table"])[seqs], toks + 1, b["scale"])
     return rows, out, lse
+
+
+# ---- which kernels a call launches ---------------------------------------------
+def kernels_of(call):
+    """(what call() returns, the names of the kernels that it launched)"""
+    from paper_2511_05589_amd import binding
+    names = []
+    binding.set_launch_hook(lambda kernel, phase, stream, user: names.append(kernel.decode()) if phase == 0 else None)
+    try:
+        return call(), names
+    finally:
+        binding.set_launch_hook(None)

@@ -82,7 +82,9 @@ def test_row_blocks_of_every_width(R, C):
                                    (321, 512, 16385), (384, 512, 20003), (385, 512, 16387), (512, 512, 20001), (600, 2048, 20001), *RUNS}))
 def test_runs_of_vocabulary_rows(R, C, H, V):
     inp = W.make_small_lmhead_case(C * 19 + V, C, H, V, W.BF16, w_std=0.1)
-    tok, lp, lse = R.run_lmhead_logprob(inp, W.BF16)
+    (tok, lp, lse), kernels = P.kernels_of(lambda: R.run_lmhead_logprob(inp, W.BF16))
+    if (C, H, V) in RUNS:
+        assert kernels == ["lmhead_run_kernel", "lmhead_merge_kernel"]
     # every row's log-sum-exp and log-prob follow from the logits; tokens are checked on a sample of rows (the noise
     # of a row is V numbers)
     rows = np.unique(np.concatenate([np.arange(0, C, max(1, C // 12)), [C - 1]]))
