@@ -160,7 +160,7 @@ int copris_decode_attn(const void* q, const void* k_cache, const void* v_cache,
  *   out  [T, Hq, D]  dtype        lse [T, Hq] fp32 or NULL
  *   max_seqlen  an upper bound of the sequence lengths (sizes the launch: a loose one costs time)
  *
- * Every call gives the same bits for the same arguments.  B, T, Hq and max_seqlen decide how the keys of a
+ * Every call gives the same bits for the same arguments.  B, T, Hq, Hkv and max_seqlen decide how the keys of a
  * query are shared out and summed, so a sequence's out and lse may differ in their last bits between
  * batches, or with another max_seqlen; the pages do not.
  *

@@ -418,4 +418,39 @@ COPRIS_RULE PrefillShape prefill_shape(int B, int64_t T, int Hq, int max_seqlen)
   return best;
 }
 
+// Sums that the keys of a query are shared out to, step i to sum i % sums, each with a softmax reference of its own: 4, 2 or 1.
+// The weights are rounded to bf16 against their sum's reference, so the sums decide the result, and more of them, whose references lie
+// nearer to their weights, are more exact (1e-3 of the result, its own rounding being 1.6; 1 / 2 / 4 sums):
+//   100 tokens 1.89 / 1.85 / 1.84     300 2.00 / 1.96 / 1.92     900 2.08 / 2.03 / 1.99     2500 2.10 / 2.07 / 2.03
+// They do not follow the workgroup's shape, which is chosen for its time: a shape with fewer groups of waves than sums keeps several
+// per wave (prefill_plan), one with more has as many as groups.  The lines are where two and four groups of waves paid when each had a CU's
+// whole chain to itself; moving them changes results.
+COPRIS_RULE int prefill_sums(int B, int64_t T, int Hq, int group, int max_seqlen) {
+  const int64_t units = (T / 32 + B) * Hq;
+  const int64_t launched = ((static_cast<int64_t>(max_seqlen) + 31) / 32) * B * Hq;
+  const int64_t steps = (prefill_chain(B, T, max_seqlen) + 31) / 32;
+  if (launched - units > (B == 1 ? 250 : 100) * steps) return 1;
+  if (units <= 256 && launched <= 512) return 4;
+  if (units <= 512 && (launched <= 600 || 5 * launched <= 8 * units)) return steps > (group == 1 ? 18 : 24) ? 4 : 2;
+  return units <= 2048 && units <= (units <= 1728 ? 36 : 24) * steps ? 2 : 1;
+}
+
+// The shape of prefill_shape, unless its waves cannot hold the sums: two states of 32 queries do not fit a wave's registers, nor do
+// four of 16 (one sequence of 151 tokens, 32 / 4 heads: 9.4 us with spills, 8.0 as 2 x 2).  A second state costs up to 0.8 us (two
+// sequences of 942 + 356 tokens, 12 / 2 heads: 15.7 / 16.5 us; 172 + 115, 16 / 4: 7.7 / 8.0).
+struct PrefillPlan {
+  PrefillShape shape;
+  int sums;                            // of a wave
+};
+COPRIS_RULE PrefillPlan prefill_plan(int B, int64_t T, int Hq, int group, int max_seqlen) {
+  const int64_t most_steps = ((max_seqlen < T ? max_seqlen : T) + 31) / 32;
+  int sums = prefill_sums(B, T, Hq, group, max_seqlen);
+  while (sums > 1 && sums / 2 >= most_steps) sums /= 2;                    // (the others would stay empty)
+  PrefillShape shape = prefill_shape(B, T, Hq, max_seqlen);
+  if (shape == kPrefillWhole && sums > 1) shape = kPrefillHalf;
+  if (shape == kPrefillHalf && sums > 2) shape = kPrefill2x2;
+  const int groups = kPrefillCost[shape].groups;
+  return {shape, sums > groups ? sums / groups : 1};
+}
+
 }  // namespace copris

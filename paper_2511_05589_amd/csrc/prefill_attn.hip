@@ -62,16 +62,17 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kSlack = 6.0f;   // scores may exceed the softmax reference by 2^kSlack
 constexpr float kBig = 64.0f;    // = 2^kSlack
 
-// A workgroup is GROUPS groups of UNITS waves, one unit (query head, tile of 16 * NB query tokens) per wave of a group.
-template <int GROUPS, int UNITS, int NB> struct Shape {
+// A workgroup is GROUPS groups of UNITS waves, one unit (query head, tile of 16 * NB query tokens) per wave of a group; a wave
+// keeps SUMS softmax states, step i of its group in state i % SUMS.
+template <int GROUPS, int UNITS, int NB, int SUMS> struct Shape {
   static constexpr int kTileQ = 16 * NB;
   static constexpr int kUnits = UNITS;
   static constexpr int kThreads = 64 * GROUPS * UNITS;
   static constexpr int kRows = kStepTok / kUnits;          // K and V rows of a step that a wave fetches
   static constexpr int kGroupLds = 2 * kRing * kHalfBytes;
-  static constexpr int kState = NB * (8 * 64 * 16 + 64 * 8); // bytes of a wave's softmax state: O, then (m, l)
-  static constexpr int kRings = GROUPS * kGroupLds, kStates = GROUPS == 1 ? 0 : GROUPS * UNITS * kState;
-  static constexpr int kLds = kRings > kStates ? kRings : kStates;   // 64 KB (two workgroups per CU), 128 .. 136 KB or all 160 KB
+  static constexpr int kState = NB * (8 * 64 * 16 + 64 * 8); // bytes of a softmax state of a wave: O, then (m, l)
+  static constexpr int kRings = GROUPS * kGroupLds, kStates = GROUPS == 1 ? 0 : GROUPS * UNITS * SUMS * kState;
+  static constexpr int kLds = kRings > kStates ? kRings : kStates;   // 64 KB (two workgroups per CU); two groups: 128 KB, or 136
 };
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -204,14 +205,14 @@ __device__ __forceinline__ Place place_flat(const int32_t* __restrict__ cu_seqle
   return p;
 }
 
-template <int GROUPS, int UNITS, int NB>
+template <int GROUPS, int UNITS, int NB, int SUMS>
 __device__ __forceinline__ void prefill_attn_body(
     char* __restrict__ smem, const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
     const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ block_table,
     u32x4* __restrict__ k_cache, u32x4* __restrict__ v_cache, uint16_t* __restrict__ out,
     float* __restrict__ lse, PrefillGrid pg, int Hq, int Hkv, int max_pages,
     float scale_log2e) {
-  using S = Shape<GROUPS, UNITS, NB>;
+  using S = Shape<GROUPS, UNITS, NB, SUMS>;
   constexpr int kTileQ = S::kTileQ, kProducts = 8 * NB;     // products of a step's scores: pages x blocks x 4
   const int g = static_cast<int>(pg.group.d);
   const Place at = pg.flat ? place_flat<S>(cu_seqlens, pg) : place_grid<S>(cu_seqlens, pg);
@@ -312,14 +313,17 @@ __device__ __forceinline__ void prefill_attn_body(
       v_off[dt] = ring0 + kRing * kHalfBytes + swz_v(vrow, 2 * dt + ((n & 3) >> 1)) * 16 + (n & 1) * 8;
   }
 
-  float m_run[NB], l_run[NB];
-  f32x4 o[NB][8];
+  struct State {
+    float m[NB], l[NB];
+    f32x4 o[NB][8];
+  } state[SUMS];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    m_run[nb] = -INFINITY;
-    l_run[nb] = 0.0f;
+  for (int e = 0; e < SUMS * NB; ++e) {
+    State& st = state[e / NB];
+    st.m[e % NB] = -INFINITY;
+    st.l[e % NB] = 0.0f;
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) o[nb][dt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int dt = 0; dt < 8; ++dt) st.o[e % NB][dt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
 
   // K rows of a step as the A operand (token = lane & 15), read once for both query blocks: a page's
@@ -351,8 +355,8 @@ __device__ __forceinline__ void prefill_attn_body(
   // wave's last step; it carries the causal mask and the end of the sequence (a block whose queries all lie before a
   // page's tokens is fully masked there: its weights are exp2(-inf - m) = 0).
   // (k_fill, v_fill: the ring buffers that the step's requests fill; V's go out first.)
-  auto compute = [&](const int i, const int k_slot, const int v_slot, const int k_fill, const int v_fill, auto lastc, auto kslotc,
-                     auto vslotc) __attribute__((always_inline)) {
+  auto compute = [&](const int i, State& st, const int k_slot, const int v_slot, const int k_fill, const int v_fill, auto lastc,
+                     auto kslotc, auto vslotc) __attribute__((always_inline)) {
     constexpr bool kLast = decltype(lastc)::value;
     BufferRsrc rsrc;
     // the step's requests, spread over eight places
@@ -400,7 +404,7 @@ __device__ __forceinline__ void prefill_attn_body(
     float w[NB][kSubs][4], add[NB];
     auto weight = [&](const int e) __attribute__((always_inline)) {
       const int nb = e >> 3, sub = (e >> 2) & 1, rr = e & 3;
-      w[nb][sub][rr] = __builtin_amdgcn_exp2f(__builtin_fmaf(t[sub][nb][rr], scale_log2e, -m_run[nb]));
+      w[nb][sub][rr] = __builtin_amdgcn_exp2f(__builtin_fmaf(t[sub][nb][rr], scale_log2e, -st.m[nb]));
     };
     auto sum = [&](const int nb) __attribute__((always_inline)) {
       add[nb] = ((w[nb][0][0] + w[nb][0][1]) + (w[nb][0][2] + w[nb][0][3])) +
@@ -430,13 +434,13 @@ __device__ __forceinline__ void prefill_attn_body(
         mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
         // only a query whose own scores outgrew its reference moves it, so a query's
         // arithmetic does not depend on the other queries of the wave
-        const float m_new = (mx > m_run[nb] + kSlack) ? mx : m_run[nb];
-        alpha[nb] = __builtin_amdgcn_exp2f(m_run[nb] - m_new);
-        m_run[nb] = m_new;
-        l_run[nb] *= alpha[nb];
+        const float m_new = (mx > st.m[nb] + kSlack) ? mx : st.m[nb];
+        alpha[nb] = __builtin_amdgcn_exp2f(st.m[nb] - m_new);
+        st.m[nb] = m_new;
+        st.l[nb] *= alpha[nb];
       }
 #pragma unroll
-      for (int e = 0; e < 8 * NB; ++e) o[e >> 3][e & 7] *= alpha[e >> 3];
+      for (int e = 0; e < 8 * NB; ++e) st.o[e >> 3][e & 7] *= alpha[e >> 3];
 #pragma unroll
       for (int e = 0; e < kProducts; ++e) weight(e);
 #pragma unroll
@@ -447,7 +451,7 @@ __device__ __forceinline__ void prefill_attn_body(
     bf16x8 pf[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      l_run[nb] += add[nb];
+      st.l[nb] += add[nb];
       pf[nb] = __builtin_bit_cast(
           bf16x8, u32x4{pack_bf16x2(w[nb][0][0], w[nb][0][1]), pack_bf16x2(w[nb][0][2], w[nb][0][3]),
                         pack_bf16x2(w[nb][1][0], w[nb][1][1]), pack_bf16x2(w[nb][1][2], w[nb][1][3])});
@@ -462,7 +466,7 @@ __device__ __forceinline__ void prefill_attn_body(
       const s16x8 vv = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
       const bf16x8 va = __builtin_bit_cast(bf16x8, vv);
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) o[nb][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pf[nb], o[nb][dt], 0, 0, 0);
+      for (int nb = 0; nb < NB; ++nb) st.o[nb][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pf[nb], st.o[nb][dt], 0, 0, 0);
       if (!kLast && dt < 4) read_k(kf, dt, kslotc, k_slot);
       if (!kLast) request(dt);
       __builtin_amdgcn_sched_barrier(0);
@@ -478,7 +482,7 @@ __device__ __forceinline__ void prefill_attn_body(
   // A group's steps: `steps` in all, of which this wave computes the first `mine`.
   const int steps = last_step / GROUPS + 1;
   const int mine = computes && own_step >= grp ? (own_step - grp) / GROUPS + 1 : 0;
-  // In step i the rows of V(i + kRingV - 1) and K(i + kRingK + 1) are requested, in this order, into the buffers of
+  // In step i the rows of V(i + kRing - 1) and K(i + kRing + 1) are requested, in this order, into the buffers of
   // V(i - 1) and K(i + 1), which every wave has read before the barrier that precedes step i; behind that barrier
   // V(i) and K(i + 2) have landed.  A wave's loads complete in issue order.
   auto wait_next = [&]() __attribute__((always_inline)) {
@@ -557,11 +561,11 @@ __device__ __forceinline__ void prefill_attn_body(
   int i = 0;
   auto fixed = [&](auto pc) __attribute__((always_inline)) {
     constexpr int p = decltype(pc)::value;
-    compute(i + p, 0, 0, (p + 1) % kRing, (p + 3) % kRing, std::false_type{}, std::integral_constant<int, (p + 2) % kRing>{},
-            std::integral_constant<int, p>{});
+    compute(i + p, state[p % SUMS], 0, 0, (p + 1) % kRing, (p + 3) % kRing, std::false_type{},
+            std::integral_constant<int, (p + 2) % kRing>{}, std::integral_constant<int, p>{});
     wait_next();
   };
-  static_assert(kRing == 4, "the steps below");
+  static_assert(kRing == 4 && kRing % SUMS == 0, "the steps below");
   for (; i + 4 < mine; i += 4) {
     fixed(std::integral_constant<int, 0>{});
     fixed(std::integral_constant<int, 1>{});
@@ -569,9 +573,14 @@ __device__ __forceinline__ void prefill_attn_body(
     fixed(std::integral_constant<int, 3>{});
   }
   auto slot = [&](const int of) __attribute__((always_inline)) { return of & (kRing - 1); };
-  for (; i + 1 < mine; ++i) {
-    compute(i, slot(i + 2), slot(i), slot(i + 1), slot(i + 3), std::false_type{}, kAny, kAny);
-    wait_next();
+  while (i + 1 < mine) {
+#pragma unroll
+    for (int e = 0; e < SUMS; ++e) {                     // (i % SUMS == e)
+      if (e > 0 && i + 1 >= mine) break;
+      compute(i, state[e], slot(i + 2), slot(i), slot(i + 1), slot(i + 3), std::false_type{}, kAny, kAny);
+      wait_next();
+      ++i;
+    }
   }
   auto fetch_step = [&]() __attribute__((always_inline)) {
     fetch_v(slot(i + 3));
@@ -580,7 +589,9 @@ __device__ __forceinline__ void prefill_attn_body(
   if (i < mine) {
     const bool more = i + 1 < steps;         // another wave has further steps
     if (more) fetch_step();
-    compute(i, 0, slot(i), 0, 0, std::true_type{}, kAny, kAny);
+#pragma unroll
+    for (int e = 0; e < SUMS; ++e)
+      if (SUMS == 1 || i % SUMS == e) compute(i, state[e], 0, slot(i), 0, 0, std::true_type{}, kAny, kAny);
     if (more) wait_next();
     ++i;
   }
@@ -607,76 +618,108 @@ __device__ __forceinline__ void prefill_attn_body(
       lse[static_cast<size_t>(s0 + tq) * Hq + head] = (m + __builtin_amdgcn_logf(l)) * kLn2;
     return 1.0f / l;
   };
+  // The states of a query's keys are put together in the order of their first steps.  One without a step (m = -inf) would weigh
+  // 0 and is passed over; the first has seen token 0, so the common reference is finite.
+  auto weights = [](float& m, float& l, const float m1, const float l1, float& w0, float& w1) __attribute__((always_inline)) {
+    const float m_all = fmaxf(m, m1);
+    w0 = __builtin_amdgcn_exp2f(m - m_all);
+    w1 = __builtin_amdgcn_exp2f(m1 - m_all);
+    m = m_all;
+    l = __builtin_fmaf(w0, l, w1 * l1);
+  };
+  auto mix = [](f32x4& x, const float w0, const float w1, const f32x4& y) __attribute__((always_inline)) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = __builtin_fmaf(w0, x[r], w1 * y[r]);
+  };
   if constexpr (GROUPS == 1) {
     if (!computes) return;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const float inv = finish(nb, m_run[nb], l_run[nb]);
+      State& all = state[0];
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) store(nb, dt, o[nb][dt], inv);
+      for (int e = 1; e < SUMS; ++e) {
+        if (e > own_step) break;
+        float w0, w1;
+        weights(all.m[nb], all.l[nb], state[e].m[nb], state[e].l[nb], w0, w1);
+#pragma unroll
+        for (int dt = 0; dt < 8; ++dt) mix(all.o[nb][dt], w0, w1, state[e].o[nb][dt]);
+      }
+      const float inv = finish(nb, all.m[nb], all.l[nb]);
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) store(nb, dt, all.o[nb][dt], inv);
     }
   } else {
-    // The softmax states of a unit's groups are put together by all of its waves, each an equal part of the head dimension (by
-    // the first group's alone it took 128 vector instructions per other group, 1.3 us for four).  A group without a step has
-    // m = -inf and weighs 0 (the first group has seen token 0, so the common reference is finite).
-    constexpr int kDt = 8 / GROUPS;
+    // ... by all waves of a unit, each an equal part of the head dimension (by the first group's alone it took 128 vector
+    // instructions per other group of 32 queries, 1.3 us for four): a wave hands the others their parts of its states, and all of
+    // its (m, l).  State a of the unit is state a / GROUPS of group a % GROUPS.
+    constexpr int kDt = 8 / GROUPS, kAll = GROUPS * SUMS;
     __syncthreads();                       // every load has landed and every buffer has been read
-    char* const states = smem + wave * GROUPS * S::kState;
-    char* const mine_at = states + grp * S::kState;
-    if (computes) {
+    char* const states = smem + wave * kAll * S::kState;
+    auto hand = [&](auto group) __attribute__((always_inline)) {
+      constexpr int G = decltype(group)::value;
 #pragma unroll
-      for (int e = 0; e < 8 * NB; ++e)
-        reinterpret_cast<float4*>(mine_at)[e * 64 + lane] =
-            make_float4(o[e >> 3][e & 7][0], o[e >> 3][e & 7][1], o[e >> 3][e & 7][2], o[e >> 3][e & 7][3]);
+      for (int s = 0; s < SUMS; ++s) {
+        char* const to = states + (s * GROUPS + G) * S::kState;
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        reinterpret_cast<float2*>(mine_at + NB * 8 * 64 * 16)[nb * 64 + lane] = make_float2(m_run[nb], l_run[nb]);
-    }
-    __syncthreads();
-    if (!computes) return;
+        for (int e = 0; e < 8 * NB; ++e)
+          if ((e & 7) / kDt != G) reinterpret_cast<f32x4*>(to)[e * 64 + lane] = state[s].o[e >> 3][e & 7];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      float2 ml[GROUPS];
-#pragma unroll
-      for (int og = 0; og < GROUPS; ++og)
-        ml[og] = reinterpret_cast<const float2*>(states + og * S::kState + NB * 8 * 64 * 16)[nb * 64 + lane];
-      float m = ml[0].x, l = 0.0f, w[GROUPS];
-#pragma unroll
-      for (int og = 1; og < GROUPS; ++og) m = fmaxf(m, ml[og].x);
-#pragma unroll
-      for (int og = 0; og < GROUPS; ++og) {
-        w[og] = __builtin_amdgcn_exp2f(ml[og].x - m);
-        l += w[og] * ml[og].y;
+        for (int nb = 0; nb < NB; ++nb)
+          reinterpret_cast<float2*>(to + NB * 8 * 64 * 16)[nb * 64 + lane] = make_float2(state[s].m[nb], state[s].l[nb]);
       }
-      const float inv = finish(nb, m, l);
+    };
+    auto take = [&](auto group) __attribute__((always_inline)) {
+      constexpr int G = decltype(group)::value;
 #pragma unroll
-      for (int e = 0; e < kDt; ++e) {
-        const int dt = kDt * grp + e;
-        f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+      for (int nb = 0; nb < NB; ++nb) {
+        float2 ml[kAll];
+        f32x4 o[kAll][kDt];
 #pragma unroll
-        for (int og = 0; og < GROUPS; ++og) {
-          const float4 y = reinterpret_cast<const float4*>(states + og * S::kState)[(8 * nb + dt) * 64 + lane];
-          x[0] += w[og] * y.x;
-          x[1] += w[og] * y.y;
-          x[2] += w[og] * y.z;
-          x[3] += w[og] * y.w;
+        for (int a = 0; a < kAll; ++a) {
+          const char* const from = states + a * S::kState;
+          const State& own = state[a / GROUPS];
+          if (a % GROUPS == G) ml[a] = make_float2(own.m[nb], own.l[nb]);
+          else ml[a] = reinterpret_cast<const float2*>(from + NB * 8 * 64 * 16)[nb * 64 + lane];
+#pragma unroll
+          for (int e = 0; e < kDt; ++e) {
+            const int dt = kDt * G + e;
+            o[a][e] = a % GROUPS == G ? own.o[nb][dt] : reinterpret_cast<const f32x4*>(from)[(8 * nb + dt) * 64 + lane];
+          }
         }
-        store(nb, dt, x, inv);
+        float m = ml[0].x, l = ml[0].y;
+#pragma unroll
+        for (int a = 1; a < kAll; ++a) {
+          if (a > own_step) break;
+          float w0, w1;
+          weights(m, l, ml[a].x, ml[a].y, w0, w1);
+#pragma unroll
+          for (int e = 0; e < kDt; ++e) mix(o[0][e], w0, w1, o[a][e]);
+        }
+        const float inv = finish(nb, m, l);
+#pragma unroll
+        for (int e = 0; e < kDt; ++e) store(nb, kDt * G + e, o[0][e], inv);
       }
-    }
+    };
+    static_assert(GROUPS == 2, "the two branches");
+    if (computes && grp == 0) hand(std::integral_constant<int, 0>{});
+    if (computes && grp == 1) hand(std::integral_constant<int, 1>{});
+    __syncthreads();
+    if (computes && grp == 0) take(std::integral_constant<int, 0>{});
+    if (computes && grp == 1) take(std::integral_constant<int, 1>{});
   }
 }
 
 #define COPRIS_PREFILL_KERNEL(NAME, GROUPS, UNITS, NB, WAVES)                                            \
-  __global__ __launch_bounds__((Shape<GROUPS, UNITS, NB>::kThreads))                                   \
+  template <int SUMS>                                                                                    \
+  __global__ __launch_bounds__(GROUPS * 256)                                                           \
   __attribute__((amdgpu_waves_per_eu(WAVES, 2))) void NAME(                                            \
       const uint16_t* __restrict__ q, const u32x4* __restrict__ k, const u32x4* __restrict__ v,        \
       const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ block_table,                 \
       u32x4* __restrict__ k_cache, u32x4* __restrict__ v_cache, uint16_t* __restrict__ out,            \
       float* __restrict__ lse, PrefillGrid pg, int Hq, int Hkv, int max_pages, float scale_log2e) {    \
-    __shared__ __attribute__((aligned(1024))) char smem[Shape<GROUPS, UNITS, NB>::kLds];               \
-    prefill_attn_body<GROUPS, UNITS, NB>(smem, q, k, v, cu_seqlens, block_table, k_cache, v_cache, out, \
-                                         lse, pg, Hq, Hkv, max_pages, scale_log2e);                    \
+    __shared__ __attribute__((aligned(1024))) char smem[Shape<GROUPS, UNITS, NB, SUMS>::kLds];         \
+    prefill_attn_body<GROUPS, UNITS, NB, SUMS>(smem, q, k, v, cu_seqlens, block_table, k_cache, v_cache, out, \
+                                               lse, pg, Hq, Hkv, max_pages, scale_log2e);              \
   }
 // (two workgroups per CU: 256 registers per lane)
 COPRIS_PREFILL_KERNEL(prefill_attn_kernel, 1, 4, 2, 2)
@@ -684,6 +727,8 @@ COPRIS_PREFILL_KERNEL(prefill_attn_kernel, 1, 4, 2, 2)
 // have half the instructions per step; and two groups of waves per unit, group i taking the steps i, i + 2, ... from rings of
 // its own, the softmax states put together at the end.  (One sequence of 4000 tokens, one head, us: 68.9 whole, 31.8 and 34.1 in
 // two groups; 40.8 in four groups of 32 queries, whose rings of two buffers were too short for the rows to arrive.)
+// The bounds of two groups allow eight waves also where there are four: with 512 registers for a wave the compiler keeps the
+// accumulators in the other register file and moves them at every use (172 + 115 tokens, 16 / 4 heads: 8.8 us / 8.1).
 COPRIS_PREFILL_KERNEL(prefill_attn_half_kernel, 1, 4, 1, 2)
 COPRIS_PREFILL_KERNEL(prefill_attn_split2x2_kernel, 2, 2, 1, 1)
 COPRIS_PREFILL_KERNEL(prefill_attn_split2x4_kernel, 2, 4, 1, 1)
@@ -703,27 +748,27 @@ int launch_prefill_attn(const void* q, const void* k, const void* v, const int32
                         float scale, hipStream_t stream) {
   const int g = Hq / Hkv;
   const float scale_log2e = scale * kLog2e;
-  const PrefillShape shape = prefill_shape(B, T, Hq, max_seqlen);
-  const int per_wg = kPrefillCost[shape].units, tile = kPrefillCost[shape].queries;
+  const PrefillPlan plan = prefill_plan(B, T, Hq, g, max_seqlen);
+  const int per_wg = kPrefillCost[plan.shape].units, tile = kPrefillCost[plan.shape].queries;
   const int64_t wgs_max = (static_cast<int64_t>((max_seqlen - 1) / tile + 1) * g + per_wg - 1) / per_wg;      // of a sequence and kv head
   const int64_t wgs = prefill_flat_grid(B, T, Hkv, g, wgs_max, tile, per_wg);
   const dim3 grid = wgs > 0 ? dim3(static_cast<unsigned>(wgs)) : dim3(static_cast<unsigned>(wgs_max), Hkv, B);
   const PrefillGrid pg = prefill_grid(B, Hkv, g, wgs > 0);
-#define COPRIS_PREFILL(KERNEL, THREADS)                                                                     \
+#define COPRIS_PREFILL(KERNEL, THREADS, SUMS)                                                               \
   COPRIS_PRE(#KERNEL);                                                                                      \
-  hipLaunchKernelGGL(KERNEL, grid, dim3(THREADS), 0, stream, static_cast<const uint16_t*>(q),              \
+  hipLaunchKernelGGL(KERNEL<SUMS>, grid, dim3(THREADS), 0, stream, static_cast<const uint16_t*>(q),         \
                      static_cast<const u32x4*>(k), static_cast<const u32x4*>(v), cu_seqlens, block_table,   \
                      static_cast<u32x4*>(k_cache), static_cast<u32x4*>(v_cache), static_cast<uint16_t*>(out), \
-                     lse, pg, Hq, Hkv, max_pages, scale_log2e);            \
+                     lse, pg, Hq, Hkv, max_pages, scale_log2e);                                             \
   COPRIS_POST(#KERNEL)
-  if (shape == kPrefillWhole) {
-    COPRIS_PREFILL(prefill_attn_kernel, 256);
-  } else if (shape == kPrefillHalf) {
-    COPRIS_PREFILL(prefill_attn_half_kernel, 256);
-  } else if (shape == kPrefill2x2) {
-    COPRIS_PREFILL(prefill_attn_split2x2_kernel, 256);
-  } else {
-    COPRIS_PREFILL(prefill_attn_split2x4_kernel, 512);
+  switch (10 * plan.shape + plan.sums) {
+    case 10 * kPrefillHalf + 1: COPRIS_PREFILL(prefill_attn_half_kernel, 256, 1); break;
+    case 10 * kPrefillHalf + 2: COPRIS_PREFILL(prefill_attn_half_kernel, 256, 2); break;
+    case 10 * kPrefill2x2 + 1: COPRIS_PREFILL(prefill_attn_split2x2_kernel, 256, 1); break;
+    case 10 * kPrefill2x2 + 2: COPRIS_PREFILL(prefill_attn_split2x2_kernel, 256, 2); break;
+    case 10 * kPrefill2x4 + 1: COPRIS_PREFILL(prefill_attn_split2x4_kernel, 512, 1); break;
+    case 10 * kPrefill2x4 + 2: COPRIS_PREFILL(prefill_attn_split2x4_kernel, 512, 2); break;
+    default: COPRIS_PREFILL(prefill_attn_kernel, 256, 1); break;
   }
 #undef COPRIS_PREFILL
   return 0;
