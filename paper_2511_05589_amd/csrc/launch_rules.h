@@ -209,7 +209,9 @@ COPRIS_RULE int lm_run_rows(int C, int V, int width) {
 }
 
 // LM head, calls with few vocabulary rows (and fp32): vocabulary and batch rows of a workgroup of the small-call kernel,
-// or no rows where another kernel takes the call.  max_parts: partials per row that the workspace has room for.
+// or no rows where another kernel takes the call.  max_parts: partials per row that the workspace has room for; whether the call
+// is the small-call kernel's does not depend on it, only how far it may be cut: the fastest tile that fits (which of them it is
+// does not change a result), or none if the workspace has no room for a partial per 64 rows.
 //
 // The other bf16 kernels give a workgroup 128 vocabulary rows and more and walk the hidden dimension slab by slab, so
 // below 32768 rows most of the chip is idle while the call lasts as long as that chain.  Here the waves of a workgroup
@@ -236,6 +238,8 @@ COPRIS_RULE int lm_run_rows(int C, int V, int width) {
 struct LmSmall {
   int rows, cols;
 };
+// Places for partials in a row of the workspace: whole 64 vocabulary rows, so that a lane of the merge loads those of 64 rows at once.
+COPRIS_RULE int64_t lm_small_parts(int V, int rows) { return static_cast<int64_t>((V - 1) / kLmTileV + 1) * (kLmTileV / rows); }
 constexpr int kSmMaxRows = 512;        // more batch rows: never
 constexpr int kSmMaxV = 32768;         // more vocabulary rows: not in bf16
 COPRIS_RULE LmSmall lm_small_tile(int C, int H, int V, bool given, bool f32, int64_t max_parts) {
@@ -260,11 +264,13 @@ COPRIS_RULE LmSmall lm_small_tile(int C, int H, int V, bool given, bool f32, int
     }
   }
   int64_t fewest = 0;                  // workgroups of the best tile; of two as fast the one with fewer of them
+  LmSmall fits = {0, 0};
+  int64_t least_fits = INT64_MAX;
   for (int rows = 16; rows <= 64; rows *= 2)
     for (int cols = 16; cols <= 64; cols *= 2) {
       if ((cols > 16 && cols / 2 >= C) || (rows == 16 && cols == 64)) continue;
-      const int64_t parts = (V - 1) / rows + 1, wgs = parts * ((C - 1) / cols + 1), rounds = (wgs + 255) / 256;
-      if (parts > max_parts || rounds > (1 << 13)) continue;               // (a grid has fewer than 2^32 threads)
+      const int64_t wgs = ((V - 1) / rows + 1) * static_cast<int64_t>((C - 1) / cols + 1), rounds = (wgs + 255) / 256;
+      if (rounds > (1 << 13)) continue;                                    // (a grid has fewer than 2^32 threads)
       const bool alone = rows == 64 && cols == 64;                         // on its CU
       int64_t cost = (alone ? 6400 : 5200) + (rounds - 1) * (alone ? 5000 : 1100) + rounds * (rows + cols) * pitch * (alone && rounds > 1 ? 4 : 3) / 100;
       if (cost < stream) cost = stream;
@@ -273,8 +279,12 @@ COPRIS_RULE LmSmall lm_small_tile(int C, int H, int V, bool given, bool f32, int
         fewest = wgs;
         best = {rows, cols};
       }
+      if (lm_small_parts(V, rows) <= max_parts && cost <= least_fits) {    // (at the same cost the one with fewer partials)
+        least_fits = cost;
+        fits = {rows, cols};
+      }
     }
-  return best;
+  return best.rows == 0 || lm_small_parts(V, best.rows) <= max_parts ? best : fits;
 }
 
 // LM head, 384 given tokens and more: the 256 x 256 kernel's row blocks and lanes, one workgroup per CU.  A last row

@@ -48,6 +48,21 @@ __device__ __forceinline__ void combine(LmPartial& a, const LmPartial& o) {
   }
 }
 
+// Two neighbouring runs of vocabulary rows.  The same bits with the two exchanged, and wherever it is called.
+__device__ __forceinline__ void join(LmPartial& a, const LmPartial& o) {
+#pragma clang fp contract(off)
+  const float m = fmaxf(a.m, o.m);
+  const float sa = a.m == -INFINITY ? 0.0f : a.s * __expf(a.m - m);
+  const float sb = o.m == -INFINITY ? 0.0f : o.s * __expf(o.m - m);
+  a.m = m;
+  a.s = sa + sb;
+  if (better(o.best, o.idx, a.best, a.idx)) {
+    a.best = o.best;
+    a.idx = o.idx;
+    a.z = o.z;
+  }
+}
+
 __device__ __forceinline__ LmPartial wave_combine(LmPartial p) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -1836,9 +1851,11 @@ __device__ __forceinline__ void lm_sample_words(const float (&a)[4], LmLaneState
 // Operands come straight from memory, DEEP steps of each in flight in a wave's registers: lane (n, b) of a product holds granule b
 // of row n, which is the same in both operands, so fp32 feeds four products with a granule and bf16 one.  The buffer loads
 // take the lane's row from a register and the step from a scalar, so that a step has no address arithmetic and a wave fits
-// 128 registers (two workgroups per CU; 64 x 64: one).  The runs' sums are added in order through LDS, and then every thread has one
-// Philox block of a column (two at 64 x 64), whose words it drew while the first operands were on their way; the lanes of
-// a column meet by DPP.
+// 128 registers (two workgroups per CU; 64 x 64: one; two or three of the bf16 64 x 32 kernels' spill).  The runs' sums are added in
+// order through LDS, and then every thread has one Philox block of a column (two at 64 x 64), whose words it drew while the first
+// operands were on their way; the lanes of a column meet by DPP.
+// The tile follows what fills the chip and what the workspace has room for, the result does not: 16 rows of a column have one maximum,
+// and sixteens are joined by pairs to 64 rows, here or, from smaller tiles, by the merge (join, the same arithmetic in both).
 // What bounds it: a CU's requests.  In operand order neighbouring lanes fetch from different rows, and a load of 64 such pieces
 // of 16 bytes takes 64 clocks (33 GB/s).  With 32 batch rows and more (kGather) four neighbouring lanes fetch 64 bytes of one
 // row instead and the operands are put in order by a lane permutation through LDS: C = 41, H = 3584, V = 3251 18.6 -> 12.7 us; C = 126,
@@ -1867,11 +1884,11 @@ __global__ __launch_bounds__(kSmThreads) __attribute__((amdgpu_waves_per_eu(NV *
 void lmhead_small_kernel(
     const T* __restrict__ hidden, const T* __restrict__ weight, const int64_t* __restrict__ seq_id,
     const int32_t* __restrict__ step, const int32_t* __restrict__ target, uint32_t key0, uint32_t key1,
-    float inv_temperature, LmPartial* __restrict__ part, int C, int H, int V, int col_blocks, int n_tiles) {
+    float inv_temperature, LmPartial* __restrict__ part, int C, int H, int V, int col_blocks, int n_tiles, int part_pitch) {
   constexpr int kRows = 16 * NV, kCols = 16 * NC, kPitch = kRows + 4;
   constexpr int kQuads = kRows / 4;                   // Philox blocks of a column
   constexpr bool kGather = NC > 1;
-  constexpr int kSwaps = NV == 4 ? 4 : (NV == 2 ? 3 : 2);   // exchanges that bring a column's lanes together
+  constexpr int kSwaps = NV == 4 ? 4 : (NV == 2 ? 3 : 2);   // exchanges that bring a column's lanes together; two: those of 16 rows
   constexpr int kEach = (kCols * kQuads + kSmThreads - 1) / kSmThreads;   // ... of a thread
   __shared__ __attribute__((aligned(16))) float s_z[kSmRuns][kCols][kPitch];
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -2006,10 +2023,10 @@ void lmhead_small_kernel(
       a[i] = sizeof(T) == 2 ? z[i] : z[i] * inv_temperature;
       if (vq + i >= V) a[i] = -INFINITY;
     }
-    // one maximum for the column
+    // one maximum for 16 rows of the column
     float m = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
     if (sizeof(T) == 2) m = fmaxf(m, -INFINITY);       // (not a number only in fp32: as in the other kernels)
-    static_for<kSwaps>([&](auto s) __attribute__((always_inline)) { m = fmaxf(m, lane_swap<s.value>(m)); });
+    static_for<2>([&](auto s) __attribute__((always_inline)) { m = fmaxf(m, lane_swap<s.value>(m)); });
     LmPartial p;
     if constexpr (sizeof(T) == 2) {
       LmLaneState st{m, 0.0f, -INFINITY, 0.0f, 0.0f, 0x7fffffff};
@@ -2032,7 +2049,7 @@ void lmhead_small_kernel(
         }
       }
     }
-    static_for<kSwaps>([&](auto s) __attribute__((always_inline)) {
+    static_for<2>([&](auto s) __attribute__((always_inline)) {
       p.s += lane_swap<s.value>(p.s);
       const float best = lane_swap<s.value>(p.best), logit = lane_swap<s.value>(p.z);
       const int idx = lane_swap<s.value>(p.idx);
@@ -2042,7 +2059,17 @@ void lmhead_small_kernel(
         p.idx = idx;
       }
     });
-    if (quad == 0 && c < C) part[static_cast<size_t>(c) * n_tiles + tile] = p;
+    static_for<kSwaps - 2>([&](auto i) __attribute__((always_inline)) {
+      constexpr int s = 2 + i.value;
+      LmPartial o;
+      o.m = lane_swap<s>(p.m);
+      o.s = lane_swap<s>(p.s);
+      o.best = lane_swap<s>(p.best);
+      o.z = lane_swap<s>(p.z);
+      o.idx = lane_swap<s>(p.idx);
+      join(p, o);
+    });
+    if (quad == 0 && c < C) part[static_cast<size_t>(c) * part_pitch + tile] = p;
   }
 }
 
@@ -2056,9 +2083,10 @@ void lmhead_small_kernel(
 // V = 50257 90.1 / 88.2; given tokens M = 4164, H = 256, V = 5269 30.1 / 25.6, M = 8192, H = 256, V = 20011 106.1 / 95.9.  With 2374
 // partials of a row (C = 5, H = 72, V = 151936) 29.9 / 27.6, and 30.3 with one wavefront.
 // --------------------------------------------------------------------------
-// (Rows from `rest` on have n_rest partials, in rows of n_tiles like the others.)
+// (Rows from `rest` on have n_rest partials, in rows of n_tiles like the others.)  PER neighbouring partials are joined first: those of
+// the small-call kernel's tiles, to the 64 rows of its largest.
 constexpr int kMergeAlone = 1024;
-template <int WAVES>
+template <int WAVES, int PER>
 __global__ __launch_bounds__(WAVES * kWave) void lmhead_merge_kernel(const LmPartial* __restrict__ part,
                                                              int n_tiles, int n_all, int rest, int n_rest,
                                                              int32_t* __restrict__ token,
@@ -2068,11 +2096,35 @@ __global__ __launch_bounds__(WAVES * kWave) void lmhead_merge_kernel(const LmPar
   const int c = blockIdx.x, tid = threadIdx.x, lane = tid & (kWave - 1);
   const LmPartial* row = part + static_cast<size_t>(c) * n_tiles;
   LmPartial p = empty_partial();
-  const int n = c < rest ? n_all : n_rest;
+  const int n_parts = c < rest ? n_all : n_rest, n = (n_parts - 1) / PER + 1;
   for (int t = tid; t < n; t += kDeep * WAVES * kWave) {
     LmPartial q[kDeep];
+    if constexpr (PER == 1) {
 #pragma unroll
-    for (int u = 0; u < kDeep; ++u) q[u] = row[min(t + u * WAVES * kWave, n - 1)];
+      for (int u = 0; u < kDeep; ++u) q[u] = row[min(t + u * WAVES * kWave, n - 1)];
+    } else {
+      typedef unsigned int Words __attribute__((ext_vector_type(PER)));
+      static_assert(sizeof(LmPartial) == 5 * sizeof(unsigned int), "PER partials are five loads");
+      alignas(16) LmPartial x[kDeep][PER];
+#pragma unroll
+      for (int u = 0; u < kDeep; ++u)
+        if (u == 0 || t - tid + u * WAVES * kWave < n) {       // (all lanes or none)
+#pragma unroll
+          for (int e = 0; e < 5; ++e)                          // (whole groups have places in the workspace)
+            reinterpret_cast<Words*>(&x[u])[e] = reinterpret_cast<const Words*>(row + static_cast<size_t>(min(t + u * WAVES * kWave, n - 1)) * PER)[e];
+        }
+#pragma unroll
+      for (int u = 0; u < kDeep; ++u) {
+        if (u != 0 && t - tid + u * WAVES * kWave >= n) continue;
+#pragma unroll
+        for (int e = 1; e < PER; ++e)
+          if ((t + u * WAVES * kWave) * PER + e >= n_parts) x[u][e] = empty_partial();
+#pragma unroll
+        for (int e = 0; e < PER; e += 2) join(x[u][e], x[u][e + 1]);
+        if constexpr (PER == 4) join(x[u][0], x[u][2]);
+        q[u] = x[u][0];
+      }
+    }
     const float before = p.m;
 #pragma unroll
     for (int u = 0; u < kDeep; ++u) {
@@ -2179,7 +2231,7 @@ static LmSmall lm_use_small(int C, int H, int V, int dtype, bool given, int64_t 
 // (W comes from HBM once and is shared through the caches) and each keeps its rows' state
 // across all of its tiles.
 static int lm_parts(int C, int H, int V, int dtype, bool given, int64_t max_parts) {
-  if (const LmSmall sm = lm_use_small(C, H, V, dtype, given, max_parts); sm.rows != 0) return (V - 1) / sm.rows + 1;
+  if (const LmSmall sm = lm_use_small(C, H, V, dtype, given, max_parts); sm.rows != 0) return static_cast<int>(lm_small_parts(V, sm.rows));
   if (!lm_use_mfma(C, H, V, dtype)) return (V - 1) / kLmTileV + 1;
   if (const int width = lm_use_run(C, H, V, dtype, given)) return (V - 1) / lm_run_rows(C, V, width) + 1;
   if (lm_use_skinny(C, H, V, dtype, given)) return (V - 1) / lm_skinny_rows(V) + 1;
@@ -2247,16 +2299,17 @@ static int launch_lmhead(const void* hidden, const void* weight, const int64_t* 
   const float inv_t = 1.0f / temperature;
   const bool given = target != nullptr;
   const LmSmall sm = lm_use_small(C, H, V, dtype, given, room);
-  const int n_parts = sm.rows != 0 ? (V - 1) / sm.rows + 1 : lm_parts(C, H, V, dtype, given, 0);
+  const int n_parts = static_cast<int>(sm.rows != 0 ? lm_small_parts(V, sm.rows) : lm_parts(C, H, V, dtype, given, 0));
   int n_all = n_parts, rest = C, n_rest = 0;   // partials of a row; first row that has n_rest of them
   if (sm.rows != 0) {
     const int col_blocks = (C - 1) / sm.cols + 1;
-    const dim3 grid((n_parts + 7) / 8 * 8 * col_blocks);
+    n_all = (V - 1) / sm.rows + 1;
+    const dim3 grid((n_all + 7) / 8 * 8 * col_blocks);
     COPRIS_PRE("lmhead_small_kernel");
 #define COPRIS_LM_SMALL(T, G, NV, NC, D)                                                                    \
   hipLaunchKernelGGL((lmhead_small_kernel<T, G, NV, NC, D>), grid, dim3(kSmThreads), 0, stream,             \
                      static_cast<const T*>(hidden), static_cast<const T*>(weight), seq_id, step, target,    \
-                     key0, key1, inv_t, part, C, H, V, col_blocks, n_parts)
+                     key0, key1, inv_t, part, C, H, V, col_blocks, n_all, n_parts)
 #define COPRIS_LM_SMALLS(T, G)                                                  \
   switch (100 * sm.rows + sm.cols) {                                            \
     case 1616: COPRIS_LM_SMALL(T, G, 1, 1, 8); break;                           \
@@ -2386,12 +2439,20 @@ static int launch_lmhead(const void* hidden, const void* weight, const int64_t* 
     COPRIS_POST("lmhead_generic_kernel");
   }
   COPRIS_PRE("lmhead_merge_kernel");
-  if (n_parts <= kMergeAlone)
-    hipLaunchKernelGGL(lmhead_merge_kernel<1>, dim3(C), dim3(kWave), 0, stream, part, n_parts, n_all, rest, n_rest, token,
-                       logprob, lse);
-  else
-    hipLaunchKernelGGL(lmhead_merge_kernel<4>, dim3(C), dim3(4 * kWave), 0, stream, part, n_parts, n_all, rest, n_rest, token,
-                       logprob, lse);
+  const int per = sm.rows != 0 ? kLmTileV / sm.rows : 1;
+#define COPRIS_LM_MERGE(PER)                                                                                              \
+  if ((n_parts - 1) / PER < kMergeAlone)                                                                                  \
+    hipLaunchKernelGGL((lmhead_merge_kernel<1, PER>), dim3(C), dim3(kWave), 0, stream, part, n_parts, n_all, rest, n_rest, \
+                       token, logprob, lse);                                                                              \
+  else                                                                                                                    \
+    hipLaunchKernelGGL((lmhead_merge_kernel<4, PER>), dim3(C), dim3(4 * kWave), 0, stream, part, n_parts, n_all, rest,     \
+                       n_rest, token, logprob, lse)
+  switch (per) {
+    case 1: COPRIS_LM_MERGE(1); break;
+    case 2: COPRIS_LM_MERGE(2); break;
+    default: COPRIS_LM_MERGE(4); break;
+  }
+#undef COPRIS_LM_MERGE
   COPRIS_POST("lmhead_merge_kernel");
   return 0;
 }

@@ -161,6 +161,28 @@ def test_small_calls_with_room_for_a_partial_per_64_rows_only(R, dtype):
     assert binding.lmhead_logprob_workspace_bytes(C, H, V) > least
 
 
+@pytest.mark.parametrize("dtype,C,H,V", [(W.BF16, 1, 3584, 3483), (W.BF16, 3, 512, 1009), (W.BF16, 8, 2048, 7732), (W.BF16, 24, 3584, 3185), (W.BF16, 41, 3584, 3251),
+                                         (W.F32, 6, 256, 1009), (W.F32, 5, 1024, 3003), (W.F32, 20, 512, 5000), (W.F32, 48, 256, 146851)])
+def test_small_calls_do_not_depend_on_the_room(R, dtype, C, H, V):
+    # tiles of 16 and 32 vocabulary rows with the workspace that is asked for, of 64 with the smallest that is accepted: the same bits
+    import torch
+
+    from paper_2511_05589_amd import binding
+    inp = W.make_small_lmhead_case(C * 19 + V, C, H, V, dtype, w_std=0.05)
+    least, asked = -(-C * -(-V // 64) * 20 // 256) * 256, binding.lmhead_logprob_workspace_bytes(C, H, V)
+    assert asked > least
+    got = []
+    for room in (asked, least, 2 * least - 256, 4 * asked):
+        d = R.stage_lmhead(inp, dtype)
+        d.ws = torch.empty(room, dtype=torch.uint8, device=d.ws.device)
+        d.run()
+        torch.cuda.synchronize()
+        got.append([x.cpu().numpy() for x in (d.token, d.logprob, d.lse)])
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            np.testing.assert_array_equal(a, b)
+
+
 def test_small_calls_infinities(R):
     # as in the other kernels: an infinite logit has no log-prob, minus infinity no weight, and no other row is touched
     import torch

@@ -50,3 +50,14 @@ def test_no_alloc_entry_point_matches_the_workspace_one():
     assert e.value.code == binding.COPRIS_EWORKSPACE and "static" in str(e.value)
     torch.cuda.synchronize()
     assert (d.token.cpu().numpy() == -5).all()
+
+
+@pytest.mark.parametrize("dtype,shape", [(W.F32, (48, 256, 146851)), (W.F32, (58, 64, 146851)), (W.BF16, (1, 3584, 3483)), (W.BF16, (400, 256, 30000))])
+def test_no_alloc_entry_point_where_the_array_limits_the_tile(dtype, shape):
+    # fp32: the array has room for larger vocabulary tiles than a workspace of the size that is asked for
+    import torch
+    from paper_2511_05589_amd import binding, runner as R
+    R.require_gpu()
+    inp = W.make_small_lmhead_case(sum(shape), *shape, dtype)
+    for g, r in zip(*_both(R, binding, torch, inp, dtype)):
+        np.testing.assert_array_equal(g, r)
