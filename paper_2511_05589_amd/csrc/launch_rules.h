@@ -241,11 +241,12 @@ struct LmSmall {
 // Places for partials in a row of the workspace: whole 64 vocabulary rows, so that a lane of the merge loads those of 64 rows at once.
 COPRIS_RULE int64_t lm_small_parts(int V, int rows) { return static_cast<int64_t>((V - 1) / kLmTileV + 1) * (kLmTileV / rows); }
 constexpr int kSmMaxRows = 512;        // more batch rows: never
+constexpr int kSmMaxGiven = 383;       // ... of given tokens in bf16
 constexpr int kSmMaxV = 32768;         // more vocabulary rows: not in bf16
 COPRIS_RULE LmSmall lm_small_tile(int C, int H, int V, bool given, bool f32, int64_t max_parts) {
   LmSmall best = {0, 0};
-  if (C > kSmMaxRows || (V > kSmMaxV && (!f32 || C <= 8))) return best;
-  if (!f32 && ((given && C >= 384) || lm_run_cols(C, H, V, given) != 0)) return best;
+  if (C > kSmMaxRows || (V > kSmMaxV && (!f32 || C <= 8)) || max_parts < lm_small_parts(V, kLmTileV)) return best;
+  if (!f32 && ((given && C > kSmMaxGiven) || lm_run_cols(C, H, V, given) != 0)) return best;
   const int64_t pitch = static_cast<int64_t>(H) * (f32 ? 4 : 2);
   const int64_t stream = 6000 + V * pitch / 5200;
   int64_t least = INT64_MAX;           // the other kernel
@@ -285,6 +286,19 @@ COPRIS_RULE LmSmall lm_small_tile(int C, int H, int V, bool given, bool f32, int
       }
     }
   return best.rows == 0 || lm_small_parts(V, best.rows) <= max_parts ? best : fits;
+}
+// Most places for partials, rows x partials of each, that calls with up to M rows of given tokens have where they are the small-call
+// kernel's.  Its tile is the same for the rows 16 i + 1 .. 16 i + 16 (test_most_partials_of_small_calls).
+COPRIS_RULE int64_t lm_small_most_parts(int M, int H, int V, bool f32) {
+  int64_t most = 0;
+  if (V > kSmMaxV && !f32) return most;
+  const int rows = f32 ? kSmMaxRows : kSmMaxGiven;
+  for (int m = M < rows ? M : rows; m > 0; m = (m - 1) & ~15) {
+    const LmSmall t = lm_small_tile(m, H, V, true, f32, INT64_MAX);
+    const int64_t parts = t.rows != 0 ? m * lm_small_parts(V, t.rows) : 0;
+    if (parts > most) most = parts;
+  }
+  return most;
 }
 
 // LM head, 384 given tokens and more: the 256 x 256 kernel's row blocks and lanes, one workgroup per CU.  A last row

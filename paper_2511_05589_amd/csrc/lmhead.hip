@@ -2220,9 +2220,12 @@ static int lm_use_run(int C, int H, int V, int dtype, bool given) {
 }
 // Tile of the small-call kernel, for a workspace with room for max_parts partials per row; no rows: another kernel
 // takes the call.
+static bool lm_small_takes(int C, int H, int V, int dtype) {
+  const int64_t pitch = static_cast<int64_t>(H) * (dtype == 0 ? 4 : 2), most = ((1ll << 32) - 1) / pitch;   // (bytes of a buffer)
+  return pitch % (dtype == 0 ? kSmStep : 2 * kSmStep) == 0 && V <= most && C <= most;
+}
 static LmSmall lm_use_small(int C, int H, int V, int dtype, bool given, int64_t max_parts) {
-  const int64_t pitch = static_cast<int64_t>(H) * (dtype == 0 ? 4 : 2);
-  if (pitch % (dtype == 0 ? kSmStep : 2 * kSmStep) != 0 || V * pitch >= (1ll << 32) || C * pitch >= (1ll << 32)) return {0, 0};
+  if (!lm_small_takes(C, H, V, dtype)) return {0, 0};
   return lm_small_tile(C, H, V, given, dtype == 0, max_parts);
 }
 // Partials per row.  Matrix-core kernels: the grid is (parts, blocks of 256 rows) with
@@ -2273,17 +2276,16 @@ size_t lm_token_workspace_need(int M, int H, int V, int dtype) { return lm_token
 // sizes its workspace for its largest micro-batch.
 size_t lm_token_workspace_bytes(int M, int H, int V, int dtype) {
   size_t most = lm_token_workspace_need(M, H, V, dtype);
-  for (int m = 1; m <= M && m <= kSmMaxRows; ++m) most = std::max(most, lm_token_bytes(m, H, V, dtype, kLmAnyParts));
+  if (lm_small_takes(1, H, V, dtype))
+    most = std::max(most, align256(static_cast<size_t>(lm_small_most_parts(M, H, V, dtype == 0)) * sizeof(LmPartial)));
   if (!lm_use_mfma(M, H, V, dtype)) return most;   // (a part per 64 vocabulary rows: as many as there can be)
   // the parts per row are constant between these numbers of rows
   const int ends[] = {8, 32, kSkMaxRows, 128, 160, 192, 256, 320, kGmMinRows - 1};
   for (int m : ends)
-    if (m < M && lm_token_workspace_need(m, H, V, dtype) > most) most = lm_token_workspace_need(m, H, V, dtype);
+    if (m < M) most = std::max(most, lm_token_workspace_need(m, H, V, dtype));
   for (int64_t m = kMfBN; m < M; m += kMfBN)
-    for (int rest : {0, 64, 128, 160}) {
-      const size_t need = m + rest < M ? lm_token_workspace_need(static_cast<int>(m + rest), H, V, dtype) : 0;
-      if (need > most) most = need;
-    }
+    for (int rest : {0, 64, 128, 160})
+      if (m + rest < M) most = std::max(most, lm_token_workspace_need(static_cast<int>(m + rest), H, V, dtype));
   return most;
 }
 
