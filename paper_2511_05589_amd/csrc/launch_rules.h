@@ -72,8 +72,9 @@ COPRIS_RULE int lm_block_width(int C) {
 // as many workgroups on the chip with half the products and half the sampler each; W is read once more, from the caches.
 // With a CU for each of them that is faster (C = 129 .. 640, H = 64 .. 3584: 0.66 .. 0.99 of the time; blocks of
 // 192 with H above 1024 lose where they had more than 192: 226 workgroups 1.04).  With more, two workgroups of a CU share it, and
-// only a short H, whose sampler is what counts, gains (H <= 256 0.79 .. 0.97, to 1024 workgroups, but in place of one block of
-// 192 columns 1.04 above 512; H = 512 0.86 .. 1.22, H = 1024 1.05 .. 1.14;
+// only a short H, whose sampler is what counts, gains (H <= 256 0.72 .. 0.98, to 1024 workgroups, but in place of one block of
+// 192 columns 1.04 above 512, with H = 256 1.02 .. 1.06 from 470; more than 512 have a second round, which loses where there are
+// three row blocks, up to 768 workgroups 1.00 .. 1.08, or five, up to 600 1.01 .. 1.03; H = 512 0.86 .. 1.22, H = 1024 1.05 .. 1.14;
 // given tokens 0.97 .. 1.13).  Whole calls in us, 256 columns / 128:
 //   C = 244, H =  512, V = 13430   24.4 / 16.9       C = 202, H = 3584, V =  4656   59.9 / 44.2     C = 256, H =  256, V = 28975   22.5 / 19.8
 //   C = 476, H =  256, V =  8027   21.6 / 14.7       C = 277, H = 3584, V =  9125   55.4 / 42.6     C = 480, H =   64, V = 42332   33.2 / 27.6
@@ -84,8 +85,9 @@ struct LmBlocks {
 COPRIS_RULE LmBlocks lm_tile_blocks(int C, int H, int V, bool given) {
   const int narrow = (C - 1) / 128 + 1;
   const int64_t wgs = static_cast<int64_t>((V - 1) / 128 + 1) * narrow;
-  const int64_t most = H <= 256 && !given ? (C <= 192 ? 512 : 1024) : (C <= 192 && H > 1024 ? 192 : 256);
-  if (C > 128 && C <= 640 && wgs <= most) return {narrow, ((C - 1) / narrow + 32) & ~31, 128};
+  const int64_t most = H <= 256 && !given ? (C <= 192 ? (H <= 192 ? 512 : 440) : 1024) : (C <= 192 && H > 1024 ? 192 : 256);
+  const bool loses = wgs > 512 && ((narrow == 3 && wgs <= 768) || (narrow == 5 && wgs <= 640));
+  if (C > 128 && C <= 640 && wgs <= most && !loses) return {narrow, ((C - 1) / narrow + 32) & ~31, 128};
   return {lm_row_blocks(C), lm_block_rows(C), lm_block_width(C)};
 }
 
@@ -190,10 +192,10 @@ COPRIS_RULE int lm_run_width(int C, int H, int V, bool given) {
   return pays ? width : 0;
 }
 
-// Up to 12288 vocabulary rows the run kernel was the fastest of the above with few of them, but blocks of 128 rows (lm_tile_blocks) and
-// the small-call kernel (lm_small_tile) are faster: C = 207, H = 512, V = 6922 20.7 / 15.7 us; C = 305, H = 512, V = 4484 18.6 / 15.5; C = 210, H = 512,
-// V = 1026 19.7 / 8.6.  Calls with H below 256 or fewer than 64 vocabulary rows stay (C = 200, H = 128, V = 8195 16.6 / 11.3 all the same):
-// they are the short way to its tiles of at most 128 rows.
+// The columns with which a call takes the run kernel, or 0.  Up to 12288 vocabulary rows it was the fastest of the above, but blocks of 128
+// rows (lm_tile_blocks) and the small-call kernel (lm_small_tile) are faster: C = 207, H = 512, V = 6922 20.7 / 15.7 us; C = 305,
+// H = 512, V = 4484 18.6 / 15.5; C = 210, H = 512, V = 1026 19.7 / 8.6.  Calls with H below 256 or fewer than 64 vocabulary rows have
+// not been moved: the one that was measured, C = 200, H = 128, V = 8195, takes 16.6 where narrow blocks take 11.3.
 COPRIS_RULE int lm_run_cols(int C, int H, int V, bool given) {
   return V <= 12288 && V >= 64 && H >= 256 ? 0 : lm_run_width(C, H, V, given);
 }
@@ -218,9 +220,11 @@ COPRIS_RULE int lm_run_rows(int C, int V, int width) {
 // share the hidden dimension and the tile is as small as fills the chip.  A CU's requests are what
 // bounds it, about 33 GB/s of rows, so a tile's time is its rows, and the estimate (ns) is
 //     start + (rounds - 1) * end of a tile + rounds * (rows + cols) * pitch * 0.03,  at least the stream of W,
-// against the other kernel's: start + H * slope, whatever V is.  (Tiles of 32 and 64 batch rows have become up to 0.61 of the estimate since, where
-// the hidden dimension is long; a slope of 0.02 for all tiles took calls that lose: C = 178, H = 64, V = 18749 given tokens 9.9 / 15.9.)  Whole calls in us, other kernel / small-call kernel with its tile
-// (sampling):
+// against the other kernel's: start + H * slope, whatever V is.  (Tiles of 32 and 64 batch rows take down to 0.61 of the estimate where
+// the hidden dimension is long.)  With a short H the tiles' ends decide, not their rows, and both sides have lines of their own:
+// without them C = 76, H = 64, V = 18900 given tokens 11.5 (9.0 with tiles of 128 rows), C = 150, H = 64, V = 18500 given 14.8 / 10.6,
+// C = 96, H = 64, V = 22500 14.8 / 11.9, C = 64, H = 128, V = 22500 given 11.2 / 9.5.  Whole calls in us, other kernel / small-call
+// kernel with its tile (sampling):
 //   C =   1, H = 3584, V =  3483   34.6 / 10.8 (16 x 16)      C =  41, H = 3584, V =  3251   39.9 / 12.5 (32 x 32)
 //   C =   2, H =  256, V = 16384   12.7 /  7.7 (64 x 16)      C =  63, H = 1024, V =  3554   19.7 / 10.5 (32 x 32)
 //   C =   8, H = 2048, V =  7732   25.2 / 12.3 (32 x 16)      C =  69, H =  512, V =  1885   15.3 /  8.2 (32 x 32)
@@ -228,8 +232,8 @@ COPRIS_RULE int lm_run_rows(int C, int V, int width) {
 //   C =  25, H = 1024, V = 24622   19.0 / 20.2, not taken     C = 192, H = 3584, V =  4804   51.1 / 22.9 (64 x 64)
 //   C = 125, H = 1024, V = 10419   20.6 / 23.8, not taken     C = 387, H =  512, V =  1515   24.1 / 11.6 (64 x 64)
 //   given tokens: C = 1, H = 1536, V = 3405  19.6 / 7.9;  C = 29, H = 2048, V = 6569  23.9 / 13.7;  C = 126, H = 3584, V = 6545  40.5 / 33.3
-// 260 drawn calls (C = 1 .. 512, H = 64 .. 3584, V = 1000 .. 32768): at most 1.02 of the other kernel's time, 0.31 at best; some keep the
-// other kernel where this one was 10 - 25 % faster.  A second round of 64 x 64 tiles is slower than the first (C = 334, H = 2048, V = 5313
+// 674 drawn calls (C = 1 .. 512, H = 64 .. 3584, V = 1000 .. 32768): at most 1.00 of the time without this kernel and the narrow blocks, 0.31 at
+// best; some keep the other kernel where this one was 10 - 25 % faster.  A second round of 64 x 64 tiles is slower than the first (C = 334, H = 2048, V = 5313
 // 55.7 for two, 32.7 with tiles of 128 rows), so it is priced higher.  Where the run kernel's rule takes the call it keeps it.
 // fp32 against the kernel with four quarters of the hidden dimension and tiles of 64 rows: C = 8, H = 256, V = 1024 9.3 / 7.2;
 // C = 4, H = 1024, V = 2994 17.1 / 9.5; C = 62, H = 3584, V = 1945 82.1 / 26.7; C = 22, H = 512, V = 109750 82.1 / 71.0; 0.33 .. 1.00 of the time
@@ -258,6 +262,10 @@ COPRIS_RULE LmSmall lm_small_tile(int C, int H, int V, bool given, bool f32, int
     else if (C <= 384) least = 14500 + 105 * static_cast<int64_t>(H) / 10;
     else least = 18000 + 126 * static_cast<int64_t>(H) / 10;
     if (given) least = least * 85 / 100;
+    // (the lines above are for a long H; a short one takes)
+    const int64_t h = H, brief = C <= 32 ? 9200 + 21 * h / 2 : (C <= 64 ? 11200 + 23 * h / 2 : 11200 + 9 * h);
+    if (C <= 128 && brief - (given ? (C <= 32 ? 2000 : 3000) : 0) < least) least = brief - (given ? (C <= 32 ? 2000 : 3000) : 0);
+    if (C > 128 && given && 9600 + 9 * h < least) least = 9600 + 9 * h;
     const LmBlocks tiles = lm_tile_blocks(C, H, V, given);
     if (C > 128 && tiles.width == 128) {
       least = 10800 + 9 * static_cast<int64_t>(H) - (given ? 2800 : 0);
@@ -270,11 +278,18 @@ COPRIS_RULE LmSmall lm_small_tile(int C, int H, int V, bool given, bool f32, int
   for (int rows = 16; rows <= 64; rows *= 2)
     for (int cols = 16; cols <= 64; cols *= 2) {
       if ((cols > 16 && cols / 2 >= C) || (rows == 16 && cols == 64)) continue;
-      const int64_t wgs = ((V - 1) / rows + 1) * static_cast<int64_t>((C - 1) / cols + 1), rounds = (wgs + 255) / 256;
-      if (rounds > (1 << 13)) continue;                                    // (a grid has fewer than 2^32 threads)
+      const int64_t tiles = (V - 1) / rows + 1, col_blocks = (C - 1) / cols + 1, wgs = tiles * col_blocks;
       const bool alone = rows == 64 && cols == 64;                         // on its CU
+      const int64_t rounds = (wgs + 255) / 256;
+      if (rounds > (1 << 13)) continue;                                    // (a grid has fewer than 2^32 threads)
       int64_t cost = (alone ? 6400 : 5200) + (rounds - 1) * (alone ? 5000 : 1100) + rounds * (rows + cols) * pitch * (alone && rounds > 1 ? 4 : 3) / 100;
       if (cost < stream) cost = stream;
+      // With a short H more tiles than CUs cost what their ends do, on one CU side by side; a tile that has its CU alone waits where an
+      // XCD has more than its 32 CUs' (84 tiles in 3 column blocks are 252 workgroups, 33 of them on four XCDs).
+      int64_t ends = (given ? 5200 : 6000) + 1600 * rounds;
+      if (alone) ends = (given ? 7200 : 8000) + ((tiles + 7) / 8 * col_blocks > 32 * rounds ? 2500 : 0);
+      ends += 6 * static_cast<int64_t>(H);
+      if (!f32 && (alone || rounds > (cols == 16 ? 2 : 1)) && cost < ends) cost = ends;
       if (cost < least || (cost == least && wgs < fewest)) {
         least = cost;
         fewest = wgs;
