@@ -58,7 +58,7 @@ extern "C" {
 
 #define COPRIS_OK            0
 #define COPRIS_EINVAL       -1   /* null pointer, bad shape, misaligned base, bad scalar */
-#define COPRIS_EWORKSPACE   -2   /* workspace smaller than the *_workspace_bytes query   */
+#define COPRIS_EWORKSPACE   -2   /* workspace too small; never one of *_workspace_bytes  */
 #define COPRIS_EUNSUPPORTED -3   /* dtype / head_dim / page_size / group size not built  */
 #define COPRIS_ELAUNCH      -4   /* the HIP runtime reported an error at launch          */
 
@@ -198,7 +198,9 @@ int copris_prefill_attn(const void* q, const void* k, const void* v,
  *   seq_id  [C] int64  stable trajectory id (not the slot index)
  *   step    [C] int32  index of the token being generated within its response
  *   token   [C] int32 out     logprob [C] fp32 out     lse [C] fp32 out or NULL
- *   workspace  at least copris_lmhead_logprob_workspace_bytes() bytes, 256-byte aligned
+ *   workspace  at least copris_lmhead_logprob_workspace_bytes() bytes, 256-byte aligned.
+ *              C * ceil(V / 64) * 20 bytes, in whole 256, are accepted too and give the same
+ *              bits, but a call with few vocabulary rows may take longer
  *
  * Requires temperature > 0, H % 8 == 0 for bf16 (H % 4 == 0 for fp32), V < 2^31.
  * ------------------------------------------------------------------------ */
@@ -221,10 +223,11 @@ int copris_lmhead_logprob(const void* hidden, const void* weight,
  * nothing.  The device that `stream` belongs to must be the current device.
  *
  * A shape that needs more partials than the array holds returns COPRIS_EWORKSPACE (the
- * text of copris_last_error_detail() gives the sizes) and enqueues nothing.  The need
- * is C x parts x 20 bytes: for bf16 with H % 64 == 0, parts is at most
- * max(1, min(512 / ceil(C / 256), ceil(V / 64))), i.e. 2.6 MB for any C up to 131 072 and 20 x C bytes
- * beyond (209 715 rows fill the array); for other shapes parts = ceil(V / 64), e.g. C <= 88 at V = 151 936.
+ * text of copris_last_error_detail() gives the sizes) and enqueues nothing.  That is
+ * where C x parts x 20 bytes exceed the array, with
+ * parts = max(1, min(512 / ceil(C / 256), ceil(V / 64))) for bf16 with H % 64 == 0, i.e. 2.6 MB for any C up to 131 072
+ * and 20 x C bytes beyond (209 715 rows fill the array); for other shapes parts = ceil(V / 64), e.g. C <= 88 at
+ * V = 151 936.  (Calls with few vocabulary rows are cut into as many as ceil(V / 16) parts where the array has room.)
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU
  * (different streams, or threads) race.  Nothing in it needs clearing between calls:
  * every partial a call reads it has written first.
@@ -254,7 +257,9 @@ int copris_lmhead_logprob_noalloc(const void* hidden, const void* weight,
  *   hidden  [M, H] dtype       weight [V, H] dtype (row v = vocabulary entry v)
  *   tokens  [M] int32          logprob [M] fp32 out     lse [M] fp32 out or NULL
  *   workspace  at least copris_lmhead_token_logprob_workspace_bytes() bytes, 256-byte aligned;
- *              one that serves M positions serves fewer too
+ *              one that serves M positions serves fewer too, with the same bits as its own
+ *              query's would give.  (A smaller one is accepted where another kernel can do
+ *              with it; the last bits may then be others.)
  *
  * Requires temperature > 0, H % 8 == 0 for bf16 (H % 4 == 0 for fp32), V < 2^31.
  * ------------------------------------------------------------------------ */
