@@ -7,7 +7,7 @@ import pytest
 from oracle import copris_oracle as O
 from paper_2511_05589_amd import workloads as W
 from tests import parity as P
-from tests.test_launch_rules import RUNS, SMALL
+from tests.test_launch_rules import NARROW, RUNS, SMALL, WIDE
 
 pytestmark = pytest.mark.gpu
 
@@ -111,9 +111,10 @@ def test_fp32_ends_of_rows_and_quarters(R, C, H, V):
     P.check_token_logprob(lp2, lse2, P.oracle_token_logprob(inp["hidden"], inp["weight"], given, 1.0, W.F32), f"f32 given {C}x{H}x{V}")
 
 
-@pytest.mark.parametrize("C,H,V", [(129, 64, 16384), (193, 512, 12289), (256, 64, 16385), (193, 192, 65001),   # two blocks, more tiles than workgroups of one
-                                   (257, 512, 10241), (384, 64, 20001), (385, 512, 8193), (640, 64, 20001)])   # three, four and five
+@pytest.mark.parametrize("C,H,V", [*NARROW, *WIDE])
 def test_tiles_of_many_narrow_row_blocks(R, C, H, V):
+    # two to five blocks of 128 columns, more tiles than workgroups of one; one to three of 192 and of 256 (which of them:
+    # test_row_blocks_narrow_and_wide)
     inp = W.make_small_lmhead_case(C * 29 + V, C, H, V, W.BF16, w_std=0.1)
     (tok, lp, lse), kernels = P.kernels_of(lambda: R.run_lmhead_logprob(inp, W.BF16))
     assert kernels == ["lmhead_mfma_kernel", "lmhead_merge_kernel"]
@@ -246,6 +247,7 @@ def test_log_sum_exp_has_no_bias(R, C):
 # 256 x 256 one with a last block of another width and without, the generic one)
 EVERY_KERNEL = [(48, 384, 65537), (20, 64, 5003), (200, 64, 20011), (200, 128, 8195), (150, 512, 8195), (300, 512, 3001), (320, 1024, 33001),
                 (400, 64, 20011), (448, 64, 20011), (5, 72, 260)]
+WIDE_BLOCKS = [(160, 512, 20011), (200, 512, 20011)]   # tiles with 192 and 256 columns
 
 
 def _scored(R, hidden, weight, temperature):
@@ -258,7 +260,7 @@ def _scored(R, hidden, weight, temperature):
     return tok, (lp, lse), R.run_token_logprob(hidden, weight, tok, temperature, W.BF16)
 
 
-@pytest.mark.parametrize("C,H,V", EVERY_KERNEL + [(5, 64, 1), (200, 64, 1), (300, 64, 1), (400, 64, 1)])
+@pytest.mark.parametrize("C,H,V", EVERY_KERNEL + WIDE_BLOCKS + [(5, 64, 1), (200, 64, 1), (300, 64, 1), (400, 64, 1)])
 def test_a_peaked_row_has_no_positive_log_prob(R, C, H, V):
     # one logit of lo .. 2 * lo, the others noise around 0: the log-prob is -ln(1 + less than 70000 e^-35), so 0 up to the
     # rounding of a sum near 1 and of its logarithm.  The last two are near the end of fp32's range.
@@ -280,7 +282,7 @@ def test_a_peaked_row_has_no_positive_log_prob(R, C, H, V):
             np.testing.assert_allclose(lse, z, rtol=3e-7)
 
 
-@pytest.mark.parametrize("C,H,V", EVERY_KERNEL)
+@pytest.mark.parametrize("C,H,V", EVERY_KERNEL + WIDE_BLOCKS)
 def test_log_probs_have_no_bias_at_any_temperature(R, C, H, V):
     # Logits whose fp32 sums are exact (small whole numbers over a power of two), deviation 3 to 5 around 20, so that what
     # differs from the 64-bit log-prob is the rounding of the temperature, of the exponentials and of the results.
