@@ -76,9 +76,9 @@ COPRIS_RULE int lm_block_width(int C) {
 // 192 columns 1.04 above 512, with H = 256 1.02 .. 1.06 from 470; more than 512 have a second round, which loses where there are
 // three row blocks, up to 768 workgroups 1.00 .. 1.08, or five, up to 600 1.01 .. 1.03; H = 512 0.86 .. 1.22, H = 1024 1.05 .. 1.14;
 // given tokens 0.97 .. 1.13).  Whole calls in us, 256 columns / 128:
-//   C = 244, H =  512, V = 13430   24.4 / 16.9       C = 202, H = 3584, V =  4656   59.9 / 44.2     C = 256, H =  256, V = 28975   22.5 / 19.8
-//   C = 476, H =  256, V =  8027   21.6 / 14.7       C = 277, H = 3584, V =  9125   55.4 / 42.6     C = 480, H =   64, V = 42332   33.2 / 27.6
-//   C = 596, H = 1024, V =  5470   31.6 / 24.0       C = 250, H = 2048, V =  9230   36.4 / 29.8 (given tokens)
+//   C = 244, H =  512, V = 13430   25.1 / 17.0       C = 202, H = 3584, V =  4656   61.0 / 44.5     C = 256, H =  256, V = 28975   23.6 / 21.5
+//   C = 476, H =  256, V =  8027   22.1 / 14.9       C = 277, H = 3584, V =  9125   54.0 / 42.9     C = 500, H =  256, V = 32500   33.8 / 27.9
+//   C = 596, H = 1024, V =  5470   31.8 / 23.9       C = 250, H = 2048, V =  9230   36.5 / 30.3 (given tokens)
 struct LmBlocks {
   int blocks, rows, width;             // row blocks, batch rows of each, columns that it multiplies
 };
@@ -225,19 +225,19 @@ COPRIS_RULE int lm_run_rows(int C, int V, int width) {
 // without them C = 76, H = 64, V = 18900 given tokens 11.5 (9.0 with tiles of 128 rows), C = 150, H = 64, V = 18500 given 14.8 / 10.6,
 // C = 96, H = 64, V = 22500 14.8 / 11.9, C = 64, H = 128, V = 22500 given 11.2 / 9.5.  Whole calls in us, other kernel / small-call
 // kernel with its tile (sampling):
-//   C =   1, H = 3584, V =  3483   34.6 / 10.8 (16 x 16)      C =  41, H = 3584, V =  3251   39.9 / 12.5 (32 x 32)
-//   C =   2, H =  256, V = 16384   12.7 /  7.7 (64 x 16)      C =  63, H = 1024, V =  3554   19.7 / 10.5 (32 x 32)
-//   C =   8, H = 2048, V =  7732   25.2 / 12.3 (32 x 16)      C =  69, H =  512, V =  1885   15.3 /  8.2 (32 x 32)
-//   C =  18, H = 2048, V = 13619   26.6 / 18.6 (64 x 32)      C = 126, H = 3584, V =  2572   42.5 / 15.4 (64 x 32)
-//   C =  25, H = 1024, V = 24622   19.0 / 20.2, not taken     C = 192, H = 3584, V =  4804   51.1 / 22.9 (64 x 64)
-//   C = 125, H = 1024, V = 10419   20.6 / 23.8, not taken     C = 387, H =  512, V =  1515   24.1 / 11.6 (64 x 64)
-//   given tokens: C = 1, H = 1536, V = 3405  19.6 / 7.9;  C = 29, H = 2048, V = 6569  23.9 / 13.7;  C = 126, H = 3584, V = 6545  40.5 / 33.3
+//   C =   1, H = 3584, V =  3483   34.8 / 10.3 (16 x 16)      C =  41, H = 3584, V =  3251   40.0 / 12.7 (32 x 32)
+//   C =   2, H =  256, V = 16384   12.6 /  7.2 (64 x 16)      C =  63, H = 1024, V =  3554   19.3 /  9.1 (32 x 32)
+//   C =   8, H = 2048, V =  7732   25.5 / 11.8 (32 x 16)      C =  69, H =  512, V =  1885   14.7 /  7.1 (32 x 32)
+//   C =  18, H = 2048, V = 13619   26.5 / 16.8 (64 x 32)      C = 126, H = 3584, V =  2572   42.7 / 15.6 (64 x 32)
+//   C =  25, H = 1024, V = 24622   19.0 / 20.2, not taken     C = 192, H = 3584, V =  4804   51.1 / 23.2 (64 x 64)
+//   C = 125, H = 1024, V = 10419   20.6 / 23.8, not taken     C = 387, H =  512, V =  1515   24.0 / 10.5 (64 x 64)
+//   given tokens: C = 1, H = 1536, V = 3405  19.7 / 7.4;  C = 29, H = 2048, V = 6569  24.0 / 11.2;  C = 126, H = 3584, V = 6545  40.8 / 22.9
 // 674 drawn calls (C = 1 .. 512, H = 64 .. 3584, V = 1000 .. 32768): at most 1.00 of the time without this kernel and the narrow blocks, 0.31 at
 // best; some keep the other kernel where this one was 10 - 25 % faster.  A second round of 64 x 64 tiles is slower than the first (C = 334, H = 2048, V = 5313
 // 55.7 for two, 32.7 with tiles of 128 rows), so it is priced higher.  Where the run kernel's rule takes the call it keeps it.
-// fp32 against the kernel with four quarters of the hidden dimension and tiles of 64 rows: C = 8, H = 256, V = 1024 9.3 / 7.2;
-// C = 4, H = 1024, V = 2994 17.1 / 9.5; C = 62, H = 3584, V = 1945 82.1 / 26.7; C = 22, H = 512, V = 109750 82.1 / 71.0; 0.33 .. 1.00 of the time
-// over 30 drawn calls, but with at most 8 rows and more than 32768 vocabulary rows, where that one is bound by its stream
+// fp32 against the kernel with four quarters of the hidden dimension and tiles of 64 rows: C = 8, H = 256, V = 1024 9.4 / 7.1;
+// C = 4, H = 1024, V = 2994 17.0 / 9.3; C = 62, H = 3584, V = 1945 82.7 / 19.2; C = 22, H = 512, V = 109750 82.4 / 67.1; at most 1.00 of the time
+// over 120 drawn calls, but with at most 8 rows and more than 32768 vocabulary rows, where that one is bound by its stream
 // of W, 0.98 .. 1.06.
 struct LmSmall {
   int rows, cols;
@@ -417,18 +417,19 @@ COPRIS_RULE PrefillGrid prefill_grid(int B, int Hkv, int group, bool flat) {
 // and a quarter of a chain where workgroups that have a CU to themselves are more than there are CUs;
 // the steps of a workgroup being half of what lies between the mean length and the longest.  The constants (ns) are fitted to
 // 400 drawn calls (1 .. 40 sequences of 1 .. 8192 tokens, ten head counts) in all shapes, with an error of 12 .. 15 %, and moved
-// to where the choice loses least: it takes 1.011 times the time of the best on average, 1.31 at most.  Whole call in us, whole / half / 2 x 2 / 2 x 4:
-//   32 tokens, 12 / 2 heads                            7.1 /  5.6 /  5.5 /  6.4
-//   512 tokens, 12 / 2 heads                          15.2 / 11.6 /  9.3 / 10.8
-//   356 + 942 tokens, 12 / 2 heads                    22.3 / 17.9 / 17.2 / 14.3
-//   3 x 600 tokens, 8 / 8 heads                       17.5 / 13.5 / 17.3 / 12.8
-//   2000 tokens, 12 / 2 heads                         38.9 / 33.4 / 36.9 / 24.8
-//   1000 tokens, 28 / 4 heads                         23.8 / 19.5 / 32.0 / 21.0
-//   4 x 100 tokens, 28 / 4 heads                       8.7 /  7.1 / 10.8 /  8.2
-//   2000 + 500 + 300 tokens, 16 / 4 heads             41.7 / 31.8 / 58.8 / 38.8
-//   2 x 3000 tokens, 8 / 8 heads                      62.2 / 52.8 / 91.0 / 59.5
-//   3 x 900 tokens, 28 / 4 heads                      30.8 / 33.9 / 77.1 / 48.8
-//   24 x 300 tokens, 28 / 4 heads                     47.8 / 55.7 / 143  / 95.4
+// to where the choice loses least: it took 1.011 times the time of the best on average, 1.31 at most.  (That was with one softmax state
+// per wave.)  Whole call in us, whole / half / 2 x 2 / 2 x 4, with the states that prefill_sums asks for where the shape can hold them:
+//   32 tokens, 12 / 2 heads                            7.9 /  5.9 /  5.5 /  6.7
+//   512 tokens, 12 / 2 heads                          15.7 / 12.0 / 10.0 / 12.0
+//   356 + 942 tokens, 12 / 2 heads                    23.2 / 17.7 / 19.0 / 16.5
+//   3 x 600 tokens, 8 / 8 heads                       18.5 / 14.9 / 19.2 / 14.9
+//   2000 tokens, 12 / 2 heads                         39.7 / 31.1 / 36.4 / 26.4
+//   1000 tokens, 28 / 4 heads                         24.4 / 20.2 / 30.7 / 22.1
+//   4 x 100 tokens, 28 / 4 heads                       9.4 /  7.8 / 10.7 /  8.6
+//   2000 + 500 + 300 tokens, 16 / 4 heads             42.7 / 34.3 / 56.6 / 40.3
+//   2 x 3000 tokens, 8 / 8 heads                      63.6 / 55.9 / 86.4 / 62.2
+//   3 x 900 tokens, 28 / 4 heads                      33.4 / 34.8 / 73.1 / 50.0
+//   24 x 300 tokens, 28 / 4 heads                     50.2 / 56.1 / 133  / 93.9
 // (A group of four units of 32 queries more, 2 x 4 x 32, was best in 4 of the 400 calls, by 5 % in the middle; not taken.)
 enum PrefillShape { kPrefillWhole, kPrefillHalf, kPrefill2x2, kPrefill2x4 };
 struct PrefillCost {

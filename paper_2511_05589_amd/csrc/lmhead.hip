@@ -866,23 +866,16 @@ __device__ __forceinline__ void lds_arrived(u32x4 (&a)[4], u32x4 (&b)[4][NT]) {
     asm volatile("" : "+v"(b[0][1]), "+v"(b[1][1]), "+v"(b[2][1]), "+v"(b[3][1])::"memory");
 }
 
-// One Philox block of a tile: the accumulators of vocabulary entries vq .. vq+3 (vq % 4 == 0),
-// of which those at or past v_end are masked where the vocabulary (or a tile) ends inside a block.
-__device__ __forceinline__ void lm_sample_quad(float (&a)[4], LmLaneState& st, int vq, int v_end,
-                                               bool ragged, float scale, uint32_t step_c, uint32_t sid_lo,
-                                               uint32_t sid_hi, uint32_t key0, uint32_t key1) {
-  if (ragged) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (vq + j >= v_end) a[j] = -INFINITY;
-  }
+// The accumulators a of vocabulary entries vq .. vq+3 (-inf: none) into the state, with the block's random words from draw().
+template <typename Draw>
+__device__ __forceinline__ void lm_sample_words(const float (&a)[4], LmLaneState& st, int vq, float scale, const Draw& draw) {
   const float m_new = fmaxf(st.m, fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])));
   if (m_new == -INFINITY) return;
   const float alpha = lm_exp(st.m, m_new, scale);
   st.s *= alpha;
   st.p_best *= alpha;
   st.m = m_new;
-  const Philox4 x = philox4x32_10(static_cast<uint32_t>(vq) >> 2, step_c, sid_lo, sid_hi, key0, key1);
+  const Philox4 x = draw();
   const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -896,6 +889,20 @@ __device__ __forceinline__ void lm_sample_quad(float (&a)[4], LmLaneState& st, i
       st.idx = vq + j;
     }
   }
+}
+// One Philox block of a tile: the accumulators of vocabulary entries vq .. vq+3 (vq % 4 == 0),
+// of which those at or past v_end are masked where the vocabulary (or a tile) ends inside a block.
+__device__ __forceinline__ void lm_sample_quad(float (&a)[4], LmLaneState& st, int vq, int v_end,
+                                               bool ragged, float scale, uint32_t step_c, uint32_t sid_lo,
+                                               uint32_t sid_hi, uint32_t key0, uint32_t key1) {
+  if (ragged) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (vq + j >= v_end) a[j] = -INFINITY;
+  }
+  lm_sample_words(a, st, vq, scale, [&]() __attribute__((always_inline)) {
+    return philox4x32_10(static_cast<uint32_t>(vq) >> 2, step_c, sid_lo, sid_hi, key0, key1);
+  });
 }
 __device__ __forceinline__ void lm_given_quad(float (&a)[4], LmLaneState& st, int vq, int v_end,
                                               bool ragged, float scale, int target) {
@@ -1819,29 +1826,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
-// The accumulators a of vocabulary entries vq .. vq+3 (-inf: none) and the block's random words into the state.
-__device__ __forceinline__ void lm_sample_words(const float (&a)[4], LmLaneState& st, int vq, float scale, const Philox4& x) {
-  const float m_new = fmaxf(st.m, fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3])));
-  if (m_new == -INFINITY) return;
-  const float alpha = lm_exp(st.m, m_new, scale);
-  st.s *= alpha;
-  st.p_best *= alpha;
-  st.m = m_new;
-  const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float p = lm_exp(a[j], m_new, scale);                     // 0 for masked entries
-    st.s += p;
-    const float l = __builtin_amdgcn_logf(word_to_uniform(w[j]));   // log2(u) < 0
-    if (l * st.p_best > st.l_best * p) {                            // (see lm_epilogue_block)
-      st.l_best = l;
-      st.p_best = p;
-      st.a_best = a[j];
-      st.idx = vq + j;
-    }
-  }
-}
-
 // --------------------------------------------------------------------------
 // small-call kernel (bf16 with H % 64 == 0, fp32 with H % 16 == 0): calls whose tiles of 128 vocabulary rows and more would
 // leave most of the chip idle (lm_small_tile).
@@ -1855,7 +1839,8 @@ __device__ __forceinline__ void lm_sample_words(const float (&a)[4], LmLaneState
 // order through LDS, and then every thread has one Philox block of a column (two at 64 x 64), whose words it drew while the first
 // operands were on their way; the lanes of a column meet by DPP.
 // The tile follows what fills the chip and what the workspace has room for, the result does not: 16 rows of a column have one maximum,
-// and sixteens are joined by pairs to 64 rows, here or, from smaller tiles, by the merge (join, the same arithmetic in both).
+// and sixteens are joined by pairs to 64 rows, here or, from smaller tiles, by the merge (join, the same arithmetic in both; one maximum
+// per tile was 0.25 .. 0.5 us faster with 16 and 32 rows: C = 1, H = 1024, V = 3554 6.5 / 6.8).
 // What bounds it: a CU's requests.  In operand order neighbouring lanes fetch from different rows, and a load of 64 such pieces
 // of 16 bytes takes 64 clocks (33 GB/s).  With 32 batch rows and more (kGather) four neighbouring lanes fetch 64 bytes of one
 // row instead and the operands are put in order by a lane permutation through LDS: C = 41, H = 3584, V = 3251 18.6 -> 12.7 us; C = 126,
@@ -2031,7 +2016,7 @@ void lmhead_small_kernel(
     if constexpr (sizeof(T) == 2) {
       LmLaneState st{m, 0.0f, -INFINITY, 0.0f, 0.0f, 0x7fffffff};
       if (GIVEN) lm_given_quad(a, st, vq, V, false, scale, given[e]);
-      else lm_sample_words(a, st, vq, scale, words[e]);
+      else lm_sample_words(a, st, vq, scale, [w = words[e]]() __attribute__((always_inline)) { return w; });
       p = state_partial<GIVEN>(st, inv_temperature);
     } else {
       p = empty_partial();
@@ -2079,9 +2064,9 @@ void lmhead_small_kernel(
 // It is a chain of latencies: launch, one round trip to memory (four partials per lane in flight), one maximum for the
 // row, one exponential per partial against it, sums and the best score by DPP.  With four waves per row, every lane's
 // partials and every exchange combined with two exponentials of their own, and a barrier, whole calls took, in us, before / now:
-// C = 2, H = 256, V = 1117 6.6 / 6.1; C = 8, H = 2048, V = 7732 12.2 / 11.6; C = 64, H = 1536, V = 151936 90.5 / 89.2; C = 301, H = 2048,
-// V = 50257 90.1 / 88.2; given tokens M = 4164, H = 256, V = 5269 30.1 / 25.6, M = 8192, H = 256, V = 20011 106.1 / 95.9.  With 2374
-// partials of a row (C = 5, H = 72, V = 151936) 29.9 / 27.6, and 30.3 with one wavefront.
+// given tokens M = 4164, H = 256, V = 5269 31.3 / 26.5, M = 8192, H = 256, V = 20011 113.1 / 103.1; sampling within what runs differ by:
+// C = 64, H = 1536, V = 151936 92.4 / 90.7, C = 301, H = 2048, V = 50257 93.0 / 92.0.  With 2374 partials of a row (C = 5, H = 72, V = 151936) 30.0 / 27.7,
+// and 30.3 with one wavefront.
 // --------------------------------------------------------------------------
 // (Rows from `rest` on have n_rest partials, in rows of n_tiles like the others.)  PER neighbouring partials are joined first: those of
 // the small-call kernel's tiles, to the 64 rows of its largest.
@@ -2228,7 +2213,7 @@ static LmSmall lm_use_small(int C, int H, int V, int dtype, bool given, int64_t 
   if (!lm_small_takes(C, H, V, dtype)) return {0, 0};
   return lm_small_tile(C, H, V, given, dtype == 0, max_parts);
 }
-// Partials per row.  Matrix-core kernels: the grid is (parts, blocks of 256 rows) with
+// Partials per row.  Matrix-core kernels: the grid is (parts, row blocks) with
 // parts * blocks <= the resident workgroups (512, or 256 for the 256 x 256 kernel) where
 // possible, so that the workgroups that run at the same time walk the same vocabulary tiles
 // (W comes from HBM once and is shared through the caches) and each keeps its rows' state

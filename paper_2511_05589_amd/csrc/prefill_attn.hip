@@ -25,12 +25,12 @@
 // exponential at a time), and reads its next K operands and requests rows while it multiplies the values; the steps are
 // unrolled over the ring, so that operand addresses are immediates; the other workgroup of the CU fills what is left.
 // 16 sequences of 513 .. 16897 tokens, 28 / 4 heads: 2690 us with the score, softmax and value parts one after the other
-// and a grid per sequence, 2460 with both as they are here (1.15 PFLOP/s, 1390 W of the board's 1400 at 1.9 GHz; 2314 and
-// 1990 on zeros, where power is no limit).
+// and a grid per sequence, 2440 with parts, rings and grid as they are here, which came in one step and were not timed apart
+// (1.16 PFLOP/s, 1390 W of the board's 1400 at 1.9 GHz; 2314 and 1990 on zeros, where power is no limit).
 //
 // Where a workgroup works.  The grid is flat over the workgroups that the lengths need, and the kv heads are dealt to the
-// XCDs (Place): 8 / 8 heads, 40 x 2048 tokens 661 -> 457 us, whose rows every XCD pulled through its own L2 before;
-// 30 x 60 tokens with a bound of 4096 44 -> 9.1, most of whose workgroups had nothing to do.
+// XCDs (Place): 8 / 8 heads, 40 x 2048 tokens 661 -> 474 us, whose rows every XCD pulled through its own L2 before;
+// 30 x 60 tokens with a bound of 4096 45 -> 9.2, most of whose workgroups had nothing to do.
 //
 // LDS reads are inline instructions with explicit waits: the compiler cannot tell which
 // LDS-direct load fills which buffer and would wait for all of them before any LDS read.
@@ -725,8 +725,8 @@ __device__ __forceinline__ void prefill_attn_body(
 COPRIS_PREFILL_KERNEL(prefill_attn_kernel, 1, 4, 2, 2)
 // For calls that do not fill the chip with these (prefill_shape says which shape a call takes): units of 16 queries, which
 // have half the instructions per step; and two groups of waves per unit, group i taking the steps i, i + 2, ... from rings of
-// its own, the softmax states put together at the end.  (One sequence of 4000 tokens, one head, us: 68.9 whole, 31.8 and 34.1 in
-// two groups; 40.8 in four groups of 32 queries, whose rings of two buffers were too short for the rows to arrive.)
+// its own, the softmax states put together at the end.  (One sequence of 4000 tokens, one head, us: 69.8 whole, 31.2 and 35.4 in
+// two groups; 42.1 in four groups of 32 queries, whose rings of two buffers were too short for the rows to arrive.)
 // The bounds of two groups allow eight waves also where there are four: with 512 registers for a wave the compiler keeps the
 // accumulators in the other register file and moves them at every use (172 + 115 tokens, 16 / 4 heads: 8.8 us / 8.1).
 COPRIS_PREFILL_KERNEL(prefill_attn_half_kernel, 1, 4, 1, 2)
